@@ -140,7 +140,7 @@ int ee_model_free(ee_model *m);
 int ee_model_info(const ee_model *m, ee_model_config *out);
 
 /* A session owns a paged bf16 KV cache for up to max_ctx positions, scratch
-   for one pass, a stream, events and a pinned result block.
+   for one pass and for one prefill chunk (up to 2048 rows), a stream, events and a pinned result block.
    max_gamma in [1, EE_MAX_M-1]. */
 int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, unsigned flags,
                       ee_session **out);

@@ -1,0 +1,540 @@
+// gfx950 kernels of a prefill chunk of many rows (prompt tokens, embedding rows).
+//
+// A verify pass has up to 48 rows and is bound by streaming the weights once; its kernels give
+// every workgroup whole n-tiles and copy the whole input into each of them.  A prompt has
+// hundreds of rows: streamed 16 or 48 at a time, every group of rows pays for the whole model's
+// weights again.  The kernels here take up to PF_ROWS rows at once and are bound by the
+// matrix cores and by what feeds them from the L2:
+//   pf_gemm_kernel   output tile of n-tiles x row tiles per workgroup, both operands through LDS
+//   pf_att_kernel    causal attention of the chunk over the cache, 64 or 128 query rows per workgroup
+//   pf_embed_kernel  embedding gather, first norm input
+//   pf_last_kernel   the last row as the LM head's input
+// Arithmetic is that of the verify pass: bf16 weights, every other operand as two bf16 terms, fp32
+// accumulation, residual stream, norms and softmax; the same weight tiles (GemmPlan's order) and
+// the same KV records are used, so nothing is stored twice.
+#pragma once
+
+#include "ee_kernels.hpp"
+
+namespace ee {
+
+constexpr int PF_ROWS = 2048;     // rows of one chunk (a multiple of 128)
+constexpr int PF_THREADS = 256;   // four waves
+
+// Buffers of a prefill chunk (per session, for `16 * rt` rows).  GEMM inputs are stored as MFMA
+// operands: [k-tile][term][row tile][lane][8] bf16, lane = (k % 32 / 8) * 16 + row % 16, so that
+// one operand of 16 rows x 32 k is one contiguous kilobyte, read by lane number.
+struct PfScratch {
+    float *h;          // [rows][d]  residual stream
+    float *q;          // [rows][d]  queries after RoPE
+    uint16_t *xn;      // gain * h, input of QKV and gate/up
+    uint16_t *attn;    // attention output
+    uint16_t *u;       // silu(gate) * up
+    float *ss;         // [slots][rows]  partial sums of h^2 of the rows (two buffers, see ss_in / ss_out)
+    int rt;            // row tiles the buffers are laid out for
+};
+
+struct PfArgs {
+    PfScratch b;
+    int rows;                 // rows of this chunk
+    int pos0;                 // position of row 0 (a multiple of KV_PAGE)
+    int layer;
+    int d, F, H, hd;
+    float eps, att_scale;
+    // GEMM
+    const uint4 *W;           // the layer's weights in GemmPlan's order
+    const int2 *tab;          // [NT] per n-tile: first tile and distance between k-tiles 8 apart, in tiles of 1 KB
+    int NT, KT, N;
+    int nb, mb;               // workgroup tiles along N and along the rows
+    const float *gain;        // O / DN: gain of the next GEMM input, or nullptr
+    const float *ss_in;       // partial sums of squares of the input's rows (QKV, GU)
+    int ss_slots;
+    float *ss_out;            // O / DN
+    // attention, KV write
+    uint16_t *kpool, *vpool;
+    const float2 *rope;
+    const int *page_table;
+    int contig_base, n_pages;
+    // embedding
+    const int *tokens;
+    const uint16_t *emb_rows, *emb;
+};
+
+__device__ __forceinline__ size_t pf_index(int rt, int m, int k, int term)
+{
+    return ((size_t)((k >> 5) * 2 + term) * rt + (m >> 4)) * 512 + ((k & 31) >> 3) * 128 + (m & 15) * 8 + (k & 7);
+}
+
+// four consecutive columns k .. k+3 (k a multiple of 4) of row m, as two bf16 terms
+__device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int k, const float *v)
+{
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split_bf16(v[e], h[e], l[e]);
+    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+    const size_t i = pf_index(rt, m, k, 0);
+    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i) = (u32x2_t){h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i + (size_t)rt * 512) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+}
+
+// One kilobyte from memory straight into LDS: lane l's 16 bytes at src + off land at LDS byte
+// dst + 16 l.  Inline assembly because the compiler makes every LDS read wait for all such loads it
+// knows of; here a stage is read while the next ones are on their way, and the kernels wait
+// themselves (pf_wait, then a barrier).  No vector register is written; M0, which nothing else in
+// these kernels uses, needs one wait state.
+__device__ __forceinline__ void pf_load_lds(const void *src, int off, unsigned dst)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(off), "s"(src), "s"(dst)
+                 : "memory");
+}
+template <int N>
+__device__ __forceinline__ void pf_wait()   // at most N vector memory operations of this wave are pending
+{
+    static_assert(N < 64, "vmcnt has 6 bits");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ const void *uniform_ptr(const void *p)
+{
+    const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return reinterpret_cast<const void *>(((unsigned long long)hi << 32) | lo);
+}
+
+// LDS byte offset of the dynamic LDS block's start
+__device__ __forceinline__ unsigned lds_offset(const char *p)
+{
+    return __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<unsigned long long>((const EE_LDS char *)p));
+}
+
+// Stages of the ring a tile shape uses: what fits 64 to 72 KB, so that two workgroups share a
+// compute unit and one's barrier and epilogue run under the other's products.
+constexpr int pf_stages(int wn, int wm) { return (wn + 2 * wm) * 2 >= 32 ? 2 : ((wn + 2 * wm) * 2 >= 24 ? 3 : 4); }
+constexpr size_t pf_gemm_lds(int wn, int wm) { return (size_t)pf_stages(wn, wm) * (wn + 2 * wm) * 2048 + (size_t)wm * 32 * 4; }
+
+// One GEMM of the chunk.  Workgroup tile: 2 WN n-tiles x 2 WM row tiles, four waves as 2 x 2, each
+// WN x WM accumulators.  Per k-tile of 32 the stage's W tiles and both terms of the X tiles travel to
+// LDS (1 KB per load instruction, already in operand order: every LDS read is a contiguous
+// kilobyte), NS stages in a ring, one barrier per k-tile.
+// Bound by what a compute unit gets through its memory pipeline (about 64 KB in flight), then by the
+// matrix cores.  Measured with 2041 rows, 7B shape, both terms' products counted: gate/up 551 us
+// (1.34 PFLOP/s), QKV 315 us (1.31), down 312 us (1.18), output projection 132 us (1.04; 256
+// workgroups, one per unit).  The same rows in chunks of 16 through the streaming kernels: 3 ms per
+// chunk, 486 ms per prompt against 50 ms.
+template <int KIND, int WN, int WM>
+__global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
+{
+    constexpr int BNT = 2 * WN, BMT = 2 * WM, NS = pf_stages(WN, WM);
+    constexpr int WL = BNT / 4, XL = 2 * BMT / 4;            // loads per wave and stage
+    constexpr int PER = WL + XL;
+    constexpr unsigned STAGE = (BNT + 2 * BMT) * 1024;
+    static_assert(BNT % 4 == 0 && BMT % 2 == 0, "tile shape");
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, wm = wave >> 1;
+    // Workgroups are dealt to the XCDs round-robin; each XCD gets a contiguous run of the tile
+    // sequence, which walks groups of four n-blocks over all row blocks: the workgroups that run together on
+    // an XCD then share a few W and X blocks in its L2.
+    const int T = a.nb * a.mb;
+    int t;
+    {
+        const int x = blockIdx.x % NUM_XCD, j = blockIdx.x / NUM_XCD;
+        const int base = T / NUM_XCD, extra = T % NUM_XCD;
+        t = x * base + min(x, extra) + j;
+    }
+    const int gsz = 4 * a.mb, grp = div_small(t, gsz), rem = t - grp * gsz;
+    const int gw = min(4, a.nb - grp * 4);
+    const int mblk = div_small(rem, gw), nblk = grp * 4 + (rem - mblk * gw);
+    const int nt0 = nblk * BNT, mt0 = mblk * BMT;
+
+    float *rstd = reinterpret_cast<float *>(lds + NS * STAGE);
+    const unsigned lds0 = lds_offset(lds);
+    // this wave's share of a stage
+    const char *wbase[WL];
+    int wstride[WL];
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+        const int2 e = a.tab[min(nt0 + wave * WL + i, a.NT - 1)];
+        wbase[i] = reinterpret_cast<const char *>(uniform_ptr(reinterpret_cast<const char *>(a.W) + (size_t)__builtin_amdgcn_readfirstlane(e.x) * 1024));
+        wstride[i] = __builtin_amdgcn_readfirstlane(e.y);
+    }
+    const uint16_t *X = KIND == G_O ? a.b.attn : (KIND == G_DN ? a.b.u : a.b.xn);
+    const int term = wave >> 1, xt0 = (wave & 1) * XL;       // waves 0, 1: hi term, 2, 3: lo term; XL row tiles each
+    const char *xbase = reinterpret_cast<const char *>(X) + ((size_t)term * a.b.rt) * 1024;
+    int xrow[XL];
+#pragma unroll
+    for (int i = 0; i < XL; ++i) xrow[i] = min(mt0 + xt0 + i, a.b.rt - 1);
+    const size_t xstep = (size_t)2 * a.b.rt * 1024;
+    const int lane16 = lane * 16;
+    auto request = [&](int kt, int buf) __attribute__((always_inline)) {
+        const unsigned dst = lds0 + buf * STAGE;
+#pragma unroll
+        for (int i = 0; i < WL; ++i)
+            pf_load_lds(wbase[i] + ((size_t)(kt >> 3) * wstride[i] + (kt & 7)) * 1024, lane16, dst + (wave * WL + i) * 1024);
+#pragma unroll
+        for (int i = 0; i < XL; ++i)
+            pf_load_lds(xbase + (size_t)kt * xstep + (size_t)xrow[i] * 1024, lane16, dst + (BNT + term * BMT + xt0 + i) * 1024);
+    };
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < a.KT) request(s, s);
+    // row factors of the norm
+    if (KIND == G_QKV || KIND == G_GU) {
+        for (int r = tid; r < BMT * 16; r += PF_THREADS) {
+            const int m = min(mt0 * 16 + r, a.rows - 1);
+            float s = 0.f;
+#pragma unroll 8
+            for (int j = 0; j < a.ss_slots; ++j) s += as_global(a.ss_in)[(size_t)j * a.b.rt * 16 + m];
+            rstd[r] = 1.0f / sqrtf(s / (float)a.d + a.eps);
+        }
+    }
+
+    f32x4_t acc[WN][WM];
+#pragma unroll
+    for (int i = 0; i < WN; ++i)
+#pragma unroll
+        for (int j = 0; j < WM; ++j) acc[i][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+
+    int buf = 0;
+    for (int kt = 0; kt < a.KT; ++kt) {
+        // this wave's loads of stage kt have landed; after the barrier everybody's have, and nobody
+        // reads the buffer of stage kt - 1 any more
+        if (kt + NS - 2 < a.KT)
+            pf_wait<PER *(NS - 2)>();
+        else
+            pf_wait<0>();
+        lds_barrier();
+        if (kt + NS - 1 < a.KT) request(kt + NS - 1, buf == 0 ? NS - 1 : buf - 1);
+        const char *st = lds + buf * STAGE;
+        const char *sw = st + (wn * WN) * 1024 + lane16;
+        const char *sx = st + (BNT + wm * WM) * 1024 + lane16;
+        bf16x8_t w[WN], xh[WM], xl[WM];
+#pragma unroll
+        for (int i = 0; i < WN; ++i) w[i] = *reinterpret_cast<const bf16x8_t *>(sw + i * 1024);
+#pragma unroll
+        for (int j = 0; j < WM; ++j) {
+            xh[j] = *reinterpret_cast<const bf16x8_t *>(sx + j * 1024);
+            xl[j] = *reinterpret_cast<const bf16x8_t *>(sx + (BMT + j) * 1024);
+        }
+#pragma unroll
+        for (int j = 0; j < WM; ++j) {
+#pragma unroll
+            for (int i = 0; i < WN; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], xh[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < WN; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], xl[j], acc[i][j], 0, 0, 0);
+        }
+        buf = buf + 1 == NS ? 0 : buf + 1;
+    }
+
+    // epilogue from the accumulators: lane holds columns n .. n+3 (n = n-tile * 16 + (lane >> 4) * 4) of row m
+    const int quad = lane >> 4, lm = lane & 15;
+#pragma unroll
+    for (int j = 0; j < WM; ++j) {
+        const int m = (mt0 + wm * WM + j) * 16 + lm;
+        const bool live = m < a.rows;
+        if (KIND == G_GU) {
+            const float rs = rstd[(wm * WM + j) * 16 + lm];
+#pragma unroll
+            for (int i = 0; i < WN; i += 2) {
+                const int nt = nt0 + wn * WN + i;
+                float o[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float g = acc[i][j][e] * rs, u = acc[i + 1][j][e] * rs;
+                    o[e] = g / (1.0f + __expf(-g)) * u;
+                }
+                if (live && nt < a.NT) pf_store_split4(a.b.u, a.b.rt, m, (nt >> 1) * 16 + quad * 4, o);
+            }
+        } else if (KIND == G_O || KIND == G_DN) {
+            float sq = 0.f;
+            EE_GLOBAL float *hp = as_global_mut(a.b.h) + (size_t)min(m, a.rows - 1) * a.d;
+            f32x4_t hv[WN], gv[WN];
+#pragma unroll
+            for (int i = 0; i < WN; ++i) {
+                const int n = min((nt0 + wn * WN + i) * 16, a.d - 16) + quad * 4;
+                hv[i] = *reinterpret_cast<const EE_GLOBAL f32x4_t *>(hp + n);
+                gv[i] = a.gain ? *as_global(reinterpret_cast<const f32x4_t *>(a.gain + n)) : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int i = 0; i < WN; ++i) {
+                const int nt = nt0 + wn * WN + i, n = nt * 16 + quad * 4;
+                if (live && nt < a.NT) {
+                    const f32x4_t v = hv[i] + acc[i][j];
+                    *reinterpret_cast<EE_GLOBAL f32x4_t *>(hp + n) = v;
+                    sq += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+                    if (a.gain) {
+                        const float x[4] = {v[0] * gv[i][0], v[1] * gv[i][1], v[2] * gv[i][2], v[3] * gv[i][3]};
+                        pf_store_split4(a.b.xn, a.b.rt, m, n, x);
+                    }
+                }
+            }
+            sq += __shfl_xor(sq, 16, 64);
+            sq += __shfl_xor(sq, 32, 64);
+            if (quad == 0 && live) as_global_mut(a.ss_out)[(size_t)(nblk * 2 + wn) * a.b.rt * 16 + m] = sq;
+        } else {
+            const float rs = rstd[(wm * WM + j) * 16 + lm];
+            const int pos = a.pos0 + min(m, a.rows - 1);
+            const int page = a.contig_base >= 0 ? a.contig_base + pos / KV_PAGE : as_global(a.page_table)[pos / KV_PAGE];
+            const size_t rec0 = (((size_t)a.layer * a.n_pages + page) * a.H) * KV_PAGE * 2 * a.hd;
+            const int slot = pos % KV_PAGE;
+#pragma unroll
+            for (int i = 0; i < WN; ++i) {
+                const int nt = nt0 + wn * WN + i;
+                if (nt >= a.NT) continue;
+                // an n-tile lies inside one head of one of the three sections
+                const int sect = div_small(nt * 16, a.d), c0 = nt * 16 - sect * a.d, head = div_small(c0, a.hd), e = c0 - head * a.hd + quad * 4;
+                float v[4] = {acc[i][j][0] * rs, acc[i][j][1] * rs, acc[i][j][2] * rs, acc[i][j][3] * rs};
+                if (sect < 2) {  // columns are pair-interleaved inside a head: (e, e+1) = RoPE pair e/2
+                    const f32x4_t cs = *as_global(reinterpret_cast<const f32x4_t *>(a.rope + (size_t)pos * (a.hd >> 1) + (e >> 1)));
+                    const float y0 = v[0] * cs[0] - v[1] * cs[1], y1 = v[1] * cs[0] + v[0] * cs[1];
+                    const float y2 = v[2] * cs[2] - v[3] * cs[3], y3 = v[3] * cs[2] + v[2] * cs[3];
+                    v[0] = y0; v[1] = y1; v[2] = y2; v[3] = y3;
+                }
+                if (!live) continue;
+                if (sect == 0) {
+                    *reinterpret_cast<EE_GLOBAL f32x4_t *>(as_global_mut(a.b.q) + (size_t)m * a.d + c0 + quad * 4) = (f32x4_t){v[0], v[1], v[2], v[3]};
+                } else {
+                    uint32_t vh[4], vl[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) split_bf16(v[r], vh[r], vl[r]);
+                    const size_t rec = rec0 + (size_t)head * KV_PAGE * 2 * a.hd;
+                    if (sect == 1) {
+                        EE_GLOBAL uint16_t *kr = as_global_mut(a.kpool) + rec + (size_t)slot * 2 * a.hd + e;
+                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+                        *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0] | (vh[1] << 16), vh[2] | (vh[3] << 16)};
+                        *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + a.hd) = (u32x2_t){vl[0] | (vl[1] << 16), vl[2] | (vl[3] << 16)};
+                    } else {
+                        EE_GLOBAL uint16_t *vr = as_global_mut(a.vpool) + rec + slot;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            vr[(size_t)(e + r) * KV_PAGE] = (uint16_t)vh[r];
+                            vr[(size_t)(a.hd + e + r) * KV_PAGE] = (uint16_t)vl[r];
+                        }
+                    }
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ attention
+
+constexpr int pf_att_stage(int hd) { return 4 * KV_PAGE * 2 * hd * 2; }   // bytes: K and V of two pages
+constexpr size_t pf_att_lds(int hd, int n_pages) { return (size_t)2 * pf_att_stage(hd) + (size_t)n_pages * 4; }
+
+// Workgroup = (head, block of 64 RT query rows); wave w has row tiles w RT .. of the block.  It walks
+// the cached positions 32 (two pages) at a time up to its last row's position, K and V of a step
+// shared by the four waves through LDS (two buffers).  Scores as S^T = K . q^T (16x16x32, K one operand per
+// page and 32 values), so that a lane holds four positions of one row; those are, without any
+// exchange, the k-slots of the second product O^T = V^T . P^T (16x16x32 over the two pages: k-slot
+// 8 q + e is position 4 q + e of the first page for e < 4, 4 q + e - 4 of the second otherwise; the V
+// operand uses the same order).  A row's maximum, sum and output stay in the lanes of its column:
+// the running rescale needs no exchange either.  Two bf16 terms of q, K, P and V, three MFMAs each.
+// 2041 rows, 32 heads of 128: 187 us (0.55 PFLOP/s with all three products counted); RT = 2 halves the
+// K and V traffic per row and is used once its blocks cover the compute units.
+template <int HD, int RT>
+__global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
+{
+    constexpr int KT = HD / 32, NT = HD / 16;
+    constexpr int PAGE_B = KV_PAGE * 2 * HD * 2;             // bytes of one (page, head) record of K or of V
+    constexpr int FR = PAGE_B / 1024;                        // kilobytes of it
+    constexpr unsigned STAGE = pf_att_stage(HD);
+    constexpr int BR = 64 * RT;
+    extern __shared__ __align__(16) char lds[];
+    int *pages = reinterpret_cast<int *>(lds + 2 * STAGE);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lm = lane & 15, quad = lane >> 4;
+    const int n_blk = (a.rows + BR - 1) / BR;
+    // heads fastest; the row blocks with the most positions first, so that the short ones fill the end
+    const int head = blockIdx.x % a.H, blk = n_blk - 1 - blockIdx.x / a.H;
+    const int r0 = blk * BR, nr = min(BR, a.rows - r0);
+    const int n_pos = a.pos0 + r0 + nr;
+    const int n_pg = (n_pos + KV_PAGE - 1) / KV_PAGE, steps = (n_pg + 1) / 2;
+    for (int i = tid; i < n_pg; i += PF_THREADS) pages[i] = a.contig_base >= 0 ? a.contig_base + i : as_global(a.page_table)[i];
+
+    // q of this wave's rows as MFMA operands
+    const int row0 = r0 + wave * 16 * RT;                    // first row of this wave
+    bf16x8_t qh[RT][KT], ql[RT][KT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const float *qp = a.b.q + (size_t)min(row0 + t * 16 + lm, a.rows - 1) * a.d + head * HD + quad * 8;
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+            const f32x4_t x = *as_global(reinterpret_cast<const f32x4_t *>(qp + kt * 32)), y = *as_global(reinterpret_cast<const f32x4_t *>(qp + kt * 32 + 4));
+            uint32_t h[8], l[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                split_bf16(x[e], h[e], l[e]);
+                split_bf16(y[e], h[4 + e], l[4 + e]);
+            }
+            qh[t][kt] = pack_bf16x8(h);
+            ql[t][kt] = pack_bf16x8(l);
+        }
+    }
+    wait_vmem();
+    __syncthreads();                                         // the page list is there; no load is pending
+
+    // wave w copies K (w even) or V (w odd) of page w >> 1 of a step; K is gathered into operand order
+    const bool is_v = wave & 1;
+    const int src_off = is_v ? lane * 16 : lm * (2 * HD * 2) + quad * 16;
+    const unsigned lds0 = lds_offset(lds);
+    auto request = [&](int step, int buf) __attribute__((always_inline)) {
+        const int page = __builtin_amdgcn_readfirstlane(pages[min(2 * step + (wave >> 1), n_pg - 1)]);
+        const size_t rec = (((size_t)a.layer * a.n_pages + page) * a.H + head) * PAGE_B;
+        const char *src = reinterpret_cast<const char *>(is_v ? a.vpool : a.kpool) + rec;
+        const unsigned dst = lds0 + buf * STAGE + wave * PAGE_B;   // [page 0: K, V][page 1: K, V]
+#pragma unroll
+        for (int f = 0; f < FR; ++f)                          // K: operand (32 values kt, term) = f; V: plain copy
+            pf_load_lds(uniform_ptr(src + (is_v ? f * 1024 : (f & 1) * HD * 2 + (f >> 1) * 64)), src_off, dst + f * 1024);
+    };
+    request(0, 0);
+
+    f32x4_t O[RT][NT];
+    float mx[RT], sum[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        mx[t] = ATT_NEG;
+        sum[t] = 0.f;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) O[t][n] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    }
+    const int wave_last = a.pos0 + min(row0 + 16 * RT, a.rows) - 1;   // last position a row of this wave sees
+    for (int step = 0; step < steps; ++step) {
+        pf_wait<0>();
+        lds_barrier();
+        if (step + 1 < steps) request(step + 1, (step + 1) & 1);
+        if (step * 32 > wave_last || row0 >= a.rows) continue;
+        const char *st = lds + (step & 1) * STAGE;
+        f32x4_t S[RT][2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) S[t][p] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                const bf16x8_t kh = *reinterpret_cast<const bf16x8_t *>(st + p * 2 * PAGE_B + (2 * kt) * 1024 + lane * 16);
+                const bf16x8_t kl = *reinterpret_cast<const bf16x8_t *>(st + p * 2 * PAGE_B + (2 * kt + 1) * 1024 + lane * 16);
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    S[t][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh, qh[t][kt], S[t][p], 0, 0, 0);
+                    S[t][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl, qh[t][kt], S[t][p], 0, 0, 0);
+                    S[t][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh, ql[t][kt], S[t][p], 0, 0, 0);
+                }
+            }
+        }
+        bf16x8_t Ph[RT], Pl[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int last_pos = a.pos0 + row0 + t * 16 + lm;   // last position this lane's row may see
+            float s[8], local = ATT_NEG;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int pos = step * 32 + (e >> 2) * 16 + quad * 4 + (e & 3);
+                s[e] = pos <= last_pos ? S[t][e >> 2][e & 3] * a.att_scale : ATT_NEG;
+                local = fmaxf(local, s[e]);
+            }
+            local = fmaxf(local, __shfl_xor(local, 16, 64));
+            local = fmaxf(local, __shfl_xor(local, 32, 64));
+            if (__any(local > mx[t])) {
+                const float m_new = fmaxf(mx[t], local), f = __expf(mx[t] - m_new);
+                mx[t] = m_new;
+                sum[t] *= f;
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) O[t][n][r] *= f;
+            }
+            uint32_t ph[8], pl[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float p = __expf(s[e] - mx[t]);
+                sum[t] += p;
+                split_bf16(p, ph[e], pl[e]);
+            }
+            Ph[t] = pack_bf16x8(ph);
+            Pl[t] = pack_bf16x8(pl);
+        }
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            // V record: [term][dim][16 positions]; dim n * 16 + lm, positions 4 quad .. + 3 of either page
+            const char *v0 = st + PAGE_B + (n * 16 + lm) * 32 + quad * 8, *v1 = v0 + 2 * PAGE_B;
+            const uint2 h0 = *reinterpret_cast<const uint2 *>(v0), h1 = *reinterpret_cast<const uint2 *>(v1);
+            const uint2 l0 = *reinterpret_cast<const uint2 *>(v0 + HD * 32), l1 = *reinterpret_cast<const uint2 *>(v1 + HD * 32);
+            const bf16x8_t Vh = __builtin_bit_cast(bf16x8_t, make_uint4(h0.x, h0.y, h1.x, h1.y));
+            const bf16x8_t Vl = __builtin_bit_cast(bf16x8_t, make_uint4(l0.x, l0.y, l1.x, l1.y));
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                O[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Vh, Ph[t], O[t][n], 0, 0, 0);
+                O[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Vh, Pl[t], O[t][n], 0, 0, 0);
+                O[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Vl, Ph[t], O[t][n], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        float s = sum[t];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        const int m = row0 + t * 16 + lm;
+        const float inv = 1.0f / s;
+        if (m < a.rows) {
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const float v[4] = {O[t][n][0] * inv, O[t][n][1] * inv, O[t][n][2] * inv, O[t][n][3] * inv};
+                pf_store_split4(a.b.attn, a.b.rt, m, head * HD + n * 16 + quad * 4, v);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ embedding, last row
+
+__device__ __forceinline__ float pf_block_sum(float s, float *red)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    float t = 0.f;
+    for (int w = 0; w < PF_THREADS / 64; ++w) t += red[w];
+    return t;
+}
+
+// one workgroup per row: h = the token's embedding (or the supplied row), first layer's GEMM input, sum of squares
+__global__ void __launch_bounds__(PF_THREADS) pf_embed_kernel(PfArgs a)
+{
+    __shared__ float red[PF_THREADS / 64];
+    const int m = blockIdx.x, tok = a.tokens[m];
+    const uint16_t *src = tok >= 0 ? a.emb + (size_t)tok * a.d : a.emb_rows + (size_t)m * a.d;
+    float sq = 0.f;
+    for (int c = threadIdx.x * 4; c < a.d; c += PF_THREADS * 4) {
+        const uint2 r = *reinterpret_cast<const uint2 *>(src + c);
+        const float v[4] = {__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xFFFF0000u)};
+        *reinterpret_cast<float4 *>(a.b.h + (size_t)m * a.d + c) = make_float4(v[0], v[1], v[2], v[3]);
+        sq += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+        const float4 g = *reinterpret_cast<const float4 *>(a.gain + c);
+        const float x[4] = {v[0] * g.x, v[1] * g.y, v[2] * g.z, v[3] * g.w};
+        pf_store_split4(a.b.xn, a.b.rt, m, c, x);
+    }
+    sq = pf_block_sum(sq, red);
+    if (threadIdx.x == 0) a.ss_out[m] = sq;
+}
+
+// one workgroup: the chunk's last row as the input of a one-row LM-head launch (xh, [nwg][rows_max] sums of squares)
+__global__ void __launch_bounds__(PF_THREADS) pf_last_kernel(PfArgs a, uint16_t *xh, float *ss_h, int nwg, int rows_max)
+{
+    __shared__ float red[PF_THREADS / 64];
+    const float *h = a.b.h + (size_t)(a.rows - 1) * a.d;
+    float sq = 0.f;
+    for (int c = threadIdx.x * 4; c < a.d; c += PF_THREADS * 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(h + c), g = *reinterpret_cast<const float4 *>(a.gain + c);
+        sq += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        const float x[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+        store_split4(xh, 1, 0, c, x);
+    }
+    sq = pf_block_sum(sq, red);
+    for (int g = threadIdx.x; g < nwg; g += PF_THREADS) ss_h[(size_t)g * rows_max] = g == 0 ? sq : 0.f;
+}
+
+}  // namespace ee

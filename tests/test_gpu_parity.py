@@ -197,6 +197,44 @@ def test_hold_last_and_embedding_prefix(tiny_pair):
         gs.free()
 
 
+@pytest.mark.parametrize("which,n_emb,n_tok,scatter", [
+    ("tiny", 0, 49, 0),        # the first size that takes the many-row kernels
+    ("tiny", 0, 63, 1), ("mid", 0, 64, 0), ("mid", 0, 65, 1),      # around a workgroup tile of 64 rows
+    ("mid", 70, 57, 0), ("tiny", 0, 129, 0),                        # around one of 128, embedding rows in front
+    ("mid", 0, 257, 1), ("tiny", 0, 2048, 0), ("tiny", 0, 2049, 1), # one chunk exactly, two chunks
+])
+def test_prefill_many_rows(tiny_pair, mid_pair, which, n_emb, n_tok, scatter):
+    """Prompts long enough for the many-row kernels: first token, then one verify round over the
+    cache they left, against the oracle.  Logits: every GEMM input and cached value is held to 17 bits, so
+    a product is off by at most 2^-17 of the sum of its terms' magnitudes; with 28 products in a row (7 a
+    layer), each error passed on in full, and logits below 8: 28 * 2^-17 * 8 = 1.7e-3 (seen: 2e-5).  HOLD_LAST runs the same
+    kernels without a head."""
+    g, o = tiny_pair if which == "tiny" else mid_pair
+    exits = TINY_EXITS if which == "tiny" else [1, 2]
+    n = n_emb + n_tok
+    emb = eegen.embedding_prefix(1300 + n, n_emb, o.d_model) if n_emb else None
+    toks = eegen.prompt_tokens(1301 + n, n_tok, o.vocab)
+    drafts = eegen.prompt_tokens(1302 + n, 6, o.vocab)
+    os_ = o.session(n + 32)
+    for hold in (0, 1):
+        gs = g.session(n + 32, max_gamma=8, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+        gs.ee_session_option(ee.OPT_SCATTER_PAGES, scatter)
+        try:
+            first = gs.ee_prefill(toks, flags=ee.HOLD_LAST if hold else 0, emb=emb)
+            if hold:
+                assert gs.ee_kv_len() == n - 1 and gs.ee_pending() == toks[-1]
+                os_.prefill(toks, flags=eo.HOLD_LAST, emb=emb)
+            else:
+                fo, margin = oracle_prefill(os_, toks, emb=emb)
+                check_first_token(gs, first, fo, margin, f"{which} {n}")
+            ro = os_.verify(drafts, exits, commit=False, want_logits=True)
+            rg = gs.verify_sync(drafts, exits)
+            exempt, err = check_pass(ro, rg, gpu_logits(gs, len(exits)), drafts, f"{which} {n}")
+            assert np.abs(ro.logits).max() < 8 and err < 1.7e-3
+        finally:
+            gs.free()
+
+
 def test_no_autocommit(tiny_pair):
     g, o = tiny_pair
     prompt = eegen.prompt_tokens(51, 20, o.vocab)
