@@ -9,7 +9,7 @@
 namespace ee {
 
 constexpr int SWAVES = 8;                // streaming waves: weight tiles -> MFMA
-constexpr int HWAVES = 4;                // helper waves: stage the input blocks while the others stream
+constexpr int HWAVES = 4;                // helper waves: work out what the epilogue needs while the others stream
 constexpr int WAVES = SWAVES + HWAVES;   // three per SIMD, 168 VGPRs each
 constexpr int WG_THREADS = WAVES * 64;
 constexpr int GROUP_TILES = 8;           // n-tiles whose accumulators a streaming wave keeps in registers at once
@@ -32,8 +32,7 @@ constexpr int KSPLIT_LOG2 = 2;           // many-row launches: workgroups (1 << 
 // ("k-steps" s = 0, 1, ...) and walks
 //   for group : for k-step s : for n-tile of the group : tile(n-tile, k-tile w + SWAVES*s)
 // keeping one accumulator per n-tile of the group in registers for the whole of K.  The order
-// does not depend on the number of rows; how many k-tiles of the input sit in LDS at a time
-// (StageLds) is chosen per launch.
+// does not depend on the number of rows.
 // In memory the tiles are interleaved over the whole chip: the i-th tile of the
 // sequence of wave w of workgroup g sits at tile slot (i*nwg + g)*SWAVES + w, so at any
 // moment all waves together read one contiguous window (measured: up to 15 % more
@@ -50,28 +49,29 @@ struct GemmPlan {
     // K split over workgroups (many-row launches): 1 << ksl consecutive workgroups share the same
     // n-tiles and take one slice of KTs k-tiles each (workgroup g: n-tiles of g >> ksl, slice
     // g & (splits - 1)); their partial tiles meet in memory and the one that arrives last adds them
-    // up and runs the epilogue.  A workgroup then copies only its slice of the input into LDS and
-    // has 1 << ksl times the n-tiles per input block.  ksl = 0, KTs = KT: no split.
+    // up and runs the epilogue.  A workgroup then reads only its slice of the input.  ksl = 0, KTs = KT: no split.
     int ksl, KTs;
 };
 
 // LDS map of one GEMM launch, chosen on the host from the rows of the launch:
-//   [input buffer 0][input buffer 1][input buffer 2] ... [misc]
-// An input block holds kbt k-tiles of the input as [k-tile][term][row][32] bf16 (both bf16
-// terms, all rows); with nkb > 1 blocks the helper waves fill the other buffers of a ring of
-// nbuf (2, or 3 when many rows leave room for short blocks only) while the streaming waves read one.  After a group's last block the same space holds the waves'
-// partial tiles for the cross-wave sum ([wave][n-tile of the chunk][row][16] floats, `chunk`
-// n-tiles at a time) and, behind them at zbuf_off, one [row][chunk*16] float tile for the
-// head's logits / the squares of the residual stream.
+//   [rings of the streaming waves | later: partial tiles] [misc]
+// While a group streams, wave w's ring of stages (weight tiles and input k-tiles) is the w-th
+// WAVE_LDS_KB kilobytes.  Afterwards the same space holds the waves' partial tiles for the
+// cross-wave sum ([wave][n-tile of the chunk][row][16] floats, `chunk` n-tiles at a time) and,
+// behind them at zbuf_off, one [row][chunk*16] float tile for the head's logits / the squares of the
+// residual stream.
 struct StageLds {
-    int kbt;         // k-tiles per input block (a multiple of SWAVES)
-    int nkb;         // input blocks along K
-    int nbuf;        // input buffers (1 when the whole of K fits one)
-    int xbuf_bytes;  // bytes of one input buffer
     int chunk;       // n-tiles reduced at a time
     int zbuf_off;
     int misc_off;
 };
+
+// Per-row partial results of the workgroups (sums of squares, argmax candidates) are stored [row][SS_LD],
+// one slot per workgroup.
+constexpr int SS_LD = 256;
+
+// GEMM inputs end with this many spare elements: a k-tile is copied in whole kilobytes.
+constexpr int X_SLACK = 512;
 
 // Units [u0, u1) of workgroup g.  Workgroups are dealt to the chip's 8 XCDs round-robin (XCD =
 // g % 8) and every XCD has its own path to memory, so the units are first split evenly over
@@ -149,17 +149,17 @@ struct Scratch {
     uint16_t *u;         // [Kpad_F/32][2][rows][32]  silu(gate)*up
     uint16_t *xa;        // [Kpad_d/32][2][rows][32]  h itself: input of an exit head's adapters
     uint16_t *t;         // [Kpad_A/32][2][rows][32]  the adapters' hidden units after the activation
-    float *ss_h;         // [nwg][rows_max]      partial sums of squares of the LM-head input's rows (head rows)
-    float *ss_a;         // [nwg][rows_max]      partial sums of h^2 after the FFN block / embedding
-    float *ss_f;         // [nwg][rows_max]      partial sums of h^2 after the attention block
+    float *ss_h;         // [rows_max][SS_LD]        partial sums of squares of the LM-head input's rows (head rows)
+    float *ss_a;         // [rows_max][SS_LD]        partial sums of h^2 after the FFN block / embedding
+    float *ss_f;         // [rows_max][SS_LD]        partial sums of h^2 after the attention block
     float *att_part;     // [items][ATT_ROWS][hd+2] attention partials (only when the position range is split)
     int *att_count;      // [units] items of the unit that have delivered their partials; zero between launches
     int *head_count;     // workgroups of a head launch that have delivered their candidates; zero between launches
     float *part;         // [K split][n-tile][rows][16] partial tiles of a launch whose K is split over workgroups
     int *part_count;     // [nwg] splits of a group of workgroups that have delivered their partial tiles; zero between launches
     float *logits;       // [heads][rows_max][V] when logits are kept
-    int2 *cand;          // [nwg][rows_max]      per-workgroup argmax candidates (value bits, index)
-    float *cand_sum;     // [nwg][rows_max]      sum over the workgroup's columns of exp(logit - candidate value)
+    int2 *cand;          // [rows_max][SS_LD]        per-workgroup argmax candidates (value bits, index)
+    float *cand_sum;     // [rows_max][SS_LD]        sum over the workgroup's columns of exp(logit - candidate value)
 };
 
 enum HeadKind { HEAD_NONE = 0, HEAD_EXIT = 1, HEAD_FINAL = 2, HEAD_PREFILL = 3 };

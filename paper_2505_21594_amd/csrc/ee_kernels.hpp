@@ -12,7 +12,7 @@
 //   HEAD    x_hat . W_lm^T, * rstd, argmax candidate and softmax denominator per workgroup
 //   ACCEPT  global argmax (lowest id wins ties), confidence, accept length, publication
 //           to pinned host memory, KV commit (run by the head launch's last workgroup).
-// Kernels: ee_gemm_kernel<MT> for the five GEMM kinds (MT = 16-row tiles of the pass, rows <= 48),
+// Kernels: ee_gemm_kernel<XC> for the GEMM kinds (rows <= 8 XC, at most 48),
 // ee_att_kernel, ee_misc_kernel (embedding).
 //
 // Every GEMM stage streams the weights once (HBM-bound).  A workgroup owns whole
@@ -141,19 +141,35 @@ __device__ __forceinline__ void wait_vmem()
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), other counters untouched
     asm volatile("" ::: "memory");
 }
-// at most n vector memory operations of this wave are still pending (n is rounded down to a
-// value with an instruction of its own, which only makes the wait stricter)
-__device__ __forceinline__ void wait_vmem_pending(int n)
+// One kilobyte from memory straight into LDS: lane l's 16 bytes at src + off land at LDS byte
+// dst + 16 l.  Inline assembly because the compiler makes every LDS read wait for all such loads it
+// knows of; here a stage is read while the next ones are on their way, and the kernels wait
+// themselves (wait_pending, then a barrier).  No vector register is written; M0, which nothing else in
+// these kernels uses, needs one wait state.
+__device__ __forceinline__ void load_lds_kb(const void *src, int off, unsigned dst)
 {
-#define EE_WAIT_CASE(N) case N: __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14)); break;
-    switch (min(n, 31)) {
-        EE_WAIT_CASE(0) EE_WAIT_CASE(1) EE_WAIT_CASE(2) EE_WAIT_CASE(3) EE_WAIT_CASE(4) EE_WAIT_CASE(5) EE_WAIT_CASE(6) EE_WAIT_CASE(7)
-        EE_WAIT_CASE(8) EE_WAIT_CASE(9) EE_WAIT_CASE(10) EE_WAIT_CASE(11) EE_WAIT_CASE(12) EE_WAIT_CASE(13) EE_WAIT_CASE(14) EE_WAIT_CASE(15)
-        EE_WAIT_CASE(16) EE_WAIT_CASE(17) EE_WAIT_CASE(18) EE_WAIT_CASE(19) EE_WAIT_CASE(20) EE_WAIT_CASE(21) EE_WAIT_CASE(22) EE_WAIT_CASE(23)
-        EE_WAIT_CASE(24) EE_WAIT_CASE(25) EE_WAIT_CASE(26) EE_WAIT_CASE(27) EE_WAIT_CASE(28) EE_WAIT_CASE(29) EE_WAIT_CASE(30) EE_WAIT_CASE(31)
-    }
-#undef EE_WAIT_CASE
-    asm volatile("" ::: "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(off), "s"(src), "s"(dst)
+                 : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_pending()   // at most N vector memory operations of this wave are pending
+{
+    static_assert(N < 64, "vmcnt has 6 bits");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ const void *uniform_ptr(const void *p)
+{
+    const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return reinterpret_cast<const void *>(((unsigned long long)hi << 32) | lo);
+}
+
+// LDS byte offset of the dynamic LDS block's start
+__device__ __forceinline__ unsigned lds_offset(const char *p)
+{
+    return __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<unsigned long long>((const EE_LDS char *)p));
 }
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits for every
 // vector memory operation of the wave, i.e. for all weight tiles a streaming wave has in
@@ -258,7 +274,7 @@ __device__ __host__ inline int wave_ksteps(int KT, int w) { return KT > w ? (KT 
 
 struct GemmIn {
     const uint16_t *x;  // the input (already scaled by the norm gain) as two bf16 terms, k-tile-major (x_index)
-    const float *ss;    // [nwg][rows_max] partial sums of squares for rstd, or nullptr
+    const float *ss;    // [rows][SS_LD] partial sums of squares for rstd, or nullptr
 };
 
 // GEMM inputs are stored the way the stages consume them: [k-tile][term][row][32] bf16 with
@@ -291,37 +307,26 @@ __device__ __forceinline__ void store_split4(uint16_t *x, int rows, int m, int k
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 1)) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
 }
 
-// Helper waves: copy k-tiles [kt0, kt0 + klen) of the input (all rows, both terms: one
-// contiguous range in memory) straight into LDS at dst.  One load instruction moves 64 x 16
-// bytes; no registers hold the data.  The caller waits (wait_vmem) before it tells the others.
-__device__ __forceinline__ int stage_block(const uint16_t *x, int rows, int kt0, int klen, char *dst, int hwave, int lane)
+// rstd[m] = 1/sqrt(sum_g ss[m][g] / d + eps) into LDS, fixed summation order; helper waves only, for
+// rows <= 8 XC.  A row's partial sums are one kilobyte (slots past the workgroups stay zero), all of a
+// wave's rows are requested together.  (With the slots of a row apart, as [g][m], these few kilobytes were
+// 64 cache lines per load: as many requests as the whole GEMM input, in front of the weight stream.)
+template <int XC>
+__device__ __forceinline__ void load_rstd(const float *ss, int rows, int d, float eps, float *rstd_lds, int hwave, int lane)
 {
-    const size_t tile_elems = (size_t)2 * rows * 32;          // one k-tile: both terms, all rows
-    const uint16_t *src = x + (size_t)kt0 * tile_elems;
-    const int nchunk = klen * 2 * rows * 4;                     // 16-byte chunks of the block
-    for (int c0 = hwave * 64; c0 < nchunk; c0 += HWAVES * 64)
-        if (c0 + lane < nchunk)
-            __builtin_amdgcn_global_load_lds((const EE_GLOBAL void *)(src + (size_t)(c0 + lane) * 8),
-                                             (EE_LDS void *)(dst + (size_t)c0 * 16), 16, 0, 0);
-    return nchunk > hwave * 64 ? (nchunk - hwave * 64 + HWAVES * 64 - 1) / (HWAVES * 64) : 0;  // load instructions of this wave
-}
-
-// rstd[m] = 1/sqrt(sum_g ss[g][m] / d + eps) into LDS, fixed summation order; helper waves only.
-// Ordinary loads, which the XCD's L2 serves to all but the first workgroup: every workgroup
-// reads the same few kilobytes.
-__device__ __forceinline__ void load_rstd(const float *ss, int nwg, int rows_max, int rows, int d, float eps,
-                                          float *rstd_lds, int hwave, int lane)
-{
-    for (int m = hwave; m < rows; m += HWAVES) {
-        float v[4];                                              // at most 256 workgroups: all four requested together
+    f32x4_t v[2 * XC];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = lane + 64 * j < nwg ? *as_global(ss + (size_t)(lane + 64 * j) * rows_max + m) : 0.f;
-        float s = 0.f;
+    for (int i = 0; i < 2 * XC; ++i) {
+        const int m = min(hwave + i * HWAVES, rows - 1);
+        v[i] = *as_global(reinterpret_cast<const f32x4_t *>(ss + (size_t)m * SS_LD + lane * 4));
+    }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s += v[j];
+    for (int i = 0; i < 2 * XC; ++i) {
+        float s = (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (lane == 0) rstd_lds[m] = 1.0f / sqrtf(s / (float)d + eps);
+        const int m = hwave + i * HWAVES;
+        if (lane == 0 && m < rows) rstd_lds[m] = 1.0f / sqrtf(s / (float)d + eps);
     }
 }
 
@@ -333,8 +338,8 @@ __device__ __forceinline__ bool cand_better(float v, int i, float bv, int bi)
 struct GemmEpi {           // what the O / DN / AU epilogue produces besides h
     const float *gain_xn;  // gain of the next GEMM input (xn), or nullptr
     const float *gain_xh;  // gain of the LM-head input (xh, at the exit's head rows), or nullptr
-    float *ss_out;         // [nwg][rows_max] partial sums of h^2, or nullptr
-    float *ss_head;        // [nwg][rows_max] partial sums of squares of the LM-head input's rows (at the head rows), or nullptr
+    float *ss_out;         // [rows][SS_LD] partial sums of h^2, or nullptr
+    float *ss_head;        // [head rows][SS_LD] partial sums of squares of the LM-head input's rows (at the head rows), or nullptr
     const float *bias;     // AD / AU: bias per output column
     int xa_out;            // DN: also emit h itself as the adapters' input (xa)
 };
@@ -614,193 +619,124 @@ __device__ __forceinline__ void split_finish(const PassArgs &a, int kind, int la
     }
 }
 
-// The streaming waves of a one-row-tile launch request the first EARLY_TILES tiles of their
-// sequence as soon as the launch's arguments are there, before the plan arithmetic and the jump
-// into the group's code (2 to 3 us on a cold instruction cache); the stage's first group takes
-// them over.  The input copy is NOT moved forward with them: a compute unit holds about 64
-// memory instructions in flight, whatever is requested first takes those slots, and the launch
-// is shortest when the HBM requests go first and the copy follows once they are back
-// (measured on the headline workload, ms per pass: neither early 3.38; tiles early 3.28; both
-// early 3.37; copy early 3.47; tiles early and the copy right behind them 3.39; copy first,
-// tiles behind it 3.45).
-constexpr int EARLY_TILES = 8;
-struct EarlyLoads {
-    uint4 tile[EARLY_TILES];
-};
-
-template <int MT>
-__device__ __forceinline__ void gemm_early(const GemmPlan &pl, const uint4 *__restrict__ W, EarlyLoads &early)
+// A streaming wave's ring of stages in LDS.  A stage is one k-step: NL weight tiles and the XC kilobytes
+// of the step's input k-tile.  As many stages as fit RING_KB (at least one; WAVE_LDS_KB holds the largest
+// stage, NL = 8 with XC = 6): eight waves then have 64 to 112 KB on their way.  More does not stream
+// faster, a compute unit's requests are served in order and the input's would wait behind
+// more weight tiles (ms per pass, headline workload, 8 / 12 / 19 KB: 3.16 / 3.18 / 3.19).
+constexpr int RING_KB = 8;
+constexpr int WAVE_LDS_KB = GROUP_TILES + (EE_MAX_ROWS + 7) / 8;
+template <int XC, int NL>
+constexpr int ring_depth()
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-#pragma unroll
-    for (int i = 0; i < EARLY_TILES; ++i) early.tile[i] = make_uint4(0u, 0u, 0u, 0u);
-    if constexpr (MT > 1) return;   // the accumulators of more row tiles need the registers
-    int nt0, n_local;
-    wg_units(pl, blockIdx.x, nt0, n_local);
-    if (n_local <= 0 || wave >= SWAVES) return;
-    const int nl = min(GROUP_TILES, n_local);
-    const int last = max(wave_ksteps(pl.KTs, wave) * nl - 1, 0);
-    const WRes wres = weight_resource(W);
-    const int wstep = pl.nwg * SWAVES * 1024;
-    const int woff = ((int)blockIdx.x * SWAVES + wave) * 1024;
-#pragma unroll
-    for (int i = 0; i < EARLY_TILES; ++i) early.tile[i] = load_tile16(wres, lane * 16, woff + min(i, last) * wstep);
+    constexpr int d = RING_KB / (NL + XC);
+    return d < 1 ? 1 : d;
 }
 
-// k-steps whose tiles a streaming wave keeps in flight, by n-tiles of the group: about 8 to 14
-// tiles (1 KB each), fewer where the accumulators of three row tiles need the registers.  More
-// does not stream faster: 12 and 16 tiles per wave measured the same pass time as 8 (what a
-// compute unit can have in flight is bounded by the hardware, about 64 KB).
-template <int MT, int NL>
-constexpr int ring_steps()
-{
-    constexpr int r = (8 + NL - 1) / NL;
-    return (MT == 3 && NL >= 5) ? 1 : r;
-}
-
-// One group of NL n-tiles (this workgroup's n-tiles nt_first .. nt_first + NL - 1) over all of K.
+// One group of NL n-tiles (this workgroup's n-tiles nt_first .. nt_first + NL - 1) over all of K,
+// for rows <= 8 XC (MT = 16-row tiles).
 //
-// Streaming wave w walks its k-steps s = 0 .. (k-tile w + SWAVES*s); per k-step it multiplies
-// the NL weight tiles of the step with the step's input rows (two bf16 terms, MT row tiles)
-// into NL x MT accumulators that stay in registers.  R k-steps of tiles are in flight: a step's
-// registers are refilled with the step R further on as soon as the step has been used.  Every load
-// is unconditional (the look-ahead is clamped to the group's last tile), nothing is pending
-// when the loop is entered and no other memory operation of the wave goes through the vector
-// path meanwhile: the compiler can then count the loads in flight and each use waits for
-// exactly its own tile (otherwise it waits for all of them, which halves what a wave pulls).
-//
-// The input reaches LDS in blocks of ly.kbt k-tiles, copied by the helper waves through a ring
-// of ly.nbuf buffers: later blocks are copied while block b is read; one barrier per block
-// boundary, the same for all twelve waves.
+// Streaming wave w walks its k-steps s = 0 .. (k-tile w + SWAVES*s).  Every k-tile of the input is
+// used by one wave only, so the wave brings both operands itself: the step's NL weight tiles and
+// the k-tile of the input (all rows, both bf16 terms: contiguous) travel from memory straight into a
+// ring of D stages in the wave's own part of LDS.  Nothing is shared between waves until the
+// cross-wave sum: there is no barrier in the stream, a wave waits for its own oldest stage, reads it,
+// requests the stage D further on into the same place and multiplies.
+// Weight tiles into NL x MT accumulators, two MFMAs (two input terms) each.
+// Bound by HBM: between the first request (2 us after entry) and the last tile the 7B shape streams at 6.2 to
+// 6.7 TB/s with 5 rows.  With helper waves that copied input blocks for all streaming waves, a barrier of
+// all waves per block and 8 tiles of every wave in registers instead (us per launch, 5 rows / 40
+// rows): QKV 20.4 / 36.2 -> 19.6 / 27.8, gate/up 31.5 / 43.4 -> 31.2 / 37.8, down 19.4 / 27.6 -> 19.0 / 27.0,
+// LM head 54 / 86 -> 51 / 70.
 //
 // Afterwards the accumulators go through LDS, `ly.chunk` n-tiles at a time, for the
 // cross-wave sum and the stage's epilogue (all waves).
-template <int MT, int NL>
+template <int XC, int NL>
 __device__ __forceinline__ void gemm_group(const PassArgs &a, int kind, int layer, const GemmPlan &pl, const StageLds &ly,
                                            const uint4 *__restrict__ W, const GemmIn &in, const GemmEpi &ep, const Misc &mi,
-                                           char *lds, int nt_first, int seq0, bool first_group, const EarlyLoads &early)
+                                           char *lds, int nt_first, int seq0, bool first_group)
 {
-    constexpr int R = ring_steps<MT, NL>();
+    constexpr int MT = (XC + 1) / 2, D = ring_depth<XC, NL>(), PER = NL + XC;
     const ModelDev &md = a.mdv;
     const int tid = opaque(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = a.rows;
-    const int S_max = wave_ksteps(pl.KTs, 0);     // k-steps of the busiest wave: everybody runs the loop this far
-    const int spb = ly.kbt / SWAVES;              // k-steps per input block
     f32x4_t acc[NL][MT];                          // streaming waves only
 
     if (wave < SWAVES) {
         // ---------------- streaming wave
+        const int S_w = wave_ksteps(pl.KTs, wave);
+        const int lane16 = lane * 16;
+        const size_t wstep = (size_t)pl.nwg * SWAVES * 1024;   // bytes from one tile of the wave's sequence to the next
+        const char *wp = reinterpret_cast<const char *>(W) + (size_t)seq0 * wstep + ((size_t)blockIdx.x * SWAVES + wave) * 1024;
+        const int tile_bytes = rows * 128;                     // one k-tile of the input: both terms, all rows
+        const char *xp = reinterpret_cast<const char *>(in.x) + (size_t)wave * tile_bytes;
+        const unsigned ring = lds_offset(lds) + wave * (WAVE_LDS_KB * 1024);
+        auto request = [&](unsigned dst) __attribute__((always_inline)) {   // the next stage of the sequence
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                load_lds_kb(wp, lane16, dst + i * 1024);
+                wp += wstep;
+            }
+#pragma unroll
+            for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, lane16, dst + (NL + i) * 1024);
+            xp += SWAVES * tile_bytes;
+        };
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if (i < S_w) request(ring + i * PER * 1024);
 #pragma unroll
         for (int nt = 0; nt < NL; ++nt)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-        const int S_w = wave_ksteps(pl.KTs, wave);
-        const WRes wres = weight_resource(W);
-        const int lane_off = lane * 16;
-        const int wstep = pl.nwg * SWAVES * 1024;  // bytes from one tile of the wave's sequence to the next
-        const int woff = ((seq0 * pl.nwg + (int)blockIdx.x) * SWAVES + wave) * 1024;  // the group's first tile
-        const int last = max(S_w * NL - 1, 0);     // the group's last tile of this wave (look-ahead is clamped to it)
-        uint4 buf[R][NL];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int nt = 0; nt < NL; ++nt) {
-                const int i = r * NL + nt;
-                if (MT == 1 && i < EARLY_TILES) {   // the stage's first group: requested at the start of the launch
-                    buf[r][nt] = early.tile[i < EARLY_TILES ? i : 0];
-                    if (!first_group) buf[r][nt] = load_tile16(wres, lane_off, woff + min(i, last) * wstep);
-                } else {
-                    buf[r][nt] = load_tile16(wres, lane_off, woff + min(i, last) * wstep);
-                }
-            }
         int brow[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) brow[mt] = min(mt * 16 + (lane & 15), rows - 1) * 64 + (lane >> 4) * 16;  // bytes inside a k-tile's hi rows
-        const int tile_bytes = rows * 128;         // one k-tile of the input: both terms, all rows
-        int blk_end = spb;                         // first k-step of the next input block
-        int blk = 0, blk_buf = 0;                  // the block being read and its buffer of the ring
-        int xoff = wave * tile_bytes;              // LDS byte offset of this wave's k-tile of step s, relative to s * SWAVES * tile_bytes
-        wait_vmem();                               // nothing pending at loop entry (see above)
-        lds_barrier();                             // input block 0 is in LDS
-        for (int s0 = 0; s0 < S_max; s0 += R) {
+        int slot = 0;
+        for (int s = 0; s < S_w; ++s) {
+            if (s + D <= S_w)
+                wait_pending<(D - 1) * PER>();     // the D - 1 stages requested after this one may still be on their way
+            else
+                wait_pending<0>();
+            const char *st = lds + wave * (WAVE_LDS_KB * 1024) + slot * (PER * 1024);
+            bf16x8_t w[NL], xh[MT], xl[MT];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int s = s0 + r;
-                if (s == blk_end && s < S_max) {   // next input block: the helpers have copied it into the next buffer of the ring
-                    lds_barrier();
-                    ++blk;
-                    blk_buf = blk_buf + 1 == ly.nbuf ? 0 : blk_buf + 1;
-                    xoff = wave * tile_bytes + blk_buf * ly.xbuf_bytes - blk * spb * SWAVES * tile_bytes;
-                    blk_end += spb;
-                }
-                // A wave whose k-steps have run out keeps loading (its last tile again) and multiplies
-                // with zeros: the stream loop then has no load under a condition.
-                const bool live = s < S_w;
-                const char *xs = lds + xoff + s * (SWAVES * tile_bytes);
+            for (int mt = 0; mt < MT; ++mt) {
+                xh[mt] = *reinterpret_cast<const bf16x8_t *>(st + NL * 1024 + brow[mt]);
+                xl[mt] = *reinterpret_cast<const bf16x8_t *>(st + NL * 1024 + brow[mt] + rows * 64);
+            }
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {  // row tile by row tile: one pair of input operands live at a time
-                    uint4 xh = make_uint4(0u, 0u, 0u, 0u), xl = xh;
-                    if (live) {
-                        xh = *reinterpret_cast<const uint4 *>(xs + brow[mt]);
-                        xl = *reinterpret_cast<const uint4 *>(xs + brow[mt] + rows * 64);
-                    }
-                    const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, xh), bl = __builtin_bit_cast(bf16x8_t, xl);
+            for (int nt = 0; nt < NL; ++nt) w[nt] = *reinterpret_cast<const bf16x8_t *>(st + nt * 1024 + lane16);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read: its place is free
+            if (s + D < S_w) request(ring + slot * (PER * 1024));
+            slot = slot + 1 == D ? 0 : slot + 1;
 #pragma unroll
-                    for (int nt = 0; nt < NL; ++nt)  // the two terms of a tile in separate sweeps: no MFMA waits for the one before it
-                        acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, buf[r][nt]), bh, acc[nt][mt], 0, 0, 0);
+            for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-                    for (int nt = 0; nt < NL; ++nt) {
-                        acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, buf[r][nt]), bl, acc[nt][mt], 0, 0, 0);
-                        // the tile's registers are free after its last use: refill them with the step R further on
-                        if (mt == MT - 1) buf[r][nt] = load_tile16(wres, lane_off, woff + min((s + R) * NL + nt, last) * wstep);
-                    }
-                }
+                for (int nt = 0; nt < NL; ++nt)    // the two terms of a tile in separate sweeps: no MFMA waits for the one before it
+                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nt], xh[mt], acc[nt][mt], 0, 0, 0);
+#pragma unroll
+                for (int nt = 0; nt < NL; ++nt)
+                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nt], xl[mt], acc[nt][mt], 0, 0, 0);
             }
         }
-    } else {
-        // ---------------- helper wave: input blocks, row factors, per-row cache addresses
+    } else if (first_group) {
+        // ---------------- helper wave: what the epilogue needs, row factors and per-row cache addresses
         const int hwave = wave - SWAVES;
-        // Input blocks through a ring of ly.nbuf buffers: nbuf - 1 blocks are requested ahead of the
-        // one being read, so that the copy of a block has the time of a whole block (or two) to arrive.
-        // Block b is announced (barrier) once its own loads have landed, i.e. when only the loads of
-        // the blocks requested after it are still pending.
-        int issued = 0, cnt[3] = {0, 0, 0};        // cnt[j % 3]: load instructions of block j (nbuf <= 3)
-        int next_buf = 0;                          // buffer of the ring the next requested block goes to (blocks are requested in order)
-        auto request = [&](int j) __attribute__((always_inline)) {
-            const int kt0 = j * ly.kbt;
-            cnt[j % 3] = stage_block(in.x, rows, kt0, min(ly.kbt, pl.KTs - kt0), lds + next_buf * ly.xbuf_bytes, hwave, lane);
-            next_buf = next_buf + 1 == ly.nbuf ? 0 : next_buf + 1;
-        };
-        for (; issued < max(ly.nbuf - 1, 1) && issued < ly.nkb; ++issued) request(issued);
-        for (int b = 0; b < ly.nkb; ++b) {
-            int after = 0;
-            for (int j = b + 1; j < issued; ++j) after += cnt[j % 3];
-            wait_vmem_pending(after);
-            lds_barrier();                         // block b ready; block b-1 no longer read: its buffer takes the next request
-            if (issued < ly.nkb) {
-                request(issued);
-                ++issued;
-            }
+        if (in.ss) load_rstd<XC>(in.ss, rows, pl.K, md.eps, mi.rstd, hwave, lane);
+        const int ht = tid - SWAVES * 64;
+        if (kind == G_QKV && ht < rows) {
+            const int m = ht;
+            const int pos = row_pos(a, m);
+            const int ses = a.mode == 1 ? 0 : div_small(m, a.M);
+            const int cbase = EE_SESS(a, ses, contig_base);
+            const int page = cbase >= 0 ? cbase + pos / KV_PAGE : as_global(EE_SESS(a, ses, page_table))[pos / KV_PAGE];
+            mi.pos[m] = pos;
+            mi.kvoff[m] = (((long long)layer * EE_SESS(a, ses, n_pages) + page) * md.H) * KV_PAGE * 2 * md.hd;  // record of head 0
         }
-        // what only the epilogue needs, once the input is on its way: row factors, cache addresses
-        // (ahead of the input copy they delayed the first MFMA of every launch by about 2 us)
-        if (first_group) {
-            if (in.ss) load_rstd(in.ss, a.nwg, md.rows_max, rows, pl.K, md.eps, mi.rstd, hwave, lane);
-            const int ht = tid - SWAVES * 64;
-            if (kind == G_QKV && ht < rows) {
-                const int m = ht;
-                const int pos = row_pos(a, m);
-                const int ses = a.mode == 1 ? 0 : div_small(m, a.M);
-                const int cbase = EE_SESS(a, ses, contig_base);
-                const int page = cbase >= 0 ? cbase + pos / KV_PAGE : as_global(EE_SESS(a, ses, page_table))[pos / KV_PAGE];
-                mi.pos[m] = pos;
-                mi.kvoff[m] = (((long long)layer * EE_SESS(a, ses, n_pages) + page) * md.H) * KV_PAGE * 2 * md.hd;  // record of head 0
-            }
-            wait_vmem();
-        }
+        wait_vmem();
     }
-    // ---- cross-wave sum and epilogue, ly.chunk n-tiles at a time (the input buffers are free now)
-    lds_barrier();                                 // every streaming wave is done with the input
+    // ---- cross-wave sum and epilogue, ly.chunk n-tiles at a time (the rings are free now)
+    lds_barrier();                                 // every streaming wave has read its last stage
     float *slots = reinterpret_cast<float *>(lds);
     for (int c0 = 0; c0 < NL; c0 += ly.chunk) {
         const int gn = min(ly.chunk, NL - c0);
@@ -828,10 +764,11 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, int kind, int laye
 }
 
 // One GEMM stage of this workgroup: its n-tiles in groups of up to GROUP_TILES.
-template <int MT>
+template <int XC>
 __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, int kind, int layer, const GemmPlan &pl, const StageLds &ly,
-                             const uint4 *__restrict__ W, const GemmIn &in_all, const GemmEpi &ep, char *lds, const EarlyLoads &early)
+                             const uint4 *__restrict__ W, const GemmIn &in_all, const GemmEpi &ep, char *lds)
 {
+    constexpr int MT = (XC + 1) / 2;
     const ModelDev &md = a.mdv;
     const int tid = opaque(threadIdx.x);
     const int rows = a.rows;
@@ -854,7 +791,7 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, int kind, int la
             const int nl = min(GROUP_TILES, n_local - g0);
             const bool first = g0 == 0;
 #define EE_GROUP(NLV) \
-    case NLV: gemm_group<MT, NLV>(a, kind, layer, pl, ly, W, in, ep, mi, lds, nt0 + g0, seq, first, early); break;
+    case NLV: gemm_group<XC, NLV>(a, kind, layer, pl, ly, W, in, ep, mi, lds, nt0 + g0, seq, first); break;
             switch (nl) {
                 EE_GROUP(1) EE_GROUP(2) EE_GROUP(3) EE_GROUP(4) EE_GROUP(5) EE_GROUP(6) EE_GROUP(7) EE_GROUP(8)
             }
@@ -866,12 +803,12 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, int kind, int la
     // what the workgroup hands to the following launch
     auto hand_over = [&](int slot, bool mine) __attribute__((always_inline)) {
         const float ss = mine ? mi.rowss[tid] : 0.f;
-        if (ep.ss_out) as_global_mut(ep.ss_out)[(size_t)slot * md.rows_max + tid] = ss;
-        if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)slot * md.rows_max + a.head_row0 + tid] = ss;
+        if (ep.ss_out) as_global_mut(ep.ss_out)[(size_t)tid * SS_LD + slot] = ss;
+        if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)(a.head_row0 + tid) * SS_LD + slot] = ss;
         if (kind == G_HEAD) {  // device-scope stores: the accept step may run in another workgroup of this launch
-            store_dev64(a.sc.cand + (size_t)slot * md.rows_max + tid,
+            store_dev64(a.sc.cand + (size_t)tid * SS_LD + slot,
                         make_uint2(__float_as_uint(mine ? mi.bestv[tid] : -INFINITY), (unsigned)(mine ? mi.besti[tid] : 0x7FFFFFFF)));
-            store_dev32(a.sc.cand_sum + (size_t)slot * md.rows_max + tid, mine ? mi.sume[tid] : 0.f);
+            store_dev32(a.sc.cand_sum + (size_t)tid * SS_LD + slot, mine ? mi.sume[tid] : 0.f);
         }
     };
     if (tid < rows) {
@@ -919,7 +856,7 @@ __device__ __forceinline__ void embed_stage(const PassArgs &a, char *lds)
     if (tid < rows) {
         float t = 0.f;
         for (int j = 0; j < nq; ++j) t += sq[tid * nq + j];
-        as_global_mut(a.sc.ss_a)[(size_t)blockIdx.x * md.rows_max + tid] = t;
+        as_global_mut(a.sc.ss_a)[(size_t)tid * SS_LD + blockIdx.x] = t;
     }
 }
 
@@ -1230,8 +1167,8 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
             c[j] = make_int2(__float_as_int(-INFINITY), 0x7FFFFFFF);
             sg[j] = 0.f;
             if (g < a.nwg) {
-                c[j] = load_cand(a.sc.cand + (size_t)g * md.rows_max + m);
-                sg[j] = load_dev32(a.sc.cand_sum + (size_t)g * md.rows_max + m);
+                c[j] = load_cand(a.sc.cand + (size_t)m * SS_LD + g);
+                sg[j] = load_dev32(a.sc.cand_sum + (size_t)m * SS_LD + g);
             }
         }
         float bv = -INFINITY;
@@ -1599,16 +1536,14 @@ __device__ __forceinline__ GemmEpi gemm_epi(const PassArgs &a, int kind, int lay
     return ep;
 }
 
-// The GEMM stage a.stage of the stage list.  MT = 16-row tiles of the pass (rows <= 16 * MT).
-template <int MT>
+// The GEMM stage a.stage of the stage list, for rows <= 8 XC.
+template <int XC>
 __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
-    EarlyLoads early;
-    gemm_early<MT>(a.plan0, a.W0, early);
     const StageDesc st = stage_decode(a, a.stage);
-    gemm_stage_t<MT>(a, st.kind, st.layer, a.plan0, a.lay, a.W0, gemm_input(a, st.kind), gemm_epi(a, st.kind, st.layer), lds, early);
+    gemm_stage_t<XC>(a, st.kind, st.layer, a.plan0, a.lay, a.W0, gemm_input(a, st.kind), gemm_epi(a, st.kind, st.layer), lds);
     if (a.fuse_accept) {
         // A head stage: the workgroup whose candidates arrive last also runs the accept step
         // (one launch less per head); the counter is left at zero.

@@ -77,37 +77,6 @@ __device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int 
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i + (size_t)rt * 512) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
 }
 
-// One kilobyte from memory straight into LDS: lane l's 16 bytes at src + off land at LDS byte
-// dst + 16 l.  Inline assembly because the compiler makes every LDS read wait for all such loads it
-// knows of; here a stage is read while the next ones are on their way, and the kernels wait
-// themselves (pf_wait, then a barrier).  No vector register is written; M0, which nothing else in
-// these kernels uses, needs one wait state.
-__device__ __forceinline__ void pf_load_lds(const void *src, int off, unsigned dst)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(off), "s"(src), "s"(dst)
-                 : "memory");
-}
-template <int N>
-__device__ __forceinline__ void pf_wait()   // at most N vector memory operations of this wave are pending
-{
-    static_assert(N < 64, "vmcnt has 6 bits");
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ const void *uniform_ptr(const void *p)
-{
-    const unsigned long long v = reinterpret_cast<unsigned long long>(p);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-    return reinterpret_cast<const void *>(((unsigned long long)hi << 32) | lo);
-}
-
-// LDS byte offset of the dynamic LDS block's start
-__device__ __forceinline__ unsigned lds_offset(const char *p)
-{
-    return __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<unsigned long long>((const EE_LDS char *)p));
-}
-
 // Stages of the ring a tile shape uses: what fits 64 to 72 KB, so that two workgroups share a
 // compute unit and one's barrier and epilogue run under the other's products.
 constexpr int pf_stages(int wn, int wm) { return (wn + 2 * wm) * 2 >= 32 ? 2 : ((wn + 2 * wm) * 2 >= 24 ? 3 : 4); }
@@ -171,10 +140,10 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
         const unsigned dst = lds0 + buf * STAGE;
 #pragma unroll
         for (int i = 0; i < WL; ++i)
-            pf_load_lds(wbase[i] + ((size_t)(kt >> 3) * wstride[i] + (kt & 7)) * 1024, lane16, dst + (wave * WL + i) * 1024);
+            load_lds_kb(wbase[i] + ((size_t)(kt >> 3) * wstride[i] + (kt & 7)) * 1024, lane16, dst + (wave * WL + i) * 1024);
 #pragma unroll
         for (int i = 0; i < XL; ++i)
-            pf_load_lds(xbase + (size_t)kt * xstep + (size_t)xrow[i] * 1024, lane16, dst + (BNT + term * BMT + xt0 + i) * 1024);
+            load_lds_kb(xbase + (size_t)kt * xstep + (size_t)xrow[i] * 1024, lane16, dst + (BNT + term * BMT + xt0 + i) * 1024);
     };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
@@ -201,9 +170,9 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
         // this wave's loads of stage kt have landed; after the barrier everybody's have, and nobody
         // reads the buffer of stage kt - 1 any more
         if (kt + NS - 2 < a.KT)
-            pf_wait<PER *(NS - 2)>();
+            wait_pending<PER *(NS - 2)>();
         else
-            pf_wait<0>();
+            wait_pending<0>();
         lds_barrier();
         if (kt + NS - 1 < a.KT) request(kt + NS - 1, buf == 0 ? NS - 1 : buf - 1);
         const char *st = lds + buf * STAGE;
@@ -386,7 +355,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
         const unsigned dst = lds0 + buf * STAGE + wave * PAGE_B;   // [page 0: K, V][page 1: K, V]
 #pragma unroll
         for (int f = 0; f < FR; ++f)                          // K: operand (32 values kt, term) = f; V: plain copy
-            pf_load_lds(uniform_ptr(src + (is_v ? f * 1024 : (f & 1) * HD * 2 + (f >> 1) * 64)), src_off, dst + f * 1024);
+            load_lds_kb(uniform_ptr(src + (is_v ? f * 1024 : (f & 1) * HD * 2 + (f >> 1) * 64)), src_off, dst + f * 1024);
     };
     request(0, 0);
 
@@ -401,7 +370,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
     }
     const int wave_last = a.pos0 + min(row0 + 16 * RT, a.rows) - 1;   // last position a row of this wave sees
     for (int step = 0; step < steps; ++step) {
-        pf_wait<0>();
+        wait_pending<0>();
         lds_barrier();
         if (step + 1 < steps) request(step + 1, (step + 1) & 1);
         if (step * 32 > wave_last || row0 >= a.rows) continue;
@@ -521,8 +490,8 @@ __global__ void __launch_bounds__(PF_THREADS) pf_embed_kernel(PfArgs a)
     if (threadIdx.x == 0) a.ss_out[m] = sq;
 }
 
-// one workgroup: the chunk's last row as the input of a one-row LM-head launch (xh, [nwg][rows_max] sums of squares)
-__global__ void __launch_bounds__(PF_THREADS) pf_last_kernel(PfArgs a, uint16_t *xh, float *ss_h, int nwg, int rows_max)
+// one workgroup: the chunk's last row as the input of a one-row LM-head launch (xh, sums of squares)
+__global__ void __launch_bounds__(PF_THREADS) pf_last_kernel(PfArgs a, uint16_t *xh, float *ss_h)
 {
     __shared__ float red[PF_THREADS / 64];
     const float *h = a.b.h + (size_t)(a.rows - 1) * a.d;
@@ -534,7 +503,7 @@ __global__ void __launch_bounds__(PF_THREADS) pf_last_kernel(PfArgs a, uint16_t 
         store_split4(xh, 1, 0, c, x);
     }
     sq = pf_block_sum(sq, red);
-    for (int g = threadIdx.x; g < nwg; g += PF_THREADS) ss_h[(size_t)g * rows_max] = g == 0 ? sq : 0.f;
+    for (int g = threadIdx.x; g < SS_LD; g += PF_THREADS) ss_h[g] = g == 0 ? sq : 0.f;
 }
 
 }  // namespace ee

@@ -121,7 +121,14 @@ typedef void (*pass_kernel_t)(PassArgs);
 
 static pass_kernel_t gemm_kernel(int rows)
 {
-    return rows <= 16 ? ee_gemm_kernel<1> : (rows <= 32 ? ee_gemm_kernel<2> : ee_gemm_kernel<3>);
+    switch ((rows + 7) / 8) {
+    case 1: return ee_gemm_kernel<1>;
+    case 2: return ee_gemm_kernel<2>;
+    case 3: return ee_gemm_kernel<3>;
+    case 4: return ee_gemm_kernel<4>;
+    case 5: return ee_gemm_kernel<5>;
+    default: return ee_gemm_kernel<6>;
+    }
 }
 
 static pass_kernel_t att_kernel(int hd) { return hd == 128 ? ee_att_kernel<128> : ee_att_kernel<64>; }
@@ -194,24 +201,8 @@ static bool plan_lds(const GemmPlan &p, int rows, size_t lds_total, StageLds &ly
     const size_t misc = (MISC_BYTES + 255) / 256 * 256;
     if (lds_total < misc + 4096) return false;
     const size_t avail = (lds_total - misc) / 256 * 256;
-    const size_t tile_bytes = (size_t)rows * 128;           // one k-tile of the input: two terms, all rows
-    const int KT8 = (p.KTs + SWAVES - 1) / SWAVES * SWAVES;   // the k-tiles one workgroup streams
     memset(&ly, 0, sizeof ly);
-    if ((size_t)KT8 * tile_bytes <= avail) {
-        ly.kbt = KT8;
-        ly.nkb = 1;
-        ly.nbuf = 1;
-    } else {
-        ly.nbuf = 2;
-        ly.kbt = (int)(avail / 2 / tile_bytes) / SWAVES * SWAVES;
-        if (ly.kbt < SWAVES) return false;
-        // blocks of one k-step per wave: a block is read faster than its copy arrives; a third
-        // buffer lets the copy run two blocks ahead
-        if (ly.kbt == SWAVES && avail / 3 / tile_bytes >= (size_t)SWAVES) ly.nbuf = 3;
-        ly.nkb = (p.KTs + ly.kbt - 1) / ly.kbt;
-        if (ly.nkb < ly.nbuf) ly.nbuf = std::max(ly.nkb, 1);
-    }
-    ly.xbuf_bytes = (int)((size_t)ly.kbt * tile_bytes);
+    if (avail < (size_t)SWAVES * WAVE_LDS_KB * 1024) return false;
     // cross-wave sum: SWAVES partial tiles plus one logits / squares tile per n-tile of a chunk
     int chunk = (int)(avail / ((size_t)rows * 64 * (SWAVES + 1)));
     chunk = std::min(chunk, GROUP_TILES);
@@ -406,7 +397,7 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
     ee_model *m = new (std::nothrow) ee_model();
     if (!m) return fail(EE_EDEVICE, "out of host memory");
     m->device = device;
-    m->nwg = std::min(prop.multiProcessorCount, 256);   // one workgroup per compute unit; the accept step reads at most 256 candidates per row
+    m->nwg = std::min(prop.multiProcessorCount, SS_LD);   // one workgroup per compute unit; the accept step reads at most 256 candidates per row
     c.max_rows = max_rows;
     c.n_workgroups = m->nwg;
     m->cfg = c;
@@ -493,7 +484,8 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             ee_model_free(m);
             return fail(EE_EDEVICE, "ee_model_load: not enough LDS");
         }
-        pass_kernel_t ks[6] = {gemm_kernel(16), gemm_kernel(32), gemm_kernel(48), att_kernel(64), att_kernel(128), ee_misc_kernel};
+        pass_kernel_t ks[] = {gemm_kernel(8), gemm_kernel(16), gemm_kernel(24), gemm_kernel(32), gemm_kernel(40), gemm_kernel(48),
+                              att_kernel(64), att_kernel(128), ee_misc_kernel};
         for (pass_kernel_t k : ks) {
             hipError_t fe = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->lds_budget);
@@ -809,15 +801,15 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
     const ModelDev &md = m->host_md;
     S_TRY(dev_alloc(s->allocs, &sc.h, (size_t)rows_max * d));
     S_TRY(dev_alloc(s->allocs, &sc.q, (size_t)rows_max * d));
-    S_TRY(dev_alloc(s->allocs, &sc.xn, (size_t)2 * rows_max * md.Kpad_d));
-    S_TRY(dev_alloc(s->allocs, &sc.xh, (size_t)2 * rows_max * md.Kpad_d));
-    S_TRY(dev_alloc(s->allocs, &sc.attn, (size_t)2 * rows_max * md.Kpad_d));
-    S_TRY(dev_alloc(s->allocs, &sc.u, (size_t)2 * rows_max * md.Kpad_F));
-    S_TRY(dev_alloc(s->allocs, &sc.xa, (size_t)2 * rows_max * md.Kpad_d));
-    S_TRY(dev_alloc(s->allocs, &sc.t, (size_t)2 * rows_max * std::max(md.Kpad_A, 32)));
-    S_TRY(dev_alloc(s->allocs, &sc.ss_h, (size_t)m->nwg * rows_max));
-    S_TRY(dev_alloc(s->allocs, &sc.ss_a, (size_t)m->nwg * rows_max));
-    S_TRY(dev_alloc(s->allocs, &sc.ss_f, (size_t)m->nwg * rows_max));
+    S_TRY(dev_alloc(s->allocs, &sc.xn, (size_t)2 * rows_max * md.Kpad_d + X_SLACK));
+    S_TRY(dev_alloc(s->allocs, &sc.xh, (size_t)2 * rows_max * md.Kpad_d + X_SLACK));
+    S_TRY(dev_alloc(s->allocs, &sc.attn, (size_t)2 * rows_max * md.Kpad_d + X_SLACK));
+    S_TRY(dev_alloc(s->allocs, &sc.u, (size_t)2 * rows_max * md.Kpad_F + X_SLACK));
+    S_TRY(dev_alloc(s->allocs, &sc.xa, (size_t)2 * rows_max * md.Kpad_d + X_SLACK));
+    S_TRY(dev_alloc(s->allocs, &sc.t, (size_t)2 * rows_max * std::max(md.Kpad_A, 32) + X_SLACK));
+    S_TRY(dev_alloc(s->allocs, &sc.ss_h, (size_t)SS_LD * rows_max));
+    S_TRY(dev_alloc(s->allocs, &sc.ss_a, (size_t)SS_LD * rows_max));
+    S_TRY(dev_alloc(s->allocs, &sc.ss_f, (size_t)SS_LD * rows_max));
     {
         // items = units * splits; splits are chosen per pass and clamped to this room.  Units: a
         // batch of sessions with one chunk of rows each, or one session with the rows of a prefill chunk.
@@ -848,8 +840,8 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
             S_TRY(dev_alloc(s->allocs, &sc.part_count, (size_t)m->nwg));
         }
     }
-    S_TRY(dev_alloc(s->allocs, &sc.cand, (size_t)m->nwg * rows_max));
-    S_TRY(dev_alloc(s->allocs, &sc.cand_sum, (size_t)m->nwg * rows_max));
+    S_TRY(dev_alloc(s->allocs, &sc.cand, (size_t)SS_LD * rows_max));
+    S_TRY(dev_alloc(s->allocs, &sc.cand_sum, (size_t)SS_LD * rows_max));
     S_HIP(hipDeviceSynchronize());
 #undef S_TRY
 #undef S_HIP
@@ -1177,7 +1169,7 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
             p.rows = rows;
             p.d = c.d_model;
             p.gain = m->host_md.g_final;
-            hipLaunchKernelGGL(pf_last_kernel, dim3(1), dim3(PF_THREADS), 0, s->stream, p, s->sc.xh, s->sc.ss_h, m->nwg, c.max_rows);
+            hipLaunchKernelGGL(pf_last_kernel, dim3(1), dim3(PF_THREADS), 0, s->stream, p, s->sc.xh, s->sc.ss_h);
             HIP_TRY(hipGetLastError());
             a.layer_begin = c.n_layers;
             a.do_embed = 0;
@@ -1275,17 +1267,17 @@ static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_ma
     memset(&sc, 0, sizeof sc);
     sc.h = reinterpret_cast<float *>(take(rows * d * 4));
     sc.q = reinterpret_cast<float *>(take(rows * d * 4));
-    sc.xn = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
-    sc.xh = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
-    sc.attn = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
-    sc.u = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_F * 2));
-    sc.xa = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
-    sc.t = reinterpret_cast<uint16_t *>(take(2 * rows * std::max(md.Kpad_A, 32) * 2));
-    sc.ss_h = reinterpret_cast<float *>(take((size_t)m->nwg * md.rows_max * 4));
-    sc.ss_a = reinterpret_cast<float *>(take((size_t)m->nwg * md.rows_max * 4));
-    sc.ss_f = reinterpret_cast<float *>(take((size_t)m->nwg * md.rows_max * 4));
-    sc.cand = reinterpret_cast<int2 *>(take((size_t)m->nwg * md.rows_max * 8));
-    sc.cand_sum = reinterpret_cast<float *>(take((size_t)m->nwg * md.rows_max * 4));
+    sc.xn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+    sc.xh = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+    sc.attn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+    sc.u = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_F + X_SLACK) * 2));
+    sc.xa = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+    sc.t = reinterpret_cast<uint16_t *>(take((2 * rows * std::max(md.Kpad_A, 32) + X_SLACK) * 2));
+    sc.ss_h = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+    sc.ss_a = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+    sc.ss_f = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+    sc.cand = reinterpret_cast<int2 *>(take((size_t)SS_LD * md.rows_max * 8));
+    sc.cand_sum = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
     sc.att_count = reinterpret_cast<int *>(take((size_t)md.H * 4));
     sc.head_count = reinterpret_cast<int *>(take(4));
     sc.logits = lead->sc.logits;   // kept logits are an output of the session, not scratch

@@ -405,6 +405,12 @@ def test_empty_cache_and_exit_after_every_layer(model_dir):
         g.free()
 
 
+# rows at both edges of every number of kilobytes a k-tile of the input has (8 rows each): 8, 9, 16, 18, 25, 32, 33, 40, 42
+@pytest.mark.parametrize("B,gamma", [(1, 7), (1, 8), (2, 7), (2, 8), (5, 4), (4, 7), (3, 10), (5, 7), (6, 6)])
+def test_rows_at_the_edges_of_input_kilobytes(model_dir, B, gamma):
+    test_batch_shapes(model_dir, B, gamma, 48)
+
+
 @pytest.mark.parametrize("B,gamma,max_rows", [(5, 2, 15), (7, 1, 14), (3, 7, 24), (6, 4, 30), (3, 15, 48), (16, 2, 48)])
 def test_batch_shapes(model_dir, B, gamma, max_rows):
     """Batches of one, two and three 16-row tiles with ragged last tiles (15, 14, 24, 30, 48
