@@ -315,7 +315,7 @@ def main():
     pass_gbps = mean_bytes / (mean_dev_ms * 1e-3) / 1e9
     achieved = g_bytes / (g_ms * 1e-3) / 1e9
     committed = sum(a + B for a in accepted)
-    kernel_name = "ee_gemm_kernel<%d>" % ((B * M + 7) // 8)
+    kernel_name = "ee_gemm_kernel<*,%d>" % ((B * M + 7) // 8)   # all GEMM kinds
     out = {
         "metric": "verify passes/s (Llama2-7B-shape, gamma=4, ctx 512)" if args.workload == "llama7b_g4_ctx512"
         else f"verify passes/s ({args.workload})",

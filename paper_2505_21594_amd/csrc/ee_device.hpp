@@ -110,7 +110,6 @@ __host__ __device__ inline void unit_range(int U, int nwg, int g, int &u0, int &
 
 enum RowPerm { PERM_NONE = 0, PERM_QKV = 1, PERM_GU = 2 };
 enum GemmKind { G_QKV = 0, G_O = 1, G_GU = 2, G_DN = 3, G_HEAD = 4, G_AD = 5, G_AU = 6, G_KINDS = 7 };  // AD / AU: an exit head's adapter, down and up
-enum StageType { ST_EMBED = 0, ST_GEMM = 1, ST_ATT = 2, ST_ACCEPT = 3, ST_NONE = 4 };
 
 struct ModelDev {
     int L, d, H, hd, F, V;
@@ -187,7 +186,7 @@ struct PassArgs {
     const int *pf_tokens;                // prefill: [rows] token ids, < 0 => embedding row
     const uint16_t *pf_emb;              // prefill: [rows][d] bf16
     int pf_pos0;                         // prefill: position of row 0
-    int layer_begin, layer_end;          // layers [begin, end) of this segment, 0-based
+    int layer_begin, layer_end;          // (host) layers [begin, end) of this segment, 0-based
     int do_embed;
     int head_kind, head_idx;             // head_idx: result slot of the (first) head of this segment's head launch
     const float *head_gain;
@@ -202,7 +201,10 @@ struct PassArgs {
     int att_splits;
     int H, d, Kpad_d;                    // copies of the model descriptor's fields for the attention kernel
     float att_scale;
-    int stage;                           // index of this launch's stage in the segment's stage list
+    int layer;                           // layer of this launch's stage
+    const float *gain_xn, *gain_xh;      // O, DN: gain of the next GEMM input; DN, AU: gain of the LM head's input (each may be null)
+    const float *bias;                   // AD, AU: bias per output column
+    int xa_out;                          // DN: also emit h itself as the adapters' input
     const SessDev *sess;                 // device array [n_sess]
     SessDev sess0;                       // copy of sess[0]
     SampleDev sm;

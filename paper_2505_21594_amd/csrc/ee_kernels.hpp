@@ -12,7 +12,7 @@
 //   HEAD    x_hat . W_lm^T, * rstd, argmax candidate and softmax denominator per workgroup
 //   ACCEPT  global argmax (lowest id wins ties), confidence, accept length, publication
 //           to pinned host memory, KV commit (run by the head launch's last workgroup).
-// Kernels: ee_gemm_kernel<XC> for the GEMM kinds (rows <= 8 XC, at most 48),
+// Kernels: ee_gemm_kernel<KIND, XC> for the GEMM kinds (rows <= 8 XC, at most 48),
 // ee_att_kernel, ee_misc_kernel (embedding).
 //
 // Every GEMM stage streams the weights once (HBM-bound).  A workgroup owns whole
@@ -347,14 +347,15 @@ struct GemmEpi {           // what the O / DN / AU epilogue produces besides h
 // Epilogue of one chunk of gn n-tiles starting at n-tile nt_first: sum the nsum partial tiles in
 // the slot buffer (the streaming waves', or the K splits' when K is split over workgroups; fixed
 // order), apply the stage's element-wise tail.  All threads.
-__device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int layer, const StageLds &ly, int nt_first,
+template <int KIND>
+__device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds &ly, int nt_first,
                                               int gn, int rows, const GemmEpi &ep, const Misc &mi, char *lds, const int nsum)
 {
     const ModelDev &md = a.mdv;
     const float *slots = reinterpret_cast<const float *>(lds);
     const int tid = opaque(threadIdx.x);
     const size_t wstride = (size_t)ly.chunk * rows * 16;  // floats per wave in the slot buffer
-    if (kind == G_GU) {
+    if (KIND == G_GU) {
         const int items = (gn >> 1) * rows * 4;
         for (int idx = tid; idx < items; idx += WG_THREADS) {
             int p = div_small(idx, rows * 4), rem = idx - p * rows * 4;
@@ -390,14 +391,14 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
         // sum, these loads were two memory latencies at the end of every launch).
         f32x4_t g_a = (f32x4_t){0.f, 0.f, 0.f, 0.f}, g_b = g_a, g_c = g_a;
         int qkv_sect = 0, qkv_c = 0, qkv_head = 0, qkv_e = 0, qkv_ses = 0;
-        if (kind == G_O || kind == G_DN || kind == G_AU) {
+        if (KIND == G_O || KIND == G_DN || KIND == G_AU) {
             if (n < md.d) {
                 g_a = *as_global(reinterpret_cast<const f32x4_t *>(a.sc.h + (size_t)m * md.d + n));
-                if (kind == G_AU) g_b = *as_global(reinterpret_cast<const f32x4_t *>(ep.bias + n));
+                if (KIND == G_AU) g_b = *as_global(reinterpret_cast<const f32x4_t *>(ep.bias + n));
                 if (ep.gain_xn) g_b = *as_global(reinterpret_cast<const f32x4_t *>(ep.gain_xn + n));
                 if (ep.gain_xh) g_c = *as_global(reinterpret_cast<const f32x4_t *>(ep.gain_xh + n));
             }
-        } else if (kind == G_QKV) {
+        } else if (KIND == G_QKV) {
             qkv_sect = div_small(n, md.d);
             qkv_c = n - qkv_sect * md.d;
             qkv_head = div_small(qkv_c, md.hd);
@@ -405,7 +406,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
             qkv_ses = a.mode == 1 ? 0 : div_small(m, a.M);
             if (qkv_sect < 2)  // (cos, sin) of the row's position for the RoPE pairs of these four columns
                 g_a = *as_global(reinterpret_cast<const f32x4_t *>(EE_SESS(a, qkv_ses, rope) + (size_t)mi.pos[m] * (md.hd >> 1) + (qkv_e >> 1)));
-        } else if (kind == G_AD) {
+        } else if (KIND == G_AD) {
             if (n < md.A) g_a = *as_global(reinterpret_cast<const f32x4_t *>(ep.bias + n));
         }
         const float *sp = slots + ((size_t)ntg * rows + m) * 16 + qd * 4;
@@ -415,7 +416,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
             float4 x = *reinterpret_cast<const float4 *>(sp + w * wstride);
             S.x += x.x; S.y += x.y; S.z += x.z; S.w += x.w;
         }
-        if (kind == G_AD) {
+        if (KIND == G_AD) {
             // hidden units of the exit head's adapters: silu(W_down . h + b_down)
             if (n < md.A) {
                 const f32x4_t b = g_a;
@@ -424,13 +425,13 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
                 for (int e = 0; e < 4; ++e) o[e] = pre[e] / (1.0f + __expf(-pre[e]));
                 store_split4(a.sc.t, rows, m, n, o);
             }
-        } else if (kind == G_O || kind == G_DN || kind == G_AU) {
+        } else if (KIND == G_O || KIND == G_DN || KIND == G_AU) {
             float sq = 0.f;
             if (n < md.d) {
                 EE_GLOBAL f32x4_t *hp = reinterpret_cast<EE_GLOBAL f32x4_t *>(as_global_mut(a.sc.h) + (size_t)m * md.d + n);
                 const f32x4_t hv = g_a;
                 float v[4] = {hv[0] + S.x, hv[1] + S.y, hv[2] + S.z, hv[3] + S.w};
-                if (kind == G_AU) {  // a side branch: a = h + W_up . t + b_up feeds the exit's LM head, h stays as it is
+                if (KIND == G_AU) {  // a side branch: a = h + W_up . t + b_up feeds the exit's LM head, h stays as it is
                     const f32x4_t b = g_b;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] += b[e];
@@ -451,7 +452,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
                 }
             }
             zbuf[idx] = sq;  // (ntg, m, quad) order
-        } else if (kind == G_QKV) {
+        } else if (KIND == G_QKV) {
             const int d = md.d, hd = md.hd;
             const float rs = mi.rstd[m];
             float v[4] = {S.x * rs, S.y * rs, S.z * rs, S.w * rs};
@@ -505,7 +506,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
             }
         }
     }
-    if (kind == G_O || kind == G_DN || kind == G_AU) {
+    if (KIND == G_O || KIND == G_DN || KIND == G_AU) {
         lds_barrier();
         if (tid < rows) {  // this chunk's sum of squares per row, fixed order
             float t = 0.f;
@@ -514,7 +515,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, int kind, int l
             mi.rowss[tid] += t;
         }
     }
-    if (kind == G_HEAD) {
+    if (KIND == G_HEAD) {
         lds_barrier();
         const int lane = tid & 63, wave = tid >> 6;
         for (int m = wave; m < rows; m += WAVES) {
@@ -586,7 +587,8 @@ __device__ __forceinline__ void partial_store(const PassArgs &a, const GemmPlan 
 // counter; the workgroup that arrives last (the counter goes back to zero for the next launch)
 // fetches all splits' partial tiles, chunk by chunk, into the slot buffer in split order and
 // runs the epilogue on them.  The result does not depend on who arrives last; nothing waits.
-__device__ __forceinline__ void split_finish(const PassArgs &a, int kind, int layer, const GemmPlan &pl, const StageLds &ly,
+template <int KIND>
+__device__ __forceinline__ void split_finish(const PassArgs &a, const GemmPlan &pl, const StageLds &ly,
                                              const GemmEpi &ep, const Misc &mi, char *lds, int nt0, int n_local)
 {
     const int tid = opaque(threadIdx.x);
@@ -614,7 +616,7 @@ __device__ __forceinline__ void split_finish(const PassArgs &a, int kind, int la
                 load_dev128(part, (int)((((size_t)s * pl.NT + nt0 + c0) * rows * 16 + (size_t)rem * 4) * sizeof(float)));
         }
         lds_barrier();
-        gemm_epilogue(a, kind, layer, ly, nt0 + c0, gn, rows, ep, mi, lds, ks);
+        gemm_epilogue<KIND>(a, ly, nt0 + c0, gn, rows, ep, mi, lds, ks);
         lds_barrier();
     }
 }
@@ -651,12 +653,13 @@ constexpr int ring_depth()
 //
 // Afterwards the accumulators go through LDS, `ly.chunk` n-tiles at a time, for the
 // cross-wave sum and the stage's epilogue (all waves).
-template <int XC, int NL>
-__device__ __forceinline__ void gemm_group(const PassArgs &a, int kind, int layer, const GemmPlan &pl, const StageLds &ly,
+template <int KIND, int XC, int NL>
+__device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl, const StageLds &ly,
                                            const uint4 *__restrict__ W, const GemmIn &in, const GemmEpi &ep, const Misc &mi,
                                            char *lds, int nt_first, int seq0, bool first_group)
 {
     constexpr int MT = (XC + 1) / 2, D = ring_depth<XC, NL>(), PER = NL + XC;
+    constexpr int NW = MT == 3 && NL > 4 ? 4 : NL;   // weight tiles read at a time (registers: three waves per SIMD)
     const ModelDev &md = a.mdv;
     const int tid = opaque(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = a.rows;
@@ -698,25 +701,31 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, int kind, int laye
             else
                 wait_pending<0>();
             const char *st = lds + wave * (WAVE_LDS_KB * 1024) + slot * (PER * 1024);
-            bf16x8_t w[NL], xh[MT], xl[MT];
+            bf16x8_t w[NW], xh[MT], xl[MT];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 xh[mt] = *reinterpret_cast<const bf16x8_t *>(st + NL * 1024 + brow[mt]);
                 xl[mt] = *reinterpret_cast<const bf16x8_t *>(st + NL * 1024 + brow[mt] + rows * 64);
             }
 #pragma unroll
-            for (int nt = 0; nt < NL; ++nt) w[nt] = *reinterpret_cast<const bf16x8_t *>(st + nt * 1024 + lane16);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read: its place is free
-            if (s + D < S_w) request(ring + slot * (PER * 1024));
-            slot = slot + 1 == D ? 0 : slot + 1;
+            for (int n0 = 0; n0 < NL; n0 += NW) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
+                for (int i = 0; i < NW; ++i)
+                    if (n0 + i < NL) w[i] = *reinterpret_cast<const bf16x8_t *>(st + (n0 + i) * 1024 + lane16);
+                if (n0 + NW >= NL) {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read: its place is free
+                    if (s + D < S_w) request(ring + slot * (PER * 1024));
+                    slot = slot + 1 == D ? 0 : slot + 1;
+                }
 #pragma unroll
-                for (int nt = 0; nt < NL; ++nt)    // the two terms of a tile in separate sweeps: no MFMA waits for the one before it
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nt], xh[mt], acc[nt][mt], 0, 0, 0);
+                for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-                for (int nt = 0; nt < NL; ++nt)
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nt], xl[mt], acc[nt][mt], 0, 0, 0);
+                    for (int i = 0; i < NW; ++i)   // the two terms of a tile in separate sweeps: no MFMA waits for the one before it
+                        if (n0 + i < NL) acc[n0 + i][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], xh[mt], acc[n0 + i][mt], 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < NW; ++i)
+                        if (n0 + i < NL) acc[n0 + i][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], xl[mt], acc[n0 + i][mt], 0, 0, 0);
+                }
             }
         }
     } else if (first_group) {
@@ -724,14 +733,14 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, int kind, int laye
         const int hwave = wave - SWAVES;
         if (in.ss) load_rstd<XC>(in.ss, rows, pl.K, md.eps, mi.rstd, hwave, lane);
         const int ht = tid - SWAVES * 64;
-        if (kind == G_QKV && ht < rows) {
+        if (KIND == G_QKV && ht < rows) {
             const int m = ht;
             const int pos = row_pos(a, m);
             const int ses = a.mode == 1 ? 0 : div_small(m, a.M);
             const int cbase = EE_SESS(a, ses, contig_base);
             const int page = cbase >= 0 ? cbase + pos / KV_PAGE : as_global(EE_SESS(a, ses, page_table))[pos / KV_PAGE];
             mi.pos[m] = pos;
-            mi.kvoff[m] = (((long long)layer * EE_SESS(a, ses, n_pages) + page) * md.H) * KV_PAGE * 2 * md.hd;  // record of head 0
+            mi.kvoff[m] = (((long long)a.layer * EE_SESS(a, ses, n_pages) + page) * md.H) * KV_PAGE * 2 * md.hd;  // record of head 0
         }
         wait_vmem();
     }
@@ -758,14 +767,14 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, int kind, int laye
         if (MT > 1 && pl.ksl)   // (K is split only for launches of more than one row tile)
             partial_store(a, pl, ly, nt_first + c0, gn, rows, lds);
         else
-            gemm_epilogue(a, kind, layer, ly, nt_first + c0, gn, rows, ep, mi, lds, SWAVES);
+            gemm_epilogue<KIND>(a, ly, nt_first + c0, gn, rows, ep, mi, lds, SWAVES);
         lds_barrier();
     }
 }
 
 // One GEMM stage of this workgroup: its n-tiles in groups of up to GROUP_TILES.
-template <int XC>
-__device__ __forceinline__ void gemm_stage_t(const PassArgs &a, int kind, int layer, const GemmPlan &pl, const StageLds &ly,
+template <int KIND, int XC>
+__device__ __forceinline__ void gemm_stage_t(const PassArgs &a, const GemmPlan &pl, const StageLds &ly,
                              const uint4 *__restrict__ W, const GemmIn &in_all, const GemmEpi &ep, char *lds)
 {
     constexpr int MT = (XC + 1) / 2;
@@ -791,21 +800,21 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, int kind, int la
             const int nl = min(GROUP_TILES, n_local - g0);
             const bool first = g0 == 0;
 #define EE_GROUP(NLV) \
-    case NLV: gemm_group<XC, NLV>(a, kind, layer, pl, ly, W, in, ep, mi, lds, nt0 + g0, seq, first); break;
+    case NLV: gemm_group<KIND, XC, NLV>(a, pl, ly, W, in, ep, mi, lds, nt0 + g0, seq, first); break;
             switch (nl) {
                 EE_GROUP(1) EE_GROUP(2) EE_GROUP(3) EE_GROUP(4) EE_GROUP(5) EE_GROUP(6) EE_GROUP(7) EE_GROUP(8)
             }
 #undef EE_GROUP
             seq += S0 * nl;
         }
-        if (MT > 1 && pl.ksl) split_finish(a, kind, layer, pl, ly, ep, mi, lds, nt0, n_local);
+        if (MT > 1 && pl.ksl) split_finish<KIND>(a, pl, ly, ep, mi, lds, nt0, n_local);
     }
     // what the workgroup hands to the following launch
     auto hand_over = [&](int slot, bool mine) __attribute__((always_inline)) {
         const float ss = mine ? mi.rowss[tid] : 0.f;
         if (ep.ss_out) as_global_mut(ep.ss_out)[(size_t)tid * SS_LD + slot] = ss;
         if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)(a.head_row0 + tid) * SS_LD + slot] = ss;
-        if (kind == G_HEAD) {  // device-scope stores: the accept step may run in another workgroup of this launch
+        if (KIND == G_HEAD) {  // device-scope stores: the accept step may run in another workgroup of this launch
             store_dev64(a.sc.cand + (size_t)tid * SS_LD + slot,
                         make_uint2(__float_as_uint(mine ? mi.bestv[tid] : -INFINITY), (unsigned)(mine ? mi.besti[tid] : 0x7FFFFFFF)));
             store_dev32(a.sc.cand_sum + (size_t)tid * SS_LD + slot, mine ? mi.sume[tid] : 0.f);
@@ -838,7 +847,7 @@ __device__ __forceinline__ void embed_stage(const PassArgs &a, char *lds)
     const int n0 = blockIdx.x * cw;
     const int nq = max(0, min(cw, d - n0)) >> 2;          // quads of columns here
     float *sq = reinterpret_cast<float *>(lds);           // [rows][cw/4]
-    const float *gain = md.g_attn + (size_t)a.layer_begin * d;
+    const float *gain = md.g_attn;
     for (int it = tid; it < rows * nq; it += WG_THREADS) {
         int m = div_small(it, nq), c = n0 + (it - m * nq) * 4;
         int tok = row_token(a, m);
@@ -1450,54 +1459,14 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
 
 // ------------------------------------------------------------------ kernels of the pass
 //
-// Stage list of a segment: [EMBED] { QKV ATT O GU DN } x layers [HEAD]; one launch per stage.
+// Stage list of a segment: [EMBED] { QKV ATT O GU DN } x layers [AD AU] [HEAD]; one launch per stage.
 // The accept step runs inside the head's launch, in the workgroup that finishes last.
 
-struct StageDesc {
-    int type, kind, layer;
-};
-
-__device__ __forceinline__ StageDesc stage_decode(const PassArgs &a, int ph)
+// The input and what the epilogue produces, by GEMM kind (what varies inside a kind travels in the arguments).
+template <int KIND>
+__device__ __forceinline__ GemmIn gemm_input(const PassArgs &a)
 {
-    StageDesc sd = {ST_NONE, 0, 0};
-    const int per_layer = 5;
-    int idx = ph - (a.do_embed ? 1 : 0);
-    if (idx < 0) {
-        sd.type = ST_EMBED;
-        return sd;
-    }
-    const int nl = a.layer_end - a.layer_begin;
-    if (idx < per_layer * nl) {
-        int li = idx / per_layer, r = idx - li * per_layer;
-        sd.layer = a.layer_begin + li;
-        if (r == 0) {
-            sd.type = ST_GEMM;
-            sd.kind = G_QKV;
-        } else if (r == 1) {
-            sd.type = ST_ATT;
-        } else {
-            sd.type = ST_GEMM;
-            sd.kind = G_O + (r - 2);
-        }
-        return sd;
-    }
-    idx -= per_layer * nl;
-    if (a.head_kind != HEAD_NONE) {  // [AD AU] [HEAD]
-        const int n_ad = a.adapter ? 2 : 0;
-        if (idx < n_ad) {
-            sd.type = ST_GEMM;
-            sd.kind = G_AD + idx;
-        } else if (idx == n_ad && a.head_stage) {
-            sd.type = ST_GEMM;
-            sd.kind = G_HEAD;
-        }
-    }
-    return sd;
-}
-
-__device__ __forceinline__ GemmIn gemm_input(const PassArgs &a, int kind)
-{
-    switch (kind) {
+    switch (KIND) {
     case G_QKV: return GemmIn{a.sc.xn, a.sc.ss_a};
     case G_O: return GemmIn{a.sc.attn, nullptr};
     case G_GU: return GemmIn{a.sc.xn, a.sc.ss_f};
@@ -1508,44 +1477,42 @@ __device__ __forceinline__ GemmIn gemm_input(const PassArgs &a, int kind)
     }
 }
 
-__device__ __forceinline__ GemmEpi gemm_epi(const PassArgs &a, int kind, int layer)
+template <int KIND>
+__device__ __forceinline__ GemmEpi gemm_epi(const PassArgs &a)
 {
-    const ModelDev &md = a.mdv;
     GemmEpi ep = {nullptr, nullptr, nullptr, nullptr, nullptr, 0};
-    if (kind == G_O) {
-        ep.gain_xn = md.g_ffn + (size_t)layer * md.d;
+    if (KIND == G_O) {
+        ep.gain_xn = a.gain_xn;
         ep.ss_out = a.sc.ss_f;
-    } else if (kind == G_DN) {
-        if (layer + 1 < md.L) ep.gain_xn = md.g_attn + (size_t)(layer + 1) * md.d;
-        if (layer + 1 == a.layer_end && a.head_kind != HEAD_NONE) {
-            if (a.adapter) {
-                ep.xa_out = 1;                 // the exit's adapters come first
-            } else {
-                ep.gain_xh = a.head_gain;      // the LM head's input rows and their sums of squares
-                ep.ss_head = a.sc.ss_h;
-            }
-        }
+    } else if (KIND == G_DN) {
+        ep.gain_xn = a.gain_xn;                // null after the last layer
+        ep.gain_xh = a.gain_xh;                // set where an exit (or the final head) takes this layer's output
+        ep.ss_head = a.gain_xh ? a.sc.ss_h : nullptr;
+        ep.xa_out = a.xa_out;                  // the exit's adapters come first
         ep.ss_out = a.sc.ss_a;
-    } else if (kind == G_AD) {
-        ep.bias = a.ad_bdown;
-    } else if (kind == G_AU) {
-        ep.bias = a.ad_bup;
-        ep.gain_xh = a.head_gain;
+    } else if (KIND == G_AD) {
+        ep.bias = a.bias;
+    } else if (KIND == G_AU) {
+        ep.bias = a.bias;
+        ep.gain_xh = a.gain_xh;
         ep.ss_head = a.sc.ss_h;
     }
     return ep;
 }
 
-// The GEMM stage a.stage of the stage list, for rows <= 8 XC.
-template <int XC>
+// One GEMM of the pass, for rows <= 8 XC.  The kind is a template parameter: a launch's first requests
+// leave after about 200 instructions instead of 700 (every instruction of a launch is executed once, at
+// the speed of instruction-cache misses), and its epilogue holds no other kind's code.  Against one
+// kernel for all kinds, us per launch, 5 rows of the 7B shape: QKV 19.6 -> 18.5, O 10.2 -> 9.1, gate/up
+// 31.2 -> 30.8, down 19.0 -> 18.2, head 51.2 -> 49.8; the smallest model's launches 4.9-6.7 -> 3.8-4.8.
+template <int KIND, int XC>
 __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
-    const StageDesc st = stage_decode(a, a.stage);
-    gemm_stage_t<XC>(a, st.kind, st.layer, a.plan0, a.lay, a.W0, gemm_input(a, st.kind), gemm_epi(a, st.kind, st.layer), lds);
-    if (a.fuse_accept) {
-        // A head stage: the workgroup whose candidates arrive last also runs the accept step
+    gemm_stage_t<KIND, XC>(a, a.plan0, a.lay, a.W0, gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
+    if (KIND == G_HEAD && a.fuse_accept) {
+        // The workgroup whose candidates arrive last also runs the accept step
         // (one launch less per head); the counter is left at zero.
         int *lastf = misc_views(a.lay, lds).lastf;
         wait_vmem();      // this workgroup's candidates are visible device-wide ...
@@ -1585,7 +1552,7 @@ __global__ void __launch_bounds__(WG_THREADS) ee_att_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
-    att_stage<HD>(a, stage_decode(a, a.stage).layer, lds);
+    att_stage<HD>(a, a.layer, lds);
 }
 
 // embedding
@@ -1593,7 +1560,7 @@ __global__ void __launch_bounds__(WG_THREADS) ee_misc_kernel(PassArgs a_by_value
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
-    if (stage_decode(a, a.stage).type == ST_EMBED) embed_stage(a, lds);
+    embed_stage(a, lds);
 }
 
 // ------------------------------------------------------------------ load-time kernels

@@ -119,15 +119,29 @@ struct ee_session {
 
 typedef void (*pass_kernel_t)(PassArgs);
 
-static pass_kernel_t gemm_kernel(int rows)
+template <int KIND>
+static pass_kernel_t gemm_kernel_of(int rows)
 {
     switch ((rows + 7) / 8) {
-    case 1: return ee_gemm_kernel<1>;
-    case 2: return ee_gemm_kernel<2>;
-    case 3: return ee_gemm_kernel<3>;
-    case 4: return ee_gemm_kernel<4>;
-    case 5: return ee_gemm_kernel<5>;
-    default: return ee_gemm_kernel<6>;
+    case 1: return ee_gemm_kernel<KIND, 1>;
+    case 2: return ee_gemm_kernel<KIND, 2>;
+    case 3: return ee_gemm_kernel<KIND, 3>;
+    case 4: return ee_gemm_kernel<KIND, 4>;
+    case 5: return ee_gemm_kernel<KIND, 5>;
+    default: return ee_gemm_kernel<KIND, 6>;
+    }
+}
+
+static pass_kernel_t gemm_kernel(int kind, int rows)
+{
+    switch (kind) {
+    case G_QKV: return gemm_kernel_of<G_QKV>(rows);
+    case G_O: return gemm_kernel_of<G_O>(rows);
+    case G_GU: return gemm_kernel_of<G_GU>(rows);
+    case G_DN: return gemm_kernel_of<G_DN>(rows);
+    case G_AD: return gemm_kernel_of<G_AD>(rows);
+    case G_AU: return gemm_kernel_of<G_AU>(rows);
+    default: return gemm_kernel_of<G_HEAD>(rows);
     }
 }
 
@@ -484,8 +498,9 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             ee_model_free(m);
             return fail(EE_EDEVICE, "ee_model_load: not enough LDS");
         }
-        pass_kernel_t ks[] = {gemm_kernel(8), gemm_kernel(16), gemm_kernel(24), gemm_kernel(32), gemm_kernel(40), gemm_kernel(48),
-                              att_kernel(64), att_kernel(128), ee_misc_kernel};
+        std::vector<pass_kernel_t> ks = {att_kernel(64), att_kernel(128), ee_misc_kernel};
+        for (int k = 0; k < G_KINDS; ++k)
+            for (int rows = 8; rows <= EE_MAX_ROWS; rows += 8) ks.push_back(gemm_kernel(k, rows));
         for (pass_kernel_t k : ks) {
             hipError_t fe = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->lds_budget);
@@ -927,15 +942,31 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot)
         const int code = launch_code(a, ph);
         if (code < 0) break;
         const bool gemm = code != EE_LAUNCH_EMBED && code != EE_LAUNCH_ATT;
-        a.stage = ph;
+        const int idx = ph - (a.do_embed ? 1 : 0);
+        a.layer = a.layer_begin + std::max(idx, 0) / per_layer;
+        // what the O, DN, AD and AU epilogues produce and read (gemm_epi)
+        a.gain_xn = a.gain_xh = a.bias = nullptr;
+        a.xa_out = 0;
+        if (code == EE_LAUNCH_O) a.gain_xn = a.mdv.g_ffn + (size_t)a.layer * a.d;
+        if (code == EE_LAUNCH_DN) {
+            if (a.layer + 1 < m->cfg.n_layers) a.gain_xn = a.mdv.g_attn + (size_t)(a.layer + 1) * a.d;
+            if (a.layer + 1 == a.layer_end && a.head_kind != HEAD_NONE) {
+                a.xa_out = a.adapter;
+                if (!a.adapter) a.gain_xh = a.head_gain;
+            }
+        }
+        if (code == EE_LAUNCH_ADAPTER_DOWN) a.bias = a.ad_bdown;
+        if (code == EE_LAUNCH_ADAPTER_UP) {
+            a.bias = a.ad_bup;
+            a.gain_xh = a.head_gain;
+        }
         a.fuse_accept = (code == EE_LAUNCH_HEAD && !a.sm.on) ? 1 : 0;
         a.rows = code == EE_LAUNCH_HEAD ? a.head_rows : rows;   // the head launch carries the rows of all exits of its group
-        pass_kernel_t k = gemm ? gemm_kernel(a.rows) : (code == EE_LAUNCH_ATT ? att_kernel(m->cfg.head_dim) : ee_misc_kernel);
+        pass_kernel_t k = gemm ? gemm_kernel(code, a.rows) : (code == EE_LAUNCH_ATT ? att_kernel(m->cfg.head_dim) : ee_misc_kernel);
         if (gemm) {  // the stage's plan, LDS map and weights travel with the launch
             static_assert(EE_LAUNCH_QKV == G_QKV && EE_LAUNCH_HEAD == G_HEAD && EE_LAUNCH_ADAPTER_DOWN == G_AD && EE_LAUNCH_ADAPTER_UP == G_AU,
                           "launch codes of GEMM stages are their GemmKind");
-            const int idx = ph - (a.do_embed ? 1 : 0);
-            const int slice = code == EE_LAUNCH_HEAD ? 0 : (code >= EE_LAUNCH_ADAPTER_DOWN ? adapter_slot : a.layer_begin + idx / per_layer);
+            const int slice = code == EE_LAUNCH_HEAD ? 0 : (code >= EE_LAUNCH_ADAPTER_DOWN ? adapter_slot : a.layer);
             // more than 16 rows: the K-split variant of the kind, where the model has one and the scratch its buffers
             const int v = (a.rows > 16 && m->plan[1][code].nwg > 0 && a.sc.part) ? 1 : 0;
             a.plan0 = m->plan[v][code];
