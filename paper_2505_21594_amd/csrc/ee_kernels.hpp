@@ -1165,7 +1165,7 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int *tok = reinterpret_cast<int *>(lds);
     float *conf = reinterpret_cast<float *>(lds) + EE_MAX_ROWS;
-    for (int m = wave; m < rows; m += WAVES) {
+    for (int m = wave; m < rows; m += blockDim.x >> 6) {
         // all of the row's candidates and partial sums are requested before the first is used
         constexpr int PER = 4;                     // workgroups per lane: the launch has at most 256
         int2 c[PER];
@@ -1297,7 +1297,8 @@ __device__ __forceinline__ u64 wave_sum(u64 x)
     return x;
 }
 
-constexpr int SAMPLE_CH = 22;   // blocks of 64 tokens a wave requests in one go (all loads in flight together)
+constexpr int SAMPLE_WAVES = 16;
+constexpr int SAMPLE_CH = 32;   // blocks of 64 tokens a wave holds in registers at once (a chunk)
 
 // values first + 64 j + lane, j < SAMPLE_CH, of a row; `fill` past the end t1
 __device__ __forceinline__ void load_chunk(const EE_GLOBAL float *row, int first, int t1, int lane, float fill, float (&out)[SAMPLE_CH])
@@ -1305,7 +1306,8 @@ __device__ __forceinline__ void load_chunk(const EE_GLOBAL float *row, int first
 #pragma unroll
     for (int j = 0; j < SAMPLE_CH; ++j) {
         const int k = first + 64 * j + lane;
-        out[j] = k < t1 ? row[k] : fill;
+        out[j] = fill;
+        if (k < t1) out[j] = row[k];
     }
 }
 
@@ -1319,36 +1321,52 @@ __device__ __forceinline__ void load_chunk(const EE_GLOBAL float *row, int first
 //
 // Wave w owns the tokens [w * S, (w + 1) * S) and walks them in chunks of SAMPLE_CH blocks of
 // 64 (lane l: token first + 64 j + l, coalesced; a chunk's loads are all requested before the
-// first is used: a pass over the row costs one memory latency per chunk, not one per token).
+// first is used).  Up to 32768 tokens a wave's share is one chunk: logits (then their exponentials)
+// and draft probabilities are loaded once and stay in registers through all the steps; a longer row
+// loads them again in every step.
 // The sums are integers, so the cumulative sum up to a token is the earlier waves' totals + this
 // wave's earlier blocks + a scan inside the block, whatever the order they were added in.
+// One row is one workgroup: bound by the latency of its steps and by one compute unit's vector unit
+// (about 45 instructions per token, a third of them for the two fixed-point conversions).  32000 tokens,
+// 5 rows: 28.7 us; with 12 waves that loaded the row again in every step, 41.9 us.
 __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds)
 {
-    static_assert(WAVES * 8 * 2 + WAVES * 4 + 16 <= SAMPLE_LDS_BYTES && EE_MAX_ROWS * 8 <= SAMPLE_LDS_BYTES, "LDS of the sampling launch");
+    static_assert(SAMPLE_WAVES * 8 * 2 + SAMPLE_WAVES * 4 + 16 <= SAMPLE_LDS_BYTES && EE_MAX_ROWS * 8 <= SAMPLE_LDS_BYTES, "LDS of the sampling launch");
     const int V = a.mdv.V, M = a.M, gamma = M - 1;
     const int per_head = a.n_sess * M;                          // the launch's rows: head after head, session after session
     const int hj = div_small(r, per_head), rr = r - hj * per_head;
     const int ses = div_small(rr, M), i = rr - ses * M;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    u64 *wtot = reinterpret_cast<u64 *>(lds);                   // [WAVES] the waves' totals (target terms)
-    u64 *rtot = wtot + WAVES;                                   // [WAVES] the same for the residual weights
-    float *wmax = reinterpret_cast<float *>(rtot + WAVES);      // [WAVES]
-    int *found = reinterpret_cast<int *>(wmax + WAVES);
+    u64 *wtot = reinterpret_cast<u64 *>(lds);                   // [SAMPLE_WAVES] the waves' totals (target terms)
+    u64 *rtot = wtot + SAMPLE_WAVES;                            // [SAMPLE_WAVES] the same for the residual weights
+    float *wmax = reinterpret_cast<float *>(rtot + SAMPLE_WAVES);   // [SAMPLE_WAVES]
+    int *found = reinterpret_cast<int *>(wmax + SAMPLE_WAVES);
     const EE_GLOBAL float *z = as_global(a.sc.logits) + ((size_t)(a.head_idx + hj) * a.mdv.rows_max + rr) * V;
     const EE_GLOBAL float *p = as_global(a.sm.probs) + ((size_t)ses * gamma + min(i, gamma - 1)) * V;
     const EE_GLOBAL float *uv = as_global(a.sm.uv) + (size_t)ses * (2 * gamma + 2);   // the session's u, v and 1 / temperature
-    const float inv_T = uv[2 * gamma + 1];
-    const int S = ((V + WAVES - 1) / WAVES + 63) & ~63;         // tokens per wave, whole blocks of 64
+    const int S = ((V + SAMPLE_WAVES - 1) / SAMPLE_WAVES + 63) & ~63;   // tokens per wave, whole blocks of 64
     const int t0 = min(V, wave * S), t1 = min(V, t0 + S);
     constexpr int CHUNK = SAMPLE_CH * 64;
-    float zc[SAMPLE_CH], pc[SAMPLE_CH];
+    const bool once = S <= CHUNK;                               // the wave's share is one chunk
+    const bool drafted = i < gamma;
+    float e[SAMPLE_CH], pc[SAMPLE_CH];                          // logits, then e_k; draft probabilities
+    load_chunk(z, t0, t1, lane, -INFINITY, e);
+    if (drafted) load_chunk(p, t0, t1, lane, 0.f, pc);
+    const float inv_T = uv[2 * gamma + 1], v_row = uv[gamma + i];
+    float zx = 0.f, px = 0.f, u_row = 0.f;
+    if (drafted) {
+        const int x = as_global(EE_SESS(a, ses, drafts))[i];
+        zx = z[x];
+        px = p[x];
+        u_row = uv[i];
+    }
 
     // largest logit
     float mx = -INFINITY;
     for (int c0 = t0; c0 < t1; c0 += CHUNK) {
-        load_chunk(z, c0, t1, lane, -INFINITY, zc);
+        if (!once) load_chunk(z, c0, t1, lane, -INFINITY, e);
 #pragma unroll
-        for (int j = 0; j < SAMPLE_CH; ++j) mx = fmaxf(mx, zc[j]);
+        for (int j = 0; j < SAMPLE_CH; ++j) mx = fmaxf(mx, e[j]);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
@@ -1357,44 +1375,50 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
     __syncthreads();
     float zmax = wmax[0];
 #pragma unroll
-    for (int w = 1; w < WAVES; ++w) zmax = fmaxf(zmax, wmax[w]);
+    for (int w = 1; w < SAMPLE_WAVES; ++w) zmax = fmaxf(zmax, wmax[w]);
 
     // Z = sum_k e_k  (a logit of -inf past the row's end contributes exp(-inf) = 0)
     u64 part = 0;
     for (int c0 = t0; c0 < t1; c0 += CHUNK) {
-        load_chunk(z, c0, t1, lane, -INFINITY, zc);
+        if (!once) load_chunk(z, c0, t1, lane, -INFINITY, e);
 #pragma unroll
-        for (int j = 0; j < SAMPLE_CH; ++j) part += fixed_weight(target_term(zc[j], zmax, inv_T));
+        for (int j = 0; j < SAMPLE_CH; ++j) {
+            e[j] = target_term(e[j], zmax, inv_T);
+            part += fixed_weight(e[j]);
+        }
     }
     part = wave_sum(part);
     if (lane == 0) wtot[wave] = part;
     __syncthreads();
     u64 Zi = 0;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) Zi += wtot[w];
+    for (int w = 0; w < SAMPLE_WAVES; ++w) Zi += wtot[w];
     const float inv_Z = 1.0f / (float)((double)Zi * (1.0 / (double)SAMPLE_UNIT));
 
     const u64 *tot = wtot;
     u64 w_total = Zi;
     bool residual = false;
     int kept = 0;
-    if (i < gamma) {
-        const int x = as_global(EE_SESS(a, ses, drafts))[i];
-        const float qx = target_term(z[x], zmax, inv_T) * inv_Z;
-        kept = uv[i] * p[x] < qx ? 1 : 0;
+    if (drafted) {
+        const float qx = target_term(zx, zmax, inv_T) * inv_Z;
+        kept = u_row * px < qx ? 1 : 0;
         u64 rp = 0;
         for (int c0 = t0; c0 < t1; c0 += CHUNK) {
-            load_chunk(z, c0, t1, lane, -INFINITY, zc);
-            load_chunk(p, c0, t1, lane, 0.f, pc);
+            if (!once) {
+                load_chunk(z, c0, t1, lane, -INFINITY, e);
+                load_chunk(p, c0, t1, lane, 0.f, pc);
 #pragma unroll
-            for (int j = 0; j < SAMPLE_CH; ++j) rp += fixed_weight(residual_term(target_term(zc[j], zmax, inv_T), inv_Z, pc[j]));
+                for (int j = 0; j < SAMPLE_CH; ++j) e[j] = target_term(e[j], zmax, inv_T);
+            }
+#pragma unroll
+            for (int j = 0; j < SAMPLE_CH; ++j) rp += fixed_weight(residual_term(e[j], inv_Z, pc[j]));
         }
         rp = wave_sum(rp);
         if (lane == 0) rtot[wave] = rp;
         __syncthreads();
         u64 W = 0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) W += rtot[w];
+        for (int w = 0; w < SAMPLE_WAVES; ++w) W += rtot[w];
         if (W > 0) {  // otherwise q = p: the draft is always kept and the row never emits; it then draws from q
             residual = true;
             tot = rtot;
@@ -1402,7 +1426,7 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
         }
     }
     // the first token whose cumulative weight exceeds the target; v < 1, so target < w_total
-    const double vd = (double)uv[gamma + i];
+    const double vd = (double)v_row;
     u64 target = (u64)(vd * (double)w_total);
     if (target >= w_total) target = w_total - 1;
     u64 before = 0;                                              // cumulative weight of the waves before this one
@@ -1411,31 +1435,36 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
         u64 run = before;
         bool done = false;
         for (int c0 = t0; c0 < t1 && !done; c0 += CHUNK) {
-            load_chunk(z, c0, t1, lane, -INFINITY, zc);
-            if (residual) load_chunk(p, c0, t1, lane, 0.f, pc);
-            // the blocks' sums first, all of them (independent reductions overlap), then the search
-            u64 wk[SAMPLE_CH], blk[SAMPLE_CH];
+            if (!once) {
+                load_chunk(z, c0, t1, lane, -INFINITY, e);
+                if (residual) load_chunk(p, c0, t1, lane, 0.f, pc);
 #pragma unroll
-            for (int j = 0; j < SAMPLE_CH; ++j) {
-                const float e = target_term(zc[j], zmax, inv_T);
-                wk[j] = fixed_weight(residual ? residual_term(e, inv_Z, pc[j]) : e);
+                for (int j = 0; j < SAMPLE_CH; ++j) e[j] = target_term(e[j], zmax, inv_T);
             }
-#pragma unroll
-            for (int j = 0; j < SAMPLE_CH; ++j) {
-                const u64 t = wave_sum(wk[j]);
-                blk[j] = ((u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)t);
-            }
+            // the blocks' sums, eight at a time (independent reductions overlap), until the target's block is found
             int jh = -1;
             u64 mine = 0;
 #pragma unroll
-            for (int j = 0; j < SAMPLE_CH; ++j)
+            for (int j0 = 0; j0 < SAMPLE_CH; j0 += 8)
                 if (jh < 0) {
-                    if (run + blk[j] > target) {
-                        jh = j;
-                        mine = wk[j];
-                    } else {
-                        run += blk[j];
+                    u64 wk[8], blk[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) wk[j] = fixed_weight(residual ? residual_term(e[j0 + j], inv_Z, pc[j0 + j]) : e[j0 + j]);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const u64 t = wave_sum(wk[j]);
+                        blk[j] = ((u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)t);
                     }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (jh < 0) {
+                            if (run + blk[j] > target) {
+                                jh = j0 + j;
+                                mine = wk[j];
+                            } else {
+                                run += blk[j];
+                            }
+                        }
                 }
             if (jh >= 0) {                                       // the token is in block jh: scan it
                 u64 incl = mine;
@@ -1530,7 +1559,7 @@ __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value
 // Probabilistic verification: one workgroup per row of the head launch before it (whose logits
 // it reads); the workgroup that finishes last applies the accept rule and publishes, as the
 // head launch's last workgroup does under exact-match verification.
-__global__ void __launch_bounds__(WG_THREADS) ee_sample_kernel(PassArgs a_by_value)
+__global__ void __launch_bounds__(SAMPLE_WAVES * 64) ee_sample_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();

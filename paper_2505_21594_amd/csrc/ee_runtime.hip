@@ -1000,7 +1000,7 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot)
                 lead->lt_codes.push_back(EE_LAUNCH_SAMPLE);
                 HIP_TRY(hipEventRecord(lead->lt_events[2 * i], lead->run_stream));
             }
-            hipLaunchKernelGGL(ee_sample_kernel, dim3(a.head_rows), dim3(WG_THREADS), SAMPLE_LDS_BYTES, lead->run_stream, a);
+            hipLaunchKernelGGL(ee_sample_kernel, dim3(a.head_rows), dim3(SAMPLE_WAVES * 64), SAMPLE_LDS_BYTES, lead->run_stream, a);
             HIP_TRY(hipGetLastError());
             if (timed) HIP_TRY(hipEventRecord(lead->lt_events[2 * lead->lt_codes.size() - 1], lead->run_stream));
         }

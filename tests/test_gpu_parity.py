@@ -728,6 +728,25 @@ def test_sampled_verification_mid(mid_pair):
     assert bound >= 0.8 * rounds * 3 * (gamma + 2), (bound, exempt_rounds)
 
 
+@pytest.mark.parametrize("vocab", [1000, 32768, 32832])
+def test_sampled_verification_at_the_register_limit(model_dir, vocab):
+    """A row's logits stay in registers up to 32768 tokens (1000: most waves own none); one block more
+    and every step loads them again in two chunks."""
+    p = f"{model_dir}/gpu_vocab.bin"
+    eegen.write_model(p, eegen.ModelConfig(2, 256, 4, 64, 688, vocab, (1,)), 78, gains="uniform", std=0.06)
+    g, o = ee.Model(p), eo.Model(p)
+    try:
+        rounds, gamma = 4, 5
+        exempt_rounds, bound, kept, more = sampled_chain(g, o, eegen.prompt_tokens(44, 40, vocab), gamma, [1], rounds, 0.2, seed=23,
+                                                         what=f"sampled V={vocab}")
+        # every decision that can bind has been compared.  A draw that lands in the flat tail cannot: there a token's
+        # interval of the cumulative sum is about 1 / V = 3e-5 wide at 32768 tokens, less than 2 eps > 4e-5; with
+        # these inputs that is about a quarter of the decisions (43 of 56 bind), so 0.6 says the test is not empty
+        assert bound >= 0.6 * rounds * 2 * (gamma + 2), (bound, exempt_rounds)
+    finally:
+        g.free()
+
+
 @pytest.mark.parametrize("B,gamma,max_rows", [(3, 4, 16), (5, 4, 25), (4, 7, 32)])
 def test_sampled_verification_batch(model_dir, B, gamma, max_rows):
     """Probabilistic verification for several sessions in one pass (one, two row tiles): each
