@@ -128,11 +128,11 @@ struct SessDev {
     uint16_t *kpool, *vpool;             // per (layer, page, head) a record of KV_PAGE*2*hd bf16, value = hi + lo:
                                          // K [position][term][hd], V [term][hd][position]
     const float2 *rope;                  // [max_ctx][hd/2] (cos, sin)
-    const int *drafts;                   // device copy of this pass's drafts
     ee_verify_result *result;            // device address of the pinned result block
     int n_pages;
     int kv_len;                          // positions cached before this pass (host mirror of state[0])
     int pending;                         // token of row 0 (host mirror of state[1])
+    int drafts[EE_MAX_M - 1];            // this pass's drafts
     int contig_base;                     // >= 0: logical page i is physical page contig_base + i (no table lookup needed)
 };
 
@@ -205,8 +205,8 @@ struct PassArgs {
     const float *gain_xn, *gain_xh;      // O, DN: gain of the next GEMM input; DN, AU: gain of the LM head's input (each may be null)
     const float *bias;                   // AD, AU: bias per output column
     int xa_out;                          // DN: also emit h itself as the adapters' input
-    const SessDev *sess;                 // device array [n_sess]
-    SessDev sess0;                       // copy of sess[0]
+    const SessDev *sess;                 // device array [n_sess] (passes of several sessions only)
+    SessDev sess0;                       // session 0: a pass of one session needs nothing but its launch arguments
     SampleDev sm;
 };
 

@@ -193,8 +193,8 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f)
 
 // ------------------------------------------------------------------ rows
 
-// Fields of session s's descriptor.  Session 0's descriptor also travels by value in the launch
-// arguments, so the common one-session pass needs no load from memory to find them.
+// Fields of session s's descriptor.  Session 0's descriptor travels by value in the launch
+// arguments, so the common one-session pass needs no load from memory to find them, and no upload.
 // (written so that the two sources are never merged into one pointer of unknown address space)
 template <typename T>
 __device__ __forceinline__ T sess_pick(bool first, const T &own, const T *other)
@@ -212,11 +212,19 @@ __device__ __forceinline__ int row_pos(const PassArgs &a, int r)
     return EE_SESS(a, s, kv_len) + (r - s * a.M);
 }
 
+// draft i of session s
+__device__ __forceinline__ int draft_of(const PassArgs &a, int s, int i)
+{
+    int v = a.sess0.drafts[i];
+    if (s != 0) v = *as_global(&a.sess[s].drafts[i]);
+    return v;
+}
+
 __device__ __forceinline__ int row_token(const PassArgs &a, int r)
 {
     if (a.mode == 1) return a.pf_tokens[r];
     int s = div_small(r, a.M), i = r - s * a.M;
-    return i == 0 ? EE_SESS(a, s, pending) : EE_SESS(a, s, drafts)[i - 1];
+    return i == 0 ? EE_SESS(a, s, pending) : draft_of(a, s, i - 1);
 }
 
 // ------------------------------------------------------------------ LDS map
@@ -1216,15 +1224,15 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
     // one thread per (head of this launch, session)
     if ((int)threadIdx.x < a.n_heads * a.n_sess) {
         const int hj = div_small(threadIdx.x, a.n_sess), s = threadIdx.x - hj * a.n_sess, head = a.head_idx + hj;
-        const SessDev &sd = a.sess[s];
-        ee_verify_result *res = sd.result;
+        ee_verify_result *res = EE_SESS(a, s, result);
+        int *state = EE_SESS(a, s, state);
         const int *t = tok + (hj * a.n_sess + s) * M;
         const float *cf = conf + (hj * a.n_sess + s) * M;
         if (a.head_kind == HEAD_PREFILL) {
             int last = t[M - 1];
             res->next_token = last;
             res->device_status = 0;
-            sd.state[1] = last;
+            state[1] = last;
         } else {
             const int gamma = M - 1;
             int delta = 0;
@@ -1242,7 +1250,7 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
             } else {
                 int dr[EE_MAX_M];
 #pragma unroll
-                for (int i = 0; i < EE_MAX_M - 1; ++i) dr[i] = i < gamma ? sd.drafts[i] : -1;
+                for (int i = 0; i < EE_MAX_M - 1; ++i) dr[i] = i < gamma ? draft_of(a, s, i) : -1;
 #pragma unroll
                 for (int i = 0; i < EE_MAX_M - 1; ++i)
                     if (delta == i && i < gamma && dr[i] == t[i]) delta = i + 1;
@@ -1262,8 +1270,8 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
                 res->next_token = t[delta];
                 res->device_status = 0;
                 if (a.commit) {
-                    sd.state[0] = sd.state[0] + delta + 1;
-                    sd.state[1] = t[delta];
+                    state[0] = state[0] + delta + 1;
+                    state[1] = t[delta];
                 }
             }
         }
@@ -1355,7 +1363,7 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
     const float inv_T = uv[2 * gamma + 1], v_row = uv[gamma + i];
     float zx = 0.f, px = 0.f, u_row = 0.f;
     if (drafted) {
-        const int x = as_global(EE_SESS(a, ses, drafts))[i];
+        const int x = draft_of(a, ses, i);
         zx = z[x];
         px = p[x];
         u_row = uv[i];

@@ -81,9 +81,9 @@ struct ee_session {
     float2 *rope;
     // device state and staging
     int *dev_state;
-    int *dev_drafts;
-    int *host_drafts;                // pinned
     float *host_sample;              // pinned staging of a sampled pass: draft distributions, then u, then v (EE_SAMPLING)
+    hipStream_t copy_stream;         // uploads of a sampled pass's distributions (EE_SAMPLING)
+    hipEvent_t ev_copy;
     float *dev_sample;               // device copy of the same
     int *dev_sample_out;             // [2 * EE_MAX_ROWS + 1] rows' tokens, keep flags, arrival counter
     int *dev_pf_tokens;
@@ -692,9 +692,9 @@ extern "C" int ee_session_free(ee_session *s)
     if (!s) return EE_OK;
     hipSetDevice(s->m->device);
     if (s->stream) hipStreamSynchronize(s->stream);
+    if (s->copy_stream) hipStreamSynchronize(s->copy_stream);
     for (void *p : s->allocs) hipFree(p);
     if (s->host_page_table) hipHostFree(s->host_page_table);
-    if (s->host_drafts) hipHostFree(s->host_drafts);
     if (s->host_sample) hipHostFree(s->host_sample);
     if (s->host_pf_tokens) hipHostFree(s->host_pf_tokens);
     if (s->result) hipHostFree(s->result);
@@ -704,6 +704,8 @@ extern "C" int ee_session_free(ee_session *s)
     for (hipEvent_t e : s->ev_exit)
         if (e) hipEventDestroy(e);
     for (hipEvent_t e : s->lt_events) hipEventDestroy(e);
+    if (s->ev_copy) hipEventDestroy(s->ev_copy);
+    if (s->copy_stream) hipStreamDestroy(s->copy_stream);
     if (s->stream) hipStreamDestroy(s->stream);
     delete s;
     return EE_OK;
@@ -783,8 +785,6 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
     }
 
     S_TRY(dev_alloc(s->allocs, &s->dev_state, 4));
-    S_TRY(dev_alloc(s->allocs, &s->dev_drafts, EE_MAX_M));
-    S_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->host_drafts), EE_MAX_M * sizeof(int), hipHostMallocDefault));
     {
         // prefill: a chunk of up to pf_cap rows at once (pf_gemm_kernel and friends).  About a tenth of
         // the KV cache of as many positions.  Padding columns (K not a multiple of 32) are read and
@@ -843,6 +843,8 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         const size_t n = (size_t)rows_max * c.vocab + (size_t)EE_MAX_BATCH * (2 * EE_MAX_M + 2);
         S_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->host_sample), n * sizeof(float), hipHostMallocDefault));
         S_TRY(dev_alloc(s->allocs, &s->dev_sample, n));
+        S_HIP(hipStreamCreate(&s->copy_stream));
+        S_HIP(hipEventCreateWithFlags(&s->ev_copy, hipEventDisableTiming));
         S_TRY(dev_alloc(s->allocs, &s->dev_sample_out, 2 * EE_MAX_ROWS + 1));
     }
     {
@@ -894,7 +896,6 @@ static void fill_sessdev(SessDev &sd, const ee_session *s)
     sd.kpool = s->kpool;
     sd.vpool = s->vpool;
     sd.rope = s->rope;
-    sd.drafts = s->dev_drafts;
     sd.result = s->dev_result;
     sd.n_pages = s->n_pages;
     sd.kv_len = s->kv_len;
@@ -932,8 +933,36 @@ static int launch_code(const PassArgs &a, int ph)
     return -1;
 }
 
+// Draft distributions and numbers of a sampled pass that are not on their way to the device yet.
+struct SampleUpload {
+    const ee_sampling *sp;   // [n_sessions], null once uploaded
+    int n_sessions, gamma;
+};
+
+// [session][gamma][V] distributions, then per session u, v and 1 / temperature (SampleDev).  The copy runs on a
+// stream of its own and the pass's stream waits for it: called when the launches before the first sampling
+// launch have been enqueued, the staging (512 KB for four drafts of 32000 tokens) and the transfer
+// take place while the layers run.
+static int upload_sampling(ee_session *lead, SampleUpload &up)
+{
+    const size_t V = (size_t)lead->m->cfg.vocab, np = (size_t)up.n_sessions * up.gamma * V, blk = 2 * (size_t)up.gamma + 2;
+    for (int b = 0; b < up.n_sessions; ++b) {
+        const ee_sampling &q = up.sp[b];
+        memcpy(lead->host_sample + (size_t)b * up.gamma * V, q.draft_probs, (size_t)up.gamma * V * sizeof(float));
+        float *uv = lead->host_sample + np + (size_t)b * blk;
+        memcpy(uv, q.u, (size_t)up.gamma * sizeof(float));
+        memcpy(uv + up.gamma, q.v, (size_t)(up.gamma + 1) * sizeof(float));
+        uv[2 * up.gamma + 1] = 1.0f / q.temperature;
+    }
+    HIP_TRY(hipMemcpyAsync(lead->dev_sample, lead->host_sample, (np + (size_t)up.n_sessions * blk) * sizeof(float), hipMemcpyHostToDevice, lead->copy_stream));
+    HIP_TRY(hipEventRecord(lead->ev_copy, lead->copy_stream));
+    HIP_TRY(hipStreamWaitEvent(lead->run_stream, lead->ev_copy, 0));
+    up.sp = nullptr;
+    return EE_OK;
+}
+
 // Enqueues the stages of one segment, one launch each, on the leader's stream.
-static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot)
+static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, SampleUpload *up = nullptr)
 {
     const ee_model *m = lead->m;
     const int per_layer = 5;
@@ -990,6 +1019,10 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot)
         if (code == EE_LAUNCH_HEAD && a.sm.on) {
             // probabilistic verification: the rows' keep tests and draws, one workgroup per head row,
             // then the accept rule and the publication (in the workgroup that finishes last)
+            if (up && up->sp) {
+                const int rc = upload_sampling(lead, *up);
+                if (rc != EE_OK) return rc;
+            }
             if (timed) {
                 const size_t i = lead->lt_codes.size();
                 while (lead->lt_events.size() < 2 * (i + 1)) {
@@ -1147,7 +1180,6 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
     if ((rc = ensure_pages(s, total + 1, s->stream)) != EE_OK) return rc;
 
     fill_sessdev(s->host_sessdev[0], s);
-    HIP_TRY(hipMemcpyAsync(s->dev_sessdev, s->host_sessdev, sizeof(SessDev), hipMemcpyHostToDevice, s->stream));
     // More rows than one streamed launch takes: chunks of many rows, of nearly equal size.  61 rows of a
     // 1280-wide model, 3 layers, prefill and one pass: 513 us against 946 us in streamed chunks of 16;
     // 640 rows of 8 layers of the 7B shape 5.7 ms against 19.8 ms in chunks of 40.
@@ -1404,8 +1436,6 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
         ee_session *s = sessions[i];
         if (s != lead) HIP_TRY(hipStreamSynchronize(s->stream));
         if ((rc = ensure_pages(s, s->kv_len + M, lead->run_stream)) != EE_OK) return rc;
-        memcpy(s->host_drafts, drafts[i], (size_t)gamma * sizeof(int));
-        HIP_TRY(hipMemcpyAsync(s->dev_drafts, s->host_drafts, (size_t)gamma * sizeof(int), hipMemcpyHostToDevice, lead->run_stream));
         s->result->gamma = gamma;
         s->result->n_exits = n_exits;
         s->result->device_status = 0;
@@ -1416,16 +1446,7 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
     a.mode = 0;
     a.commit = (lead->flags & EE_NO_AUTOCOMMIT) ? 0 : 1;
     if (sp) {
-        // [session][gamma][V] distributions, then per session u, v and 1 / temperature (SampleDev)
-        const size_t V = (size_t)c.vocab, np = (size_t)n_sessions * gamma * V, blk = 2 * (size_t)gamma + 2;
-        for (int b = 0; b < n_sessions; ++b) {
-            memcpy(lead->host_sample + (size_t)b * gamma * V, sp[b].draft_probs, (size_t)gamma * V * sizeof(float));
-            float *uv = lead->host_sample + np + (size_t)b * blk;
-            memcpy(uv, sp[b].u, (size_t)gamma * sizeof(float));
-            memcpy(uv + gamma, sp[b].v, (size_t)(gamma + 1) * sizeof(float));
-            uv[2 * gamma + 1] = 1.0f / sp[b].temperature;
-        }
-        HIP_TRY(hipMemcpyAsync(lead->dev_sample, lead->host_sample, (np + (size_t)n_sessions * blk) * sizeof(float), hipMemcpyHostToDevice, lead->run_stream));
+        const size_t np = (size_t)n_sessions * gamma * c.vocab;
         a.sm.probs = lead->dev_sample;
         a.sm.uv = lead->dev_sample + np;
         a.sm.on = 1;
@@ -1434,14 +1455,20 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
         a.sm.count = lead->dev_sample_out + 2 * EE_MAX_ROWS;
         a.keep_logits = 1;   // the sampling launch reads the head launch's logits
     }
-    for (int i = 0; i < n_sessions; ++i) fill_sessdev(lead->host_sessdev[i], sessions[i]);
-    HIP_TRY(hipMemcpyAsync(lead->dev_sessdev, lead->host_sessdev, (size_t)n_sessions * sizeof(SessDev),
-                           hipMemcpyHostToDevice, lead->run_stream));
+    // The first session's descriptor, drafts included, travels with every launch's arguments; a pass of
+    // several sessions uploads all of them in one copy (a copy is a launch of its own: 4 us and a gap).
+    for (int i = 0; i < n_sessions; ++i) {
+        fill_sessdev(lead->host_sessdev[i], sessions[i]);
+        memcpy(lead->host_sessdev[i].drafts, drafts[i], (size_t)gamma * sizeof(int));
+    }
+    if (n_sessions > 1)
+        HIP_TRY(hipMemcpyAsync(lead->dev_sessdev, lead->host_sessdev, (size_t)n_sessions * sizeof(SessDev), hipMemcpyHostToDevice, lead->run_stream));
     a.sess = lead->dev_sessdev;
     a.sess0 = lead->host_sessdev[0];
 
     HIP_TRY(hipEventRecord(lead->ev_start, lead->run_stream));
     lead->lt_codes.clear();
+    SampleUpload upload = {sp, n_sessions, gamma};
     // Exit heads run in groups of up to head_batch consecutive exits: every exit deposits its
     // LM-head input rows when its layer is done, and the last one of the group runs the LM head
     // over the rows of all of them (one stream of W_lm per group), after which the group's results
@@ -1465,7 +1492,7 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
         a.adapter = (!fin && m->host_md.A > 0) ? 1 : 0;
         a.ad_bdown = a.adapter ? m->ad_bdown[slots[e]] : nullptr;
         a.ad_bup = a.adapter ? m->ad_bup[slots[e]] : nullptr;
-        if ((rc = launch_segment(lead, a, fin ? 0 : slots[e])) != EE_OK) return rc;
+        if ((rc = launch_segment(lead, a, fin ? 0 : slots[e], &upload)) != EE_OK) return rc;
         if (fin) {
             HIP_TRY(hipEventRecord(lead->ev_final, lead->run_stream));
         } else if (a.head_stage) {
