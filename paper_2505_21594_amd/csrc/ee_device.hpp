@@ -15,7 +15,7 @@ constexpr int WG_THREADS = WAVES * 64;
 constexpr int GROUP_TILES = 8;           // n-tiles whose accumulators a streaming wave keeps in registers at once
 constexpr int KV_PAGE = 16;              // positions per KV page
 constexpr int ATT_ROWS = 16;             // query rows of one attention item (one MFMA tile)
-constexpr int ATT_TILES = 8;             // KV pages (score tiles) a wave keeps in registers per item
+constexpr int ATT_TILES = 8;             // KV pages a wave takes at most per launch of the attention
 constexpr int ATT_MAX_SPLITS = 16;
 constexpr int KSPLIT_LOG2 = 2;           // many-row launches: workgroups (1 << this) that share n-tiles and split K (at most SWAVES)
 
@@ -151,7 +151,7 @@ struct Scratch {
     float *ss_h;         // [rows_max][SS_LD]        partial sums of squares of the LM-head input's rows (head rows)
     float *ss_a;         // [rows_max][SS_LD]        partial sums of h^2 after the FFN block / embedding
     float *ss_f;         // [rows_max][SS_LD]        partial sums of h^2 after the attention block
-    float *att_part;     // [items][ATT_ROWS][hd+2] attention partials (only when the position range is split)
+    float *att_part;     // [items][ATT_ROWS][hd+4] attention partials (only when the position range is split)
     int *att_count;      // [units] items of the unit that have delivered their partials; zero between launches
     int *head_count;     // workgroups of a head launch that have delivered their candidates; zero between launches
     float *part;         // [K split][n-tile][rows][16] partial tiles of a launch whose K is split over workgroups

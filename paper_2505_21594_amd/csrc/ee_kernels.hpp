@@ -895,85 +895,96 @@ __device__ __forceinline__ bf16x8_t pack_bf16x8(const uint32_t *h)
     return __builtin_bit_cast(bf16x8_t, make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)));
 }
 
-// Work item = (session, head, chunk of up to ATT_ROWS = 16 query rows, split of the cache's
-// pages); the host picks the number of splits so that the items cover the chip and no wave
-// gets more than ATT_TILES pages.  A wave takes whole pages (16 positions), page
-// pg_lo + wave + t * WAVES being its tile t, and runs both products on the matrix cores:
-//   scores  S[pos][row] = K . q^T   v_mfma_f32_16x16x32_bf16, A = 16 cached positions x 32
+// floats of one row's partial result: output, maximum, sum, padding to 16 bytes
+constexpr int att_rec(int hd) { return hd + 4; }
+constexpr size_t att_lds(int hd, int rows) { return (size_t)WAVES * (rows < ATT_ROWS ? rows : ATT_ROWS) * att_rec(hd) * sizeof(float) + 16; }
+
+__device__ __forceinline__ float4 load_f4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+
+// Workgroup = (split of the cache's pages, head, session or chunk of up to ATT_ROWS = 16 query
+// rows); the host picks the number of splits so that the workgroups cover the chip.  Wave w takes the pages
+// pg_lo + w, pg_lo + w + WAVES, ... of the split (16 positions each), both products on the matrix cores:
+//   scores  S[pos][row] = K . q^T     v_mfma_f32_16x16x32_bf16, A = 16 cached positions x 32
 //           values straight from the page (lane l: position l & 15, values (l >> 4) * 8 ..),
 //           B = the rows' q; three MFMAs per 32 values (k_hi q_hi + k_lo q_hi + k_hi q_lo);
-//   output  O[row][dim] = p . V     v_mfma_f32_16x16x16bf16_1k, A = p in the layout the score
-//           MFMA left it in (lane l: row l & 15, positions (l >> 4) * 4 ..), B = V, which the
+//   output  O[dim][row] = V^T . P     v_mfma_f32_16x16x16bf16_1k, B = p in the layout the score
+//           MFMA left it in (lane l: row l & 15, positions (l >> 4) * 4 ..), A = V, which the
 //           cache stores transposed inside a page ([term][dim][position]) so that a lane's
 //           four positions are 8 contiguous bytes; p and V as two bf16 terms, three MFMAs.
-// All of a wave's score tiles stay in registers, so the softmax is two-pass inside the wave
-// (no rescaling).  q and the cached k use the same pair-interleaved order inside a head, so
-// their dot product is unchanged.  The waves' un-normalised results (accumulator, max, sum)
-// are merged through LDS in wave order.  With one split the normalised output is written
-// directly; otherwise every item writes its partial and counts itself in the unit's counter,
-// and the item that arrives last merges the unit's partials in split order (the result does
-// not depend on arrival order) and clears the counter for the next launch.  Nothing waits.
+// A row's maximum, sum and output live in the lanes of its column, so the running rescale from page to
+// page needs no exchange.  q and the cached k use the same pair-interleaved order inside a head, so
+// their dot product is unchanged.  The waves' un-normalised results are merged through LDS in wave
+// order.  With one split the normalised output is written directly; otherwise every workgroup
+// writes its partial and counts itself in the unit's counter, and the one that arrives
+// last merges the unit's partials in split order (the result does not depend on arrival order)
+// and clears the counter for the next launch.  Nothing waits.
+// With few rows the launch is a chain of latencies (arguments, K and V, merge, count, final merge), and
+// its instructions are executed once, from a cold instruction cache: the code is kept short, one loop over
+// pages (K of the next page requested as soon as this one's scores are done).  us per launch against a
+// version that unrolled eight pages per wave and looped over work items: 5 rows at 512 positions 11.8 ->
+// 9.0, the smallest model 7.3 -> 5.4; eight sessions of 640 positions (175 MB of cache) 34.2 -> 33.6.
 template <int HD>
-__device__ __forceinline__ void att_stage(const PassArgs &a, int layer, char *lds)
+__device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
 {
     constexpr int KT = HD / 32;  // 32-value steps of a score
-    constexpr int NT = HD / 16;  // 16-column tiles of the output
-    constexpr int REC = HD + 2;
-    const int H = a.H, d = a.d, M = a.M;  // copies in the launch arguments: no load before the first address
-    const int n_chunks = (M + ATT_ROWS - 1) / ATT_ROWS;
-    const int n_splits = a.att_splits;
-    const int n_items = a.n_sess * H * n_chunks * n_splits;
+    constexpr int NT = HD / 16;  // 16-dim tiles of the output
+    constexpr int REC = att_rec(HD);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, quad = lane >> 4;
-    float *wbuf = reinterpret_cast<float *>(lds);  // [WAVES][ATT_ROWS][REC]
-    int *lastf = reinterpret_cast<int *>(wbuf + (size_t)WAVES * ATT_ROWS * REC);
-    const size_t rec_page = (size_t)KV_PAGE * 2 * HD;  // elements of one (page, head) record
-    for (int item = blockIdx.x; item < n_items; item += a.nwg) {
-        int unit = div_small(item, n_splits), sp = item - unit * n_splits;
-        int s = div_small(unit, H * n_chunks), rem = unit - s * (H * n_chunks);
-        int hh = div_small(rem, n_chunks), ch = rem - hh * n_chunks;
-        int r0 = ch * ATT_ROWS, nr = min(ATT_ROWS, M - r0);
-        // session 0's descriptor also travels by value in the launch arguments: no dependent load
-        const int *page_table = EE_SESS(a, s, page_table);
-        const uint16_t *kpool = EE_SESS(a, s, kpool);
-        const uint16_t *vpool = EE_SESS(a, s, vpool);
-        const int n_pages = EE_SESS(a, s, n_pages);
-        const int P = a.mode == 1 ? a.pf_pos0 : EE_SESS(a, s, kv_len);  // position of the first row
-        const int n_pos = P + r0 + nr;  // positions visible to the chunk's last row
-        const int n_pg = (n_pos + KV_PAGE - 1) / KV_PAGE;
-        const int pg_lo = div_small(n_pg * sp, n_splits), pg_hi = div_small(n_pg * (sp + 1), n_splits);
-        const int T = max(0, (pg_hi - pg_lo - wave + WAVES - 1) / WAVES);  // tiles of this wave, <= ATT_TILES
-        const int cbase = EE_SESS(a, s, contig_base);
-        int my_pg = 0;  // physical page of this wave's tile number `lane`
-        if (cbase >= 0)
-            my_pg = cbase + pg_lo + wave + lane * WAVES;  // consecutive pages: no lookup, K can be requested together with q
-        else if (lane < T)
-            my_pg = as_global(page_table)[pg_lo + wave + lane * WAVES];
-
-        // Requests first, uses after: the rows' q and the K of the wave's first tile (most waves
-        // have one tile) travel together; with consecutive pages nothing had to be loaded to
-        // know where K is.
-        const int mrow = min(lm, nr - 1);
+    const int sp = blockIdx.x, hh = blockIdx.y, n_splits = a.att_splits, M = a.M;
+    const int s = a.mode == 1 ? 0 : blockIdx.z, ch = a.mode == 1 ? blockIdx.z : 0;
+    const int r0 = ch * ATT_ROWS, nr = min(ATT_ROWS, M - r0);
+    const int P = a.mode == 1 ? a.pf_pos0 : EE_SESS(a, s, kv_len);  // position of the first row
+    const int n_pg = (P + r0 + nr + KV_PAGE - 1) / KV_PAGE;         // pages visible to the chunk's last row
+    const int pg_lo = div_small(n_pg * sp, n_splits), pg_hi = div_small(n_pg * (sp + 1), n_splits);
+    const int cbase = EE_SESS(a, s, contig_base), n_pages = EE_SESS(a, s, n_pages);
+    const int *page_table = EE_SESS(a, s, page_table);
+    const uint16_t *kpool = EE_SESS(a, s, kpool), *vpool = EE_SESS(a, s, vpool);
+    const int mrow = min(lm, nr - 1);                               // rows past the chunk repeat its last row
+    const int last_pos = P + r0 + mrow;                             // last position this lane's row may see
+    f32x4_t O[NT];
+    float mx = ATT_NEG, sum = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) O[nt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    int pg = pg_lo + wave;
+    if (pg < pg_hi) {
+        uint4 kh[KT], kl[KT];
+        uint2 vh[NT], vl[NT];
+        auto record = [&](int page_idx) __attribute__((always_inline)) {   // first element of the (page, head) record
+            const int page = cbase >= 0 ? cbase + page_idx : __builtin_amdgcn_readfirstlane(as_global(page_table)[page_idx]);
+            return (((size_t)a.layer * n_pages + page) * a.H + hh) * (size_t)(KV_PAGE * 2 * HD);
+        };
+        auto request_k = [&](size_t rec) __attribute__((always_inline)) {
+            const uint16_t *kb = reinterpret_cast<const uint16_t *>(uniform_ptr(kpool + rec));
+            const unsigned off = lm * (2 * HD) + quad * 8;
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                kh[kt] = load_global16(kb + off + kt * 32);
+                kl[kt] = load_global16(kb + off + HD + kt * 32);
+            }
+        };
+        auto request_v = [&](size_t rec) __attribute__((always_inline)) {
+            const uint16_t *vb = reinterpret_cast<const uint16_t *>(uniform_ptr(vpool + rec));
+            const unsigned off = lm * KV_PAGE + quad * 4;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                vh[nt] = load_global8(vb + off + nt * 16 * KV_PAGE);
+                vl[nt] = load_global8(vb + off + (HD + nt * 16) * KV_PAGE);
+            }
+        };
+        // the rows' q, K and V of the first page travel together
         f32x4_t qraw[KT][2];
         {
-            const float *qp = a.sc.q + (size_t)(s * M + r0 + mrow) * d + hh * HD + quad * 8;
+            const float *qp = a.sc.q + (size_t)(s * M + r0 + mrow) * a.d + hh * HD + quad * 8;
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
                 qraw[kt][0] = *as_global(reinterpret_cast<const f32x4_t *>(qp + kt * 32));
                 qraw[kt][1] = *as_global(reinterpret_cast<const f32x4_t *>(qp + kt * 32 + 4));
             }
         }
-        uint4 k0h[KT], k0l[KT];
-        if (T > 0) {
-            const int page = __builtin_amdgcn_readlane(my_pg, 0);
-            const uint16_t *kb = kpool + (((size_t)layer * n_pages + page) * H + hh) * rec_page + (size_t)lm * (2 * HD) + quad * 8;
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                k0h[kt] = load_global16(kb + kt * 32);
-                k0l[kt] = load_global16(kb + HD + kt * 32);
-            }
-        }
-        // q as MFMA B operands, two bf16 terms (rows past the chunk repeat its last row)
+        size_t rec = record(pg);
+        request_k(rec);
+        request_v(rec);
         bf16x8_t qh[KT], ql[KT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
@@ -986,173 +997,139 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, int layer, char *ld
             qh[kt] = pack_bf16x8(h);
             ql[kt] = pack_bf16x8(l);
         }
-        // pass 1: score tiles
-        f32x4_t S[ATT_TILES];
-        const int last_pos = P + r0 + mrow;  // last position this lane's row may see
+        for (;;) {
+            f32x4_t S = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < ATT_TILES; ++t) {
-            S[t] = (f32x4_t){ATT_NEG, ATT_NEG, ATT_NEG, ATT_NEG};
-            if (t < T) {
-                const int page = __builtin_amdgcn_readlane(my_pg, t);
-                const uint16_t *kb = kpool + (((size_t)layer * n_pages + page) * H + hh) * rec_page + (size_t)lm * (2 * HD) + quad * 8;
-                uint4 kh[KT], kl[KT];
-#pragma unroll
-                for (int kt = 0; kt < KT; ++kt) {
-                    kh[kt] = t == 0 ? k0h[kt] : load_global16(kb + kt * 32);
-                    kl[kt] = t == 0 ? k0l[kt] : load_global16(kb + HD + kt * 32);
-                }
-                f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kt = 0; kt < KT; ++kt) {
-                    const bf16x8_t Ah = __builtin_bit_cast(bf16x8_t, kh[kt]), Al = __builtin_bit_cast(bf16x8_t, kl[kt]);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, qh[kt], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Al, qh[kt], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, ql[kt], acc, 0, 0, 0);
-                }
-                const int pos0 = (pg_lo + wave + t * WAVES) * KV_PAGE + quad * 4;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) S[t][r] = pos0 + r <= last_pos ? acc[r] * a.att_scale : ATT_NEG;
+            for (int kt = 0; kt < KT; ++kt) {
+                const bf16x8_t Ah = __builtin_bit_cast(bf16x8_t, kh[kt]), Al = __builtin_bit_cast(bf16x8_t, kl[kt]);
+                S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, qh[kt], S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Al, qh[kt], S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, ql[kt], S, 0, 0, 0);
             }
-        }
-        float mx = ATT_NEG;
-#pragma unroll
-        for (int t = 0; t < ATT_TILES; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[t][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-
-        // pass 2: probabilities and output tiles
-        f32x4_t O[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) O[nt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-        float lsum = 0.f;
-#pragma unroll
-        for (int t = 0; t < ATT_TILES; ++t) {
-            if (t < T) {
-                const int page = __builtin_amdgcn_readlane(my_pg, t);
-                const uint16_t *vb = vpool + (((size_t)layer * n_pages + page) * H + hh) * rec_page + (size_t)lm * KV_PAGE + quad * 4;
-                uint2 vh[NT], vl[NT];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    vh[nt] = load_global8(vb + (size_t)(nt * 16) * KV_PAGE);
-                    vl[nt] = load_global8(vb + (size_t)(HD + nt * 16) * KV_PAGE);
-                }
-                uint32_t ph[4], pl[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float pr = S[t][r] > 0.5f * ATT_NEG ? __expf(S[t][r] - mx) : 0.f;
-                    lsum += pr;
-                    split_bf16(pr, ph[r], pl[r]);
-                }
-                const s16x4_t Ph = __builtin_bit_cast(s16x4_t, make_uint2(ph[0] | (ph[1] << 16), ph[2] | (ph[3] << 16)));
-                const s16x4_t Pl = __builtin_bit_cast(s16x4_t, make_uint2(pl[0] | (pl[1] << 16), pl[2] | (pl[3] << 16)));
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const s16x4_t Vh = __builtin_bit_cast(s16x4_t, vh[nt]), Vl = __builtin_bit_cast(s16x4_t, vl[nt]);
-                    O[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ph, Vh, O[nt], 0, 0, 0);
-                    O[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Pl, Vh, O[nt], 0, 0, 0);
-                    O[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ph, Vl, O[nt], 0, 0, 0);
-                }
+            const int pos0 = pg * KV_PAGE + quad * 4;
+            pg += WAVES;
+            const bool more = pg < pg_hi;
+            if (more) {
+                rec = record(pg);
+                request_k(rec);
             }
+            float m_new = mx;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                S[r] = pos0 + r <= last_pos ? S[r] * a.att_scale : ATT_NEG;
+                m_new = fmaxf(m_new, S[r]);
+            }
+            m_new = fmaxf(m_new, __shfl_xor(m_new, 16, 64));
+            m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
+            const float f = __expf(mx - m_new);
+            mx = m_new;
+            sum *= f;
+            uint32_t ph[4], pl[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float pr = S[r] > 0.5f * ATT_NEG ? __expf(S[r] - mx) : 0.f;
+                sum += pr;
+                split_bf16(pr, ph[r], pl[r]);
+            }
+            const s16x4_t Ph = __builtin_bit_cast(s16x4_t, make_uint2(ph[0] | (ph[1] << 16), ph[2] | (ph[3] << 16)));
+            const s16x4_t Pl = __builtin_bit_cast(s16x4_t, make_uint2(pl[0] | (pl[1] << 16), pl[2] | (pl[3] << 16)));
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) O[nt][r] *= f;
+                const s16x4_t Vh = __builtin_bit_cast(s16x4_t, vh[nt]), Vl = __builtin_bit_cast(s16x4_t, vl[nt]);
+                O[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Vh, Ph, O[nt], 0, 0, 0);
+                O[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Vh, Pl, O[nt], 0, 0, 0);
+                O[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Vl, Ph, O[nt], 0, 0, 0);
+            }
+            if (!more) break;
+            request_v(rec);
         }
-        lsum += __shfl_xor(lsum, 16, 64);
-        lsum += __shfl_xor(lsum, 32, 64);
-        // this wave's record: lane holds O[row quad*4 + r][column nt*16 + lm]; max and sum per row lm
+        sum += __shfl_xor(sum, 16, 64);
+        sum += __shfl_xor(sum, 32, 64);
+    }
+    // this wave's record: lane holds O[dims nt*16 + quad*4 ..][row lm]
+    float *wbuf = reinterpret_cast<float *>(lds);                   // [WAVES][nr][REC]
+    int *lastf = reinterpret_cast<int *>(wbuf + (size_t)WAVES * nr * REC);
+    if (lm < nr) {
+        float *w = wbuf + (wave * nr + lm) * REC;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (quad * 4 + r < nr) wbuf[((size_t)wave * ATT_ROWS + quad * 4 + r) * REC + nt * 16 + lm] = O[nt][r];
-        if (quad == 0 && lm < nr) {
-            float *w = wbuf + ((size_t)wave * ATT_ROWS + lm) * REC;
+        for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<float4 *>(w + nt * 16 + quad * 4) = make_float4(O[nt][0], O[nt][1], O[nt][2], O[nt][3]);
+        if (quad == 0) {
             w[HD] = mx;
-            w[HD + 1] = lsum;
+            w[HD + 1] = sum;
+        }
+    }
+    lds_barrier();
+    // merge the waves, fixed order; thread = (row, four dims)
+    const int i = tid / (HD / 4), e = (tid - i * (HD / 4)) * 4;
+    const bool mine = i < nr;                                       // WG_THREADS >= ATT_ROWS * HD / 4
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    float den = 0.f, gm = ATT_NEG;
+    static_assert(WG_THREADS >= ATT_ROWS * HD / 4, "one thread per row and four dims");
+    if (mine) {
+        const int act = min(WAVES, pg_hi - pg_lo);                  // waves that had a page
+        const float *w0 = wbuf + i * REC;
+        for (int w = 0; w < act; ++w) gm = fmaxf(gm, w0[w * nr * REC + HD]);
+        for (int w = 0; w < act; ++w) {
+            const float *wr = w0 + w * nr * REC;
+            const float f = __expf(wr[HD] - gm);
+            const float4 o = load_f4(wr + e);
+            num.x += o.x * f; num.y += o.y * f; num.z += o.z * f; num.w += o.w * f;
+            den += wr[HD + 1] * f;
+        }
+    }
+    if (n_splits > 1) {
+        const int unit = blockIdx.z * a.H + hh;
+        const WRes part = buffer_resource(a.sc.att_part + (size_t)unit * n_splits * ATT_ROWS * REC);
+        constexpr int SP_BYTES = ATT_ROWS * REC * 4;
+        if (mine) {
+            const int off = sp * SP_BYTES + i * REC * 4;
+            store_dev128(part, off + e * 4, num);
+            if (e == 0) store_dev128(part, off + HD * 4, make_float4(gm, den, 0.f, 0.f));
+        }
+        wait_vmem();      // this workgroup's partials are visible device-wide ...
+        __syncthreads();  // ... for every wave, before it is counted
+        if (tid == 0) {
+            const int before = __hip_atomic_fetch_add(a.sc.att_count + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *lastf = before == n_splits - 1 ? 1 : 0;
+            if (*lastf) __hip_atomic_store(a.sc.att_count + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
-        // merge the waves, fixed order
-        if (n_splits == 1) {
-            for (int t = tid; t < nr * HD; t += WG_THREADS) {
-                int i = t / HD, e = t - i * HD;
-                float gm = ATT_NEG;
-                for (int w = 0; w < WAVES; ++w) gm = fmaxf(gm, wbuf[((size_t)w * ATT_ROWS + i) * REC + HD]);
-                float num = 0.f, den = 0.f;
-                for (int w = 0; w < WAVES; ++w) {
-                    const float *wr = wbuf + ((size_t)w * ATT_ROWS + i) * REC;
-                    float f = __expf(wr[HD] - gm);
-                    num += wr[e] * f;
-                    den += wr[HD + 1] * f;
-                }
-                uint32_t vh, vl;
-                split_bf16(num / den, vh, vl);
-                a.sc.attn[x_index(a.rows, s * M + r0 + i, hh * HD + e, 0)] = (uint16_t)vh;
-                a.sc.attn[x_index(a.rows, s * M + r0 + i, hh * HD + e, 1)] = (uint16_t)vl;
-            }
-        } else {
-            float *out = a.sc.att_part + (size_t)item * ATT_ROWS * REC;
-            for (int t = tid; t < nr * REC; t += WG_THREADS) {
-                int i = t / REC, e = t - i * REC;
-                float gm = ATT_NEG;
-                for (int w = 0; w < WAVES; ++w) gm = fmaxf(gm, wbuf[((size_t)w * ATT_ROWS + i) * REC + HD]);
-                float r;
-                if (e == HD) {
-                    r = gm;
-                } else {
-                    r = 0.f;
-                    for (int w = 0; w < WAVES; ++w) {
-                        const float *wr = wbuf + ((size_t)w * ATT_ROWS + i) * REC;
-                        r += wr[e] * __expf(wr[HD] - gm);
-                    }
-                }
-                store_dev32(out + (size_t)i * REC + e, r);
-            }
-            wait_vmem();      // this item's partials are visible device-wide ...
-            __syncthreads();  // ... for every wave, before it is counted
-            if (tid == 0) {
-                int before = __hip_atomic_fetch_add(a.sc.att_count + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                *lastf = before == n_splits - 1 ? 1 : 0;
-            }
-            __syncthreads();
-            if (*lastf) {
-                // (the split count goes through an opaque copy here: otherwise everything below that
-                // depends only on it -- sixteen clamped offsets, sixteen conditions -- is worked out
-                // at the start of the kernel, by every workgroup, before its first load)
-                const int n_splits = opaque(a.att_splits);
-                const float *base = a.sc.att_part + (size_t)unit * n_splits * ATT_ROWS * REC;
-                const size_t sp_stride = (size_t)ATT_ROWS * REC;
-                for (int t = tid; t < nr * HD; t += WG_THREADS) {
-                    int i = t / HD, e = t - i * HD;
-                    const float *row = base + (size_t)i * REC;
-                    // all loads first, so that they are in flight together
-                    float pm[ATT_MAX_SPLITS], pv[ATT_MAX_SPLITS], pl[ATT_MAX_SPLITS];
+        if (!*lastf) return;
+        if (mine) {
+            // eight splits' loads in flight together; a second round only for more than eight
+            num = make_float4(0.f, 0.f, 0.f, 0.f);
+            den = 0.f;
+            gm = ATT_NEG;
+            for (int k0 = 0; k0 < n_splits; k0 += 8) {
+                float4 pv[8], pm[8];
 #pragma unroll
-                    for (int k = 0; k < ATT_MAX_SPLITS; ++k) {
-                        const float *r = row + min(k, n_splits - 1) * sp_stride;
-                        pm[k] = load_dev32(r + HD);
-                        pv[k] = load_dev32(r + e);
-                        pl[k] = load_dev32(r + HD + 1);
-                    }
-                    float gm = ATT_NEG;
-#pragma unroll
-                    for (int k = 0; k < ATT_MAX_SPLITS; ++k)
-                        if (k < n_splits) gm = fmaxf(gm, pm[k]);
-                    float num = 0.f, den = 0.f;
-#pragma unroll
-                    for (int k = 0; k < ATT_MAX_SPLITS; ++k)
-                        if (k < n_splits) {
-                            float f = __expf(pm[k] - gm);
-                            num += pv[k] * f;
-                            den += pl[k] * f;
-                        }
-                    uint32_t vh, vl;
-                    split_bf16(num / den, vh, vl);
-                    a.sc.attn[x_index(a.rows, s * M + r0 + i, hh * HD + e, 0)] = (uint16_t)vh;
-                    a.sc.attn[x_index(a.rows, s * M + r0 + i, hh * HD + e, 1)] = (uint16_t)vl;
+                for (int k = 0; k < 8; ++k) {
+                    const int off = min(k0 + k, n_splits - 1) * SP_BYTES + i * REC * 4;
+                    pv[k] = load_dev128(part, off + e * 4);
+                    pm[k] = load_dev128(part, off + HD * 4);
                 }
-                if (tid == 0) __hip_atomic_store(a.sc.att_count + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                float m_new = gm;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) m_new = fmaxf(m_new, pm[k].x);
+                const float f0 = __expf(gm - m_new);
+                gm = m_new;
+                num.x *= f0; num.y *= f0; num.z *= f0; num.w *= f0;
+                den *= f0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float f = k0 + k < n_splits ? __expf(pm[k].x - gm) : 0.f;
+                    num.x += pv[k].x * f; num.y += pv[k].y * f; num.z += pv[k].z * f; num.w += pv[k].w * f;
+                    den += pm[k].y * f;
+                }
             }
         }
-        __syncthreads();
+    }
+    if (mine) {
+        const float inv = 1.0f / den;
+        const float v[4] = {num.x * inv, num.y * inv, num.z * inv, num.w * inv};
+        store_split4(a.sc.attn, a.rows, s * M + r0 + i, hh * HD + e, v);
     }
 }
 
@@ -1589,7 +1566,7 @@ __global__ void __launch_bounds__(WG_THREADS) ee_att_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
-    att_stage<HD>(a, a.layer, lds);
+    att_stage<HD>(a, lds);
 }
 
 // embedding

@@ -492,7 +492,7 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             m->wstride[v][k] = (long long)pl.steps * pl.nwg * SWAVES * 64;
         }
     {
-        const size_t att = (size_t)WAVES * ATT_ROWS * (c.head_dim + 2) * sizeof(float) + 16;  // wave partials + the "last item of the unit" flag
+        const size_t att = att_lds(c.head_dim, ATT_ROWS);
         const size_t emb = (size_t)max_rows * (((c.d_model + m->nwg - 1) / m->nwg + 3) / 4 + 1) * sizeof(float);
         if (att > m->lds_budget || emb > m->lds_budget) {
             ee_model_free(m);
@@ -832,7 +832,7 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         const size_t forced = ((size_t)s->n_pages + ATT_TILES * WAVES - 1) / (ATT_TILES * WAVES);
         const size_t max_items = max_units * std::max<size_t>(forced, 2) + (size_t)m->nwg;
         s->att_items_cap = (int)max_items;
-        S_TRY(dev_alloc(s->allocs, &sc.att_part, max_items * ATT_ROWS * (c.head_dim + 2)));
+        S_TRY(dev_alloc(s->allocs, &sc.att_part, max_items * ATT_ROWS * att_rec(c.head_dim)));
         S_TRY(dev_alloc(s->allocs, &sc.att_count, max_units));
         S_TRY(dev_alloc(s->allocs, &sc.head_count, 1));
     }
@@ -1013,7 +1013,11 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             lead->lt_codes.push_back(code);
             HIP_TRY(hipEventRecord(lead->lt_events[2 * i], lead->run_stream));
         }
-        hipLaunchKernelGGL(k, dim3(m->nwg), dim3(WG_THREADS), m->lds_budget, lead->run_stream, a);
+        if (code == EE_LAUNCH_ATT)
+            hipLaunchKernelGGL(k, dim3(a.att_splits, a.H, a.mode == 1 ? (a.M + ATT_ROWS - 1) / ATT_ROWS : a.n_sess), dim3(WG_THREADS),
+                               att_lds(m->cfg.head_dim, a.M), lead->run_stream, a);
+        else
+            hipLaunchKernelGGL(k, dim3(m->nwg), dim3(WG_THREADS), m->lds_budget, lead->run_stream, a);
         HIP_TRY(hipGetLastError());
         if (timed) HIP_TRY(hipEventRecord(lead->lt_events[2 * lead->lt_codes.size() - 1], lead->run_stream));
         if (code == EE_LAUNCH_HEAD && a.sm.on) {
@@ -1345,7 +1349,7 @@ static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_ma
     sc.head_count = reinterpret_cast<int *>(take(4));
     sc.logits = lead->sc.logits;   // kept logits are an output of the session, not scratch
     // attention partials: what is left, at most one item per compute unit and split
-    const size_t item_bytes = (size_t)ATT_ROWS * (md.hd + 2) * 4;
+    const size_t item_bytes = (size_t)ATT_ROWS * att_rec(md.hd) * 4;
     if (off + (size_t)md.H * item_bytes > EE_STATIC_SCRATCH_BYTES)
         return fail(EE_ECAPACITY, "ee_verify_static: %d rows of this model need more than the %d bytes of static scratch", M, EE_STATIC_SCRATCH_BYTES);
     const int items_cap = (int)std::min<size_t>((EE_STATIC_SCRATCH_BYTES - off) / item_bytes, (size_t)md.H * ATT_MAX_SPLITS);

@@ -355,6 +355,16 @@ def test_attention_several_pages_per_wave(mid_pair, splits, prompt_len):
     assert err <= 3e-2
 
 
+@pytest.mark.parametrize("splits,prompt_len", [(8, 500), (9, 500), (16, 700), (16, 40), (1, 1)])
+def test_attention_merge_of_many_splits(tiny_pair, mid_pair, splits, prompt_len):
+    """Up to eight partial results are merged in one round, more in two; 16 splits of three pages leave
+    most splits (and most waves) without a page."""
+    for (g, o), exits in ((tiny_pair, TINY_EXITS), (mid_pair, [1, 2])):
+        prompt = eegen.prompt_tokens(620 + splits, prompt_len, o.vocab)
+        drafts = eegen.prompt_tokens(621 + splits, 5, o.vocab)
+        _one_round(g, o, prompt, drafts, exits, what=f"{splits} splits of {prompt_len}", options=[(ee.OPT_ATT_SPLITS, splits)])
+
+
 def test_gamma_extremes_and_page_boundary(tiny_pair):
     """gamma = 1 and gamma = 15 (the most rows of one attention item), prompts that end right
     before, on and after a page boundary."""
