@@ -46,6 +46,9 @@ struct PfArgs {
     const int2 *tab;          // [NT] per n-tile: first tile and distance between k-tiles 8 apart, in tiles of 1 KB
     int NT, KT, N;
     int nb, mb;               // workgroup tiles along N and along the rows
+    int ks;                   // workgroups that share a tile, each with its part of K
+    float *part;              // ks > 1: [tile][part][wave][accumulator][lane][4] partial tiles
+    int *part_count;          // ks > 1: [tile] parts delivered; zero between launches
     const float *gain;        // O / DN: gain of the next GEMM input, or nullptr
     const float *ss_in;       // partial sums of squares of the input's rows (QKV, GU)
     int ss_slots;
@@ -80,7 +83,8 @@ __device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int 
 // Stages of the ring a tile shape uses: what fits 64 to 72 KB, so that two workgroups share a
 // compute unit and one's barrier and epilogue run under the other's products.
 constexpr int pf_stages(int wn, int wm) { return (wn + 2 * wm) * 2 >= 32 ? 2 : ((wn + 2 * wm) * 2 >= 24 ? 3 : 4); }
-constexpr size_t pf_gemm_lds(int wn, int wm) { return (size_t)pf_stages(wn, wm) * (wn + 2 * wm) * 2048 + (size_t)wm * 32 * 4; }
+constexpr size_t pf_gemm_lds(int wn, int wm) { return (size_t)pf_stages(wn, wm) * (wn + 2 * wm) * 2048 + (size_t)wm * 32 * 4 + 16; }
+constexpr size_t pf_tile_floats(int wn, int wm) { return (size_t)wn * wm * 1024; }
 
 // One GEMM of the chunk.  Workgroup tile: 2 WN n-tiles x 2 WM row tiles, four waves as 2 x 2, each
 // WN x WM accumulators.  Per k-tile of 32 the stage's W tiles and both terms of the X tiles travel to
@@ -91,6 +95,11 @@ constexpr size_t pf_gemm_lds(int wn, int wm) { return (size_t)pf_stages(wn, wm) 
 // (1.34 PFLOP/s), QKV 315 us (1.31), down 312 us (1.18), output projection 132 us (1.04; 256
 // workgroups, one per unit).  The same rows in chunks of 16 through the streaming kernels: 3 ms per
 // chunk, 486 ms per prompt against 50 ms.
+// With few rows the tiles do not cover the chip and a workgroup alone on its unit needs 0.27 us (2 x 2)
+// to 0.85 us (8 x 4) per k-tile, mostly a chain of barrier, LDS reads and products: then ks workgroups
+// share a tile, each with a part of K (pf_choose).  64 rows, 7B shape, us without / with: down 86 / 29,
+// output 35 / 18, QKV 40 / 34.  (A deeper ring, operands read a stage ahead into registers, the 32x32x16
+// instruction and starting places along K that differ between workgroups: each within 3 % or slower.)
 template <int KIND, int WN, int WM>
 __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
 {
@@ -105,13 +114,20 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
     // Workgroups are dealt to the XCDs round-robin; each XCD gets a contiguous run of the tile
     // sequence, which walks groups of four n-blocks over all row blocks: the workgroups that run together on
     // an XCD then share a few W and X blocks in its L2.
-    const int T = a.nb * a.mb;
-    int t;
+    const int T = a.nb * a.mb * a.ks;
+    int t, part = 0;
     {
         const int x = blockIdx.x % NUM_XCD, j = blockIdx.x / NUM_XCD;
         const int base = T / NUM_XCD, extra = T % NUM_XCD;
         t = x * base + min(x, extra) + j;
+        if (a.ks > 1) {                                      // the parts of a tile follow each other
+            const int tile = div_small(t, a.ks);
+            part = t - tile * a.ks;
+            t = tile;
+        }
     }
+    const int tile = t;
+    const int kt_lo = a.ks > 1 ? div_small(a.KT * part, a.ks) : 0, kt_hi = a.ks > 1 ? div_small(a.KT * (part + 1), a.ks) : a.KT;
     const int gsz = 4 * a.mb, grp = div_small(t, gsz), rem = t - grp * gsz;
     const int gw = min(4, a.nb - grp * 4);
     const int mblk = div_small(rem, gw), nblk = grp * 4 + (rem - mblk * gw);
@@ -147,7 +163,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
     };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
-        if (s < a.KT) request(s, s);
+        if (kt_lo + s < kt_hi) request(kt_lo + s, s);
     // row factors of the norm
     if (KIND == G_QKV || KIND == G_GU) {
         for (int r = tid; r < BMT * 16; r += PF_THREADS) {
@@ -166,15 +182,15 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
         for (int j = 0; j < WM; ++j) acc[i][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
     int buf = 0;
-    for (int kt = 0; kt < a.KT; ++kt) {
+    for (int kt = kt_lo; kt < kt_hi; ++kt) {
         // this wave's loads of stage kt have landed; after the barrier everybody's have, and nobody
         // reads the buffer of stage kt - 1 any more
-        if (kt + NS - 2 < a.KT)
+        if (kt + NS - 2 < kt_hi)
             wait_pending<PER *(NS - 2)>();
         else
             wait_pending<0>();
         lds_barrier();
-        if (kt + NS - 1 < a.KT) request(kt + NS - 1, buf == 0 ? NS - 1 : buf - 1);
+        if (kt + NS - 1 < kt_hi) request(kt + NS - 1, buf == 0 ? NS - 1 : buf - 1);
         const char *st = lds + buf * STAGE;
         const char *sw = st + (wn * WN) * 1024 + lane16;
         const char *sx = st + (BNT + wm * WM) * 1024 + lane16;
@@ -196,6 +212,43 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
         buf = buf + 1 == NS ? 0 : buf + 1;
     }
 
+    if (a.ks > 1) {
+        // K shared by several workgroups: the partial tiles meet in memory and the workgroup that arrives last adds
+        // them up in the order of the parts and goes on alone.  Nothing waits.
+        int *lastf = reinterpret_cast<int *>(lds + NS * STAGE + WM * 32 * 4);
+        constexpr int TILE_B = WN * WM * 4096;               // bytes of a partial tile
+        const WRes mem = buffer_resource(a.part + (size_t)tile * a.ks * (TILE_B / 4));
+        const int off = wave * (WN * WM * 1024) + lane16;
+#pragma unroll
+        for (int i = 0; i < WN; ++i)
+#pragma unroll
+            for (int j = 0; j < WM; ++j)
+                store_dev128(mem, part * TILE_B + off + (i * WM + j) * 1024, make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]));
+        wait_vmem();      // this workgroup's part is visible device-wide ...
+        __syncthreads();  // ... for every wave, before it is counted
+        if (tid == 0) {
+            const int before = __hip_atomic_fetch_add(a.part_count + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *lastf = before == a.ks - 1 ? 1 : 0;
+            if (*lastf) __hip_atomic_store(a.part_count + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!*lastf) return;
+#pragma unroll
+        for (int j = 0; j < WM; ++j) {
+            f32x4_t total[WN];
+#pragma unroll
+            for (int i = 0; i < WN; ++i) total[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            for (int p = 0; p < a.ks; ++p) {
+                float4 x[WN];
+#pragma unroll
+                for (int i = 0; i < WN; ++i) x[i] = load_dev128(mem, p * TILE_B + off + (i * WM + j) * 1024);
+#pragma unroll
+                for (int i = 0; i < WN; ++i) total[i] += (f32x4_t){x[i].x, x[i].y, x[i].z, x[i].w};
+            }
+#pragma unroll
+            for (int i = 0; i < WN; ++i) acc[i][j] = total[i];
+        }
+    }
     // epilogue from the accumulators: lane holds columns n .. n+3 (n = n-tile * 16 + (lane >> 4) * 4) of row m
     const int quad = lane >> 4, lm = lane & 15;
 #pragma unroll

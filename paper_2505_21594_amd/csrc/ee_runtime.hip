@@ -95,6 +95,8 @@ struct ee_session {
     SessDev *host_sessdev;           // pinned staging for them
     PfScratch pf;                    // buffers of a prefill chunk
     float *pf_ss[2];                 // sums of squares: after the FFN block / embedding, after the attention block
+    float *pf_part;                  // partial tiles of prefill GEMMs whose K is shared by several workgroups
+    int *pf_part_count;              // [PF_PART_TILES] parts delivered
     int pf_cap;                      // rows of the largest prefill chunk
     Scratch sc;
     int att_items_cap;               // attention work items the partials buffer has room for
@@ -147,6 +149,9 @@ static pass_kernel_t gemm_kernel(int kind, int rows)
 
 static pass_kernel_t att_kernel(int hd) { return hd == 128 ? ee_att_kernel<128> : ee_att_kernel<64>; }
 
+constexpr size_t PF_PART_FLOATS = (size_t)12 << 20;   // partial tiles of one launch: at most 48 MB
+constexpr int PF_PART_TILES = 4096;
+
 typedef void (*pf_kernel_t)(PfArgs);
 struct PfShape {
     int wn, wm;                  // a wave's accumulators: n-tiles x row tiles (workgroup: twice that each way)
@@ -160,15 +165,46 @@ static pf_kernel_t pf_att(int hd, int rt)
     return hd == 128 ? (rt == 2 ? pf_att_kernel<128, 2> : pf_att_kernel<128, 1>) : (rt == 2 ? pf_att_kernel<64, 2> : pf_att_kernel<64, 1>);
 }
 
-// The largest workgroup tile that still gives every compute unit one: a larger tile needs fewer bytes per
-// product (32 KB per 64 MFMAs of a wave for 8 x 4, 12 KB per 8 for 2 x 2).
-static const PfShape &pf_shape(const ee_model *m, const GemmPlan &pl, int rows)
+// Shape of the workgroup tile and parts of K of one prefill GEMM: the least estimated time.  The estimate, in us
+// per k-tile: t1 where a workgroup is alone on its compute unit (a chain of latencies), t2 per workgroup where a
+// unit has several (occ fit); a split adds the exchange of the partial tiles (measured: about 5 us, 0.7 us
+// per part read one after the other, and the bytes at 3.5 TB/s).  Fitted to QKV, O, GU and DN of the 7B
+// shape at 64 to 2048 rows; its choice is within 8 % of the best measured one, most often the best.
+struct PfChoice {
+    const PfShape *shape;
+    int nb, mb, ks;
+};
+static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows)
 {
-    for (const PfShape &s : PF_SHAPES) {
+    static const struct {
+        double t1, t2;
+        int occ;
+    } cost[] = {{0.85, 0.72, 2}, {0.55, 0.41, 2}, {0.36, 0.27, 2}, {0.27, 0.175, 3}};
+    PfChoice best = {};
+    double best_t = 0;
+    const double cu = m->nwg;
+    for (size_t i = 0; i < sizeof PF_SHAPES / sizeof PF_SHAPES[0]; ++i) {
+        const PfShape &s = PF_SHAPES[i];
         const int nb = (pl.NT + 2 * s.wn - 1) / (2 * s.wn), mb = (rows + 32 * s.wm - 1) / (32 * s.wm);
-        if (nb * mb >= m->nwg) return s;
+        for (int ks : {1, 2, 3, 4, 6, 8}) {
+            const size_t part = (size_t)nb * mb * ks * pf_tile_floats(s.wn, s.wm);
+            if (ks > 1 && (pl.KT < 8 * ks || part > PF_PART_FLOATS || nb * mb > PF_PART_TILES)) break;
+            double left = (double)nb * mb * ks, f = 0;
+            const double slots = cu * cost[i].occ;
+            while (left > slots) {   // full rounds
+                f += cost[i].occ * cost[i].t2;
+                left -= slots;
+            }
+            f += left <= cu ? cost[i].t1 : std::max(1.25 * cost[i].t1, left / cu * cost[i].t2);
+            double t = f * ((pl.KT + ks - 1) / ks);
+            if (ks > 1) t += 5.0 + 0.7 * ks + (double)part * 8.0 / 3.5e6;
+            if (!best.shape || t < best_t) {
+                best = {&s, nb, mb, ks};
+                best_t = t;
+            }
+        }
     }
-    return PF_SHAPES[sizeof PF_SHAPES / sizeof PF_SHAPES[0] - 1];
+    return best;
 }
 
 // n-tiles the busiest workgroup owns
@@ -802,6 +838,11 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         S_TRY(dev_alloc(s->allocs, &b.u, 2 * cap * pm.Kpad_F, pad));
         const size_t slots = 2 * (((size_t)pm.d + 63) / 64);   // two per workgroup tile of the narrowest shape
         for (int i = 0; i < 2; ++i) S_TRY(dev_alloc(s->allocs, &s->pf_ss[i], slots * cap, false));
+        // room for the largest split the rule may choose: every GEMM's tiles (whole tiles: up to 255 columns and
+        // 127 rows more) times the parts, or the cap
+        const size_t n_max = align_up(std::max<size_t>(3 * d, 2 * (size_t)pm.F), 256), part_max = 8 * n_max * align_up(cap, 128);
+        S_TRY(dev_alloc(s->allocs, &s->pf_part, std::min<size_t>(part_max, PF_PART_FLOATS), false));
+        S_TRY(dev_alloc(s->allocs, &s->pf_part_count, (size_t)PF_PART_TILES));
         S_TRY(dev_alloc(s->allocs, &s->dev_pf_tokens, pf_rows));
         S_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->host_pf_tokens), pf_rows * sizeof(int), hipHostMallocDefault));
         S_TRY(dev_alloc(s->allocs, &s->dev_pf_emb, pf_rows * d, false));
@@ -1110,6 +1151,8 @@ static int prefill_chunk(ee_session *s, int start, int rows)
     a.tokens = s->dev_pf_tokens;
     a.emb_rows = s->dev_pf_emb;
     a.emb = md.emb;
+    a.part = s->pf_part;
+    a.part_count = s->pf_part_count;
     a.gain = md.g_attn;
     a.ss_out = s->pf_ss[0];
     hipLaunchKernelGGL(pf_embed_kernel, dim3(rows), dim3(PF_THREADS), 0, s->stream, a);
@@ -1117,15 +1160,17 @@ static int prefill_chunk(ee_session *s, int start, int rows)
     int slots = 1;                                          // partial sums per row in pf_ss[0]
     auto gemm = [&](int kind, int layer) {
         const GemmPlan &pl = m->plan[0][kind];
-        const PfShape &sh = pf_shape(m, pl, rows);
+        const PfChoice ch = pf_choose(m, pl, rows);
+        const PfShape &sh = *ch.shape;
         a.W = m->w[0][kind] + (size_t)layer * m->wstride[0][kind];
         a.tab = m->tile_tab[kind];
         a.NT = pl.NT;
         a.KT = pl.KT;
         a.N = pl.N;
-        a.nb = (pl.NT + 2 * sh.wn - 1) / (2 * sh.wn);
-        a.mb = (rows + 32 * sh.wm - 1) / (32 * sh.wm);
-        hipLaunchKernelGGL(sh.gemm[kind], dim3(a.nb * a.mb), dim3(PF_THREADS), pf_gemm_lds(sh.wn, sh.wm), s->stream, a);
+        a.nb = ch.nb;
+        a.mb = ch.mb;
+        a.ks = ch.ks;
+        hipLaunchKernelGGL(sh.gemm[kind], dim3(a.nb * a.mb * a.ks), dim3(PF_THREADS), pf_gemm_lds(sh.wn, sh.wm), s->stream, a);
     };
     for (int l = 0; l < c.n_layers; ++l) {
         a.layer = l;
@@ -1187,7 +1232,7 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
     // More rows than one streamed launch takes: chunks of many rows, of nearly equal size.  61 rows of a
     // 1280-wide model, 3 layers, prefill and one pass: 513 us against 946 us in streamed chunks of 16;
     // 640 rows of 8 layers of the 7B shape 5.7 ms against 19.8 ms in chunks of 40.
-    const bool many = total > EE_MAX_ROWS;
+    const bool many = total > c.max_rows;
     const int n_chunks = (total + s->pf_cap - 1) / s->pf_cap;
     const int chunk = many ? std::min(s->pf_cap, (int)align_up((size_t)((total + n_chunks - 1) / n_chunks), 128)) : c.max_rows;
     const size_t d = (size_t)c.d_model;
