@@ -82,8 +82,8 @@ __device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int 
 
 // Stages of the ring a tile shape uses: what fits 64 to 72 KB, so that two workgroups share a
 // compute unit and one's barrier and epilogue run under the other's products.
-constexpr int pf_stages(int wn, int wm) { return (wn + 2 * wm) * 2 >= 32 ? 2 : ((wn + 2 * wm) * 2 >= 24 ? 3 : 4); }
-constexpr size_t pf_gemm_lds(int wn, int wm) { return (size_t)pf_stages(wn, wm) * (wn + 2 * wm) * 2048 + (size_t)wm * 32 * 4 + 16; }
+constexpr int pf_stages(int wn, int wm, int grp) { return grp > 1 ? 144 / (grp * (wn + 2 * wm) * 2) : (wn + 2 * wm) * 2 >= 32 ? 2 : ((wn + 2 * wm) * 2 >= 24 ? 3 : 4); }
+constexpr size_t pf_gemm_lds(int wn, int wm, int grp) { return (size_t)grp * pf_stages(wn, wm, grp) * (wn + 2 * wm) * 2048 + (size_t)wm * 32 * 4 + 16; }
 constexpr size_t pf_tile_floats(int wn, int wm) { return (size_t)wn * wm * 1024; }
 
 // One GEMM of the chunk.  Workgroup tile: 2 WN n-tiles x 2 WM row tiles, four waves as 2 x 2, each
@@ -97,19 +97,20 @@ constexpr size_t pf_tile_floats(int wn, int wm) { return (size_t)wn * wm * 1024;
 // chunk, 486 ms per prompt against 50 ms.
 // With few rows the tiles do not cover the chip and a workgroup alone on its unit needs 0.27 us (2 x 2)
 // to 0.85 us (8 x 4) per k-tile, mostly a chain of barrier, LDS reads and products: then ks workgroups
-// share a tile, each with a part of K (pf_choose).  64 rows, 7B shape, us without / with: down 86 / 29,
-// output 35 / 18, QKV 40 / 34.  (A deeper ring, operands read a stage ahead into registers, the 32x32x16
+// share a tile, each with a part of K, and GRP groups of four waves share a workgroup's K, group g taking the
+// k-tiles g, g + GRP, ... through a ring of its own (pf_choose).  64 rows, 7B shape, us without / with: down 86 / 29,
+// output 35 / 18, QKV 40 / 34; four groups instead of one, 1280-wide model, 64 rows: QKV 16 / 11, gate/up 13 / 9.  (A deeper ring, operands read a stage ahead into registers, the 32x32x16
 // instruction and starting places along K that differ between workgroups: each within 3 % or slower.)
-template <int KIND, int WN, int WM>
-__global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
+template <int KIND, int WN, int WM, int GRP>
+__global__ void __launch_bounds__(PF_THREADS * GRP, GRP > 1 ? GRP : 2) pf_gemm_kernel(PfArgs a)
 {
-    constexpr int BNT = 2 * WN, BMT = 2 * WM, NS = pf_stages(WN, WM);
+    constexpr int BNT = 2 * WN, BMT = 2 * WM, NS = pf_stages(WN, WM, GRP);
     constexpr int WL = BNT / 4, XL = 2 * BMT / 4;            // loads per wave and stage
     constexpr int PER = WL + XL;
     constexpr unsigned STAGE = (BNT + 2 * BMT) * 1024;
     static_assert(BNT % 4 == 0 && BMT % 2 == 0, "tile shape");
     extern __shared__ __align__(16) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, grp = __builtin_amdgcn_readfirstlane(tid >> 8), wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
     const int wn = wave & 1, wm = wave >> 1;
     // Workgroups are dealt to the XCDs round-robin; each XCD gets a contiguous run of the tile
     // sequence, which walks groups of four n-blocks over all row blocks: the workgroups that run together on
@@ -128,13 +129,14 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
     }
     const int tile = t;
     const int kt_lo = a.ks > 1 ? div_small(a.KT * part, a.ks) : 0, kt_hi = a.ks > 1 ? div_small(a.KT * (part + 1), a.ks) : a.KT;
-    const int gsz = 4 * a.mb, grp = div_small(t, gsz), rem = t - grp * gsz;
-    const int gw = min(4, a.nb - grp * 4);
-    const int mblk = div_small(rem, gw), nblk = grp * 4 + (rem - mblk * gw);
+    const int gsz = 4 * a.mb, tg = div_small(t, gsz), rem = t - tg * gsz;
+    const int gw = min(4, a.nb - tg * 4);
+    const int mblk = div_small(rem, gw), nblk = tg * 4 + (rem - mblk * gw);
     const int nt0 = nblk * BNT, mt0 = mblk * BMT;
 
-    float *rstd = reinterpret_cast<float *>(lds + NS * STAGE);
-    const unsigned lds0 = lds_offset(lds);
+    float *rstd = reinterpret_cast<float *>(lds + GRP * NS * STAGE);
+    char *ring = lds + grp * NS * STAGE;                     // this group's ring
+    const unsigned lds0 = lds_offset(ring);
     // this wave's share of a stage
     const char *wbase[WL];
     int wstride[WL];
@@ -163,10 +165,10 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
     };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
-        if (kt_lo + s < kt_hi) request(kt_lo + s, s);
+        if (kt_lo + grp + s * GRP < kt_hi) request(kt_lo + grp + s * GRP, s);
     // row factors of the norm
     if (KIND == G_QKV || KIND == G_GU) {
-        for (int r = tid; r < BMT * 16; r += PF_THREADS) {
+        for (int r = tid; r < BMT * 16; r += PF_THREADS * GRP) {
             const int m = min(mt0 * 16 + r, a.rows - 1);
             float s = 0.f;
 #pragma unroll 8
@@ -182,16 +184,19 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
         for (int j = 0; j < WM; ++j) acc[i][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
     int buf = 0;
-    for (int kt = kt_lo; kt < kt_hi; ++kt) {
+    for (int kt0 = kt_lo; kt0 < kt_hi; kt0 += GRP) {         // (all groups run the same number of rounds)
+        const int kt = kt0 + grp;
         // this wave's loads of stage kt have landed; after the barrier everybody's have, and nobody
         // reads the buffer of stage kt - 1 any more
-        if (kt + NS - 2 < kt_hi)
+        if (kt + (NS - 2) * GRP < kt_hi)
             wait_pending<PER *(NS - 2)>();
         else
             wait_pending<0>();
         lds_barrier();
-        if (kt + NS - 1 < kt_hi) request(kt + NS - 1, buf == 0 ? NS - 1 : buf - 1);
-        const char *st = lds + buf * STAGE;
+        if (kt + (NS - 1) * GRP < kt_hi) request(kt + (NS - 1) * GRP, buf == 0 ? NS - 1 : buf - 1);
+        const char *st = ring + buf * STAGE;
+        buf = buf + 1 == NS ? 0 : buf + 1;
+        if (GRP > 1 && kt >= kt_hi) continue;
         const char *sw = st + (wn * WN) * 1024 + lane16;
         const char *sx = st + (BNT + wm * WM) * 1024 + lane16;
         bf16x8_t w[WN], xh[WM], xl[WM];
@@ -209,13 +214,35 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
 #pragma unroll
             for (int i = 0; i < WN; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], xl[j], acc[i][j], 0, 0, 0);
         }
-        buf = buf + 1 == NS ? 0 : buf + 1;
     }
 
+    if (GRP > 1) {
+        // the groups' partial tiles meet in LDS; group 0 adds them up in group order and goes on
+        lds_barrier();
+        float4 *mine = reinterpret_cast<float4 *>(lds) + ((size_t)grp * 4 + wave) * (WN * WM * 64) + lane;
+        if (grp > 0) {
+#pragma unroll
+            for (int i = 0; i < WN; ++i)
+#pragma unroll
+                for (int j = 0; j < WM; ++j) mine[(i * WM + j) * 64] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        }
+        lds_barrier();
+        if (grp == 0) {
+#pragma unroll
+            for (int q = 1; q < GRP; ++q)
+#pragma unroll
+                for (int i = 0; i < WN; ++i)
+#pragma unroll
+                    for (int j = 0; j < WM; ++j) {
+                        const float4 x = mine[(size_t)q * 4 * (WN * WM * 64) + (i * WM + j) * 64];
+                        acc[i][j] += (f32x4_t){x.x, x.y, x.z, x.w};
+                    }
+        }
+    }
     if (a.ks > 1) {
         // K shared by several workgroups: the partial tiles meet in memory and the workgroup that arrives last adds
         // them up in the order of the parts and goes on alone.  Nothing waits.
-        int *lastf = reinterpret_cast<int *>(lds + NS * STAGE + WM * 32 * 4);
+        int *lastf = reinterpret_cast<int *>(lds + GRP * NS * STAGE + WM * 32 * 4);
         constexpr int TILE_B = WN * WM * 4096;               // bytes of a partial tile
         const WRes mem = buffer_resource(a.part + (size_t)tile * a.ks * (TILE_B / 4));
         const int off = wave * (WN * WM * 1024) + lane16;
@@ -223,7 +250,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
         for (int i = 0; i < WN; ++i)
 #pragma unroll
             for (int j = 0; j < WM; ++j)
-                store_dev128(mem, part * TILE_B + off + (i * WM + j) * 1024, make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]));
+                if (grp == 0) store_dev128(mem, part * TILE_B + off + (i * WM + j) * 1024, make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]));
         wait_vmem();      // this workgroup's part is visible device-wide ...
         __syncthreads();  // ... for every wave, before it is counted
         if (tid == 0) {
@@ -232,7 +259,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
             if (*lastf) __hip_atomic_store(a.part_count + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
-        if (!*lastf) return;
+        if (!*lastf || grp > 0) return;
 #pragma unroll
         for (int j = 0; j < WM; ++j) {
             f32x4_t total[WN];
@@ -249,6 +276,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_gemm_kernel(PfArgs a)
             for (int i = 0; i < WN; ++i) acc[i][j] = total[i];
         }
     }
+    if (GRP > 1 && grp > 0) return;
     // epilogue from the accumulators: lane holds columns n .. n+3 (n = n-tile * 16 + (lane >> 4) * 4) of row m
     const int quad = lane >> 4, lm = lane & 15;
 #pragma unroll

@@ -155,10 +155,17 @@ constexpr int PF_PART_TILES = 4096;
 typedef void (*pf_kernel_t)(PfArgs);
 struct PfShape {
     int wn, wm;                  // a wave's accumulators: n-tiles x row tiles (workgroup: twice that each way)
+    int grp;                     // groups of four waves that share the workgroup's K
+    double t1, t2;               // us per k-tile: a workgroup alone on its compute unit; per workgroup where a unit has `occ`
+    int occ;
     pf_kernel_t gemm[G_DN + 1];
 };
-#define EE_PF_SHAPE(WN, WM) {WN, WM, {pf_gemm_kernel<G_QKV, WN, WM>, pf_gemm_kernel<G_O, WN, WM>, pf_gemm_kernel<G_GU, WN, WM>, pf_gemm_kernel<G_DN, WN, WM>}}
-static const PfShape PF_SHAPES[] = {EE_PF_SHAPE(8, 4), EE_PF_SHAPE(4, 4), EE_PF_SHAPE(4, 2), EE_PF_SHAPE(2, 2)};
+#define EE_PF_SHAPE(WN, WM, GRP, T1, T2, OCC)                                                    \
+    {WN, WM, GRP, T1, T2, OCC, {pf_gemm_kernel<G_QKV, WN, WM, GRP>, pf_gemm_kernel<G_O, WN, WM, GRP>, \
+                                pf_gemm_kernel<G_GU, WN, WM, GRP>, pf_gemm_kernel<G_DN, WN, WM, GRP>}}
+static const PfShape PF_SHAPES[] = {
+    EE_PF_SHAPE(8, 4, 1, 0.85, 0.72, 2), EE_PF_SHAPE(4, 4, 1, 0.55, 0.41, 2), EE_PF_SHAPE(4, 2, 1, 0.36, 0.27, 2), EE_PF_SHAPE(2, 2, 1, 0.27, 0.175, 3),
+    EE_PF_SHAPE(4, 4, 2, 0.48, 0.48, 1), EE_PF_SHAPE(4, 2, 2, 0.29, 0.29, 1), EE_PF_SHAPE(2, 2, 4, 0.17, 0.17, 1)};
 
 static pf_kernel_t pf_att(int hd, int rt)
 {
@@ -166,8 +173,8 @@ static pf_kernel_t pf_att(int hd, int rt)
 }
 
 // Shape of the workgroup tile and parts of K of one prefill GEMM: the least estimated time.  The estimate, in us
-// per k-tile: t1 where a workgroup is alone on its compute unit (a chain of latencies), t2 per workgroup where a
-// unit has several (occ fit); a split adds the exchange of the partial tiles (measured: about 5 us, 0.7 us
+// per k-tile (PfShape): t1 where a workgroup is alone on its compute unit (a chain of latencies), t2 per workgroup
+// where a unit has several (occ fit); a split adds the exchange of the partial tiles (measured: about 5 us, 0.7 us
 // per part read one after the other, and the bytes at 3.5 TB/s).  Fitted to QKV, O, GU and DN of the 7B
 // shape at 64 to 2048 rows; its choice is within 8 % of the best measured one, most often the best.
 struct PfChoice {
@@ -176,26 +183,21 @@ struct PfChoice {
 };
 static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows)
 {
-    static const struct {
-        double t1, t2;
-        int occ;
-    } cost[] = {{0.85, 0.72, 2}, {0.55, 0.41, 2}, {0.36, 0.27, 2}, {0.27, 0.175, 3}};
     PfChoice best = {};
     double best_t = 0;
     const double cu = m->nwg;
-    for (size_t i = 0; i < sizeof PF_SHAPES / sizeof PF_SHAPES[0]; ++i) {
-        const PfShape &s = PF_SHAPES[i];
+    for (const PfShape &s : PF_SHAPES) {
         const int nb = (pl.NT + 2 * s.wn - 1) / (2 * s.wn), mb = (rows + 32 * s.wm - 1) / (32 * s.wm);
         for (int ks : {1, 2, 3, 4, 6, 8}) {
             const size_t part = (size_t)nb * mb * ks * pf_tile_floats(s.wn, s.wm);
             if (ks > 1 && (pl.KT < 8 * ks || part > PF_PART_FLOATS || nb * mb > PF_PART_TILES)) break;
             double left = (double)nb * mb * ks, f = 0;
-            const double slots = cu * cost[i].occ;
+            const double slots = cu * s.occ;
             while (left > slots) {   // full rounds
-                f += cost[i].occ * cost[i].t2;
+                f += s.occ * s.t2;
                 left -= slots;
             }
-            f += left <= cu ? cost[i].t1 : std::max(1.25 * cost[i].t1, left / cu * cost[i].t2);
+            f += left <= cu ? s.t1 : std::max(1.25 * s.t1, left / cu * s.t2);
             double t = f * ((pl.KT + ks - 1) / ks);
             if (ks > 1) t += 5.0 + 0.7 * ks + (double)part * 8.0 / 3.5e6;
             if (!best.shape || t < best_t) {
@@ -550,7 +552,7 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
     {
         std::vector<std::pair<const void *, size_t>> ks;
         for (const PfShape &sh : PF_SHAPES)
-            for (pf_kernel_t k : sh.gemm) ks.push_back({reinterpret_cast<const void *>(k), pf_gemm_lds(sh.wn, sh.wm)});
+            for (pf_kernel_t k : sh.gemm) ks.push_back({reinterpret_cast<const void *>(k), pf_gemm_lds(sh.wn, sh.wm, sh.grp)});
         for (int rt = 1; rt <= 2; ++rt) ks.push_back({reinterpret_cast<const void *>(pf_att(c.head_dim, rt)), pf_att_lds(c.head_dim, ATT_MAX_SPLITS * ATT_TILES * WAVES)});
         for (const auto &k : ks) {
             hipError_t fe = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
@@ -1170,7 +1172,7 @@ static int prefill_chunk(ee_session *s, int start, int rows)
         a.nb = ch.nb;
         a.mb = ch.mb;
         a.ks = ch.ks;
-        hipLaunchKernelGGL(sh.gemm[kind], dim3(a.nb * a.mb * a.ks), dim3(PF_THREADS), pf_gemm_lds(sh.wn, sh.wm), s->stream, a);
+        hipLaunchKernelGGL(sh.gemm[kind], dim3(a.nb * a.mb * a.ks), dim3(PF_THREADS * sh.grp), pf_gemm_lds(sh.wn, sh.wm, sh.grp), s->stream, a);
     };
     for (int l = 0; l < c.n_layers; ++l) {
         a.layer = l;
