@@ -525,43 +525,45 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
     }
     if (KIND == G_HEAD) {
         lds_barrier();
-        const int lane = tid & 63, wave = tid >> 6;
-        for (int m = wave; m < rows; m += WAVES) {
-            float bv = -INFINITY;
-            int bi = 0x7FFFFFFF;
-            for (int c = lane; c < gn * 16; c += 64) {
-                float z = zbuf[(size_t)m * ly.chunk * 16 + c];
-                int n = nt_first * 16 + c;
-                if (cand_better(z, n, bv, bi)) {
-                    bv = z;
-                    bi = n;
-                }
-            }
+        // Sixteen lanes per row (all rows at once, 48 groups): lane l has column l of every n-tile of the chunk.
+        static_assert(WG_THREADS / 16 >= EE_MAX_ROWS && GROUP_TILES <= 8, "a group of lanes per row");
+        const int m = tid >> 4, l = tid & 15;
+        float z[GROUP_TILES], bv = -INFINITY;
+        int bi = 0x7FFFFFFF;
+        const float *zr = zbuf + (size_t)min(m, rows - 1) * ly.chunk * 16 + l;
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                float ov = __shfl_xor(bv, off, 64);
-                int oi = __shfl_xor(bi, off, 64);
-                if (cand_better(ov, oi, bv, bi)) {
-                    bv = ov;
-                    bi = oi;
-                }
+        for (int j = 0; j < GROUP_TILES; ++j) {
+            z[j] = j < gn ? zr[j * 16] : -INFINITY;
+            if (z[j] > bv) {
+                bv = z[j];
+                bi = (nt_first + j) * 16 + l;
             }
-            // sum of exp(z - bv) over the chunk's columns (masked columns hold -inf and add 0):
-            // the softmax denominator for the confidence score (paper Eq. 4), kept relative to the
-            // running maximum like the argmax candidate
-            float se = 0.f;
-            for (int c = lane; c < gn * 16; c += 64) se += __expf(zbuf[(size_t)m * ly.chunk * 16 + c] - bv);
+        }
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) se += __shfl_xor(se, off, 64);
-            if (lane == 0 && bv > -INFINITY) {  // (a chunk of masked columns only contributes nothing)
-                const float ov = mi.bestv[m];
-                if (cand_better(bv, bi, ov, mi.besti[m])) {
-                    mi.sume[m] = mi.sume[m] * __expf(ov - bv) + se;  // exp(-inf) = 0 the first time
-                    mi.bestv[m] = bv;
-                    mi.besti[m] = bi;
-                } else {
-                    mi.sume[m] += se * __expf(bv - ov);
-                }
+        for (int off = 8; off >= 1; off >>= 1) {
+            const float ov = __shfl_xor(bv, off, 64);
+            const int oi = __shfl_xor(bi, off, 64);
+            if (cand_better(ov, oi, bv, bi)) {
+                bv = ov;
+                bi = oi;
+            }
+        }
+        // sum of exp(z - bv) over the chunk's columns (masked columns hold -inf and add 0):
+        // the softmax denominator for the confidence score (paper Eq. 4), kept relative to the
+        // running maximum like the argmax candidate
+        float se = 0.f;
+#pragma unroll
+        for (int j = 0; j < GROUP_TILES; ++j) se += __expf(z[j] - bv);
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) se += __shfl_xor(se, off, 64);
+        if (l == 0 && m < rows && bv > -INFINITY) {  // (a chunk of masked columns only contributes nothing)
+            const float ov = mi.bestv[m];
+            if (cand_better(bv, bi, ov, mi.besti[m])) {
+                mi.sume[m] = mi.sume[m] * __expf(ov - bv) + se;  // exp(-inf) = 0 the first time
+                mi.bestv[m] = bv;
+                mi.besti[m] = bi;
+            } else {
+                mi.sume[m] += se * __expf(bv - ov);
             }
         }
     }
@@ -1147,23 +1149,19 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
 {
     const ModelDev &md = a.mdv;
     const int rows = a.rows, M = a.M;  // rows of the head launch: head after head, session after session, M rows each
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int *tok = reinterpret_cast<int *>(lds);
     float *conf = reinterpret_cast<float *>(lds) + EE_MAX_ROWS;
-    for (int m = wave; m < rows; m += blockDim.x >> 6) {
+    const int l = threadIdx.x & 15, m = threadIdx.x >> 4;   // sixteen lanes per row, all rows at once
+    if (m < rows) {
         // all of the row's candidates and partial sums are requested before the first is used
-        constexpr int PER = 4;                     // workgroups per lane: the launch has at most 256
+        constexpr int PER = SS_LD / 16;                     // workgroups per lane
         int2 c[PER];
         float sg[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const int g = lane + 64 * j;
-            c[j] = make_int2(__float_as_int(-INFINITY), 0x7FFFFFFF);
-            sg[j] = 0.f;
-            if (g < a.nwg) {
-                c[j] = load_cand(a.sc.cand + (size_t)m * SS_LD + g);
-                sg[j] = load_dev32(a.sc.cand_sum + (size_t)m * SS_LD + g);
-            }
+            const int g = min(l + 16 * j, a.nwg - 1);       // (slots past the workgroups: the last candidate again, counted once)
+            c[j] = load_cand(a.sc.cand + (size_t)m * SS_LD + g);
+            sg[j] = load_dev32(a.sc.cand_sum + (size_t)m * SS_LD + g);
         }
         float bv = -INFINITY;
         int bi = 0x7FFFFFFF;
@@ -1176,7 +1174,7 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
             }
         }
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
+        for (int off = 8; off >= 1; off >>= 1) {
             float ov = __shfl_xor(bv, off, 64);
             int oi = __shfl_xor(bi, off, 64);
             if (cand_better(ov, oi, bv, bi)) {
@@ -1189,10 +1187,10 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
         float se = 0.f;
 #pragma unroll
         for (int j = 0; j < PER; ++j)
-            if (sg[j] > 0.f) se += sg[j] * __expf(__int_as_float(c[j].x) - bv);
+            if (l + 16 * j < a.nwg && sg[j] > 0.f) se += sg[j] * __expf(__int_as_float(c[j].x) - bv);
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) se += __shfl_xor(se, off, 64);
-        if (lane == 0) {
+        for (int off = 8; off >= 1; off >>= 1) se += __shfl_xor(se, off, 64);
+        if (l == 0) {
             tok[m] = bi;
             conf[m] = 1.0f / se;
         }
