@@ -1595,6 +1595,14 @@ __device__ __forceinline__ int perm_row(int perm, int n, int d, int hd, int F)
     return n;
 }
 
+// cos and sin of position blockIdx.x's angle for RoPE pair threadIdx.x, in double
+__global__ void rope_table_kernel(float2 *tab, double base, int hd)
+{
+    const int j = threadIdx.x;
+    const double ang = (double)blockIdx.x * pow(base, -2.0 * (double)j / (double)hd);
+    tab[(size_t)blockIdx.x * blockDim.x + j] = make_float2((float)cos(ang), (float)sin(ang));
+}
+
 // row-major bf16 src[N][K] -> the tiled layout of GemmPlan; block g writes workgroup g's tiles,
 // sub-wave `sub` of the block those of streaming wave w = sub, sub + nsub, ...
 __global__ void tile_weights_kernel(const uint16_t *__restrict__ src, uint4 *__restrict__ dst, GemmPlan pl,
