@@ -1236,9 +1236,9 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
     if ((rc = ensure_pages(s, total + 1, s->stream)) != EE_OK) return rc;
 
     fill_sessdev(s->host_sessdev[0], s);
-    // More rows than one streamed launch takes: chunks of many rows, of nearly equal size.  61 rows of a
-    // 1280-wide model, 3 layers, prefill and one pass: 513 us against 946 us in streamed chunks of 16;
-    // 640 rows of 8 layers of the 7B shape 5.7 ms against 19.8 ms in chunks of 40.
+    // More rows than a pass of this model carries: the many-row kernels, in chunks of nearly equal size.  us with
+    // them / in streamed chunks of 16 rows: 7B shape, 4 layers, 24 rows 646 / 816, 48 rows 673 / 1238; 1280-wide model, 3
+    // layers, 24 rows 204 / 233.  (A streamed pass of 48 rows takes 600: models loaded for that many keep it.)
     const bool many = total > c.max_rows;
     const int n_chunks = (total + s->pf_cap - 1) / s->pf_cap;
     const int chunk = many ? std::min(s->pf_cap, (int)align_up((size_t)((total + n_chunks - 1) / n_chunks), 128)) : c.max_rows;
