@@ -1367,8 +1367,11 @@ __global__ void __launch_bounds__(256) ee_zero_kernel(uint4 *p, size_t n)
 // Lays the pass's scratch buffers out in the static array (sizes for M rows of this model),
 // points a.sc at them, picks the attention splits for that room and enqueues the clearing of
 // the part in use: the array keeps the last call's contents, and the padding columns of the GEMM
-// inputs and the attention / head counters must start at zero.
-static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_max)
+// inputs and the attention / head counters must start at zero.  per_group (exits whose heads share a launch
+// of the LM head, EE_OPT_HEAD_BATCH) comes in as what the session asks for and goes out as what fits: the
+// LM head's input holds the rows of a whole group.  It is lowered rather than the call refused, or
+// the attention given fewer splits: results do not depend on it, only when the exits are published.
+static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_max, int &per_group)
 {
     const ee_model *m = lead->m;
     const ModelDev &md = m->host_md;
@@ -1384,21 +1387,25 @@ static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_ma
     const size_t rows = (size_t)M, d = (size_t)md.d;
     Scratch sc;
     memset(&sc, 0, sizeof sc);
-    sc.h = reinterpret_cast<float *>(take(rows * d * 4));
-    sc.q = reinterpret_cast<float *>(take(rows * d * 4));
-    sc.xn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-    sc.xh = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-    sc.attn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-    sc.u = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_F + X_SLACK) * 2));
-    sc.xa = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-    sc.t = reinterpret_cast<uint16_t *>(take((2 * rows * std::max(md.Kpad_A, 32) + X_SLACK) * 2));
-    sc.ss_h = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
-    sc.ss_a = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
-    sc.ss_f = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
-    sc.cand = reinterpret_cast<int2 *>(take((size_t)SS_LD * md.rows_max * 8));
-    sc.cand_sum = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
-    sc.att_count = reinterpret_cast<int *>(take((size_t)md.H * 4));
-    sc.head_count = reinterpret_cast<int *>(take(4));
+    auto lay_out = [&](size_t head_rows) {   // everything but the attention partials
+        off = 0;
+        sc.h = reinterpret_cast<float *>(take(rows * d * 4));
+        sc.q = reinterpret_cast<float *>(take(rows * d * 4));
+        sc.xn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+        sc.xh = reinterpret_cast<uint16_t *>(take((2 * head_rows * md.Kpad_d + X_SLACK) * 2));
+        sc.attn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+        sc.u = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_F + X_SLACK) * 2));
+        sc.xa = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
+        sc.t = reinterpret_cast<uint16_t *>(take((2 * rows * std::max(md.Kpad_A, 32) + X_SLACK) * 2));
+        sc.ss_h = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+        sc.ss_a = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+        sc.ss_f = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+        sc.cand = reinterpret_cast<int2 *>(take((size_t)SS_LD * md.rows_max * 8));
+        sc.cand_sum = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
+        sc.att_count = reinterpret_cast<int *>(take((size_t)md.H * 4));
+        sc.head_count = reinterpret_cast<int *>(take(4));
+    };
+    lay_out(rows);
     sc.logits = lead->sc.logits;   // kept logits are an output of the session, not scratch
     // attention partials: what is left, at most one item per compute unit and split
     const size_t item_bytes = (size_t)ATT_ROWS * att_rec(md.hd) * 4;
@@ -1408,7 +1415,11 @@ static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_ma
     a.att_splits = attention_splits(lead, items_cap, 1, M, n_pos_max);
     if (a.att_splits == 0)
         return fail(EE_ECAPACITY, "ee_verify_static: a context of %d positions needs more than the %d bytes of static scratch", n_pos_max, EE_STATIC_SCRATCH_BYTES);
-    sc.att_part = reinterpret_cast<float *>(take((size_t)md.H * a.att_splits * item_bytes));
+    const size_t part_bytes = (size_t)md.H * a.att_splits * item_bytes;
+    const size_t left = EE_STATIC_SCRATCH_BYTES - off - align_up(part_bytes, 256);
+    per_group = std::min<int>(per_group, 1 + (int)(left / align_up(4 * rows * md.Kpad_d, 256)));
+    lay_out(per_group * rows);
+    sc.att_part = reinterpret_cast<float *>(take(part_bytes));
     a.sc = sc;
     hipLaunchKernelGGL(ee_zero_kernel, dim3(256), dim3(256), 0, lead->run_stream, reinterpret_cast<uint4 *>(base), off / 16);
     HIP_TRY(hipGetLastError());
@@ -1478,8 +1489,13 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
     PassArgs a;
     base_args(lead, a);
     lead->run_stream = lead->stream;
+    // Exit heads run in groups of up to head_batch consecutive exits: every exit deposits its
+    // LM-head input rows when its layer is done, and the last one of the group runs the LM head
+    // over the rows of all of them (one stream of W_lm per group), after which the group's results
+    // are published together.  head_batch = 1: every exit is published right after its layer.
+    int per_group = std::max(1, std::min({lead->head_batch, n_exits, c.max_rows / (n_sessions * M)}));
     if (static_scratch) {
-        if ((rc = use_static_scratch(lead, a, M, n_pos_max)) != EE_OK) return rc;
+        if ((rc = use_static_scratch(lead, a, M, n_pos_max, per_group)) != EE_OK) return rc;
     } else {
         a.att_splits = attention_splits(lead, lead->att_items_cap, n_sessions, M, n_pos_max);
         if (a.att_splits == 0)
@@ -1525,11 +1541,6 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
     HIP_TRY(hipEventRecord(lead->ev_start, lead->run_stream));
     lead->lt_codes.clear();
     SampleUpload upload = {sp, n_sessions, gamma};
-    // Exit heads run in groups of up to head_batch consecutive exits: every exit deposits its
-    // LM-head input rows when its layer is done, and the last one of the group runs the LM head
-    // over the rows of all of them (one stream of W_lm per group), after which the group's results
-    // are published together.  head_batch = 1: every exit is published right after its layer.
-    const int per_group = std::max(1, std::min(lead->head_batch, c.max_rows / a.rows));
     int layer = 0;
     for (int e = 0; e <= n_exits; ++e) {
         const bool fin = (e == n_exits);

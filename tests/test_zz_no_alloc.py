@@ -60,6 +60,40 @@ def test_static_scratch_matches_session_scratch(model_dir):
         g.free()
 
 
+@pytest.mark.parametrize("n_adapters,gamma,max_rows", [(0, 4, 48), (2, 4, 48), (0, 1, 48), (0, 15, 48), (2, 1, 6)])
+def test_static_scratch_holds_the_rows_of_grouped_exits(model_dir, n_adapters, gamma, max_rows):
+    """Three exits whose heads share one launch (OPT_HEAD_BATCH): the LM head's input then holds the
+    rows of all three, and layers run between the first deposit and the launch.  (15, 48): the largest group."""
+    cfg = eegen.ModelConfig(n_layers=5, d_model=512, n_heads=4, head_dim=128, d_ffn=1072, vocab=1500, exit_layers=(1, 2, 3),
+                            n_adapters=n_adapters, adapter_width=64 if n_adapters else 0)
+    path = f"{model_dir}/noalloc_groups_{n_adapters}.bin"
+    eegen.write_model(path, cfg, 92, gains="uniform", std=0.04)
+    g = ee.Model(path, max_rows=max_rows)
+    a, b, c = (g.session(256, max_gamma=gamma, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT) for _ in range(3))
+    try:
+        prompt = eegen.prompt_tokens(94, 75, cfg.vocab)
+        for s in (a, b, c):
+            s.ee_prefill(prompt)
+        a.ee_session_option(ee.OPT_HEAD_BATCH, 3)
+        b.ee_session_option(ee.OPT_HEAD_BATCH, 3)
+        exits = [1, 2, 3]
+        drafts = eegen.prompt_tokens(95, gamma, cfg.vocab)
+        a.ee_verify(drafts, exits)
+        b.ee_verify_static(drafts, exits)
+        c.ee_verify(drafts, exits)                       # one launch per exit: what grouping may not change
+        for s in (a, b, c):
+            s.ee_wait_final()
+        _same(a.final_result(), b.final_result(), "grouped exits")
+        assert np.array_equal(a.final_result().exit_tokens, c.final_result().exit_tokens)
+        for e in range(len(exits) + 1):
+            la, lb, lc = (s.ee_debug_logits(e).view(np.uint32) for s in (a, b, c))
+            assert np.array_equal(la, lb) and np.array_equal(la, lc), f"head {e}: logits differ"
+    finally:
+        for s in (a, b, c):
+            s.free()
+        g.free()
+
+
 def test_static_scratch_rejects_what_does_not_fit(model_dir):
     """Sizes beyond the array's 8 MiB are refused with EE_ECAPACITY before anything is enqueued:
     a model whose FFN width makes the gate/up output of 16 rows alone larger than the array."""
