@@ -70,7 +70,8 @@ struct StageLds {
 // one slot per workgroup.
 constexpr int SS_LD = 256;
 
-// GEMM inputs end with this many spare elements: a k-tile is copied in whole kilobytes.
+// GEMM inputs are followed by at least this many elements that may be read: a k-tile is copied in whole kilobytes (what
+// lies behind its rows ends up in lanes whose products are dropped).
 constexpr int X_SLACK = 512;
 
 // Units [u0, u1) of workgroup g.  Workgroups are dealt to the chip's 8 XCDs round-robin (XCD =
@@ -151,7 +152,7 @@ struct Scratch {
     float *ss_h;         // [rows_max][SS_LD]        partial sums of squares of the LM-head input's rows (head rows)
     float *ss_a;         // [rows_max][SS_LD]        partial sums of h^2 after the FFN block / embedding
     float *ss_f;         // [rows_max][SS_LD]        partial sums of h^2 after the attention block
-    float *att_part;     // [items][ATT_ROWS][hd+4] attention partials (only when the position range is split)
+    float *att_part;     // [items][ATT_ROWS * (hd+2)] attention partials (att_item; only when the position range is split)
     int *att_count;      // [units] items of the unit that have delivered their partials; zero between launches
     int *head_count;     // workgroups of a head launch that have delivered their candidates; zero between launches
     float *part;         // [K split][n-tile][rows][16] partial tiles of a launch whose K is split over workgroups

@@ -29,6 +29,7 @@ namespace ee {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
 // Pointers read from descriptors in memory are generic to the compiler, and generic loads go
 // through the flat path, whose completion also counts against the LDS counter: a wait for an
@@ -88,7 +89,7 @@ __device__ __forceinline__ void store_dev32(float *p, float v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// the same for 16 bytes at byte offset `off` of a buffer (weight_resource): device-scope cache policy (sc1)
+// the same for 16 or 8 bytes at byte offset `off` of a buffer (weight_resource): device-scope cache policy (sc1)
 constexpr int CACHE_POLICY_DEVICE = 16;
 __device__ __forceinline__ void store_dev128(WRes r, int off, float4 v)
 {
@@ -99,6 +100,15 @@ __device__ __forceinline__ float4 load_dev128(WRes r, int off)
 {
     const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, CACHE_POLICY_DEVICE);
     return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+}
+__device__ __forceinline__ void store_dev64(WRes r, int off, float2 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b64((u32x2_t){__float_as_uint(v.x), __float_as_uint(v.y)}, r, off, 0, CACHE_POLICY_DEVICE);
+}
+__device__ __forceinline__ float2 load_dev64(WRes r, int off)
+{
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, CACHE_POLICY_DEVICE);
+    return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
 }
 __device__ __forceinline__ float load_dev32(const float *p)
 {
@@ -310,7 +320,6 @@ __device__ __forceinline__ void store_split4(uint16_t *x, int rows, int m, int k
     uint32_t h[4], l[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) split_bf16(v[e], h[e], l[e]);
-    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 0)) = (u32x2_t){h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 1)) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
 }
@@ -484,7 +493,6 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
                 const int slot = mi.pos[m] % KV_PAGE;
                 if (sect == 1) {
                     EE_GLOBAL uint16_t *kr = as_global_mut(EE_SESS(a, ses, kpool)) + rec + (size_t)slot * 2 * hd + e;
-                    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
                     *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0] | (vh[1] << 16), vh[2] | (vh[3] << 16)};
                     *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + hd) = (u32x2_t){vl[0] | (vl[1] << 16), vl[2] | (vl[3] << 16)};
                 } else {
@@ -885,7 +893,6 @@ constexpr float ATT_NEG = -1.0e30f;  // finite stand-in for "no position seen ye
 
 __device__ __forceinline__ uint2 load_global8(const void *p)
 {
-    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
     u32x2_t v = *as_global(reinterpret_cast<const u32x2_t *>(p));
     return make_uint2(v[0], v[1]);
 }
@@ -897,8 +904,10 @@ __device__ __forceinline__ bf16x8_t pack_bf16x8(const uint32_t *h)
     return __builtin_bit_cast(bf16x8_t, make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)));
 }
 
-// floats of one row's partial result: output, maximum, sum, padding to 16 bytes
+// floats of one row's partial result in LDS (output, maximum, sum, padding to 16 bytes) ...
 constexpr int att_rec(int hd) { return hd + 4; }
+// ... and of one item's in memory: [ATT_ROWS][hd] outputs, [ATT_ROWS][2] maxima and sums (16-byte accesses without padding)
+constexpr int att_item(int hd) { return ATT_ROWS * (hd + 2); }
 constexpr size_t att_lds(int hd, int rows) { return (size_t)WAVES * (rows < ATT_ROWS ? rows : ATT_ROWS) * att_rec(hd) * sizeof(float) + 16; }
 
 __device__ __forceinline__ float4 load_f4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -1083,12 +1092,11 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
     }
     if (n_splits > 1) {
         const int unit = blockIdx.z * a.H + hh;
-        const WRes part = buffer_resource(a.sc.att_part + (size_t)unit * n_splits * ATT_ROWS * REC);
-        constexpr int SP_BYTES = ATT_ROWS * REC * 4;
+        const WRes part = buffer_resource(a.sc.att_part + (size_t)unit * n_splits * att_item(HD));
+        constexpr int SP_BYTES = att_item(HD) * 4, MS = ATT_ROWS * HD * 4;
         if (mine) {
-            const int off = sp * SP_BYTES + i * REC * 4;
-            store_dev128(part, off + e * 4, num);
-            if (e == 0) store_dev128(part, off + HD * 4, make_float4(gm, den, 0.f, 0.f));
+            store_dev128(part, sp * SP_BYTES + (i * HD + e) * 4, num);
+            if (e == 0) store_dev64(part, sp * SP_BYTES + MS + i * 8, make_float2(gm, den));
         }
         wait_vmem();      // this workgroup's partials are visible device-wide ...
         __syncthreads();  // ... for every wave, before it is counted
@@ -1105,12 +1113,13 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
             den = 0.f;
             gm = ATT_NEG;
             for (int k0 = 0; k0 < n_splits; k0 += 8) {
-                float4 pv[8], pm[8];
+                float4 pv[8];
+                float2 pm[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    const int off = min(k0 + k, n_splits - 1) * SP_BYTES + i * REC * 4;
-                    pv[k] = load_dev128(part, off + e * 4);
-                    pm[k] = load_dev128(part, off + HD * 4);
+                    const int off = min(k0 + k, n_splits - 1) * SP_BYTES;
+                    pv[k] = load_dev128(part, off + (i * HD + e) * 4);
+                    pm[k] = load_dev64(part, off + MS + i * 8);
                 }
                 float m_new = gm;
 #pragma unroll

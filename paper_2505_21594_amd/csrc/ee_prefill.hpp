@@ -74,7 +74,6 @@ __device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int 
     uint32_t h[4], l[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) split_bf16(v[e], h[e], l[e]);
-    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
     const size_t i = pf_index(rt, m, k, 0);
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i) = (u32x2_t){h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i + (size_t)rt * 512) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
@@ -351,7 +350,6 @@ __global__ void __launch_bounds__(PF_THREADS * GRP, GRP > 1 ? GRP : 2) pf_gemm_k
                     const size_t rec = rec0 + (size_t)head * KV_PAGE * 2 * a.hd;
                     if (sect == 1) {
                         EE_GLOBAL uint16_t *kr = as_global_mut(a.kpool) + rec + (size_t)slot * 2 * a.hd + e;
-                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
                         *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0] | (vh[1] << 16), vh[2] | (vh[3] << 16)};
                         *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + a.hd) = (u32x2_t){vl[0] | (vl[1] << 16), vl[2] | (vl[3] << 16)};
                     } else {

@@ -880,7 +880,7 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         const size_t forced = ((size_t)s->n_pages + ATT_TILES * WAVES - 1) / (ATT_TILES * WAVES);
         const size_t max_items = max_units * std::max<size_t>(forced, 2) + (size_t)m->nwg;
         s->att_items_cap = (int)max_items;
-        S_TRY(dev_alloc(s->allocs, &sc.att_part, max_items * ATT_ROWS * att_rec(c.head_dim)));
+        S_TRY(dev_alloc(s->allocs, &sc.att_part, max_items * att_item(c.head_dim)));
         S_TRY(dev_alloc(s->allocs, &sc.att_count, max_units));
         S_TRY(dev_alloc(s->allocs, &sc.head_count, 1));
     }
@@ -1387,16 +1387,16 @@ static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_ma
     const size_t rows = (size_t)M, d = (size_t)md.d;
     Scratch sc;
     memset(&sc, 0, sizeof sc);
-    auto lay_out = [&](size_t head_rows) {   // everything but the attention partials
+    auto lay_out = [&](size_t head_rows) {   // everything but the attention partials; behind every GEMM input lie X_SLACK elements of the next buffers
         off = 0;
         sc.h = reinterpret_cast<float *>(take(rows * d * 4));
         sc.q = reinterpret_cast<float *>(take(rows * d * 4));
-        sc.xn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-        sc.xh = reinterpret_cast<uint16_t *>(take((2 * head_rows * md.Kpad_d + X_SLACK) * 2));
-        sc.attn = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-        sc.u = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_F + X_SLACK) * 2));
-        sc.xa = reinterpret_cast<uint16_t *>(take((2 * rows * md.Kpad_d + X_SLACK) * 2));
-        sc.t = reinterpret_cast<uint16_t *>(take((2 * rows * std::max(md.Kpad_A, 32) + X_SLACK) * 2));
+        sc.xn = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
+        sc.xh = reinterpret_cast<uint16_t *>(take(2 * head_rows * md.Kpad_d * 2));
+        sc.attn = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
+        sc.u = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_F * 2));
+        sc.xa = reinterpret_cast<uint16_t *>(take(2 * rows * md.Kpad_d * 2));
+        sc.t = reinterpret_cast<uint16_t *>(take(2 * rows * std::max(md.Kpad_A, 32) * 2));
         sc.ss_h = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
         sc.ss_a = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
         sc.ss_f = reinterpret_cast<float *>(take((size_t)SS_LD * md.rows_max * 4));
@@ -1408,7 +1408,7 @@ static int use_static_scratch(ee_session *lead, PassArgs &a, int M, int n_pos_ma
     lay_out(rows);
     sc.logits = lead->sc.logits;   // kept logits are an output of the session, not scratch
     // attention partials: what is left, at most one item per compute unit and split
-    const size_t item_bytes = (size_t)ATT_ROWS * att_rec(md.hd) * 4;
+    const size_t item_bytes = (size_t)att_item(md.hd) * 4;
     if (off + (size_t)md.H * item_bytes > EE_STATIC_SCRATCH_BYTES)
         return fail(EE_ECAPACITY, "ee_verify_static: %d rows of this model need more than the %d bytes of static scratch", M, EE_STATIC_SCRATCH_BYTES);
     const int items_cap = (int)std::min<size_t>((EE_STATIC_SCRATCH_BYTES - off) / item_bytes, (size_t)md.H * ATT_MAX_SPLITS);

@@ -94,6 +94,33 @@ def test_static_scratch_holds_the_rows_of_grouped_exits(model_dir, n_adapters, g
         g.free()
 
 
+def test_static_scratch_takes_what_just_fits(model_dir):
+    """16 rows of this width leave 1408 bytes of the 8 MiB: residual stream and queries 2 * 16 * 64 * 4, five
+    inputs 4 * 16 * 64 (or 32 for the adapters' units), activations 4 * 16 * 129024, partial sums and candidates
+    24 * 256 * 16, counters 2 * 256, one attention item 16 * (64 + 2) * 4.  A second exit's head rows (4 KB) do not
+    fit beside them: grouping then has no effect."""
+    cfg = eegen.ModelConfig(n_layers=3, d_model=64, n_heads=1, head_dim=64, d_ffn=129024, vocab=512, exit_layers=(1, 2))
+    path = f"{model_dir}/noalloc_edge.bin"
+    eegen.write_model(path, cfg, 6, gains="uniform", std=0.02)
+    g = ee.Model(path, max_rows=16)
+    a, b = (g.session(64, max_gamma=15, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT) for _ in range(2))
+    try:
+        prompt, drafts = eegen.prompt_tokens(8, 12, cfg.vocab), eegen.prompt_tokens(9, 15, cfg.vocab)
+        for s in (a, b):
+            s.ee_prefill(prompt)
+            s.ee_session_option(ee.OPT_ATT_SPLITS, 1)     # (the session's own scratch has room for more)
+        b.ee_session_option(ee.OPT_HEAD_BATCH, 2)
+        a.ee_verify(drafts, [1, 2])
+        a.ee_wait_final()
+        b.ee_verify_static(drafts, [1, 2])
+        b.ee_wait_final()
+        _same(a.final_result(), b.final_result(), "at the limit")
+    finally:
+        a.free()
+        b.free()
+        g.free()
+
+
 def test_static_scratch_rejects_what_does_not_fit(model_dir):
     """Sizes beyond the array's 8 MiB are refused with EE_ECAPACITY before anything is enqueued:
     a model whose FFN width makes the gate/up output of 16 rows alone larger than the array."""
