@@ -154,14 +154,14 @@ __device__ __forceinline__ void wait_vmem()
 // One kilobyte from memory straight into LDS: lane l's 16 bytes at src + off land at LDS byte
 // dst + 16 l.  Inline assembly because the compiler makes every LDS read wait for all such loads it
 // knows of; here a stage is read while the next ones are on their way, and the kernels wait
-// themselves (wait_pending, then a barrier).  No vector register is written; M0, which nothing else in
-// these kernels uses, needs one wait state.
+// themselves (wait_pending, then a barrier).  No vector register is written; M0 is, and needs one wait
+// state before it is used.
 __device__ __forceinline__ void load_lds_kb(const void *src, int off, unsigned dst)
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :
                  : "v"(off), "s"(src), "s"(dst)
-                 : "memory");
+                 : "m0", "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_pending()   // at most N vector memory operations of this wave are pending
