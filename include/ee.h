@@ -140,7 +140,8 @@ int ee_model_free(ee_model *m);
 int ee_model_info(const ee_model *m, ee_model_config *out);
 
 /* A session owns a paged bf16 KV cache for up to max_ctx positions, scratch
-   for one pass and for one prefill chunk (up to 2048 rows), a stream, events and a pinned result block.
+   for one pass and for one prefill chunk (up to min(max_ctx, 2048) rows of 18 d_model + 4 d_ffn bytes, and up to
+   50 MB of partial tiles where d_model or d_ffn is in the thousands), a stream, events and a pinned result block.
    max_gamma in [1, EE_MAX_M-1]. */
 int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, unsigned flags,
                       ee_session **out);

@@ -209,6 +209,19 @@ static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows)
     return best;
 }
 
+// Floats of partial tiles the prefill GEMMs of chunks of up to `rows` rows need: the largest choice of pf_choose, which
+// sees the rows in blocks of 64 (the narrowest row tile).
+static size_t pf_part_floats(const ee_model *m, int rows)
+{
+    size_t need = 0;
+    for (int r = 64; r < rows + 64; r += 64)
+        for (int k = G_QKV; k <= G_DN; ++k) {
+            const PfChoice ch = pf_choose(m, m->plan[0][k], r);
+            if (ch.ks > 1) need = std::max(need, (size_t)ch.nb * ch.mb * ch.ks * pf_tile_floats(ch.shape->wn, ch.shape->wm));
+        }
+    return need;
+}
+
 // n-tiles the busiest workgroup owns
 static int plan_max_local(const GemmPlan &p)
 {
@@ -814,8 +827,9 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
 
     S_TRY(dev_alloc(s->allocs, &s->dev_state, 4));
     {
-        // prefill: a chunk of up to pf_cap rows at once (pf_gemm_kernel and friends).  About a tenth of
-        // the KV cache of as many positions.  Padding columns (K not a multiple of 32) are read and
+        // prefill: a chunk of up to pf_cap rows at once (pf_gemm_kernel and friends).  Per row 18 d + 4 F bytes and the
+        // partial tiles: for 2048 positions 290 MB with the 7B shape (a seventh of the cache of its 32 layers), 15 MB
+        // with 4 layers of 256 (nine tenths).  Padding columns (K not a multiple of 32) are read and
         // must stay zero; the buffers need no clearing otherwise.
         const ModelDev &pm = m->host_md;
         s->pf_cap = std::min(PF_ROWS, (int)align_up((size_t)max_ctx, 16));
@@ -823,10 +837,7 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         const bool pad = pm.Kpad_d != pm.d || pm.Kpad_F != pm.F;
         // One allocation for all of them (a dozen separate ones made creating a session 5 ms longer).
         const size_t slots = 2 * (((size_t)pm.d + 63) / 64);   // two per workgroup tile of the narrowest shape
-        // room for the largest split the rule may choose: every GEMM's tiles (whole tiles: up to 255 columns and
-        // 127 rows more) times the parts, or the cap
-        const size_t n_max = align_up(std::max<size_t>(3 * d, 2 * (size_t)pm.F), 256);
-        const size_t part = std::min<size_t>(8 * n_max * align_up(cap, 128), PF_PART_FLOATS);
+        const size_t part = pf_part_floats(m, s->pf_cap);
         size_t bytes = 0;
         auto place = [&](size_t n) {
             const size_t at = bytes;

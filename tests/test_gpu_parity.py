@@ -1,5 +1,7 @@
 """GPU parity: libeeverify (through its C ABI) against the CPU oracle on the
 same seeded inputs.  Everything here needs a real MI355X."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -233,6 +235,27 @@ def test_prefill_many_rows(tiny_pair, mid_pair, which, n_emb, n_tok, scatter):
             assert np.abs(ro.logits).max() < 8 and err < 1.7e-3
         finally:
             gs.free()
+
+
+def test_session_memory(tiny_pair):
+    """What a session of 2048 positions takes on the GPU, 4 layers of 256: cache 2 * 4 * 2048 * 256 * 4 = 16.8 MB, prefill
+    buffers 2048 * (18 * 256 + 4 * 704) = 15.2 MB (none of this model's GEMMs shares K between workgroups, so no
+    partial tiles); the rest is a pass's scratch and the rounding of some thirty allocations."""
+    g, _ = tiny_pair
+    lib = ee.load_library()
+
+    def free_bytes():
+        free, total = ctypes.c_size_t(), ctypes.c_size_t()
+        assert lib.hipMemGetInfo(ctypes.byref(free), ctypes.byref(total)) == 0
+        return free.value
+
+    g.session(2048, max_gamma=4).free()
+    before = free_bytes()
+    sessions = [g.session(2048, max_gamma=4) for _ in range(8)]
+    used = (before - free_bytes()) / 8
+    for s in sessions:
+        s.free()
+    assert 32e6 < used < 45e6
 
 
 def test_no_autocommit(tiny_pair):
