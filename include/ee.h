@@ -119,7 +119,8 @@ const char *ee_last_error(void);
 /* Reads a model file (header + row-major bf16 tensors, see the generator's
    format description), uploads it to GPU `device` and re-lays the weight
    matrices out in the tile order the kernels stream.  max_rows (1..EE_MAX_ROWS)
-   is the largest number of rows a pass (or a prefill chunk) will carry; ee_model_load
+   is the largest number of rows a pass will carry (and of a prompt that is prefilled like
+   a pass; longer ones go through kernels for many rows); ee_model_load
    uses 16.  With max_rows > 16 the output and down projections are kept in a second
    tile order as well, in which groups of four workgroups share their output columns and
    split K; launches of more than 16 rows use it (about a quarter more device memory for

@@ -183,10 +183,9 @@ struct PassArgs {
     Scratch sc;
     int nwg;
     int n_sess, M, rows;                 // rows = n_sess * M
-    int mode;                            // 0 verify, 1 prefill chunk
+    int mode;                            // 0 verify, 1 prefill (a prompt of up to rows_max rows, or the last row's head)
     const int *pf_tokens;                // prefill: [rows] token ids, < 0 => embedding row
     const uint16_t *pf_emb;              // prefill: [rows][d] bf16
-    int pf_pos0;                         // prefill: position of row 0
     int layer_begin, layer_end;          // (host) layers [begin, end) of this segment, 0-based
     int do_embed;
     int head_kind, head_idx;             // head_idx: result slot of the (first) head of this segment's head launch

@@ -50,24 +50,15 @@ __device__ __forceinline__ EE_GLOBAL T *as_global_mut(T *p)
     return (EE_GLOBAL T *)(p);
 }
 
-// 16-byte weight load of a tile: buffer load with the stage's weights as the resource, the
-// lane's 16 bytes as the vector offset and the tile's byte offset as the scalar offset, so the
-// stream needs no per-tile address arithmetic in vector registers.  Plain cache policy: on
-// this part non-temporal loads measured about 10 % slower for the same access pattern.
+// A buffer as a resource in scalar registers: the device-scope accesses below need it (a cache policy per access).
 typedef __amdgpu_buffer_rsrc_t WRes;
-__device__ __forceinline__ WRes weight_resource(const uint4 *W)
+__device__ __forceinline__ WRes buffer_resource(const void *ptr)
 {
-    // raw buffer, no stride, maximal range (offsets stay inside the stage's allocation).  The
+    // raw buffer, no stride, maximal range (offsets stay inside the buffer).  The
     // pointer is the same in every lane; saying so keeps the resource in scalar registers.
-    const unsigned long long p = reinterpret_cast<unsigned long long>(W);
+    const unsigned long long p = reinterpret_cast<unsigned long long>(ptr);
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(((unsigned long long)hi << 32) | lo), 0, 0x7FFFFFFF, 0x00020000);
-}
-__device__ __forceinline__ WRes buffer_resource(const void *p) { return weight_resource(reinterpret_cast<const uint4 *>(p)); }
-__device__ __forceinline__ uint4 load_tile16(WRes r, int lane_off, int tile_off)
-{
-    u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, tile_off, 0);
-    return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
 __device__ __forceinline__ uint4 load_global16(const void *p)
@@ -89,7 +80,7 @@ __device__ __forceinline__ void store_dev32(float *p, float v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// the same for 16 or 8 bytes at byte offset `off` of a buffer (weight_resource): device-scope cache policy (sc1)
+// the same for 16 or 8 bytes at byte offset `off` of a buffer: device-scope cache policy (sc1)
 constexpr int CACHE_POLICY_DEVICE = 16;
 __device__ __forceinline__ void store_dev128(WRes r, int off, float4 v)
 {
@@ -217,7 +208,7 @@ __device__ __forceinline__ T sess_pick(bool first, const T &own, const T *other)
 
 __device__ __forceinline__ int row_pos(const PassArgs &a, int r)
 {
-    if (a.mode == 1) return a.pf_pos0 + r;
+    if (a.mode == 1) return r;
     int s = div_small(r, a.M);
     return EE_SESS(a, s, kv_len) + (r - s * a.M);
 }
@@ -945,7 +936,7 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
     const int sp = blockIdx.x, hh = blockIdx.y, n_splits = a.att_splits, M = a.M;
     const int s = a.mode == 1 ? 0 : blockIdx.z, ch = a.mode == 1 ? blockIdx.z : 0;
     const int r0 = ch * ATT_ROWS, nr = min(ATT_ROWS, M - r0);
-    const int P = a.mode == 1 ? a.pf_pos0 : EE_SESS(a, s, kv_len);  // position of the first row
+    const int P = a.mode == 1 ? 0 : EE_SESS(a, s, kv_len);          // position of the first row
     const int n_pg = (P + r0 + nr + KV_PAGE - 1) / KV_PAGE;         // pages visible to the chunk's last row
     const int pg_lo = div_small(n_pg * sp, n_splits), pg_hi = div_small(n_pg * (sp + 1), n_splits);
     const int cbase = EE_SESS(a, s, contig_base), n_pages = EE_SESS(a, s, n_pages);
@@ -1268,7 +1259,8 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
 // Weights of the cumulative sums are 40-bit fixed point (integers): their sums do not depend on
 // the order of addition, so every thread's share [exclusive sum, + own sum) of the cumulative
 // distribution tiles it exactly and the search below always ends inside the owner's tokens.
-// A weight is at most 1 (largest exp term, or a probability) and a row has at most 2^15 tokens.
+// A weight is at most 1 (largest exp term, or a probability), so a row of fewer than 2^24 tokens cannot overflow 64 bits.
+static_assert(DIV_SMALL_MAX < 1 << 24, "the loader refuses vocabularies above DIV_SMALL_MAX");
 typedef unsigned long long u64;
 constexpr int SAMPLE_LDS_BYTES = 4096;             // the waves' sums and flags; the accept step's rows
 constexpr float SAMPLE_UNIT = 1099511627776.0f;  // 2^40

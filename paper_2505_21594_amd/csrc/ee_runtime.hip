@@ -535,10 +535,10 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
                 ee_model_free(m);
                 return fail(EE_EFORMAT, "ee_model_load: a weight matrix with %d rows is beyond what the kernels' index arithmetic covers", pl.N);
             }
-            // tile offsets inside a stage are 32-bit byte offsets
+            // The kernels count tiles in ints (PfArgs::tab), 1 KB each; larger matrices than this have never been run.
             if ((long long)pl.steps * pl.nwg * SWAVES * 1024 >= (1LL << 31)) {
                 ee_model_free(m);
-                return fail(EE_EFORMAT, "ee_model_load: a weight matrix of %d x %d exceeds the 2 GiB a stage can address", pl.N, pl.K);
+                return fail(EE_EFORMAT, "ee_model_load: a weight matrix of %d x %d exceeds the 2 GiB a matrix may take", pl.N, pl.K);
             }
             m->wstride[v][k] = (long long)pl.steps * pl.nwg * SWAVES * 64;
         }
@@ -598,9 +598,8 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
     if (hipMemcpy(dev_emb, emb, V * d * 2, hipMemcpyHostToDevice) != hipSuccess) return bail(fail(EE_EDEVICE, "upload of the embedding table failed"));
     md.emb = dev_emb;
 
-    // tiled weights: one allocation per GEMM kind and variant, layers at a fixed stride.  Zero-filled: tile slots no wave's
-    // sequence reaches (a wave without k-steps, the shorter sequences' tails) are still loaded by the clamped
-    // look-ahead and multiplied with zeros, so they must hold finite values.
+    // tiled weights: one allocation per GEMM kind and variant, layers at a fixed stride.  Tile slots that no wave's
+    // sequence reaches (a wave without k-steps, the shorter sequences' tails) are never read; they stay zero.
     float *g_attn = nullptr, *g_ffn = nullptr, *g_final_d = nullptr;
     const size_t Lz = (size_t)c.n_layers;
     uint4 *wdev[2][G_KINDS];
@@ -1252,7 +1251,7 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
     // layers, 24 rows 204 / 233.  (A streamed pass of 48 rows takes 600: models loaded for that many keep it.)
     const bool many = total > c.max_rows;
     const int n_chunks = (total + s->pf_cap - 1) / s->pf_cap;
-    const int chunk = many ? std::min(s->pf_cap, (int)align_up((size_t)((total + n_chunks - 1) / n_chunks), 128)) : c.max_rows;
+    const int chunk = many ? std::min(s->pf_cap, (int)align_up((size_t)((total + n_chunks - 1) / n_chunks), 128)) : total;
     const size_t d = (size_t)c.d_model;
     for (int start = 0; start < total; start += chunk) {
         const int rows = std::min(chunk, total - start);
@@ -1275,7 +1274,6 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
         a.mode = 1;
         a.pf_tokens = s->dev_pf_tokens;
         a.pf_emb = s->dev_pf_emb;
-        a.pf_pos0 = start;
         a.layer_begin = 0;
         a.layer_end = c.n_layers;
         a.do_embed = 1;
@@ -1286,11 +1284,12 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
         a.head_rows = a.rows;
         a.head_row0 = 0;
         a.head_stage = 1;
-        a.att_splits = attention_splits(s, s->att_items_cap, 1, a.rows, start + rows);
-        if (a.att_splits == 0) return fail(EE_ECAPACITY, "ee_prefill: context too long for the session's attention scratch");
         a.sess = s->dev_sessdev;
         a.sess0 = s->host_sessdev[0];
-        if (many) {
+        if (!many) {
+            a.att_splits = attention_splits(s, s->att_items_cap, 1, rows, rows);
+            if (a.att_splits == 0) return fail(EE_ECAPACITY, "ee_prefill: context too long for the session's attention scratch");
+        } else {
             if ((rc = prefill_chunk(s, start, rows)) != EE_OK) return rc;
             if (!last) continue;
             PfArgs p;
