@@ -313,10 +313,19 @@ int ee_device_synchronize(int device);
      streamed once for k consecutive exits (as many as the max_rows of the model allow) and their
      results are published together after the last of them: less traffic when many exits are
      active (the paper runs one after every layer), later results for the earlier exits of a
-     group. */
+     group.
+   EE_OPT_PREFILL_GEMM: 16 * parts + shape = every GEMM of a prompt of more than max_rows rows uses
+     this workgroup shape (1..7: 256 columns x 128 rows, 128 x 128, 128 x 64, 64 x 64; 128 x 128 and 128 x 64 with two,
+     64 x 64 with four groups of waves that share K) and this many workgroups per tile that share K (1..8, lowered
+     to what K and the partial tiles' room allow); 0 = chosen per GEMM from estimated times (the default).  Results
+     are the same up to the order of the fp32 sums.
+   EE_OPT_PREFILL_ATT_ROWS: query rows per workgroup of such a prompt's attention (64 or 128); 0 = chosen from
+     the heads, the rows and the number of compute units (the default). */
 #define EE_OPT_ATT_SPLITS 1
 #define EE_OPT_SCATTER_PAGES 2
 #define EE_OPT_HEAD_BATCH 3
+#define EE_OPT_PREFILL_GEMM 4
+#define EE_OPT_PREFILL_ATT_ROWS 5
 int ee_session_option(ee_session *s, int option, int value);
 
 /* Measurement (EE_TIME_LAUNCHES sessions, pass led by `s`): for every kernel launch of the

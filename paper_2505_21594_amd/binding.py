@@ -28,7 +28,7 @@ KEEP_LOGITS = 1
 NO_AUTOCOMMIT = 2
 SAMPLING = 4
 TIME_LAUNCHES = 16
-OPT_ATT_SPLITS, OPT_SCATTER_PAGES, OPT_HEAD_BATCH = 1, 2, 3
+OPT_ATT_SPLITS, OPT_SCATTER_PAGES, OPT_HEAD_BATCH, OPT_PREFILL_GEMM, OPT_PREFILL_ATT_ROWS = 1, 2, 3, 4, 5
 LAUNCH_NAMES = ("qkv", "o", "gu", "dn", "head", "adapter_down", "adapter_up", "embed", "att", "sample")
 
 EXPORTS = [

@@ -96,6 +96,7 @@ struct ee_session {
     PfScratch pf;                    // buffers of a prefill chunk
     float *pf_ss[2];                 // sums of squares: after the FFN block / embedding, after the attention block
     float *pf_part;                  // partial tiles of prefill GEMMs whose K is shared by several workgroups
+    size_t pf_part_cap;              // floats of them
     int *pf_part_count;              // [PF_PART_TILES] parts delivered
     int pf_cap;                      // rows of the largest prefill chunk
     Scratch sc;
@@ -103,6 +104,7 @@ struct ee_session {
     int att_splits_opt;              // EE_OPT_ATT_SPLITS (0: chosen per pass)
     int head_batch;                  // EE_OPT_HEAD_BATCH: exit heads per launch of the LM head
     bool scatter_pages;              // EE_OPT_SCATTER_PAGES
+    int pf_gemm_opt, pf_att_opt;     // EE_OPT_PREFILL_GEMM, EE_OPT_PREFILL_ATT_ROWS (0: chosen per launch)
     int flight_row0;                 // first row of this session in the pass in flight
     unsigned long long popped_mask;  // exits of the pass in flight that ee_exit_pop has handed out
     std::vector<hipEvent_t> lt_events;   // EE_TIME_LAUNCHES: event pairs around every launch of the pass
@@ -181,9 +183,16 @@ struct PfChoice {
     const PfShape *shape;
     int nb, mb, ks;
 };
-static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows)
+static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows, int forced)
 {
     PfChoice best = {};
+    if (forced) {   // EE_OPT_PREFILL_GEMM
+        const PfShape &s = PF_SHAPES[forced % 16 - 1];
+        best = {&s, (pl.NT + 2 * s.wn - 1) / (2 * s.wn), (rows + 32 * s.wm - 1) / (32 * s.wm), std::min(forced / 16, pl.KT)};
+        const size_t tiles = (size_t)best.nb * best.mb;
+        while (best.ks > 1 && (tiles > PF_PART_TILES || tiles * best.ks * pf_tile_floats(s.wn, s.wm) > PF_PART_FLOATS)) --best.ks;
+        return best;
+    }
     double best_t = 0;
     const double cu = m->nwg;
     for (const PfShape &s : PF_SHAPES) {
@@ -211,12 +220,12 @@ static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows)
 
 // Floats of partial tiles the prefill GEMMs of chunks of up to `rows` rows need: the largest choice of pf_choose, which
 // sees the rows in blocks of 64 (the narrowest row tile).
-static size_t pf_part_floats(const ee_model *m, int rows)
+static size_t pf_part_floats(const ee_model *m, int rows, int forced)
 {
     size_t need = 0;
     for (int r = 64; r < rows + 64; r += 64)
         for (int k = G_QKV; k <= G_DN; ++k) {
-            const PfChoice ch = pf_choose(m, m->plan[0][k], r);
+            const PfChoice ch = pf_choose(m, m->plan[0][k], r, forced);
             if (ch.ks > 1) need = std::max(need, (size_t)ch.nb * ch.mb * ch.ks * pf_tile_floats(ch.shape->wn, ch.shape->wm));
         }
     return need;
@@ -836,7 +845,7 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         const bool pad = pm.Kpad_d != pm.d || pm.Kpad_F != pm.F;
         // One allocation for all of them (a dozen separate ones made creating a session 5 ms longer).
         const size_t slots = 2 * (((size_t)pm.d + 63) / 64);   // two per workgroup tile of the narrowest shape
-        const size_t part = pf_part_floats(m, s->pf_cap);
+        const size_t part = s->pf_part_cap = pf_part_floats(m, s->pf_cap, 0);
         size_t bytes = 0;
         auto place = [&](size_t n) {
             const size_t at = bytes;
@@ -1177,7 +1186,7 @@ static int prefill_chunk(ee_session *s, int start, int rows)
     int slots = 1;                                          // partial sums per row in pf_ss[0]
     auto gemm = [&](int kind, int layer) {
         const GemmPlan &pl = m->plan[0][kind];
-        const PfChoice ch = pf_choose(m, pl, rows);
+        const PfChoice ch = pf_choose(m, pl, rows, s->pf_gemm_opt);
         const PfShape &sh = *ch.shape;
         a.W = m->w[0][kind] + (size_t)layer * m->wstride[0][kind];
         a.tab = m->tile_tab[kind];
@@ -1194,7 +1203,7 @@ static int prefill_chunk(ee_session *s, int start, int rows)
         a.ss_in = s->pf_ss[0];
         a.ss_slots = slots;
         gemm(G_QKV, l);
-        const int rt = md.H * ((rows + 127) / 128) >= m->nwg ? 2 : 1;
+        const int rt = s->pf_att_opt ? s->pf_att_opt / 64 : (md.H * ((rows + 127) / 128) >= m->nwg ? 2 : 1);
         hipLaunchKernelGGL(pf_att(md.hd, rt), dim3(md.H * ((rows + 64 * rt - 1) / (64 * rt))), dim3(PF_THREADS),
                            pf_att_lds(md.hd, s->pages_used), s->stream, a);
         a.gain = md.g_ffn + (size_t)l * md.d;
@@ -1876,6 +1885,23 @@ extern "C" int ee_session_option(ee_session *s, int option, int value)
     case EE_OPT_SCATTER_PAGES:
         if (value != 0 && value != 1) return fail(EE_EINVAL, "EE_OPT_SCATTER_PAGES: %d not 0 or 1", value);
         s->scatter_pages = value != 0;
+        return EE_OK;
+    case EE_OPT_PREFILL_GEMM: {
+        constexpr int shapes = sizeof PF_SHAPES / sizeof PF_SHAPES[0];
+        if (value != 0 && (value < 0 || value % 16 < 1 || value % 16 > shapes || value / 16 < 1 || value / 16 > 8))
+            return fail(EE_EINVAL, "EE_OPT_PREFILL_GEMM: %d is neither 0 nor 16 * parts (1..8) + shape (1..%d)", value, shapes);
+        const size_t need = value ? pf_part_floats(s->m, s->pf_cap, value) : 0;
+        if (need > s->pf_part_cap) {   // (the former room stays part of the session's one allocation)
+            HIP_TRY(hipSetDevice(s->m->device));
+            if ((rc = dev_alloc(s->allocs, &s->pf_part, need, false)) != EE_OK) return rc;
+            s->pf_part_cap = need;
+        }
+        s->pf_gemm_opt = value;
+        return EE_OK;
+    }
+    case EE_OPT_PREFILL_ATT_ROWS:
+        if (value != 0 && value != 64 && value != 128) return fail(EE_EINVAL, "EE_OPT_PREFILL_ATT_ROWS: %d not 0, 64 or 128", value);
+        s->pf_att_opt = value;
         return EE_OK;
     default:
         return fail(EE_EINVAL, "ee_session_option: unknown option %d", option);

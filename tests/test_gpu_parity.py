@@ -200,7 +200,8 @@ def test_hold_last_and_embedding_prefix(tiny_pair):
 
 
 @pytest.mark.parametrize("which,n_emb,n_tok,scatter", [
-    ("tiny", 0, 49, 0),        # the first size that takes the many-row kernels
+    ("tiny", 0, 16, 0),        # the last size that is one pass (the models are loaded for 16 rows)
+    ("tiny", 0, 17, 1), ("mid", 0, 17, 0), ("tiny", 0, 49, 0),     # the many-row kernels
     ("tiny", 0, 63, 1), ("mid", 0, 64, 0), ("mid", 0, 65, 1),      # around a workgroup tile of 64 rows
     ("mid", 70, 57, 0), ("tiny", 0, 129, 0),                        # around one of 128, embedding rows in front
     ("mid", 0, 257, 1), ("tiny", 0, 2048, 0), ("tiny", 0, 2049, 1), # one chunk exactly, two chunks
@@ -233,8 +234,117 @@ def test_prefill_many_rows(tiny_pair, mid_pair, which, n_emb, n_tok, scatter):
             rg = gs.verify_sync(drafts, exits)
             exempt, err = check_pass(ro, rg, gpu_logits(gs, len(exits)), drafts, f"{which} {n}")
             assert np.abs(ro.logits).max() < 8 and err < 1.7e-3
+            check_two_terms(ro, gpu_logits(gs, len(exits)))
         finally:
             gs.free()
+
+
+# A product's two-term operands are off by at most 2^-18 of themselves (the remainder of the first bf16 term, rounded
+# to bf16 again), with signs that do not depend on each other: 2^-18 / sqrt(3) = 2.2e-6 of the result in the 2-norm.  A layer has
+# four GEMMs and two attention products (two such operands and a dropped lo * lo each: three units), 10 units; four
+# layers and the head, added in quadrature as far as the residual stream carries them: sqrt(41) * 2.2e-6 = 1.4e-5.
+# (Seen: 5e-6 to 1.4e-5.)  With one operand of the prompt's layers held as a single bf16 term, planted in the oracle, the
+# logits of the round after it are 2.7e-5 (the queries of the 4-layer model) to 3e-3 off.
+TWO_TERMS = 2e-5
+
+
+def check_two_terms(ro, logits):
+    g = np.stack([np.asarray(x, dtype=np.float64) for x in logits])
+    rel = np.linalg.norm(g - ro.logits) / np.linalg.norm(ro.logits)
+    assert rel < TWO_TERMS, rel
+    return rel
+
+
+@pytest.fixture(scope="module")
+def ragged_prompt(model_dir):
+    """Prompt, drafts and the oracle's round after it, on a model whose GEMMs end in the middle of every workgroup shape
+    (20 to 134 n-tiles; 10 k-tiles, 33.5 for the down projection) and 205 rows, which do the same."""
+    p = f"{model_dir}/gpu_ragged.bin"
+    cfg = eegen.ModelConfig(n_layers=2, d_model=320, n_heads=5, head_dim=64, d_ffn=1072, vocab=1000, exit_layers=(1,))
+    eegen.write_model(p, cfg, 79, gains="uniform", std=0.05)
+    g, o = ee.Model(p), eo.Model(p, real="f64")
+    toks, drafts = eegen.prompt_tokens(1400, 205, cfg.vocab), eegen.prompt_tokens(1401, 5, cfg.vocab)
+    os_ = o.session(224)
+    first, margin = oracle_prefill(os_, toks)
+    yield g, toks, drafts, first, margin, os_.verify(drafts, [1], commit=False, want_logits=True)
+    g.free()
+
+
+@pytest.mark.parametrize("parts", [1, 2, 3, 8])
+@pytest.mark.parametrize("shape", range(1, 8))
+def test_prefill_every_gemm_shape(ragged_prompt, shape, parts):
+    """Every workgroup shape of the many-row GEMMs with K in one part, in several and in eight (one or two k-tiles
+    each: groups of waves without any), the four kinds of GEMM; the second prompt finds the counters as the first left them."""
+    g, toks, drafts, first_o, margin, ro = ragged_prompt
+    gs = g.session(224, max_gamma=8, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+    gs.ee_session_option(ee.OPT_PREFILL_GEMM, 16 * parts + shape)
+    try:
+        seen = []
+        for _ in range(2):
+            check_first_token(gs, gs.ee_prefill(toks), first_o, margin, f"shape {shape} parts {parts}")
+            check_pass(ro, gs.verify_sync(drafts, [1]), gpu_logits(gs, 1), drafts, f"shape {shape} parts {parts}")
+            check_two_terms(ro, gpu_logits(gs, 1))
+            seen.append(np.stack(gpu_logits(gs, 1)).view(np.uint32))
+        assert np.array_equal(seen[0], seen[1])
+    finally:
+        gs.free()
+
+
+@pytest.mark.parametrize("hd,att_rows,scatter", [(64, 64, 0), (64, 128, 1), (128, 64, 1), (128, 128, 0)])
+def test_prefill_attention_over_two_chunks(model_dir, hd, att_rows, scatter):
+    """64 and 128 query rows per workgroup, both head sizes, a second chunk that starts in the middle of the cache
+    (2203 rows: 1152 and 1051), through the page table and without it."""
+    p = f"{model_dir}/gpu_att_{hd}.bin"
+    cfg = eegen.ModelConfig(n_layers=2, d_model=256, n_heads=256 // hd, head_dim=hd, d_ffn=400, vocab=700, exit_layers=(1,))
+    eegen.write_model(p, cfg, 80, gains="uniform", std=0.06)
+    g, o = ee.Model(p), eo.Model(p, real="f64")
+    toks, drafts = eegen.prompt_tokens(1410, 2203, cfg.vocab), eegen.prompt_tokens(1411, 5, cfg.vocab)
+    os_ = o.session(2240)
+    gs = g.session(2240, max_gamma=8, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+    gs.ee_session_option(ee.OPT_PREFILL_ATT_ROWS, att_rows)
+    gs.ee_session_option(ee.OPT_SCATTER_PAGES, scatter)
+    try:
+        first_o, margin = oracle_prefill(os_, toks)
+        check_first_token(gs, gs.ee_prefill(toks), first_o, margin, f"hd {hd} rows {att_rows}")
+        ro = os_.verify(drafts, [1], commit=False, want_logits=True)
+        check_pass(ro, gs.verify_sync(drafts, [1]), gpu_logits(gs, 1), drafts, f"hd {hd} rows {att_rows}")
+        check_two_terms(ro, gpu_logits(gs, 1))
+    finally:
+        gs.free()
+        g.free()
+
+
+def test_prefill_tile_table_with_several_groups(model_dir):
+    """Workgroups that own more than eight n-tiles (gate/up: 2198 on 220 workgroups, two groups of tiles) with k-tiles that
+    are no multiple of eight (10; the down projection 549.5): where a tile lies then depends on the group's offset."""
+    p = f"{model_dir}/gpu_wide.bin"
+    cfg = eegen.ModelConfig(n_layers=2, d_model=320, n_heads=5, head_dim=64, d_ffn=17584, vocab=600, exit_layers=(1,))
+    eegen.write_model(p, cfg, 81, gains="uniform", std=0.03)
+    g, o = ee.Model(p), eo.Model(p, real="f64")
+    toks, drafts = eegen.prompt_tokens(1420, 70, cfg.vocab), eegen.prompt_tokens(1421, 4, cfg.vocab)
+    os_, gs = o.session(96), g.session(96, max_gamma=8, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+    try:
+        first_o, margin = oracle_prefill(os_, toks)
+        check_first_token(gs, gs.ee_prefill(toks), first_o, margin, "wide")
+        ro = os_.verify(drafts, [1], commit=False, want_logits=True)
+        check_pass(ro, gs.verify_sync(drafts, [1]), gpu_logits(gs, 1), drafts, "wide")
+        check_two_terms(ro, gpu_logits(gs, 1))
+    finally:
+        gs.free()
+        g.free()
+
+
+def test_prefill_options_are_checked(tiny_pair):
+    gs = tiny_pair[0].session(64, max_gamma=4)
+    try:
+        for opt, bad in ((ee.OPT_PREFILL_GEMM, (-17, 1, 8, 16, 24, 16 * 9 + 1)), (ee.OPT_PREFILL_ATT_ROWS, (-64, 1, 32, 192))):
+            for v in bad:
+                with pytest.raises(ee.EEError) as e:
+                    gs.ee_session_option(opt, v)
+                assert e.value.code == ee.EE_EINVAL
+            gs.ee_session_option(opt, 0)
+    finally:
+        gs.free()
 
 
 def test_session_memory(tiny_pair):
