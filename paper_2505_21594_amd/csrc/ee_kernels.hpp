@@ -208,7 +208,7 @@ __device__ __forceinline__ T sess_pick(bool first, const T &own, const T *other)
 
 __device__ __forceinline__ int row_pos(const PassArgs &a, int r)
 {
-    if (a.mode == 1) return r;
+    if (a.mode == 1) return a.pf_pos0 + r;
     int s = div_small(r, a.M);
     return EE_SESS(a, s, kv_len) + (r - s * a.M);
 }
@@ -936,7 +936,7 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
     const int sp = blockIdx.x, hh = blockIdx.y, n_splits = a.att_splits, M = a.M;
     const int s = a.mode == 1 ? 0 : blockIdx.z, ch = a.mode == 1 ? blockIdx.z : 0;
     const int r0 = ch * ATT_ROWS, nr = min(ATT_ROWS, M - r0);
-    const int P = a.mode == 1 ? 0 : EE_SESS(a, s, kv_len);          // position of the first row
+    const int P = a.mode == 1 ? a.pf_pos0 : EE_SESS(a, s, kv_len);  // position of the first row
     const int n_pg = (P + r0 + nr + KV_PAGE - 1) / KV_PAGE;         // pages visible to the chunk's last row
     const int pg_lo = div_small(n_pg * sp, n_splits), pg_hi = div_small(n_pg * (sp + 1), n_splits);
     const int cbase = EE_SESS(a, s, contig_base), n_pages = EE_SESS(a, s, n_pages);

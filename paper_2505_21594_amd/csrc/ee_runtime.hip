@@ -1283,6 +1283,7 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
         a.mode = 1;
         a.pf_tokens = s->dev_pf_tokens;
         a.pf_emb = s->dev_pf_emb;
+        a.pf_pos0 = 0;
         a.layer_begin = 0;
         a.layer_end = c.n_layers;
         a.do_embed = 1;
