@@ -632,8 +632,8 @@ __device__ __forceinline__ void split_finish(const PassArgs &a, const GemmPlan &
 
 // A streaming wave's ring of stages in LDS.  A stage is one k-step: NL weight tiles and the XC kilobytes
 // of the step's input k-tile.  As many stages as fit RING_KB (at least one; WAVE_LDS_KB holds the largest
-// stage, NL = 8 with XC = 6): eight waves then have 64 to 112 KB on their way.  More does not stream
-// faster, a compute unit's requests are served in order and the input's would wait behind
+// stage, NL = 8 with XC = 6): eight waves then have 8 D (NL + XC) KB on their way, 40 (one stage of five tiles: NL = 4,
+// XC = 1) to 112.  More does not stream faster where it was measured, a compute unit's requests are served in order and the input's would wait behind
 // more weight tiles (ms per pass, headline workload, 8 / 12 / 19 KB: 3.16 / 3.18 / 3.19).
 constexpr int RING_KB = 8;
 constexpr int WAVE_LDS_KB = GROUP_TILES + (EE_MAX_ROWS + 7) / 8;
@@ -1147,7 +1147,6 @@ __device__ __forceinline__ int2 load_cand(const int2 *p)
 // Reads the candidates with device scope: they may have been written earlier in this launch.
 __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
 {
-    const ModelDev &md = a.mdv;
     const int rows = a.rows, M = a.M;  // rows of the head launch: head after head, session after session, M rows each
     int *tok = reinterpret_cast<int *>(lds);
     float *conf = reinterpret_cast<float *>(lds) + EE_MAX_ROWS;

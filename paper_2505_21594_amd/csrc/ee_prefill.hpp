@@ -79,8 +79,9 @@ __device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int 
     *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i + (size_t)rt * 512) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
 }
 
-// Stages of the ring a tile shape uses: what fits 64 to 72 KB, so that two workgroups share a
-// compute unit and one's barrier and epilogue run under the other's products.
+// Stages of the ring a tile shape uses.  One group of waves: 48 to 72 KB, so that two workgroups (2 x 2: three) share
+// a compute unit and one's barrier and epilogue run under the other's products.  Several groups: 128 to 144 KB, the
+// workgroup has the unit to itself.
 constexpr int pf_stages(int wn, int wm, int grp) { return grp > 1 ? 144 / (grp * (wn + 2 * wm) * 2) : (wn + 2 * wm) * 2 >= 32 ? 2 : ((wn + 2 * wm) * 2 >= 24 ? 3 : 4); }
 constexpr size_t pf_gemm_lds(int wn, int wm, int grp) { return (size_t)grp * pf_stages(wn, wm, grp) * (wn + 2 * wm) * 2048 + (size_t)wm * 32 * 4 + 16; }
 constexpr size_t pf_tile_floats(int wn, int wm) { return (size_t)wn * wm * 1024; }
@@ -89,17 +90,18 @@ constexpr size_t pf_tile_floats(int wn, int wm) { return (size_t)wn * wm * 1024;
 // WN x WM accumulators.  Per k-tile of 32 the stage's W tiles and both terms of the X tiles travel to
 // LDS (1 KB per load instruction, already in operand order: every LDS read is a contiguous
 // kilobyte), NS stages in a ring, one barrier per k-tile.
-// Bound by what a compute unit gets through its memory pipeline (about 64 KB in flight), then by the
-// matrix cores.  Measured with 2041 rows, 7B shape, both terms' products counted: gate/up 551 us
-// (1.34 PFLOP/s), QKV 315 us (1.31), down 312 us (1.18), output projection 132 us (1.04; 256
-// workgroups, one per unit).  The same rows in chunks of 16 through the streaming kernels: 3 ms per
-// chunk, 486 ms per prompt against 50 ms.
+// Bound by the matrix cores (busy 51 to 63 % of a launch) and by what a compute unit gets through its memory
+// pipeline (about 64 KB in flight).  2041 rows, 7B shape, both terms' products counted: gate/up 590 us
+// (1.25 PFLOP/s), QKV 342 us (1.20), down 307 us (1.20), output projection 128 us (1.07; 256
+// workgroups, one per unit); machines differ by up to 8 % (gate/up 546 to 590).  The same rows in chunks of 16
+// through the streaming kernels: 3 ms per chunk, 486 ms per prompt against 47 ms.
 // With few rows the tiles do not cover the chip and a workgroup alone on its unit needs 0.27 us (2 x 2)
 // to 0.85 us (8 x 4) per k-tile, mostly a chain of barrier, LDS reads and products: then ks workgroups
 // share a tile, each with a part of K, and GRP groups of four waves share a workgroup's K, group g taking the
 // k-tiles g, g + GRP, ... through a ring of its own (pf_choose).  64 rows, 7B shape, us without / with: down 86 / 29,
-// output 35 / 18, QKV 40 / 34; four groups instead of one, 1280-wide model, 64 rows: QKV 16 / 11, gate/up 13 / 9.  (A deeper ring, operands read a stage ahead into registers, the 32x32x16
-// instruction and starting places along K that differ between workgroups: each within 3 % or slower.)
+// output 35 / 18, QKV 40 / 34; four groups instead of one, 1280-wide model, 64 rows: QKV 16 / 11, gate/up 13 / 9.
+// (A deeper ring, operands read a stage ahead into registers, the 32x32x16 instruction and starting places along K
+// that differ between workgroups: each within 3 % or slower.)
 template <int KIND, int WN, int WM, int GRP>
 __global__ void __launch_bounds__(PF_THREADS * GRP, GRP > 1 ? GRP : 2) pf_gemm_kernel(PfArgs a)
 {
@@ -379,7 +381,7 @@ constexpr size_t pf_att_lds(int hd, int n_pages) { return (size_t)2 * pf_att_sta
 // 8 q + e is position 4 q + e of the first page for e < 4, 4 q + e - 4 of the second otherwise; the V
 // operand uses the same order).  A row's maximum, sum and output stay in the lanes of its column:
 // the running rescale needs no exchange either.  Two bf16 terms of q, K, P and V, three MFMAs each.
-// 2041 rows, 32 heads of 128: 187 us (0.55 PFLOP/s with all three products counted); RT = 2 halves the
+// 2041 rows, 32 heads of 128: 187 to 199 us (0.52 to 0.55 PFLOP/s with all three products counted); RT = 2 halves the
 // K and V traffic per row and is used once its blocks cover the compute units.
 template <int HD, int RT>
 __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)

@@ -123,6 +123,9 @@ struct ee_session {
 
 typedef void (*pass_kernel_t)(PassArgs);
 
+// A kernel per 8 rows: the kilobytes of a k-tile of the input are compile-time.  With a kernel per 16 rows the odd classes copy
+// one kilobyte per k-tile more: 5 rows 3.01 ms a pass against 2.97, 18 rows 1.091 against 1.060, 40 rows 1.433 against
+// 1.383 (7B shape; the latter two with 8 layers).
 template <int KIND>
 static pass_kernel_t gemm_kernel_of(int rows)
 {
