@@ -26,7 +26,7 @@ constexpr int KSPLIT_LOG2 = 2;           // many-row launches: workgroups (1 << 
 // W[nt*16 + (l & 15)][kt*32 + (l >> 4)*8 .. +7]  (1 KB per tile).
 //
 // The N axis is cut into units of `tpu` n-tiles (1, or 2 for a gate/up pair);
-// workgroup g owns a contiguous range of units (unit_range below) for the whole of K, so
+// workgroup g owns a contiguous range of units (`base`, and one more if g < `rem`) for the whole of K, so
 // every output element is complete inside one workgroup.  Its n-tiles are taken in groups
 // of up to GROUP_TILES; streaming wave w owns the k-tiles w, w + SWAVES, w + 2 SWAVES, ...
 // ("k-steps" s = 0, 1, ...) and walks
@@ -41,7 +41,8 @@ struct GemmPlan {
     int N, K;        // logical shape (N counts rows after concatenation / interleaving)
     int NT, KT;      // tiles along N and K (K zero-padded to 32)
     int tpu;         // n-tiles per unit
-    int U;           // units = NT / tpu
+    int base, rem;   // units per workgroup: the first `rem` have base + 1.  Workgroups are dealt to the chip's 8 XCDs
+                     // round-robin and every XCD has its own path to memory: the larger shares are spread evenly too.
     int steps;       // tile slots per wave (longest wave sequence)
     int nwg;         // workgroups that take part in this stage kind: the fewest that keep the busiest one's
                      // share unchanged, so that all of them get (nearly) the same share; the rest idle.
@@ -74,10 +75,6 @@ constexpr int SS_LD = 256;
 // lies behind its rows ends up in lanes whose products are dropped).
 constexpr int X_SLACK = 512;
 
-// Units [u0, u1) of workgroup g.  Workgroups are dealt to the chip's 8 XCDs round-robin (XCD =
-// g % 8) and every XCD has its own path to memory, so the units are first split evenly over
-// the XCDs and then over the XCD's workgroups: with U not a multiple of nwg, a plain split
-// over g loads some XCDs up to 20 % more than others and the launch ends with them.
 constexpr int NUM_XCD = 8;
 // x / d for 0 <= x <= DIV_SMALL_MAX and d >= 1.  The GPU has no integer division: a 32-bit one is
 // about 40 instructions in a dependent chain, a 64-bit one several hundred, and the kernels divide
@@ -93,20 +90,6 @@ __host__ __device__ inline int div_small(int x, int d)
 #else
     return x / d;
 #endif
-}
-
-// (host: U * nwg <= DIV_SMALL_MAX is checked when the model is loaded)
-__host__ __device__ inline void unit_range(int U, int nwg, int g, int &u0, int &u1)
-{
-    if (nwg % NUM_XCD != 0) {
-        u0 = div_small(U * g, nwg);
-        u1 = div_small(U * (g + 1), nwg);
-        return;
-    }
-    const int x = g % NUM_XCD, j = g / NUM_XCD, per = nwg / NUM_XCD;
-    const int x0 = U * x / NUM_XCD, x1 = U * (x + 1) / NUM_XCD;
-    u0 = x0 + div_small((x1 - x0) * j, per);
-    u1 = x0 + div_small((x1 - x0) * (j + 1), per);
 }
 
 enum RowPerm { PERM_NONE = 0, PERM_QKV = 1, PERM_GU = 2 };
@@ -175,11 +158,23 @@ struct SampleDev {
     int *count;          // rows of a sampling launch that have delivered; zero between launches
 };
 
+// What a GEMM launch needs to request its first weights and input: one line of the launch arguments, read with one
+// scalar load (see gemm_entry).
+struct GemmEntry {
+    const uint4 *W;                      // the stage's weights
+    const uint16_t *X;                   // its input
+    int wstep;                           // bytes from one tile of a wave's sequence to the next
+    int tile_bytes;                      // bytes of one k-tile of the input: all rows, both terms
+    int KTs, nwg, base, rem, tpu, ksl;   // of the plan
+    int unused[4];
+};
+static_assert(sizeof(GemmEntry) == 64, "one line");
+
 struct PassArgs {
+    GemmEntry entry;                     // (first: the kernels read it at the start of their arguments)
     ModelDev mdv;                        // the model descriptor by value
-    GemmPlan plan0;                      // plan, LDS map and weights of the launch's GEMM stage
+    GemmPlan plan0;                      // plan and LDS map of the launch's GEMM stage
     StageLds lay;
-    const uint4 *W0;
     Scratch sc;
     int nwg;
     int n_sess, M, rows;                 // rows = n_sess * M

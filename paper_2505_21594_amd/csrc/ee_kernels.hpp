@@ -270,10 +270,9 @@ __device__ __forceinline__ Misc misc_views(const StageLds &ly, char *lds)
 
 __device__ __host__ inline void wg_units(const GemmPlan &pl, int g, int &nt0, int &n_local)
 {
-    int u0 = 0, u1 = 0;
-    if (g < pl.nwg) unit_range(pl.U, pl.nwg >> pl.ksl, g >> pl.ksl, u0, u1);  // workgroups past the stage's count own nothing
-    nt0 = u0 * pl.tpu;
-    n_local = (u1 - u0) * pl.tpu;
+    const int j = g >> pl.ksl;
+    nt0 = (j * pl.base + (j < pl.rem ? j : pl.rem)) * pl.tpu;
+    n_local = g < pl.nwg ? (pl.base + (j < pl.rem ? 1 : 0)) * pl.tpu : 0;  // workgroups past the stage's count own nothing
 }
 
 // k-steps of streaming wave w: its k-tiles are w, w + SWAVES, ...
@@ -282,7 +281,7 @@ __device__ __host__ inline int wave_ksteps(int KT, int w) { return KT > w ? (KT 
 // ------------------------------------------------------------------ GEMM stage
 
 struct GemmIn {
-    const uint16_t *x;  // the input (already scaled by the norm gain) as two bf16 terms, k-tile-major (x_index)
+    const char *x;      // the input (already scaled by the norm gain) as two bf16 terms, k-tile-major (x_index); K split: the slice
     const float *ss;    // [rows][SS_LD] partial sums of squares for rstd, or nullptr
 };
 
@@ -637,11 +636,54 @@ __device__ __forceinline__ void split_finish(const PassArgs &a, const GemmPlan &
 // more weight tiles (ms per pass, headline workload, 8 / 12 / 19 KB: 3.16 / 3.18 / 3.19).
 constexpr int RING_KB = 8;
 constexpr int WAVE_LDS_KB = GROUP_TILES + (EE_MAX_ROWS + 7) / 8;
-template <int XC, int NL>
-constexpr int ring_depth()
+// (a division by comparisons: the kernels need it before they know anything else)
+__device__ __host__ constexpr int ring_depth(int xc, int nl)
 {
-    constexpr int d = RING_KB / (NL + XC);
-    return d < 1 ? 1 : d;
+    const int per = nl + xc;
+    return per <= 2 ? 4 : (per <= 4 ? 2 : 1);
+}
+constexpr bool ring_depth_ok()
+{
+    for (int xc = 1; xc <= EE_MAX_ROWS / 8; ++xc)
+        for (int nl = 1; nl <= GROUP_TILES; ++nl) {
+            const int d = RING_KB / (nl + xc);
+            if (ring_depth(xc, nl) != (d < 1 ? 1 : d) || ring_depth(xc, nl) * (nl + xc) > WAVE_LDS_KB) return false;
+        }
+    return true;
+}
+static_assert(ring_depth_ok(), "as many stages as fit RING_KB, at least one, inside the wave's part of LDS");
+
+// The start of a GEMM launch: every streaming wave requests the stages its ring holds, before anything else is read or
+// worked out.  A launch's instructions come from a cold instruction cache, a line at a time, and its arguments from a
+// cold scalar cache: the code up to these requests is 70 instructions (loops, not unrolled) and needs one line of arguments.
+// With the requests behind the warming of all arguments and the plan's arithmetic, us per launch, 5 rows of the 7B shape: QKV
+// 18.6 -> 18.3, gate/up 30.9 -> 30.0, down 18.1 -> 17.9, head 50.0 -> 49.0; 40 rows, 8 layers, a pass 1390 -> 1372.
+template <int XC>
+__device__ __forceinline__ void gemm_entry(char *lds)
+{
+    typedef unsigned int u32x16_t __attribute__((ext_vector_type(16), aligned(16)));
+    const u32x16_t v = *(const __attribute__((address_space(4))) u32x16_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = blockIdx.x;
+    const int tile_bytes = v[5], KTs = v[6], nwg = v[7], base = v[8], rem = v[9], tpu = v[10], ksl = v[11];
+    if (wave >= SWAVES || g >= nwg) return;
+    const int nl = min(GROUP_TILES, (base + ((g >> ksl) < rem ? 1 : 0)) * tpu);
+    const int stages = min(ring_depth(XC, nl), wave_ksteps(KTs, wave)), lane16 = (threadIdx.x & 63) * 16;
+    const char *wp = reinterpret_cast<const char *>((((unsigned long long)v[1] << 32) | v[0]) + (unsigned)((g * SWAVES + wave) * 1024));
+    const char *xp = reinterpret_cast<const char *>((((unsigned long long)v[3] << 32) | v[2]) + (unsigned)(((g & ((1 << ksl) - 1)) * KTs + wave) * tile_bytes));
+    unsigned dst = lds_offset(lds) + wave * (WAVE_LDS_KB * 1024);
+#pragma unroll 1
+    for (int s = 0; s < stages; ++s) {
+#pragma unroll 1
+        for (int i = 0; i < nl; ++i) {
+            load_lds_kb(wp, lane16, dst);
+            wp += (int)v[4];
+            dst += 1024;
+        }
+#pragma unroll
+        for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, lane16, dst + i * 1024);
+        dst += XC * 1024;
+        xp += SWAVES * tile_bytes;
+    }
 }
 
 // One group of NL n-tiles (this workgroup's n-tiles nt_first .. nt_first + NL - 1) over all of K,
@@ -667,7 +709,7 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
                                            const uint4 *__restrict__ W, const GemmIn &in, const GemmEpi &ep, const Misc &mi,
                                            char *lds, int nt_first, int seq0, bool first_group)
 {
-    constexpr int MT = (XC + 1) / 2, D = ring_depth<XC, NL>(), PER = NL + XC;
+    constexpr int MT = (XC + 1) / 2, D = ring_depth(XC, NL), PER = NL + XC;
     constexpr int NW = MT == 3 && NL > 4 ? 4 : NL;   // weight tiles read at a time (registers: three waves per SIMD)
     const ModelDev &md = a.mdv;
     const int tid = opaque(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -681,7 +723,7 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
         const size_t wstep = (size_t)pl.nwg * SWAVES * 1024;   // bytes from one tile of the wave's sequence to the next
         const char *wp = reinterpret_cast<const char *>(W) + (size_t)seq0 * wstep + ((size_t)blockIdx.x * SWAVES + wave) * 1024;
         const int tile_bytes = rows * 128;                     // one k-tile of the input: both terms, all rows
-        const char *xp = reinterpret_cast<const char *>(in.x) + (size_t)wave * tile_bytes;
+        const char *xp = in.x + (size_t)wave * tile_bytes;
         const unsigned ring = lds_offset(lds) + wave * (WAVE_LDS_KB * 1024);
         auto request = [&](unsigned dst) __attribute__((always_inline)) {   // the next stage of the sequence
 #pragma unroll
@@ -693,9 +735,14 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
             for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, lane16, dst + (NL + i) * 1024);
             xp += SWAVES * tile_bytes;
         };
+        if (first_group) {                                     // (requested at the kernel's start: gemm_entry)
+            wp += D * NL * wstep;
+            xp += D * SWAVES * tile_bytes;
+        } else {
 #pragma unroll
-        for (int i = 0; i < D; ++i)
-            if (i < S_w) request(ring + i * PER * 1024);
+            for (int i = 0; i < D; ++i)
+                if (i < S_w) request(ring + i * PER * 1024);
+        }
 #pragma unroll
         for (int nt = 0; nt < NL; ++nt)
 #pragma unroll
@@ -794,16 +841,18 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, const GemmPlan &
     int nt0, n_local;
     wg_units(pl, blockIdx.x, nt0, n_local);
 
-    if (tid < rows) {
-        mi.bestv[tid] = -INFINITY;
-        mi.besti[tid] = 0x7FFFFFFF;
-        mi.sume[tid] = 0.f;
-        mi.rowss[tid] = 0.f;
+    const int hrow = tid - SWAVES * 64;   // the first helper wave: one lane per row, here and in hand_over
+    static_assert(EE_MAX_ROWS <= 64, "one lane per row");
+    if (hrow >= 0 && hrow < rows) {
+        mi.bestv[hrow] = -INFINITY;
+        mi.besti[hrow] = 0x7FFFFFFF;
+        mi.sume[hrow] = 0.f;
+        mi.rowss[hrow] = 0.f;
     }
     if (n_local > 0) {
         const int S0 = wave_ksteps(pl.KTs, 0);
         // K split over workgroups: this workgroup's slice of the input (k-tile-major: a contiguous range)
-        const GemmIn in = {MT > 1 ? in_all.x + (size_t)(blockIdx.x & ((1 << pl.ksl) - 1)) * pl.KTs * (2 * rows * 32) : in_all.x, in_all.ss};
+        const GemmIn in = {MT > 1 ? in_all.x + (size_t)(blockIdx.x & ((1 << pl.ksl) - 1)) * pl.KTs * (128 * rows) : in_all.x, in_all.ss};
         int seq = 0;  // tiles of a wave's sequence before the group (waves with fewer k-steps leave their slots unused)
         for (int g0 = 0; g0 < n_local; g0 += GROUP_TILES) {
             const int nl = min(GROUP_TILES, n_local - g0);
@@ -820,16 +869,16 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, const GemmPlan &
     }
     // what the workgroup hands to the following launch
     auto hand_over = [&](int slot, bool mine) __attribute__((always_inline)) {
-        const float ss = mine ? mi.rowss[tid] : 0.f;
-        if (ep.ss_out) as_global_mut(ep.ss_out)[(size_t)tid * SS_LD + slot] = ss;
-        if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)(a.head_row0 + tid) * SS_LD + slot] = ss;
+        const float ss = mine ? mi.rowss[hrow] : 0.f;
+        if (ep.ss_out) as_global_mut(ep.ss_out)[(size_t)hrow * SS_LD + slot] = ss;
+        if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)(a.head_row0 + hrow) * SS_LD + slot] = ss;
         if (KIND == G_HEAD) {  // device-scope stores: the accept step may run in another workgroup of this launch
-            store_dev64(a.sc.cand + (size_t)tid * SS_LD + slot,
-                        make_uint2(__float_as_uint(mine ? mi.bestv[tid] : -INFINITY), (unsigned)(mine ? mi.besti[tid] : 0x7FFFFFFF)));
-            store_dev32(a.sc.cand_sum + (size_t)tid * SS_LD + slot, mine ? mi.sume[tid] : 0.f);
+            store_dev64(a.sc.cand + (size_t)hrow * SS_LD + slot,
+                        make_uint2(__float_as_uint(mine ? mi.bestv[hrow] : -INFINITY), (unsigned)(mine ? mi.besti[hrow] : 0x7FFFFFFF)));
+            store_dev32(a.sc.cand_sum + (size_t)hrow * SS_LD + slot, mine ? mi.sume[hrow] : 0.f);
         }
     };
-    if (tid < rows) {
+    if (hrow >= 0 && hrow < rows) {
         if (MT > 1 && pl.ksl && n_local > 0) {
             // K split: the group's result was worked out by whichever of its workgroups arrived last; it
             // fills the slots of the whole group, the result in the first, so that what the following
@@ -1474,19 +1523,12 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
 // Stage list of a segment: [EMBED] { QKV ATT O GU DN } x layers [AD AU] [HEAD]; one launch per stage.
 // The accept step runs inside the head's launch, in the workgroup that finishes last.
 
-// The input and what the epilogue produces, by GEMM kind (what varies inside a kind travels in the arguments).
+// Where the input's sums of squares are and what the epilogue produces, by GEMM kind (what varies inside a kind travels in the arguments).
 template <int KIND>
 __device__ __forceinline__ GemmIn gemm_input(const PassArgs &a)
 {
-    switch (KIND) {
-    case G_QKV: return GemmIn{a.sc.xn, a.sc.ss_a};
-    case G_O: return GemmIn{a.sc.attn, nullptr};
-    case G_GU: return GemmIn{a.sc.xn, a.sc.ss_f};
-    case G_DN: return GemmIn{a.sc.u, nullptr};
-    case G_AD: return GemmIn{a.sc.xa, nullptr};
-    case G_AU: return GemmIn{a.sc.t, nullptr};
-    default: return GemmIn{a.sc.xh, a.sc.ss_h};
-    }
+    const char *x = reinterpret_cast<const char *>(a.entry.X);
+    return GemmIn{x, KIND == G_QKV ? a.sc.ss_a : (KIND == G_GU ? a.sc.ss_f : (KIND == G_HEAD ? a.sc.ss_h : nullptr))};
 }
 
 template <int KIND>
@@ -1521,8 +1563,9 @@ template <int KIND, int XC>
 __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
+    gemm_entry<XC>(lds);
     const PassArgs &a = warmed_arguments();
-    gemm_stage_t<KIND, XC>(a, a.plan0, a.lay, a.W0, gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
+    gemm_stage_t<KIND, XC>(a, a.plan0, a.lay, a.entry.W, gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
     if (KIND == G_HEAD && a.fuse_accept) {
         // The workgroup whose candidates arrive last also runs the accept step
         // (one launch less per head); the counter is left at zero.

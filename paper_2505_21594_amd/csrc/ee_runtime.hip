@@ -257,7 +257,7 @@ static GemmPlan make_plan(int N, int K, int tpu, int nwg_max, int ksl = 0)
     p.NT = (p.NT + tpu - 1) / tpu * tpu;
     p.KT = (K + 31) / 32;
     p.tpu = tpu;
-    p.U = p.NT / tpu;
+    const int U = p.NT / tpu;
     p.KTs = p.KT;
     if (ksl > 0 && p.KT % (1 << ksl) == 0 && (nwg_max >> ksl) >= 1) {
         p.ksl = ksl;
@@ -265,8 +265,10 @@ static GemmPlan make_plan(int N, int K, int tpu, int nwg_max, int ksl = 0)
     }
     // the fewest (groups of) workgroups that do not raise the busiest one's share
     const int groups_max = nwg_max >> p.ksl;
-    const int most = (p.U + groups_max - 1) / groups_max;
-    p.nwg = std::min(groups_max, (p.U + most - 1) / most) << p.ksl;
+    const int most = (U + groups_max - 1) / groups_max, groups = std::min(groups_max, (U + most - 1) / most);
+    p.nwg = groups << p.ksl;
+    p.base = U / groups;
+    p.rem = U % groups;
     // every wave's sequence has room for the busiest wave's k-steps of every n-tile
     p.steps = wave_ksteps(p.KTs, 0) * plan_max_local(p);
     return p;
@@ -542,8 +544,8 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
                 ee_model_free(m);
                 return fail(EE_EDEVICE, "ee_model_load: max_rows %d needs more LDS than the device's %zu bytes", max_rows, lds_cap);
             }
-            // the kernels' exact small-integer division (div_small) covers the unit arithmetic of this plan
-            if ((long long)pl.U * pl.nwg > DIV_SMALL_MAX || pl.N > DIV_SMALL_MAX) {
+            // the kernels' exact small-integer division (div_small) covers column numbers
+            if (pl.N > DIV_SMALL_MAX) {
                 ee_model_free(m);
                 return fail(EE_EFORMAT, "ee_model_load: a weight matrix with %d rows is beyond what the kernels' index arithmetic covers", pl.N);
             }
@@ -1031,6 +1033,18 @@ static int upload_sampling(ee_session *lead, SampleUpload &up)
     return EE_OK;
 }
 
+static const uint16_t *gemm_input_of(const Scratch &sc, int kind)
+{
+    switch (kind) {
+    case G_O: return sc.attn;
+    case G_DN: return sc.u;
+    case G_AD: return sc.xa;
+    case G_AU: return sc.t;
+    case G_HEAD: return sc.xh;
+    default: return sc.xn;
+    }
+}
+
 // Enqueues the stages of one segment, one launch each, on the leader's stream.
 static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, SampleUpload *up = nullptr)
 {
@@ -1069,7 +1083,17 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             // more than 16 rows: the K-split variant of the kind, where the model has one and the scratch its buffers
             const int v = (a.rows > 16 && m->plan[1][code].nwg > 0 && a.sc.part) ? 1 : 0;
             a.plan0 = m->plan[v][code];
-            a.W0 = m->w[v][code] + (size_t)slice * m->wstride[v][code];
+            GemmEntry &en = a.entry;
+            en.W = m->w[v][code] + (size_t)slice * m->wstride[v][code];
+            en.X = gemm_input_of(a.sc, code);
+            en.wstep = a.plan0.nwg * SWAVES * 1024;
+            en.tile_bytes = a.rows * 128;
+            en.KTs = a.plan0.KTs;
+            en.nwg = a.plan0.nwg;
+            en.base = a.plan0.base;
+            en.rem = a.plan0.rem;
+            en.tpu = a.plan0.tpu;
+            en.ksl = a.plan0.ksl;
             if (!plan_lds(a.plan0, a.rows, m->lds_budget, a.lay)) return fail(EE_EDEVICE, "no LDS layout for %d rows", a.rows);
         }
         const bool timed = (lead->flags & EE_TIME_LAUNCHES) && a.mode == 0;
