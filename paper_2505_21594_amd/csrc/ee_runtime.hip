@@ -169,19 +169,22 @@ struct PfShape {
     {WN, WM, GRP, T1, T2, OCC, {pf_gemm_kernel<G_QKV, WN, WM, GRP>, pf_gemm_kernel<G_O, WN, WM, GRP>, \
                                 pf_gemm_kernel<G_GU, WN, WM, GRP>, pf_gemm_kernel<G_DN, WN, WM, GRP>}}
 static const PfShape PF_SHAPES[] = {
-    EE_PF_SHAPE(8, 4, 1, 0.85, 0.72, 2), EE_PF_SHAPE(4, 4, 1, 0.55, 0.41, 2), EE_PF_SHAPE(4, 2, 1, 0.36, 0.27, 2), EE_PF_SHAPE(2, 2, 1, 0.27, 0.175, 3),
-    EE_PF_SHAPE(4, 4, 2, 0.48, 0.48, 1), EE_PF_SHAPE(4, 2, 2, 0.29, 0.29, 1), EE_PF_SHAPE(2, 2, 4, 0.17, 0.17, 1)};
+    EE_PF_SHAPE(8, 4, 1, 0.908, 0.716, 2), EE_PF_SHAPE(4, 4, 1, 0.529, 0.407, 2), EE_PF_SHAPE(4, 2, 1, 0.356, 0.247, 2),
+    EE_PF_SHAPE(2, 2, 1, 0.226, 0.186, 3), EE_PF_SHAPE(4, 4, 2, 0.480, 0.462, 1), EE_PF_SHAPE(4, 2, 2, 0.285, 0.300, 1),
+    EE_PF_SHAPE(2, 2, 4, 0.199, 0.222, 1)};
 
 static pf_kernel_t pf_att(int hd, int rt)
 {
     return hd == 128 ? (rt == 2 ? pf_att_kernel<128, 2> : pf_att_kernel<128, 1>) : (rt == 2 ? pf_att_kernel<64, 2> : pf_att_kernel<64, 1>);
 }
 
-// Shape of the workgroup tile and parts of K of one prefill GEMM: the least estimated time.  The estimate, in us
-// per k-tile (PfShape): t1 where a workgroup is alone on its compute unit (a chain of latencies), t2 per workgroup
-// where a unit has several (occ fit); a split adds the exchange of the partial tiles (measured: about 5 us, 0.7 us
-// per part read one after the other, and the bytes at 3.5 TB/s).  Fitted to QKV, O, GU and DN of the 7B
-// shape at 64 to 2048 rows; its choice is within 8 % of the best measured one, most often the best.
+// Shape of the workgroup tile and parts of K of one prefill GEMM: the least estimated time.  The estimate, in us:
+// per k-tile (PfShape) t1 where a workgroup is alone on its compute unit (a chain of latencies), t2 per workgroup
+// where a unit has several (occ fit); 2.9 per launch; a split adds the exchange of the partial tiles (4.8, 0.6
+// per part read one after the other, and the bytes at 3.5 TB/s).  Least-squares fit to every shape with 1 to 8 parts, QKV, O, GU
+// and DN of the 7B shape at 64 to 2041 rows, of the 13B shape at 128 to 1400 and of a 1280-wide model at 61 to 700: its choice is on
+// average 0.8 % above the best measured one, at worst 8 % (the constants before, fitted to fewer: 2.7 %, 28 %; 7B shape, 640
+// rows: output 64 -> 56; 256: down 73 -> 57; 900: down 180 -> 150).
 struct PfChoice {
     const PfShape *shape;
     int nb, mb, ks;
@@ -209,9 +212,9 @@ static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows, int f
                 f += s.occ * s.t2;
                 left -= slots;
             }
-            f += left <= cu ? s.t1 : std::max(1.25 * s.t1, left / cu * s.t2);
-            double t = f * ((pl.KT + ks - 1) / ks);
-            if (ks > 1) t += 5.0 + 0.7 * ks + (double)part * 8.0 / 3.5e6;
+            f += left <= cu ? s.t1 : std::max(1.4 * s.t1, left / cu * s.t2);
+            double t = 2.9 + f * ((pl.KT + ks - 1) / ks);
+            if (ks > 1) t += 4.8 + 0.6 * ks + (double)part * 8.0 / 3.5e6;
             if (!best.shape || t < best_t) {
                 best = {&s, nb, mb, ks};
                 best_t = t;
