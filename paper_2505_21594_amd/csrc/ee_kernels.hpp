@@ -184,12 +184,12 @@ __device__ __forceinline__ void lds_barrier()
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-// round to nearest even; inputs are finite
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
+// two values as bf16, round to nearest even, packed (a in the low half): one instruction
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
+    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
 }
 
 // ------------------------------------------------------------------ rows
@@ -298,20 +298,21 @@ __device__ __forceinline__ size_t x_index(int rows, int m, int k, int term)
 // feeding both terms keeps about 16 mantissa bits of the activations (weights are exact
 // bf16).  The matrix cores idle most of the time in the HBM-bound loop, so the second MFMA
 // per tile is free.
-__device__ __forceinline__ void split_bf16(float x, uint32_t &hi, uint32_t &lo)
+// Two values at a time, packed: six instructions for both (about twenty with the rounding done in integers).
+__device__ __forceinline__ void split_bf16(float a, float b, uint32_t &hi, uint32_t &lo)
 {
-    hi = f32_to_bf16(x);
-    lo = f32_to_bf16(x - __uint_as_float(hi << 16));
+    hi = pack_bf16(a, b);
+    lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
 }
 
 // four consecutive columns k .. k+3 (k a multiple of 4) of row m
 __device__ __forceinline__ void store_split4(uint16_t *x, int rows, int m, int k, const float *v)
 {
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) split_bf16(v[e], h[e], l[e]);
-    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 0)) = (u32x2_t){h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 1)) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+    uint32_t h[2], l[2];
+    split_bf16(v[0], v[1], h[0], l[0]);
+    split_bf16(v[2], v[3], h[1], l[1]);
+    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 0)) = (u32x2_t){h[0], h[1]};
+    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + x_index(rows, m, k, 1)) = (u32x2_t){l[0], l[1]};
 }
 
 // rstd[m] = 1/sqrt(sum_g ss[m][g] / d + eps) into LDS, fixed summation order; helper waves only, for
@@ -476,21 +477,21 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
             } else {
                 // cached value = hi + lo, two bf16 terms.  K: [position][term][hd]; V transposed
                 // inside the page: [term][hd][position] (see the attention stage)
-                uint32_t vh[4], vl[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) split_bf16(v[t], vh[t], vl[t]);
+                uint32_t vh[2], vl[2];
+                split_bf16(v[0], v[1], vh[0], vl[0]);
+                split_bf16(v[2], v[3], vh[1], vl[1]);
                 const size_t rec = mi.kvoff[m] + (size_t)head * KV_PAGE * 2 * hd;  // this (page, head) record
                 const int slot = mi.pos[m] % KV_PAGE;
                 if (sect == 1) {
                     EE_GLOBAL uint16_t *kr = as_global_mut(EE_SESS(a, ses, kpool)) + rec + (size_t)slot * 2 * hd + e;
-                    *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0] | (vh[1] << 16), vh[2] | (vh[3] << 16)};
-                    *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + hd) = (u32x2_t){vl[0] | (vl[1] << 16), vl[2] | (vl[3] << 16)};
+                    *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0], vh[1]};
+                    *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + hd) = (u32x2_t){vl[0], vl[1]};
                 } else {
                     EE_GLOBAL uint16_t *vr = as_global_mut(EE_SESS(a, ses, vpool)) + rec + slot;
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        vr[(size_t)(e + t) * KV_PAGE] = (uint16_t)vh[t];
-                        vr[(size_t)(hd + e + t) * KV_PAGE] = (uint16_t)vl[t];
+                        vr[(size_t)(e + t) * KV_PAGE] = (uint16_t)(vh[t >> 1] >> (16 * (t & 1)));
+                        vr[(size_t)(hd + e + t) * KV_PAGE] = (uint16_t)(vl[t >> 1] >> (16 * (t & 1)));
                     }
                 }
             }
@@ -939,9 +940,16 @@ __device__ __forceinline__ uint2 load_global8(const void *p)
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 
-__device__ __forceinline__ bf16x8_t pack_bf16x8(const uint32_t *h)
+// eight values as an MFMA operand's two bf16 terms
+__device__ __forceinline__ void split_bf16x8(f32x4_t x, f32x4_t y, bf16x8_t &hi, bf16x8_t &lo)
 {
-    return __builtin_bit_cast(bf16x8_t, make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)));
+    uint32_t h[4], l[4];
+    split_bf16(x[0], x[1], h[0], l[0]);
+    split_bf16(x[2], x[3], h[1], l[1]);
+    split_bf16(y[0], y[1], h[2], l[2]);
+    split_bf16(y[2], y[3], h[3], l[3]);
+    hi = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
+    lo = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
 // floats of one row's partial result in LDS (output, maximum, sum, padding to 16 bytes) ...
@@ -1038,16 +1046,7 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
         request_v(rec);
         bf16x8_t qh[KT], ql[KT];
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
-            uint32_t h[8], l[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                split_bf16(qraw[kt][0][e], h[e], l[e]);
-                split_bf16(qraw[kt][1][e], h[4 + e], l[4 + e]);
-            }
-            qh[kt] = pack_bf16x8(h);
-            ql[kt] = pack_bf16x8(l);
-        }
+        for (int kt = 0; kt < KT; ++kt) split_bf16x8(qraw[kt][0], qraw[kt][1], qh[kt], ql[kt]);
         for (;;) {
             f32x4_t S = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1075,15 +1074,15 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
             const float f = __expf(mx - m_new);
             mx = m_new;
             sum *= f;
-            uint32_t ph[4], pl[4];
+            uint32_t ph[2], pl[2];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float pr = S[r] > 0.5f * ATT_NEG ? __expf(S[r] - mx) : 0.f;
-                sum += pr;
-                split_bf16(pr, ph[r], pl[r]);
+                S[r] = S[r] > 0.5f * ATT_NEG ? __expf(S[r] - mx) : 0.f;
+                sum += S[r];
             }
-            const s16x4_t Ph = __builtin_bit_cast(s16x4_t, make_uint2(ph[0] | (ph[1] << 16), ph[2] | (ph[3] << 16)));
-            const s16x4_t Pl = __builtin_bit_cast(s16x4_t, make_uint2(pl[0] | (pl[1] << 16), pl[2] | (pl[3] << 16)));
+            split_bf16(S[0], S[1], ph[0], pl[0]);
+            split_bf16(S[2], S[3], ph[1], pl[1]);
+            const s16x4_t Ph = __builtin_bit_cast(s16x4_t, make_uint2(ph[0], ph[1])), Pl = __builtin_bit_cast(s16x4_t, make_uint2(pl[0], pl[1]));
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll

@@ -71,12 +71,12 @@ __device__ __forceinline__ size_t pf_index(int rt, int m, int k, int term)
 // four consecutive columns k .. k+3 (k a multiple of 4) of row m, as two bf16 terms
 __device__ __forceinline__ void pf_store_split4(uint16_t *x, int rt, int m, int k, const float *v)
 {
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) split_bf16(v[e], h[e], l[e]);
+    uint32_t h[2], l[2];
+    split_bf16(v[0], v[1], h[0], l[0]);
+    split_bf16(v[2], v[3], h[1], l[1]);
     const size_t i = pf_index(rt, m, k, 0);
-    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i) = (u32x2_t){h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i + (size_t)rt * 512) = (u32x2_t){l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i) = (u32x2_t){h[0], h[1]};
+    *reinterpret_cast<EE_GLOBAL u32x2_t *>(as_global_mut(x) + i + (size_t)rt * 512) = (u32x2_t){l[0], l[1]};
 }
 
 // Stages of the ring a tile shape uses.  One group of waves: 48 to 72 KB, so that two workgroups (2 x 2: three) share
@@ -346,20 +346,20 @@ __global__ void __launch_bounds__(PF_THREADS * GRP, GRP > 1 ? GRP : 2) pf_gemm_k
                 if (sect == 0) {
                     *reinterpret_cast<EE_GLOBAL f32x4_t *>(as_global_mut(a.b.q) + (size_t)m * a.d + c0 + quad * 4) = (f32x4_t){v[0], v[1], v[2], v[3]};
                 } else {
-                    uint32_t vh[4], vl[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) split_bf16(v[r], vh[r], vl[r]);
+                    uint32_t vh[2], vl[2];
+                    split_bf16(v[0], v[1], vh[0], vl[0]);
+                    split_bf16(v[2], v[3], vh[1], vl[1]);
                     const size_t rec = rec0 + (size_t)head * KV_PAGE * 2 * a.hd;
                     if (sect == 1) {
                         EE_GLOBAL uint16_t *kr = as_global_mut(a.kpool) + rec + (size_t)slot * 2 * a.hd + e;
-                        *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0] | (vh[1] << 16), vh[2] | (vh[3] << 16)};
-                        *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + a.hd) = (u32x2_t){vl[0] | (vl[1] << 16), vl[2] | (vl[3] << 16)};
+                        *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr) = (u32x2_t){vh[0], vh[1]};
+                        *reinterpret_cast<EE_GLOBAL u32x2_t *>(kr + a.hd) = (u32x2_t){vl[0], vl[1]};
                     } else {
                         EE_GLOBAL uint16_t *vr = as_global_mut(a.vpool) + rec + slot;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            vr[(size_t)(e + r) * KV_PAGE] = (uint16_t)vh[r];
-                            vr[(size_t)(a.hd + e + r) * KV_PAGE] = (uint16_t)vl[r];
+                            vr[(size_t)(e + r) * KV_PAGE] = (uint16_t)(vh[r >> 1] >> (16 * (r & 1)));
+                            vr[(size_t)(a.hd + e + r) * KV_PAGE] = (uint16_t)(vl[r >> 1] >> (16 * (r & 1)));
                         }
                     }
                 }
@@ -412,14 +412,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
             const f32x4_t x = *as_global(reinterpret_cast<const f32x4_t *>(qp + kt * 32)), y = *as_global(reinterpret_cast<const f32x4_t *>(qp + kt * 32 + 4));
-            uint32_t h[8], l[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                split_bf16(x[e], h[e], l[e]);
-                split_bf16(y[e], h[4 + e], l[4 + e]);
-            }
-            qh[t][kt] = pack_bf16x8(h);
-            ql[t][kt] = pack_bf16x8(l);
+            split_bf16x8(x, y, qh[t][kt], ql[t][kt]);
         }
     }
     wait_vmem();
@@ -495,15 +488,12 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) O[t][n][r] *= f;
             }
-            uint32_t ph[8], pl[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float p = __expf(s[e] - mx[t]);
-                sum[t] += p;
-                split_bf16(p, ph[e], pl[e]);
+                s[e] = __expf(s[e] - mx[t]);
+                sum[t] += s[e];
             }
-            Ph[t] = pack_bf16x8(ph);
-            Pl[t] = pack_bf16x8(pl);
+            split_bf16x8((f32x4_t){s[0], s[1], s[2], s[3]}, (f32x4_t){s[4], s[5], s[6], s[7]}, Ph[t], Pl[t]);
         }
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
