@@ -370,21 +370,29 @@ __global__ void __launch_bounds__(PF_THREADS * GRP, GRP > 1 ? GRP : 2) pf_gemm_k
 
 // ------------------------------------------------------------------ attention
 
+constexpr int PF_ATT_GROUPS = 2;          // groups of four waves that share a block's positions
+constexpr int PF_ATT_THREADS = PF_ATT_GROUPS * 256;
 constexpr int pf_att_stage(int hd) { return 4 * KV_PAGE * 2 * hd * 2; }   // bytes: K and V of two pages
-constexpr size_t pf_att_lds(int hd, int n_pages) { return (size_t)2 * pf_att_stage(hd) + (size_t)n_pages * 4; }
+constexpr size_t pf_att_lds(int hd, int n_pages) { return (size_t)2 * PF_ATT_GROUPS * pf_att_stage(hd) + (size_t)n_pages * 4; }
 
-// Workgroup = (head, block of 64 RT query rows); wave w has row tiles w RT .. of the block.  It walks
-// the cached positions 32 (two pages) at a time up to its last row's position, K and V of a step
-// shared by the four waves through LDS (two buffers).  Scores as S^T = K . q^T (16x16x32, K one operand per
-// page and 32 values), so that a lane holds four positions of one row; those are, without any
-// exchange, the k-slots of the second product O^T = V^T . P^T (16x16x32 over the two pages: k-slot
-// 8 q + e is position 4 q + e of the first page for e < 4, 4 q + e - 4 of the second otherwise; the V
-// operand uses the same order).  A row's maximum, sum and output stay in the lanes of its column:
-// the running rescale needs no exchange either.  Two bf16 terms of q, K, P and V, three MFMAs each.
-// 2041 rows, 32 heads of 128: 187 to 199 us (0.52 to 0.55 PFLOP/s with all three products counted); RT = 2 halves the
-// K and V traffic per row and is used once its blocks cover the compute units.
+// Workgroup = (head, block of 64 RT query rows); wave w of either group has row tiles w RT .. of the block.  The groups
+// walk the cached positions 32 (two pages) at a time up to the block's last row's position, group g the steps g, g + 2, ...;
+// K and V of a step are shared by the group's four waves through LDS (two buffers per group).  Scores as S^T = K . q^T
+// (16x16x32, two operands of 16 positions per 32 values): row 4 q + r of operand p is position 8 q + 4 p + r of the
+// step, so that a lane holds eight consecutive positions of one row; those are, without any exchange, the k-slots of the second
+// product O^T = V^T . P^T (16x16x32 over the step), and the V operand's eight positions are 16 contiguous bytes of the page.
+// A row's maximum, sum and output stay in the lanes of its column: the running rescale needs no exchange either.
+// Two bf16 terms of q, K, P and V, three MFMAs each.  At the end group 1's results join group 0's through LDS.
+// Bound by a step's chain (copy, scores, softmax, second product: 2 us whatever the model) where workgroups are few, by
+// vector instructions and LDS reads beside the products otherwise.  One workgroup per compute unit, the longest blocks first:
+// a long block's chain is halved and the short ones fill the end.  us per launch against one group of waves per workgroup, two
+// workgroups per unit (V in 8-byte reads, every score masked and scaled): 32 heads of 128, 64 rows 7.3 -> 7.5, 256 18.3 -> 13.5,
+// 640 46.8 -> 27.5, 2041 183 -> 117 (0.88 PFLOP/s with all three products counted); 10 heads, 700 rows 42.5 -> 25; 4 heads of 64, 2000
+// rows 72 -> 35.
+// RT = 2 halves the K and V traffic per row and is used once its blocks are more than the compute units: 32 heads, RT = 1 / 2,
+// 900 rows (256 blocks of 128) 40.5 / 46.2, 1300 rows 77 / 64, 2041 rows 154 / 117.
 template <int HD, int RT>
-__global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
+__global__ void __launch_bounds__(PF_ATT_THREADS, 2) pf_att_kernel(PfArgs a)
 {
     constexpr int KT = HD / 32, NT = HD / 16;
     constexpr int PAGE_B = KV_PAGE * 2 * HD * 2;             // bytes of one (page, head) record of K or of V
@@ -392,8 +400,8 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
     constexpr unsigned STAGE = pf_att_stage(HD);
     constexpr int BR = 64 * RT;
     extern __shared__ __align__(16) char lds[];
-    int *pages = reinterpret_cast<int *>(lds + 2 * STAGE);
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int *pages = reinterpret_cast<int *>(lds + 2 * PF_ATT_GROUPS * STAGE);
+    const int tid = threadIdx.x, lane = tid & 63, grp = __builtin_amdgcn_readfirstlane(tid >> 8), wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
     const int lm = lane & 15, quad = lane >> 4;
     const int n_blk = (a.rows + BR - 1) / BR;
     // heads fastest; the row blocks with the most positions first, so that the short ones fill the end
@@ -401,7 +409,7 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
     const int r0 = blk * BR, nr = min(BR, a.rows - r0);
     const int n_pos = a.pos0 + r0 + nr;
     const int n_pg = (n_pos + KV_PAGE - 1) / KV_PAGE, steps = (n_pg + 1) / 2;
-    for (int i = tid; i < n_pg; i += PF_THREADS) pages[i] = a.contig_base >= 0 ? a.contig_base + i : as_global(a.page_table)[i];
+    for (int i = tid; i < n_pg; i += PF_ATT_THREADS) pages[i] = a.contig_base >= 0 ? a.contig_base + i : as_global(a.page_table)[i];
 
     // q of this wave's rows as MFMA operands
     const int row0 = r0 + wave * 16 * RT;                    // first row of this wave
@@ -418,10 +426,11 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
     wait_vmem();
     __syncthreads();                                         // the page list is there; no load is pending
 
-    // wave w copies K (w even) or V (w odd) of page w >> 1 of a step; K is gathered into operand order
+    // wave w copies K (w even) or V (w odd) of page w >> 1 of its group's step; K is gathered into operand order
     const bool is_v = wave & 1;
     const int src_off = is_v ? lane * 16 : lm * (2 * HD * 2) + quad * 16;
-    const unsigned lds0 = lds_offset(lds);
+    const char *ring = lds + grp * 2 * STAGE;                // this group's two buffers
+    const unsigned lds0 = lds_offset(ring);
     auto request = [&](int step, int buf) __attribute__((always_inline)) {
         const int page = __builtin_amdgcn_readfirstlane(pages[min(2 * step + (wave >> 1), n_pg - 1)]);
         const size_t rec = (((size_t)a.layer * a.n_pages + page) * a.H + head) * PAGE_B;
@@ -431,10 +440,20 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
         for (int f = 0; f < FR; ++f)                          // K: operand (32 values kt, term) = f; V: plain copy
             load_lds_kb(uniform_ptr(src + (is_v ? f * 1024 : (f & 1) * HD * 2 + (f >> 1) * 64)), src_off, dst + f * 1024);
     };
-    request(0, 0);
+    if (grp < steps) request(grp, 0);
+
+    // the score operands' lanes: row lm of operand p is position 8 (lm >> 2) + 4 p + (lm & 3) of the step; V: the lane's eight positions
+    int koff[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int pos = 8 * (lm >> 2) + 4 * p + (lm & 3);
+        koff[p] = (pos / KV_PAGE) * (2 * PAGE_B) + (quad * 16 + pos % KV_PAGE) * 16;
+    }
+    const int voff = PAGE_B + (quad >> 1) * (2 * PAGE_B) + lm * 32 + (quad & 1) * 16;
 
     f32x4_t O[RT][NT];
-    float mx[RT], sum[RT];
+    float mx[RT], sum[RT];                                   // maxima of the scaled scores, times log2(e)
+    const float scale = a.att_scale * 1.44269504f;
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
         mx[t] = ATT_NEG;
@@ -443,21 +462,22 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
         for (int n = 0; n < NT; ++n) O[t][n] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
     const int wave_last = a.pos0 + min(row0 + 16 * RT, a.rows) - 1;   // last position a row of this wave sees
-    for (int step = 0; step < steps; ++step) {
+    for (int round = 0; round * PF_ATT_GROUPS < steps; ++round) {     // (both groups run the same number of rounds)
+        const int step = round * PF_ATT_GROUPS + grp;
         wait_pending<0>();
         lds_barrier();
-        if (step + 1 < steps) request(step + 1, (step + 1) & 1);
-        if (step * 32 > wave_last || row0 >= a.rows) continue;
-        const char *st = lds + (step & 1) * STAGE;
+        if (step + PF_ATT_GROUPS < steps) request(step + PF_ATT_GROUPS, (round + 1) & 1);
+        if (step >= steps || step * 32 > wave_last || row0 >= a.rows) continue;
+        const char *st = ring + (round & 1) * STAGE;
         f32x4_t S[RT][2];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
+        for (int t = 0; t < RT; ++t) S[t][0] = S[t][1] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < RT; ++t) S[t][p] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                const bf16x8_t kh = *reinterpret_cast<const bf16x8_t *>(st + p * 2 * PAGE_B + (2 * kt) * 1024 + lane * 16);
-                const bf16x8_t kl = *reinterpret_cast<const bf16x8_t *>(st + p * 2 * PAGE_B + (2 * kt + 1) * 1024 + lane * 16);
+            for (int p = 0; p < 2; ++p) {
+                const bf16x8_t kh = *reinterpret_cast<const bf16x8_t *>(st + koff[p] + (2 * kt) * 1024);
+                const bf16x8_t kl = *reinterpret_cast<const bf16x8_t *>(st + koff[p] + (2 * kt + 1) * 1024);
 #pragma unroll
                 for (int t = 0; t < RT; ++t) {
                     S[t][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh, qh[t][kt], S[t][p], 0, 0, 0);
@@ -465,22 +485,23 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
                     S[t][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh, ql[t][kt], S[t][p], 0, 0, 0);
                 }
             }
-        }
         bf16x8_t Ph[RT], Pl[RT];
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
-            const int last_pos = a.pos0 + row0 + t * 16 + lm;   // last position this lane's row may see
             float s[8], local = ATT_NEG;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int pos = step * 32 + (e >> 2) * 16 + quad * 4 + (e & 3);
-                s[e] = pos <= last_pos ? S[t][e >> 2][e & 3] * a.att_scale : ATT_NEG;
-                local = fmaxf(local, s[e]);
+            for (int e = 0; e < 8; ++e) s[e] = S[t][e >> 2][e & 3];
+            if (step * 32 + 31 > a.pos0 + row0 + t * 16) {   // (some row of the tile does not see the whole step)
+                const int last = a.pos0 + row0 + t * 16 + lm - step * 32 - quad * 8;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s[e] = e <= last ? s[e] : -INFINITY;   // (weighs nothing, also in a row that sees no position of the step)
             }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) local = fmaxf(local, s[e]);
             local = fmaxf(local, __shfl_xor(local, 16, 64));
-            local = fmaxf(local, __shfl_xor(local, 32, 64));
+            local = fmaxf(local, __shfl_xor(local, 32, 64)) * scale;
             if (__any(local > mx[t])) {
-                const float m_new = fmaxf(mx[t], local), f = __expf(mx[t] - m_new);
+                const float m_new = fmaxf(mx[t], local), f = __builtin_amdgcn_exp2f(mx[t] - m_new);
                 mx[t] = m_new;
                 sum[t] *= f;
 #pragma unroll
@@ -490,19 +511,15 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                s[e] = __expf(s[e] - mx[t]);
+                s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], scale, -mx[t]));
                 sum[t] += s[e];
             }
             split_bf16x8((f32x4_t){s[0], s[1], s[2], s[3]}, (f32x4_t){s[4], s[5], s[6], s[7]}, Ph[t], Pl[t]);
         }
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            // V record: [term][dim][16 positions]; dim n * 16 + lm, positions 4 quad .. + 3 of either page
-            const char *v0 = st + PAGE_B + (n * 16 + lm) * 32 + quad * 8, *v1 = v0 + 2 * PAGE_B;
-            const uint2 h0 = *reinterpret_cast<const uint2 *>(v0), h1 = *reinterpret_cast<const uint2 *>(v1);
-            const uint2 l0 = *reinterpret_cast<const uint2 *>(v0 + HD * 32), l1 = *reinterpret_cast<const uint2 *>(v1 + HD * 32);
-            const bf16x8_t Vh = __builtin_bit_cast(bf16x8_t, make_uint4(h0.x, h0.y, h1.x, h1.y));
-            const bf16x8_t Vl = __builtin_bit_cast(bf16x8_t, make_uint4(l0.x, l0.y, l1.x, l1.y));
+        for (int n = 0; n < NT; ++n) {                       // V record: [term][dim][16 positions]
+            const bf16x8_t Vh = *reinterpret_cast<const bf16x8_t *>(st + voff + n * 512);
+            const bf16x8_t Vl = *reinterpret_cast<const bf16x8_t *>(st + voff + HD * 32 + n * 512);
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
                 O[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Vh, Ph[t], O[t][n], 0, 0, 0);
@@ -511,17 +528,38 @@ __global__ void __launch_bounds__(PF_THREADS, 2) pf_att_kernel(PfArgs a)
             }
         }
     }
+    // group 1's results: [tile of the wave][outputs, maximum and sum][lane].  A row of which it saw no position has the maximum
+    // ATT_NEG there, and weighs nothing (group 0 sees position 0 of every row).
+    lds_barrier();                                           // the last step has been read
+    constexpr int REC = (NT * 4 + 2) * 64;                   // floats of a row tile
+    static_assert(4 * RT * REC * 4 <= 2 * PF_ATT_GROUPS * (int)STAGE, "inside the ring");
+    float *rec = reinterpret_cast<float *>(lds) + wave * RT * REC;
+    if (grp == 1) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            float *w = rec + t * REC;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) *reinterpret_cast<float4 *>(w + (n * 64 + lane) * 4) = make_float4(O[t][n][0], O[t][n][1], O[t][n][2], O[t][n][3]);
+            *reinterpret_cast<float2 *>(w + NT * 256 + lane * 2) = make_float2(mx[t], sum[t]);
+        }
+    }
+    lds_barrier();
+    if (grp == 1) return;
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        float s = sum[t];
+        const float *w = rec + t * REC;
+        const float2 o = *reinterpret_cast<const float2 *>(w + NT * 256 + lane * 2);
+        const float m_all = fmaxf(mx[t], o.x), f0 = __builtin_amdgcn_exp2f(mx[t] - m_all), f1 = __builtin_amdgcn_exp2f(o.x - m_all);
+        float s = sum[t] * f0 + o.y * f1;
         s += __shfl_xor(s, 16, 64);
         s += __shfl_xor(s, 32, 64);
         const int m = row0 + t * 16 + lm;
-        const float inv = 1.0f / s;
+        const float inv = 1.0f / s, c0 = f0 * inv, c1 = f1 * inv;
         if (m < a.rows) {
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
-                const float v[4] = {O[t][n][0] * inv, O[t][n][1] * inv, O[t][n][2] * inv, O[t][n][3] * inv};
+                const float4 x = load_f4(w + (n * 64 + lane) * 4);
+                const float v[4] = {O[t][n][0] * c0 + x.x * c1, O[t][n][1] * c0 + x.y * c1, O[t][n][2] * c0 + x.z * c1, O[t][n][3] * c0 + x.w * c1};
                 pf_store_split4(a.b.attn, a.b.rt, m, head * HD + n * 16 + quad * 4, v);
             }
         }

@@ -1233,8 +1233,8 @@ static int prefill_chunk(ee_session *s, int start, int rows)
         a.ss_in = s->pf_ss[0];
         a.ss_slots = slots;
         gemm(G_QKV, l);
-        const int rt = s->pf_att_opt ? s->pf_att_opt / 64 : (md.H * ((rows + 127) / 128) >= m->nwg ? 2 : 1);
-        hipLaunchKernelGGL(pf_att(md.hd, rt), dim3(md.H * ((rows + 64 * rt - 1) / (64 * rt))), dim3(PF_THREADS),
+        const int rt = s->pf_att_opt ? s->pf_att_opt / 64 : (md.H * ((rows + 127) / 128) > m->nwg ? 2 : 1);
+        hipLaunchKernelGGL(pf_att(md.hd, rt), dim3(md.H * ((rows + 64 * rt - 1) / (64 * rt))), dim3(PF_ATT_THREADS),
                            pf_att_lds(md.hd, s->pages_used), s->stream, a);
         a.gain = md.g_ffn + (size_t)l * md.d;
         a.ss_out = s->pf_ss[1];

@@ -314,6 +314,26 @@ def test_prefill_attention_over_two_chunks(model_dir, hd, att_rows, scatter):
         g.free()
 
 
+@pytest.mark.parametrize("att_rows", [64, 128])
+@pytest.mark.parametrize("n", [17, 32, 33, 64, 65, 97, 160])
+def test_prefill_attention_groups_share_steps(ragged_prompt, model_dir, n, att_rows):
+    """The positions of a block are walked 32 at a time by two groups of waves in turn: one step (the second group has none),
+    an odd and an even number, steps that only some of a tile's rows see, whole blocks behind the second group's last step."""
+    g, toks = ragged_prompt[0], ragged_prompt[1][:n]
+    drafts = ragged_prompt[2]
+    o = eo.Model(f"{model_dir}/gpu_ragged.bin", real="f64")
+    os_, gs = o.session(224), g.session(224, max_gamma=8, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+    gs.ee_session_option(ee.OPT_PREFILL_ATT_ROWS, att_rows)
+    try:
+        first_o, margin = oracle_prefill(os_, toks)
+        check_first_token(gs, gs.ee_prefill(toks), first_o, margin, f"{n} rows, {att_rows} a block")
+        ro = os_.verify(drafts, [1], commit=False, want_logits=True)
+        check_pass(ro, gs.verify_sync(drafts, [1]), gpu_logits(gs, 1), drafts, f"{n} rows, {att_rows} a block")
+        check_two_terms(ro, gpu_logits(gs, 1))
+    finally:
+        gs.free()
+
+
 def test_prefill_tile_table_with_several_groups(model_dir):
     """Workgroups that own more than eight n-tiles (gate/up: 2198 on 220 workgroups, two groups of tiles) with k-tiles that
     are no multiple of eight (10; the down projection 549.5): where a tile lies then depends on the group's offset."""
