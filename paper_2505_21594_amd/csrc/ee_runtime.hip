@@ -735,8 +735,11 @@ extern "C" int ee_model_info(const ee_model *m, ee_model_config *out)
 
 // ------------------------------------------------------------------ sessions
 
-// Splits of the cache's pages per attention unit: enough items to occupy every compute unit
-// (one unit alone pulls a head's cache too slowly), at least one page per split, no more
+// Splits of the cache's pages per attention unit.  Few pages (10 of heads of 64, 5 of 128): one, whose waves take a page
+// each; the exchange and the merge of several cost 1.3 us.  More: enough items to occupy every compute unit
+// (one unit alone pulls a head's cache too slowly), at least two pages per split.  us per launch, 4 rows, one split / one per
+// page / this rule: heads of 64, 2 pages 3.3 / 5.1 / 3.3, 5 pages 4.0 / 5.1 / 4.0, 10 pages 5.2 / 5.8 / 5.2, 12 pages 5.6 / 5.8 / 5.5;
+// 32 heads of 128, 2 pages 4.5 / 6.3 / 4.5, 5 pages 5.8 / 6.3 / 5.8, 7 pages 6.9 / 6.7 / 6.4, 9 pages 8.0 / 7.1 (8 splits) / 6.6.  No more
 // than ATT_TILES pages per wave, and no more items than the leader's partials buffer holds.
 // Returns 0 when the buffer is too small for the context.
 static int attention_splits(const ee_session *lead, int items_cap, int n_sess, int M, int n_pos_max)
@@ -747,7 +750,7 @@ static int attention_splits(const ee_session *lead, int items_cap, int n_sess, i
     const int pages = (n_pos_max + KV_PAGE - 1) / KV_PAGE;
     const int forced = (pages + ATT_TILES * WAVES - 1) / (ATT_TILES * WAVES);
     const int cap = std::min(ATT_MAX_SPLITS, items_cap / std::max(units, 1));
-    int s = std::min(m->nwg / std::max(units, 1), pages);
+    int s = pages * m->cfg.head_dim <= 640 ? 1 : std::min(m->nwg / std::max(units, 1), (pages + 1) / 2);
     if (lead->att_splits_opt > 0) s = lead->att_splits_opt;
     s = std::max(std::max(1, s), forced);
     if (forced > cap) return 0;
