@@ -663,10 +663,11 @@ template <int XC>
 __device__ __forceinline__ void gemm_entry(char *lds)
 {
     typedef unsigned int u32x16_t __attribute__((ext_vector_type(16), aligned(16)));
-    const u32x16_t v = *(const __attribute__((address_space(4))) u32x16_t *)__builtin_amdgcn_kernarg_segment_ptr();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = blockIdx.x;
+    if (wave >= SWAVES) return;   // (the helper waves do not wait for this line before they ask for the others)
+    const u32x16_t v = *(const __attribute__((address_space(4))) u32x16_t *)__builtin_amdgcn_kernarg_segment_ptr();
     const int tile_bytes = v[5], KTs = v[6], nwg = v[7], base = v[8], rem = v[9], tpu = v[10], ksl = v[11];
-    if (wave >= SWAVES || g >= nwg) return;
+    if (g >= nwg) return;
     const int nl = min(GROUP_TILES, (base + ((g >> ksl) < rem ? 1 : 0)) * tpu);
     const int stages = min(ring_depth(XC, nl), wave_ksteps(KTs, wave)), lane16 = (threadIdx.x & 63) * 16;
     const char *wp = reinterpret_cast<const char *>((((unsigned long long)v[1] << 32) | v[0]) + (unsigned)((g * SWAVES + wave) * 1024));
