@@ -337,13 +337,13 @@ int ee_session_option(ee_session *s, int option, int value);
 #define EE_LAUNCH_GU 2      /* gate/up projections + SiLU * up                           */
 #define EE_LAUNCH_DN 3      /* down projection + residual + next norm inputs             */
 #define EE_LAUNCH_HEAD 4    /* exit or final head: norm + LM head + argmax, accept rule,
-                               publication, KV commit                                    */
+                               publication                                               */
 #define EE_LAUNCH_ADAPTER_DOWN 5 /* exit-head adapters: hidden units                     */
 #define EE_LAUNCH_ADAPTER_UP 6   /* exit-head adapters: output + residual + head norm input */
 #define EE_LAUNCH_ATT 8     /* attention over the paged KV cache                         */
 #define EE_LAUNCH_EMBED 7   /* embedding gather                                          */
 #define EE_LAUNCH_SAMPLE 9  /* ee_verify_sampled: keep tests and draws of a head's rows, accept
-                               rule, publication, KV commit                              */
+                               rule, publication                                         */
 int ee_launch_times(ee_session *s, int32_t *codes, float *ms, int max_launches, int *n_launches);
 
 /* Debug: runs one v_mfma_f32_16x16x32_bf16 through the operand lane layout the

@@ -107,15 +107,14 @@ struct ModelDev {
 };
 
 struct SessDev {
-    int *state;                          // [0] kv_len, [1] pending token
     const int *page_table;               // logical page -> physical page
     uint16_t *kpool, *vpool;             // per (layer, page, head) a record of KV_PAGE*2*hd bf16, value = hi + lo:
                                          // K [position][term][hd], V [term][hd][position]
     const float2 *rope;                  // [max_ctx][hd/2] (cos, sin)
     ee_verify_result *result;            // device address of the pinned result block
     int n_pages;
-    int kv_len;                          // positions cached before this pass (host mirror of state[0])
-    int pending;                         // token of row 0 (host mirror of state[1])
+    int kv_len;                          // positions cached before this pass
+    int pending;                         // token of row 0
     int drafts[EE_MAX_M - 1];            // this pass's drafts
     int contig_base;                     // >= 0: logical page i is physical page contig_base + i (no table lookup needed)
 };
@@ -194,7 +193,7 @@ struct PassArgs {
     int head_stage;                      // 1: this segment ends with the head launch (else its exit only deposits its rows)
     int adapter;                         // 1: the exit has adapters (stages AD, AU between the last layer and the head)
     const float *ad_bdown, *ad_bup;      // adapter biases: [A] and [d] (the bottlenecks' output biases summed)
-    int commit, keep_logits;
+    int keep_logits;
     int fuse_accept;                     // the head launch also runs the accept step (in the workgroup that finishes last)
     int att_splits;
     int H, d, Kpad_d;                    // copies of the model descriptor's fields for the attention kernel

@@ -11,7 +11,7 @@
 // Head (z^(l) = LMHead(h^(l)); accept rule of Eq. 2 / Eq. 5; confidence of Eq. 4):
 //   HEAD    x_hat . W_lm^T, * rstd, argmax candidate and softmax denominator per workgroup
 //   ACCEPT  global argmax (lowest id wins ties), confidence, accept length, publication
-//           to pinned host memory, KV commit (run by the head launch's last workgroup).
+//           to pinned host memory (run by the head launch's last workgroup; the host commits).
 // Kernels: ee_gemm_kernel<KIND, XC> for the GEMM kinds (rows <= 8 XC, at most 48),
 // ee_att_kernel, ee_misc_kernel (embedding).
 //
@@ -1248,14 +1248,12 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
     if ((int)threadIdx.x < a.n_heads * a.n_sess) {
         const int hj = div_small(threadIdx.x, a.n_sess), s = threadIdx.x - hj * a.n_sess, head = a.head_idx + hj;
         ee_verify_result *res = EE_SESS(a, s, result);
-        int *state = EE_SESS(a, s, state);
         const int *t = tok + (hj * a.n_sess + s) * M;
         const float *cf = conf + (hj * a.n_sess + s) * M;
         if (a.head_kind == HEAD_PREFILL) {
             int last = t[M - 1];
             res->next_token = last;
             res->device_status = 0;
-            state[1] = last;
         } else {
             const int gamma = M - 1;
             int delta = 0;
@@ -1292,10 +1290,6 @@ __device__ __forceinline__ void accept_stage(const PassArgs &a, char *lds)
                 res->accept_len = delta;
                 res->next_token = t[delta];
                 res->device_status = 0;
-                if (a.commit) {
-                    state[0] = state[0] + delta + 1;
-                    state[1] = t[delta];
-                }
             }
         }
         __threadfence_system();
@@ -1703,14 +1697,6 @@ __global__ void bf16_to_f32_kernel(const uint16_t *__restrict__ src, float *__re
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) dst[i] = bf16_to_f32(src[i]);
-}
-
-__global__ void set_state_kernel(int *state, int kv_len, int pending, int set_kv, int set_pending)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        if (set_kv) state[0] = kv_len;
-        if (set_pending) state[1] = pending;
-    }
 }
 
 // Checks the lane layout of v_mfma_f32_16x16x32_bf16 that the kernels assume:

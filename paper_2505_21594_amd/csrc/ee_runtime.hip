@@ -79,8 +79,7 @@ struct ee_session {
     std::vector<int> free_pages;     // LIFO free list of physical pages
     int pages_used;                  // logical pages mapped
     float2 *rope;
-    // device state and staging
-    int *dev_state;
+    // staging
     float *host_sample;              // pinned staging of a sampled pass: draft distributions, then u, then v (EE_SAMPLING)
     hipStream_t copy_stream;         // uploads of a sampled pass's distributions (EE_SAMPLING)
     hipEvent_t ev_copy;
@@ -110,7 +109,7 @@ struct ee_session {
     std::vector<hipEvent_t> lt_events;   // EE_TIME_LAUNCHES: event pairs around every launch of the pass
     std::vector<int> lt_codes;           // what each timed launch ran (EE_LAUNCH_* code)
     std::vector<void *> allocs;
-    // host mirror of the session state
+    // the session's state
     int kv_len;
     int pending;
     bool has_pending;
@@ -844,7 +843,6 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
     hipLaunchKernelGGL(rope_table_kernel, dim3(max_ctx), dim3(c.head_dim / 2), 0, 0, s->rope, (double)c.rope_base, c.head_dim);
     S_HIP(hipGetLastError());
 
-    S_TRY(dev_alloc(s->allocs, &s->dev_state, 4));
     {
         // prefill: a chunk of up to pf_cap rows at once (pf_gemm_kernel and friends).  Per row 18 d + 4 F bytes and the
         // partial tiles: for 2048 positions 290 MB with the 7B shape (a seventh of the cache of its 32 layers), 15 MB
@@ -969,7 +967,6 @@ static void release_pages(ee_session *s, int keep_positions)
 
 static void fill_sessdev(SessDev &sd, const ee_session *s)
 {
-    sd.state = s->dev_state;
     sd.page_table = s->dev_page_table;
     sd.kpool = s->kpool;
     sd.vpool = s->vpool;
@@ -1175,14 +1172,6 @@ static int finish_flight(ee_session *s)
 
 // ------------------------------------------------------------------ prefill
 
-static int set_device_state(ee_session *s, bool set_kv, bool set_pending)
-{
-    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, s->stream, s->dev_state, s->kv_len, s->pending,
-                       set_kv ? 1 : 0, set_pending ? 1 : 0);
-    HIP_TRY(hipGetLastError());
-    return EE_OK;
-}
-
 // All layers of one prefill chunk of many rows; the chunk's tokens and embedding rows are on the device.
 static int prefill_chunk(ee_session *s, int start, int rows)
 {
@@ -1358,9 +1347,7 @@ extern "C" int ee_prefill_embeds(ee_session *s, const uint16_t *emb_bf16, int n_
         if (first_token) *first_token = s->pending;
     }
     s->has_pending = true;
-    // (not waited for: a pass on this stream comes after it, one led by another session synchronises this stream first.
-    // 1280-wide model, 61 rows and the first round, with a wait here and one before the first chunk: 406 us, without: 397)
-    return set_device_state(s, true, true);
+    return EE_OK;   // (kv_len and pending travel with every launch's arguments: nothing is enqueued behind the wait above)
 }
 
 extern "C" int ee_prefill(ee_session *s, const int32_t *tokens, int n, unsigned flags, int32_t *first_token)
@@ -1569,7 +1556,6 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
     a.M = M;
     a.rows = n_sessions * M;
     a.mode = 0;
-    a.commit = (lead->flags & EE_NO_AUTOCOMMIT) ? 0 : 1;
     if (sp) {
         const size_t np = (size_t)n_sessions * gamma * c.vocab;
         a.sm.probs = lead->dev_sample;
@@ -1847,8 +1833,6 @@ extern "C" int ee_kv_truncate(ee_session *s, int new_len)
     if (new_len < 0 || new_len > s->kv_len) return fail(EE_EINVAL, "ee_kv_truncate: %d not in [0, kv_len=%d]", new_len, s->kv_len);
     s->kv_len = new_len;
     release_pages(s, new_len);
-    if ((rc = set_device_state(s, true, false)) != EE_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(s->stream));
     return EE_OK;
 }
 
@@ -1861,8 +1845,6 @@ extern "C" int ee_set_pending(ee_session *s, int32_t token)
     if (rc != EE_OK) return rc;
     s->pending = token;
     s->has_pending = true;
-    if ((rc = set_device_state(s, false, true)) != EE_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(s->stream));
     return EE_OK;
 }
 

@@ -86,3 +86,12 @@ def test_k_split_tuning_values_are_checked():
     bad = ctypes.c_longlong(0)
     assert lib.ee_debug_div_small(0, d, 2, ctypes.byref(bad)) == ee.EE_EINVAL      # a divisor below 1: refused on the host
     assert lib.ee_debug_div_small(0, None, 2, ctypes.byref(bad)) == ee.EE_EINVAL
+
+
+def test_prefill_enqueues_nothing_behind_its_wait():
+    """ee_prefill is synchronous (ee.h): in its source no call follows the last wait for the session's stream but the
+    error message's.  (Whether a kernel is still pending on return is a race no caller can observe reliably.)"""
+    src = open(os.path.join(ROOT, "paper_2505_21594_amd", "csrc", "ee_runtime.hip")).read()
+    body = re.search(r"^extern \"C\" int ee_prefill_embeds\(.*?^}", src, flags=re.S | re.M).group(0)
+    tail = re.sub(r"//.*", "", body[body.rindex("hipStreamSynchronize(s->stream)"):])
+    assert set(re.findall(r"\b(\w+)\s*\(", tail)) - {"hipStreamSynchronize", "if"} <= {"fail"}
