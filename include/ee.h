@@ -302,8 +302,8 @@ int ee_device_synchronize(int device);
 
 /* Per-session options; the session must have no pass in flight.
    EE_OPT_ATT_SPLITS: parts the cached positions of a head are split into for attention
-     (1..16), 0 = chosen per pass from the context length and the number of compute units
-     (the default).  A value the context or the scratch cannot take is raised / lowered to
+     (1..16), 0 = chosen per pass from the context length, the head size, the sessions' heads and the
+     number of compute units (the default).  A value the context or the scratch cannot take is raised / lowered to
      the nearest that works.
    EE_OPT_SCATTER_PAGES: 1 = hand KV pages out in descending order from the next ee_prefill
      on, so that the pages of a session are not consecutive and every lookup goes through the page

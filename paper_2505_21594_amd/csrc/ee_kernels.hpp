@@ -974,7 +974,8 @@ constexpr size_t att_lds(int hd, int rows) { return (size_t)WAVES * (rows < ATT_
 __device__ __forceinline__ float4 load_f4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
 // Workgroup = (split of the cache's pages, head, session or chunk of up to ATT_ROWS = 16 query
-// rows); the host picks the number of splits so that the workgroups cover the chip.  Wave w takes the pages
+// rows); the host picks the number of splits from the pages, the head size and the items (attention_splits: one where
+// there are few pages, otherwise enough for the workgroups to cover the chip).  Wave w takes the pages
 // pg_lo + w, pg_lo + w + WAVES, ... of the split (16 positions each), both products on the matrix cores:
 //   scores  S[pos][row] = K . q^T     v_mfma_f32_16x16x32_bf16, A = 16 cached positions x 32
 //           values straight from the page (lane l: position l & 15, values (l >> 4) * 8 ..),

@@ -735,11 +735,15 @@ extern "C" int ee_model_info(const ee_model *m, ee_model_config *out)
 // ------------------------------------------------------------------ sessions
 
 // Splits of the cache's pages per attention unit.  Few pages (10 of heads of 64, 5 of 128): one, whose waves take a page
-// each; the exchange and the merge of several cost 1.3 us.  More: enough items to occupy every compute unit
-// (one unit alone pulls a head's cache too slowly), at least two pages per split.  us per launch, 4 rows, one split / one per
-// page / this rule: heads of 64, 2 pages 3.3 / 5.1 / 3.3, 5 pages 4.0 / 5.1 / 4.0, 10 pages 5.2 / 5.8 / 5.2, 12 pages 5.6 / 5.8 / 5.5;
-// 32 heads of 128, 2 pages 4.5 / 6.3 / 4.5, 5 pages 5.8 / 6.3 / 5.8, 7 pages 6.9 / 6.7 / 6.4, 9 pages 8.0 / 7.1 (8 splits) / 6.6.  No more
-// than ATT_TILES pages per wave, and no more items than the leader's partials buffer holds.
+// each; the exchange and the merge of several cost 1.3 us.  Up to 8 pages (one round of the merge) of few heads: one per page, as
+// long as the items cover at most half the compute units.  Otherwise one per two pages, rounded up, or fewer: as many as occupy
+// every compute unit (one unit alone pulls a head's cache too slowly).  No more than ATT_TILES pages per wave, and no more items
+// than the leader's partials buffer holds.  us per launch, one split / one per two pages / one per page (32 heads: at most 8):
+//   4 heads of 64:    5 rows, 8 pages 4.6 / 5.4 / 5.2, 10 pages 5.3 / 5.5 / 6.0, 11 pages 5.5 / 5.5 / 5.9; 16 rows, 10 pages 5.9 / 5.8 / 6.3
+//   10 heads of 128:  5 rows, 5 pages 6.0 / 6.1 / 6.0, 6 pages 6.3 / 6.2 / 6.0, 8 pages 7.1 / 6.3 / 6.0, 9 pages 7.8 / 6.2 / 6.7;
+//                     16 rows, 5 pages 6.6 / 6.9 / 6.7, 6 pages 7.1 / 7.1 / 6.7, 8 pages 8.0 / 7.1 / 6.7, 9 pages 9.0 / 7.0 / 7.7
+//   32 heads of 128:  5 rows, 5 pages 5.9 / 6.4 / 6.3, 6 pages 6.3 / 6.5 / 6.5, 8 pages 7.2 / 6.5 / 6.9, 9 pages 7.9 / 6.6 / 7.0;
+//                     16 rows, 5 pages 6.5 / 7.2 / 7.0, 6 pages 6.9 / 7.1 / 7.2, 8 pages 8.1 / 7.3 / 7.5, 9 pages 8.7 / 7.3 / 7.6
 // Returns 0 when the buffer is too small for the context.
 static int attention_splits(const ee_session *lead, int items_cap, int n_sess, int M, int n_pos_max)
 {
@@ -749,7 +753,11 @@ static int attention_splits(const ee_session *lead, int items_cap, int n_sess, i
     const int pages = (n_pos_max + KV_PAGE - 1) / KV_PAGE;
     const int forced = (pages + ATT_TILES * WAVES - 1) / (ATT_TILES * WAVES);
     const int cap = std::min(ATT_MAX_SPLITS, items_cap / std::max(units, 1));
-    int s = pages * m->cfg.head_dim <= 640 ? 1 : std::min(m->nwg / std::max(units, 1), (pages + 1) / 2);
+    int s = std::min(m->nwg / std::max(units, 1), (pages + 1) / 2);
+    if (pages * m->cfg.head_dim <= 640)
+        s = 1;
+    else if (pages <= 8 && units * pages <= m->nwg / 2)
+        s = pages;
     if (lead->att_splits_opt > 0) s = lead->att_splits_opt;
     s = std::max(std::max(1, s), forced);
     if (forced > cap) return 0;

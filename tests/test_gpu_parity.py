@@ -518,6 +518,16 @@ def test_attention_merge_of_many_splits(tiny_pair, mid_pair, splits, prompt_len)
         _one_round(g, o, prompt, drafts, exits, what=f"{splits} splits of {prompt_len}", options=[(ee.OPT_ATT_SPLITS, splits)])
 
 
+@pytest.mark.parametrize("which,prompt_len", [("tiny", 155), ("tiny", 156), ("mid", 75), ("mid", 76), ("mid", 123), ("mid", 124)])
+def test_attention_splits_chosen_by_the_context(tiny_pair, mid_pair, which, prompt_len):
+    """Five rows that end with 10 and 11 pages of heads of 64, with 5, 6, 8 and 9 of ten heads of 128: either side of the
+    lines of the default choice, one split, one per page, one per two pages (of 11 and 9 pages one has a single page)."""
+    g, o = tiny_pair if which == "tiny" else mid_pair
+    prompt = eegen.prompt_tokens(640 + prompt_len, prompt_len, o.vocab)
+    drafts = eegen.prompt_tokens(641 + prompt_len, 4, o.vocab)
+    _one_round(g, o, prompt, drafts, TINY_EXITS if which == "tiny" else [1, 2], what=f"{which} P={prompt_len}")
+
+
 def test_gamma_extremes_and_page_boundary(tiny_pair):
     """gamma = 1 and gamma = 15 (the most rows of one attention item), prompts that end right
     before, on and after a page boundary."""
