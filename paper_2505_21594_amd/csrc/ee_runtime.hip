@@ -170,7 +170,7 @@ struct PfShape {
 static const PfShape PF_SHAPES[] = {
     EE_PF_SHAPE(8, 4, 1, 0.908, 0.716, 2), EE_PF_SHAPE(4, 4, 1, 0.529, 0.407, 2), EE_PF_SHAPE(4, 2, 1, 0.356, 0.247, 2),
     EE_PF_SHAPE(2, 2, 1, 0.226, 0.186, 3), EE_PF_SHAPE(4, 4, 2, 0.480, 0.462, 1), EE_PF_SHAPE(4, 2, 2, 0.285, 0.300, 1),
-    EE_PF_SHAPE(2, 2, 4, 0.199, 0.222, 1)};
+    EE_PF_SHAPE(2, 2, 4, 0.190, 0.222, 1)};
 
 static pf_kernel_t pf_att(int hd, int rt)
 {
@@ -179,11 +179,15 @@ static pf_kernel_t pf_att(int hd, int rt)
 
 // Shape of the workgroup tile and parts of K of one prefill GEMM: the least estimated time.  The estimate, in us:
 // per k-tile (PfShape) t1 where a workgroup is alone on its compute unit (a chain of latencies), t2 per workgroup
-// where a unit has several (occ fit); 2.9 per launch; a split adds the exchange of the partial tiles (4.8, 0.6
-// per part read one after the other, and the bytes at 3.5 TB/s).  Least-squares fit to every shape with 1 to 8 parts, QKV, O, GU
-// and DN of the 7B shape at 64 to 2041 rows, of the 13B shape at 128 to 1400 and of a 1280-wide model at 61 to 700: its choice is on
-// average 0.8 % above the best measured one, at worst 8 % (the constants before, fitted to fewer: 2.7 %, 28 %; 7B shape, 640
-// rows: output 64 -> 56; 256: down 73 -> 57; 900: down 180 -> 150).
+// where a unit has several (occ fit), and in a last round that gives only some units more than one at least 1.4 t1 (where two share
+// a unit, each is slower than alone); a split adds the exchange of the partial tiles (4, 1 per part read one after the other, and the
+// bytes at 3.5 TB/s).  What is the same for all choices, such as the launch itself, is left out.  Least-squares fit to every shape
+// with 1 to 8 parts, QKV, O, GU and DN of the 7B shape at 64 to 2041 rows, of the 13B shape at 128 to 1400 and of a 1280-wide model at
+// 61 to 700; then the four-group shape's t1 and the exchange set by the splits of few rows that this fit gave away (7B shape, 17 to
+// 64 rows: down 29.2 -> 27.4, with t1 0.199 and 4.8 + 0.6 per part; 65 to 128: output 21.1 -> 20.3; 2048-wide, 193 to 256 rows: down
+// 22.8 -> 20.5, 1281 to 1344: 84 -> 70).  Over 292 GEMMs (six models 256 to 5120 wide, 4 to 25 row counts from 17 to 2041)
+// its choice is on average 1.8 % above the best measured one, at worst 23 % (output of 520 rows of the 7B shape); before the fit it was
+// 2.9 %, 33 % (7B shape, 640 rows: output 66 -> 58; 256: down 65 -> 60; 900: down 189 -> 162).
 struct PfChoice {
     const PfShape *shape;
     int nb, mb, ks;
@@ -212,8 +216,8 @@ static PfChoice pf_choose(const ee_model *m, const GemmPlan &pl, int rows, int f
                 left -= slots;
             }
             f += left <= cu ? s.t1 : std::max(1.4 * s.t1, left / cu * s.t2);
-            double t = 2.9 + f * ((pl.KT + ks - 1) / ks);
-            if (ks > 1) t += 4.8 + 0.6 * ks + (double)part * 8.0 / 3.5e6;
+            double t = f * ((pl.KT + ks - 1) / ks);
+            if (ks > 1) t += 4.0 + ks + (double)part * 8.0 / 3.5e6;
             if (!best.shape || t < best_t) {
                 best = {&s, nb, mb, ks};
                 best_t = t;
