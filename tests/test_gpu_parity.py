@@ -354,6 +354,27 @@ def test_prefill_tile_table_with_several_groups(model_dir):
         g.free()
 
 
+def test_very_wide_matrices(model_dir):
+    """More than 10000 units of columns (vocabulary 170000, FFN 170000: 42 units a workgroup, six and eleven groups of
+    tiles): the many-row kernels, a pass, and sampling over six chunks of a row, against the oracle."""
+    p = f"{model_dir}/gpu_very_wide.bin"
+    cfg = eegen.ModelConfig(n_layers=2, d_model=64, n_heads=1, head_dim=64, d_ffn=170000, vocab=170000, exit_layers=(1,))
+    eegen.write_model(p, cfg, 82, gains="uniform", std=0.03)
+    g, o = ee.Model(p), eo.Model(p, real="f64")
+    toks, drafts = eegen.prompt_tokens(1430, 30, cfg.vocab), eegen.prompt_tokens(1431, 4, cfg.vocab)
+    os_, gs = o.session(64), g.session(64, max_gamma=8, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+    try:
+        first_o, margin = oracle_prefill(os_, toks)
+        check_first_token(gs, gs.ee_prefill(toks), first_o, margin, "very wide")
+        ro = os_.verify(drafts, [1], commit=False, want_logits=True)
+        check_pass(ro, gs.verify_sync(drafts, [1]), gpu_logits(gs, 1), drafts, "very wide")
+        check_two_terms(ro, gpu_logits(gs, 1))
+        sampled_chain(g, o, toks, 4, [1], 1, 0.05, seed=24, what="sampled very wide")
+    finally:
+        gs.free()
+        g.free()
+
+
 def test_prefill_options_are_checked(tiny_pair):
     gs = tiny_pair[0].session(64, max_gamma=4)
     try:
