@@ -549,6 +549,42 @@ def test_attention_splits_chosen_by_the_context(tiny_pair, mid_pair, which, prom
     _one_round(g, o, prompt, drafts, TINY_EXITS if which == "tiny" else [1, 2], what=f"{which} P={prompt_len}")
 
 
+@pytest.mark.parametrize("splits", [0, 2, 3, 9, 16])
+def test_attention_splits_of_a_batch(model_dir, tiny_path, splits):
+    """Several sessions in one pass whose attention runs several splits: by default (0: ten of the longest context's 20
+    pages), few and more than one round of the merge holds; the sessions share the count, so that the shortest (two or three
+    pages) has splits without any.  Three rounds with commit: every one finds the units' counters as the one before left
+    them.  Every session's logits against the oracle in 64 bits, at the bound of two-term operands."""
+    g, o = ee.Model(tiny_path), eo.Model(tiny_path, real="f64")
+    sess, osess = [], []
+    try:
+        for b, n in enumerate((300, 170, 20)):
+            toks = eegen.prompt_tokens(650, n, o.vocab, session=b)
+            gs, os_ = g.session(352, max_gamma=4, flags=ee.KEEP_LOGITS), o.session(352)
+            fo, margin = oracle_prefill(os_, toks)
+            check_first_token(gs, gs.ee_prefill(toks), fo, margin, f"session {b}")
+            sess.append(gs)
+            osess.append(os_)
+        sess[0].ee_session_option(ee.OPT_ATT_SPLITS, splits)
+        for rnd in range(3):
+            drafts = [eegen.corrupt_drafts(oracle_greedy(osess[b], 4), 0.3, o.vocab, 651, rnd, session=b) for b in range(3)]
+            ee.ee_verify_batch(sess, drafts, TINY_EXITS)
+            for b in range(3):
+                sess[b].ee_wait_final()
+                ro = osess[b].verify(drafts[b], TINY_EXITS, want_logits=True)
+                rg = sess[b].final_result()
+                exempt, _ = check_pass(ro, rg, gpu_logits(sess[b], 1), drafts[b], f"{splits} splits round {rnd} session {b}")
+                check_two_terms(ro, gpu_logits(sess[b], 1))
+                if exempt and (rg.accept_len != ro.accept_len or rg.next_token != ro.next_token):
+                    sess[b].ee_kv_truncate(osess[b].kv_len)
+                    sess[b].ee_set_pending(osess[b].pending)
+                assert sess[b].ee_kv_len() == osess[b].kv_len and sess[b].ee_pending() == osess[b].pending
+    finally:
+        for s_ in sess:
+            s_.free()
+        g.free()
+
+
 def test_gamma_extremes_and_page_boundary(tiny_pair):
     """gamma = 1 and gamma = 15 (the most rows of one attention item), prompts that end right
     before, on and after a page boundary."""
