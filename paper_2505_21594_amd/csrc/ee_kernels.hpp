@@ -117,21 +117,22 @@ __device__ __forceinline__ int opaque(int x)
 // the wave has to wait out: about 0.22 us each, eight or more in a row at the start of every
 // launch.  This reads one word of every line at once, so the misses overlap, and returns the
 // argument block through a pointer the compiler cannot trace back, so that none of its own
-// fetches can be scheduled before these.
-template <int LINE, int LINES>
-__device__ __forceinline__ void warm_line(unsigned long long ka)
-{
-    if constexpr (LINE < LINES) {
-        unsigned t;
-        asm volatile("s_load_dword %0, %1, %2" : "=s"(t) : "s"(ka), "n"(LINE * 64) : "memory");
-        warm_line<LINE + 1, LINES>(ka);
-    }
-}
+// fetches can be scheduled before these.  One block of assembly with its wait: the compiler would take the
+// register as free as soon as the loads were issued.
 __device__ __forceinline__ const PassArgs &warmed_arguments()
 {
     unsigned long long ka = reinterpret_cast<unsigned long long>((const void *)__builtin_amdgcn_kernarg_segment_ptr());
-    warm_line<0, (sizeof(PassArgs) + 63 - 4) / 64>(ka);  // last word read lies inside the block
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(ka)::"memory");
+    unsigned word;
+    constexpr int LINES = (sizeof(PassArgs) + 63 - 4) / 64;   // last word read lies inside the block
+    asm volatile(".set ee_line, 0\n\t"
+                 ".rept %2\n\t"
+                 "s_load_dword %0, %1, ee_line\n\t"
+                 ".set ee_line, ee_line + 64\n\t"
+                 ".endr\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(word), "+s"(ka)
+                 : "n"(LINES)
+                 : "memory");
     return *(const PassArgs *)(const __attribute__((address_space(4))) PassArgs *)ka;
 }
 // all vector memory operations of this wave have completed

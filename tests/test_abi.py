@@ -95,3 +95,19 @@ def test_prefill_enqueues_nothing_behind_its_wait():
     body = re.search(r"^extern \"C\" int ee_prefill_embeds\(.*?^}", src, flags=re.S | re.M).group(0)
     tail = re.sub(r"//.*", "", body[body.rindex("hipStreamSynchronize(s->stream)"):])
     assert set(re.findall(r"\b(\w+)\s*\(", tail)) - {"hipStreamSynchronize", "if"} <= {"fail"}
+
+
+def test_inline_loads_wait_in_their_own_block():
+    """The compiler takes the output registers of an inline-assembly load as written at once, and may give an unused one
+    to something else while the load is still on its way: a block that loads into registers ends with its wait.  (Loads
+    straight to LDS write no register.)"""
+    folder = os.path.join(ROOT, "paper_2505_21594_amd", "csrc")
+    blocks = []
+    for name in sorted(os.listdir(folder)):
+        src = re.sub(r"//.*", "", open(os.path.join(folder, name)).read())
+        blocks += re.findall(r"\basm\b(?:\s+volatile)?\s*\(((?:[^()\"]|\"[^\"]*\"|\([^()]*\))*)\)", src)
+    assert len(blocks) > 5
+    for b in blocks:
+        code = "".join(re.findall(r"\"([^\"]*)\"", b.split(":")[0]))
+        if re.search(r"\b(s_load|s_buffer_load|global_load|flat_load|buffer_load|ds_read)(?!_lds)", code):
+            assert "s_waitcnt" in code, code
