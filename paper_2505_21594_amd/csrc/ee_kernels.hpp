@@ -711,8 +711,8 @@ __device__ __forceinline__ void gemm_entry(char *lds)
 // cross-wave sum: there is no barrier in the stream, a wave waits for its own oldest stage, reads it,
 // requests the stage D further on into the same place and multiplies.
 // Weight tiles into NL x MT accumulators, two MFMAs (two input terms) each.
-// Bound by HBM: between the first request (2 us after entry) and the last tile the 7B shape streams at 6.2 to
-// 6.7 TB/s with 5 rows.  With helper waves that copied input blocks for all streaming waves, a barrier of
+// Bound by HBM: between the first request (gemm_entry) and the last tile the 7B shape streams at 6.2 to 6.7 TB/s
+// with 5 rows.  With helper waves that copied input blocks for all streaming waves, a barrier of
 // all waves per block and 8 tiles of every wave in registers instead (us per launch, 5 rows / 40
 // rows): QKV 20.4 / 36.2 -> 19.6 / 27.8, gate/up 31.5 / 43.4 -> 31.2 / 37.8, down 19.4 / 27.6 -> 19.0 / 27.0,
 // LM head 54 / 86 -> 51 / 70.
@@ -1562,11 +1562,11 @@ __device__ __forceinline__ GemmEpi gemm_epi(const PassArgs &a)
     return ep;
 }
 
-// One GEMM of the pass, for rows <= 8 XC.  The kind is a template parameter: a launch's first requests
-// leave after about 200 instructions instead of 700 (every instruction of a launch is executed once, at
-// the speed of instruction-cache misses), and its epilogue holds no other kind's code.  Against one
-// kernel for all kinds, us per launch, 5 rows of the 7B shape: QKV 19.6 -> 18.5, O 10.2 -> 9.1, gate/up
-// 31.2 -> 30.8, down 19.0 -> 18.2, head 51.2 -> 49.8; the smallest model's launches 4.9-6.7 -> 3.8-4.8.
+// One GEMM of the pass, for rows <= 8 XC.  The kind is a template parameter: every instruction of a launch is
+// executed once, at the speed of instruction-cache misses, and neither its start nor its epilogue holds another kind's
+// code.  Against one kernel for all kinds, us per launch, 5 rows of the 7B shape, before the first requests went ahead
+// of everything else (gemm_entry): QKV 19.6 -> 18.5, O 10.2 -> 9.1, gate/up 31.2 -> 30.8, down 19.0 -> 18.2, head
+// 51.2 -> 49.8; the smallest model's launches 4.9-6.7 -> 3.8-4.8.
 template <int KIND, int XC>
 __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value)
 {
