@@ -26,7 +26,7 @@ constexpr int KSPLIT_LOG2 = 2;           // many-row launches: workgroups (1 << 
 // W[nt*16 + (l & 15)][kt*32 + (l >> 4)*8 .. +7]  (1 KB per tile).
 //
 // The N axis is cut into units of `tpu` n-tiles (1, or 2 for a gate/up pair);
-// workgroup g owns a contiguous range of units (`base`, and one more if g < `rem`; see wg_units) for the whole of K, so
+// workgroup g owns a contiguous range of units (`base`, and one more if g < `rem`) for the whole of K, so
 // every output element is complete inside one workgroup.  Its n-tiles are taken in groups
 // of up to GROUP_TILES; streaming wave w owns the k-tiles w, w + SWAVES, w + 2 SWAVES, ...
 // ("k-steps" s = 0, 1, ...) and walks

@@ -269,22 +269,10 @@ __device__ __forceinline__ Misc misc_views(const StageLds &ly, char *lds)
 
 // ------------------------------------------------------------------ weight-stream geometry
 
-// Where workgroup g's units begin, and how many n-tiles it has.  Any order would do for the stream; in memory, tiles of
-// workgroups g and g + 1 lie next to each other, and the many-row GEMMs, whose workgroups read the same k-tiles of several
-// consecutive n-tiles, are faster with those 64 KB apart than 8 (us per launch, units in the order of g / XCD after XCD: 7B
-// shape, 33 rows, O 18.2 / 17.3, down 29.1 / 27.8, 300 rows of the 13B shape, QKV 140.7 / 135.8, down 117 / 113; the other way
-// round at 256 rows of the 7B shape, QKV 69.6 / 72.1, and at 2041, down 291 / 296).  Passes: no difference beyond the noise.
 __device__ __host__ inline void wg_units(const GemmPlan &pl, int g, int &nt0, int &n_local)
 {
-    const int j = g >> pl.ksl, groups = pl.nwg >> pl.ksl;
-    if (groups % NUM_XCD == 0) {
-        // XCD after XCD: behind the groups of the XCDs before and this XCD's earlier ones, of which the first have one unit more
-        const int x = j % NUM_XCD, i = j / NUM_XCD, q = pl.rem / NUM_XCD, qr = pl.rem % NUM_XCD;
-        const int more = q * x + min(x, qr) + min(i, q + (x < qr ? 1 : 0));
-        nt0 = ((x * (groups / NUM_XCD) + i) * pl.base + more) * pl.tpu;
-    } else {
-        nt0 = (j * pl.base + min(j, pl.rem)) * pl.tpu;
-    }
+    const int j = g >> pl.ksl;
+    nt0 = (j * pl.base + (j < pl.rem ? j : pl.rem)) * pl.tpu;
     n_local = g < pl.nwg ? (pl.base + (j < pl.rem ? 1 : 0)) * pl.tpu : 0;  // workgroups past the stage's count own nothing
 }
 
