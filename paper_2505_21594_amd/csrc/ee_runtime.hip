@@ -184,10 +184,10 @@ static pf_kernel_t pf_att(int hd, int rt)
 // bytes at 3.5 TB/s).  What is the same for all choices, such as the launch itself, is left out.  Least-squares fit to every shape
 // with 1 to 8 parts, QKV, O, GU and DN of the 7B shape at 64 to 2041 rows, of the 13B shape at 128 to 1400 and of a 1280-wide model at
 // 61 to 700; then the four-group shape's t1 and the exchange set by the splits of few rows that this fit gave away (7B shape, 17 to
-// 64 rows: down 29.2 -> 27.4, with t1 0.199 and 4.8 + 0.6 per part; 65 to 128: output 21.1 -> 20.3; 2048-wide, 193 to 256 rows: down
-// 22.8 -> 20.5, 1281 to 1344: 84 -> 70).  Over 292 GEMMs (six models 256 to 5120 wide, 4 to 25 row counts from 17 to 2041)
-// its choice is on average 1.8 % above the best measured one, at worst 23 % (output of 520 rows of the 7B shape); before the fit it was
-// 2.9 %, 33 % (7B shape, 640 rows: output 66 -> 58; 256: down 65 -> 60; 900: down 189 -> 162).
+// 64 rows: down 29.4 -> 28.7, with t1 0.199 and 4.8 + 0.6 per part; 65 to 128: output 22.1 -> 21.2; 2048-wide, 193 to 256 rows: down
+// 23.0 -> 20.6, 1281 to 1344: 84 -> 70).  Over 292 GEMMs (six models 256 to 5120 wide, 4 to 25 row counts from 17 to 2041)
+// its choice is on average 2.0 % above the best measured one, at worst 25 % (gate/up of 2041 rows of the smallest model, 2 us); before the
+// fit it was 3.1 %, 34 % (7B shape, 640 rows: output 64 -> 58; 256: down 68 -> 59; 900: down 181 -> 149).
 struct PfChoice {
     const PfShape *shape;
     int nb, mb, ks;
