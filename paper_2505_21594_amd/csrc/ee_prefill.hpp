@@ -90,11 +90,11 @@ constexpr size_t pf_tile_floats(int wn, int wm) { return (size_t)wn * wm * 1024;
 // WN x WM accumulators.  Per k-tile of 32 the stage's W tiles and both terms of the X tiles travel to
 // LDS (1 KB per load instruction, already in operand order: every LDS read is a contiguous
 // kilobyte), NS stages in a ring, one barrier per k-tile.
-// Bound by the matrix cores (busy 50 to 62 % of a launch), by a step's barrier and operand reads beside them, and by a last
+// Bound by the matrix cores (busy 51 to 63 % of a launch), by a step's barrier and operand reads beside them, and by a last
 // round of tiles that leaves part of the chip idle (gate/up of 2041 rows: 1376 tiles on 512 places).  2041 rows, 7B shape, both
 // terms' products counted: gate/up 537 to 581 us (1.27 to 1.37 PFLOP/s), QKV 311 to 335 (1.23 to 1.32), down 288 to 301 (1.22 to
 // 1.28), output projection 121 to 125 (1.10 to 1.13; 256 workgroups, one per unit); the spread is that of machines.  The same
-// rows in chunks of 16 through the streaming kernels: 3 ms per chunk, 486 ms per prompt against 45 ms.
+// rows in chunks of 16 through the streaming kernels: 3 ms per chunk, 486 ms per prompt against 46 ms.
 // With few rows the tiles do not cover the chip and a workgroup alone on its unit needs 0.19 us (2 x 2, four groups of waves)
 // to 0.91 us (8 x 4) per k-tile, mostly a chain of barrier, LDS reads and products: then ks workgroups
 // share a tile, each with a part of K, and GRP groups of four waves share a workgroup's K, group g taking the
@@ -393,7 +393,8 @@ constexpr size_t pf_att_lds(int hd, int n_pages) { return (size_t)2 * PF_ATT_GRO
 // 900 rows (256 blocks of 128) 40.5 / 46.2, 1300 rows 77 / 64, 2041 rows 154 / 117; 40 heads of 128, 769 rows (280 blocks) 39.7 / 40.0,
 // 896 rows 47.8 / 46.7, 1100 rows 68 / 59, 2041 rows 192 / 160.  (32 heads of 64, whose blocks are half the work: 1300 rows 32 / 43,
 // 2041 rows 69 / 72, a line that lies too low for them.)  2041 rows: the matrix cores are busy 38 % of the launch, and 30 % of the LDS
-// cycles are conflicts, between the two pages of a score operand.
+// cycles are conflicts (a score operand's lanes of both pages fall into the same half of the banks, V's lanes of a quad take 16
+// bytes of every 32; not measured apart).
 template <int HD, int RT>
 __global__ void __launch_bounds__(PF_ATT_THREADS, 2) pf_att_kernel(PfArgs a)
 {
