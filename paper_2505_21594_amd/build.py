@@ -3,13 +3,15 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libeeverify.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unused-value", "-Wno-unused-result",
 ]
@@ -26,19 +28,26 @@ def build(force: bool = True, verbose: bool = False) -> str:
         if os.path.getmtime(LIB_PATH) >= max(os.path.getmtime(s) for s in sources()):
             return LIB_PATH
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-o", LIB_PATH,
-           os.path.join(CSRC, "ee_runtime.hip")]
-    if verbose:
-        print(" ".join(cmd))
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    report = check_resources(r.stdout)
+    units = [f for f in sources() if f.endswith(".hip")]
     noise = ("remark:", "packed-fp32-ops", "      |", "[-Rpass-analysis")
-    for line in r.stdout.splitlines():
-        if r.returncode != 0 or (verbose and not any(n in line for n in noise)):
-            print(line)
-    if r.returncode != 0:
-        raise subprocess.CalledProcessError(r.returncode, cmd)
-    for line in report:
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd))
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        for line in r.stdout.splitlines():
+            if r.returncode != 0 or (verbose and not any(n in line for n in noise)):
+                print(line)
+        if r.returncode != 0:
+            raise subprocess.CalledProcessError(r.returncode, cmd)
+        return r.stdout
+
+    with tempfile.TemporaryDirectory() as folder, ThreadPoolExecutor(os.cpu_count() or 1) as pool:
+        objects = [os.path.join(folder, os.path.basename(u) + ".o") for u in units]
+        out = list(pool.map(run, [[hipcc, *HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c", u, "-o", o]
+                                  for u, o in zip(units, objects)]))
+        run([hipcc, "--offload-arch=gfx950", "-shared", "-o", LIB_PATH, *objects])
+    for line in check_resources("\n".join(out)):
         print(line)
     return LIB_PATH
 

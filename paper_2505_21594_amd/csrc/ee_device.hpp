@@ -61,11 +61,41 @@ struct GemmPlan {
 // cross-wave sum ([wave][n-tile of the chunk][row][16] floats, `chunk` n-tiles at a time) and,
 // behind them at zbuf_off, one [row][chunk*16] float tile for the head's logits / the squares of the
 // residual stream.
+// Packed weights: behind them, at corr_off, the group's sums over the weights that the packed form leaves out,
+// [n-tile of the group][row][16] floats, in a place of their own: the helper waves fill it while the rings are in use.
 struct StageLds {
     int chunk;       // n-tiles reduced at a time
     int zbuf_off;
+    int corr_off;
     int misc_off;
 };
+
+// Packed weights: the same tiles in the same slots, a weight in 12 bits instead of 16, nothing lost.  The bf16 weights of a
+// matrix lie in few binades: with its 16 most common neighbouring exponents as a window, sign, mantissa and 4 bits of
+// exponent say all but about one weight in 10000 of a normal distribution.  Those others stand in the tile as the
+// smallest value of the window (code 0), and in a list of the matrix with the difference to what they should be;
+// helper waves add the list's products to the sums while the weights stream (escape_sums).
+// A tile is 64 lanes x 12 bytes: dwords A and B the low bytes of the lane's eight bf16 values, C their variable high bits (sign and
+// upper three exponent bits, PACK_MASK, of pair j rotated left by 4 j).  The window's exponents are moved to 112 .. 127 (a power of two that
+// the epilogue takes back exactly, GemmEntry::wscale): the constant exponent bits are 0111, and unpacking is a byte permute, a rotate and a
+// bit-field insert per pair of weights.
+constexpr int PACK_TILE = 768;
+constexpr int PACK_EXP0 = 112;                   // where the window's smallest exponent is moved to
+constexpr unsigned PACK_CONST = 0x38383838u;     // the constant exponent bits in a bf16's high byte
+constexpr unsigned PACK_MASK = 0x87008700u;      // the variable bits of a pair's high bytes
+constexpr float PACK_CODE0 = 1.0f / 32768.0f;    // what code 0 unpacks to
+__host__ __device__ constexpr int tile_bytes_of(bool packed) { return packed ? PACK_TILE : 1024; }
+
+// A weight that the packed form leaves out: what its column's sum misses per unit of x[k] (in the window's scale), and where.
+struct Escape {
+    float delta;
+    unsigned kn;     // k << 16 | (column & 0xFFFF)
+};
+// A helper wave's part of a group's escapes: the first place is the header (delta: places taken, itself included, as an integer; kn: the
+// part's first column in the group << 8 | the end of its columns), then the escapes.  Parts are multiples of eight places.
+constexpr int ESCAPES_MAX = 63;
+static_assert(sizeof(Escape) == 8, "eight are a scalar load");
+static_assert(GROUP_TILES * 16 < 256, "a column of a group in eight bits");
 
 // Per-row partial results of the workgroups (sums of squares, argmax candidates) are stored [row][SS_LD],
 // one slot per workgroup.
@@ -165,7 +195,9 @@ struct GemmEntry {
     int wstep;                           // bytes from one tile of a wave's sequence to the next
     int tile_bytes;                      // bytes of one k-tile of the input: all rows, both terms
     int KTs, nwg, base, rem, tpu, ksl;   // of the plan
-    int unused[4];
+    const Escape *esc;                   // packed weights: [workgroup][esc_groups][HWAVES][esc_cap]
+    uint16_t esc_groups, esc_cap;        // groups of n-tiles of the busiest workgroup; places of a part
+    float wscale;                        // packed weights: what the sums are multiplied by (a power of two)
 };
 static_assert(sizeof(GemmEntry) == 64, "one line");
 
@@ -207,5 +239,9 @@ struct PassArgs {
     SampleDev sm;
 };
 
+typedef void (*pass_kernel_t)(PassArgs);
+// The kernel of a GEMM kind for so many rows.  Defined per kind in a translation unit of its own (ee_gemm_*.hip): they are compiled side by side.
+template <int KIND>
+pass_kernel_t gemm_kernel_of(int rows, bool packed);
 
 }  // namespace ee

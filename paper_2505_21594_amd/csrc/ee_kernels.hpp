@@ -30,6 +30,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+typedef __attribute__((ext_vector_type(3))) unsigned int u32x3_t;
 
 // Pointers read from descriptors in memory are generic to the compiler, and generic loads go
 // through the flat path, whose completion also counts against the LDS counter: a wait for an
@@ -154,6 +155,22 @@ __device__ __forceinline__ void load_lds_kb(const void *src, int off, unsigned d
                  :
                  : "v"(off), "s"(src), "s"(dst)
                  : "m0", "memory");
+}
+// The same for a packed tile: lane l's 12 bytes at src + off land at dst + 16 l.
+__device__ __forceinline__ void load_lds_packed(const void *src, int off, unsigned dst)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx3 %0, %1"
+                 :
+                 : "v"(off), "s"(src), "s"(dst)
+                 : "m0", "memory");
+}
+template <bool PK>
+__device__ __forceinline__ void load_lds_tile(const void *src, int lane, unsigned dst)
+{
+    if (PK)
+        load_lds_packed(src, lane * 12, dst);
+    else
+        load_lds_kb(src, lane * 16, dst);
 }
 template <int N>
 __device__ __forceinline__ void wait_pending()   // at most N vector memory operations of this wave are pending
@@ -321,28 +338,35 @@ __device__ __forceinline__ void store_split4(uint16_t *x, int rows, int m, int k
 // wave's rows are requested together.  (With the slots of a row apart, as [g][m], these few kilobytes were
 // 64 cache lines per load: as many requests as the whole GEMM input, in front of the weight stream.)
 template <int XC>
-__device__ __forceinline__ void load_rstd(const float *ss, int rows, int d, float eps, float *rstd_lds, int hwave, int lane)
-{
+struct RowFactors {
     f32x4_t v[2 * XC];
+    __device__ __forceinline__ void request(const float *ss, int rows, int hwave, int lane)
+    {
 #pragma unroll
-    for (int i = 0; i < 2 * XC; ++i) {
-        const int m = min(hwave + i * HWAVES, rows - 1);
-        v[i] = *as_global(reinterpret_cast<const f32x4_t *>(ss + (size_t)m * SS_LD + lane * 4));
+        for (int i = 0; i < 2 * XC; ++i) {
+            const int m = min(hwave + i * HWAVES, rows - 1);
+            v[i] = *as_global(reinterpret_cast<const f32x4_t *>(ss + (size_t)m * SS_LD + lane * 4));
+        }
     }
+    __device__ __forceinline__ void finish(int rows, int d, float eps, float *rstd_lds, int hwave, int lane)
+    {
 #pragma unroll
-    for (int i = 0; i < 2 * XC; ++i) {
-        float s = (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+        for (int i = 0; i < 2 * XC; ++i) {
+            float s = (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-        const int m = hwave + i * HWAVES;
-        if (lane == 0 && m < rows) rstd_lds[m] = 1.0f / sqrtf(s / (float)d + eps);
+            for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+            const int m = hwave + i * HWAVES;
+            if (lane == 0 && m < rows) rstd_lds[m] = 1.0f / sqrtf(s / (float)d + eps);
+        }
     }
-}
+};
 
 __device__ __forceinline__ bool cand_better(float v, int i, float bv, int bi)
 {
     return v > bv || (v == bv && i < bi);
 }
+
+__device__ __forceinline__ float4 load_f4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
 struct GemmEpi {           // what the O / DN / AU epilogue produces besides h
     const float *gain_xn;  // gain of the next GEMM input (xn), or nullptr
@@ -356,9 +380,10 @@ struct GemmEpi {           // what the O / DN / AU epilogue produces besides h
 // Epilogue of one chunk of gn n-tiles starting at n-tile nt_first: sum the nsum partial tiles in
 // the slot buffer (the streaming waves', or the K splits' when K is split over workgroups; fixed
 // order), apply the stage's element-wise tail.  All threads.
-template <int KIND>
+// Packed weights: `corr` are the chunk's sums over the escapes, in the slot buffer's order (CORR false: the partial tiles hold them).
+template <int KIND, bool PK, bool CORR>
 __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds &ly, int nt_first,
-                                              int gn, int rows, const GemmEpi &ep, const Misc &mi, char *lds, const int nsum)
+                                              int gn, int rows, const GemmEpi &ep, const Misc &mi, char *lds, const int nsum, const float *corr)
 {
     const ModelDev &md = a.mdv;
     const float *slots = reinterpret_cast<const float *>(lds);
@@ -379,7 +404,15 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
                 G.x += x.x; G.y += x.y; G.z += x.z; G.w += x.w;
                 U.x += y.x; U.y += y.y; U.z += y.z; U.w += y.w;
             }
-            const float rs = mi.rstd[m];
+            float rs = mi.rstd[m];
+            if (PK) {
+                if (CORR) {
+                    const float4 x = load_f4(corr + ((2 * p) * rows + m) * 16 + qd * 4), y = load_f4(corr + ((2 * p + 1) * rows + m) * 16 + qd * 4);
+                    G.x += x.x; G.y += x.y; G.z += x.z; G.w += x.w;
+                    U.x += y.x; U.y += y.y; U.z += y.z; U.w += y.w;
+                }
+                rs *= a.entry.wscale;
+            }
             float g[4] = {G.x * rs, G.y * rs, G.z * rs, G.w * rs}, u[4] = {U.x * rs, U.y * rs, U.z * rs, U.w * rs};
             float o[4];
 #pragma unroll
@@ -424,6 +457,14 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
         for (int w = 0; w < nsum; ++w) {
             float4 x = *reinterpret_cast<const float4 *>(sp + w * wstride);
             S.x += x.x; S.y += x.y; S.z += x.z; S.w += x.w;
+        }
+        if (PK) {
+            if (CORR) {
+                const float4 x = load_f4(corr + idx * 4);
+                S.x += x.x; S.y += x.y; S.z += x.z; S.w += x.w;
+            }
+            const float f = a.entry.wscale;
+            S.x *= f; S.y *= f; S.z *= f; S.w *= f;
         }
         if (KIND == G_AD) {
             // hidden units of the exit head's adapters: silu(W_down . h + b_down)
@@ -570,10 +611,11 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
 }
 
 // K split over workgroups: instead of the epilogue, one chunk of gn n-tiles of this workgroup's
-// partial sums (the streaming waves' tiles added up, fixed order) goes to memory, to
+// partial sums (the streaming waves' tiles added up, fixed order, and packed weights' escapes) goes to memory, to
 // part[split][n-tile][row][16].  All threads.
+template <bool PK>
 __device__ __forceinline__ void partial_store(const PassArgs &a, const GemmPlan &pl, const StageLds &ly, int nt_first, int gn,
-                                              int rows, const char *lds)
+                                              int rows, const char *lds, const float *corr)
 {
     const float *slots = reinterpret_cast<const float *>(lds);
     const int tid = opaque(threadIdx.x);
@@ -589,6 +631,10 @@ __device__ __forceinline__ void partial_store(const PassArgs &a, const GemmPlan 
             float4 x = *reinterpret_cast<const float4 *>(p + w * wstride);
             S.x += x.x; S.y += x.y; S.z += x.z; S.w += x.w;
         }
+        if (PK) {
+            const float4 x = load_f4(corr + idx * 4);
+            S.x += x.x; S.y += x.y; S.z += x.z; S.w += x.w;
+        }
         store_dev128(out, idx * 16, S);
     }
 }
@@ -597,7 +643,7 @@ __device__ __forceinline__ void partial_store(const PassArgs &a, const GemmPlan 
 // counter; the workgroup that arrives last (the counter goes back to zero for the next launch)
 // fetches all splits' partial tiles, chunk by chunk, into the slot buffer in split order and
 // runs the epilogue on them.  The result does not depend on who arrives last; nothing waits.
-template <int KIND>
+template <int KIND, bool PK>
 __device__ __forceinline__ void split_finish(const PassArgs &a, const GemmPlan &pl, const StageLds &ly,
                                              const GemmEpi &ep, const Misc &mi, char *lds, int nt0, int n_local)
 {
@@ -626,7 +672,7 @@ __device__ __forceinline__ void split_finish(const PassArgs &a, const GemmPlan &
                 load_dev128(part, (int)((((size_t)s * pl.NT + nt0 + c0) * rows * 16 + (size_t)rem * 4) * sizeof(float)));
         }
         lds_barrier();
-        gemm_epilogue<KIND>(a, ly, nt0 + c0, gn, rows, ep, mi, lds, ks);
+        gemm_epilogue<KIND, PK, false>(a, ly, nt0 + c0, gn, rows, ep, mi, lds, ks, nullptr);
         lds_barrier();
     }
 }
@@ -655,12 +701,20 @@ constexpr bool ring_depth_ok()
 }
 static_assert(ring_depth_ok(), "as many stages as fit RING_KB, at least one, inside the wave's part of LDS");
 
+// Lane's offset in the last of the XC kilobytes of an input k-tile: lanes past its end (rows that are no multiple of 8) read its last 16
+// bytes again.  What a unit loads is bound by the bytes of its lines.
+template <int XC>
+__device__ __forceinline__ int x_last_offset(int tile_bytes, int lane)
+{
+    return min(lane * 16, tile_bytes - (XC - 1) * 1024 - 16);
+}
+
 // The start of a GEMM launch: every streaming wave requests the stages its ring holds, before anything else is read or
 // worked out.  A launch's instructions come from a cold instruction cache, a line at a time, and its arguments from a
 // cold scalar cache: the code up to these requests is 70 instructions (loops, not unrolled) and needs one line of arguments.
 // With the requests behind the warming of all arguments and the plan's arithmetic, us per launch, 5 rows of the 7B shape: QKV
 // 18.6 -> 18.3, gate/up 30.9 -> 30.0, down 18.1 -> 17.9, head 50.0 -> 49.0; 40 rows, 8 layers, a pass 1390 -> 1372.
-template <int XC>
+template <int XC, bool PK>
 __device__ __forceinline__ void gemm_entry(char *lds)
 {
     typedef unsigned int u32x16_t __attribute__((ext_vector_type(16), aligned(16)));
@@ -670,24 +724,97 @@ __device__ __forceinline__ void gemm_entry(char *lds)
     const int tile_bytes = v[5], KTs = v[6], nwg = v[7], base = v[8], rem = v[9], tpu = v[10], ksl = v[11];
     if (g >= nwg) return;
     const int nl = min(GROUP_TILES, (base + ((g >> ksl) < rem ? 1 : 0)) * tpu);
-    const int stages = min(ring_depth(XC, nl), wave_ksteps(KTs, wave)), lane16 = (threadIdx.x & 63) * 16;
-    const char *wp = reinterpret_cast<const char *>((((unsigned long long)v[1] << 32) | v[0]) + (unsigned)((g * SWAVES + wave) * 1024));
+    const int stages = min(ring_depth(XC, nl), wave_ksteps(KTs, wave)), lane = threadIdx.x & 63;
+    const int x_last = x_last_offset<XC>(tile_bytes, lane);
+    const char *wp = reinterpret_cast<const char *>((((unsigned long long)v[1] << 32) | v[0]) + (unsigned)((g * SWAVES + wave) * tile_bytes_of(PK)));
     const char *xp = reinterpret_cast<const char *>((((unsigned long long)v[3] << 32) | v[2]) + (unsigned)(((g & ((1 << ksl) - 1)) * KTs + wave) * tile_bytes));
     unsigned dst = lds_offset(lds) + wave * (WAVE_LDS_KB * 1024);
 #pragma unroll 1
     for (int s = 0; s < stages; ++s) {
 #pragma unroll 1
         for (int i = 0; i < nl; ++i) {
-            load_lds_kb(wp, lane16, dst);
+            load_lds_tile<PK>(wp, lane, dst);
             wp += (int)v[4];
             dst += 1024;
         }
 #pragma unroll
-        for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, lane16, dst + i * 1024);
+        for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, i == XC - 1 ? x_last : lane * 16, dst + i * 1024);
         dst += XC * 1024;
         xp += SWAVES * tile_bytes;
     }
 }
+
+// A lane's eight weights of a packed tile as an MFMA operand (see PACK_TILE): 11 instructions.
+__device__ __forceinline__ bf16x8_t unpack_tile(u32x3_t p)
+{
+    uint32_t o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t low = __builtin_amdgcn_perm(PACK_CONST, p[j >> 1], j & 1 ? 0x04030402u : 0x04010400u);   // [constant, low byte] x 2
+        const uint32_t var = j ? __builtin_amdgcn_alignbit(p[2], p[2], 4 * j) : p[2];
+        o[j] = (var & PACK_MASK) | (low & ~PACK_MASK);
+    }
+    return __builtin_bit_cast(bf16x8_t, make_uint4(o[0], o[1], o[2], o[3]));
+}
+
+// Packed weights, helper waves: corr[n-tile][row][16] = sum over the group's escapes of delta * x[row][k].  The host has cut
+// the group's escapes (sorted by column, then k; K split over workgroups: those of the slice) into one part per helper wave, at column
+// boundaries: a sum is one wave's, in list order.  Lane = row; the inputs of eight escapes are requested together, the first
+// ones before the wave's other work, whose latencies then overlap.  The escapes themselves come through the scalar cache: a vector load
+// would queue behind the 64 requests of the stream.  A wave has 2 to 13 escapes with normally distributed weights.
+struct EscapeSums {
+    typedef unsigned u32x16_t __attribute__((ext_vector_type(16), aligned(64)));
+    typedef const __attribute__((address_space(4))) u32x16_t *list_t;
+    list_t list;         // the part, eight escapes (the first one is the header) at a time
+    u32x16_t now;
+    const char *xm;      // this lane's row of k-tile 0
+    int rows;
+    uint16_t hi[8], lo[8];
+
+    __device__ __forceinline__ void load_part(const PassArgs &a, int group, int hwave, int lane)
+    {
+        const size_t at = ((size_t)((int)blockIdx.x * a.entry.esc_groups + group) * HWAVES + hwave) * a.entry.esc_cap;
+        list = (list_t)(a.entry.esc + at);
+        now = list[0];
+        rows = a.rows;
+        xm = reinterpret_cast<const char *>(a.entry.X) + min(lane, rows - 1) * 64;
+    }
+    __device__ __forceinline__ void request()
+    {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {   // (a list's unused places name k 0, and the header's place is read as one)
+            const int k = now[2 * j + 1] >> 16;
+            const char *p = xm + (size_t)(k >> 5) * (rows * 128) + (k & 31) * 2;
+            hi[j] = *as_global(reinterpret_cast<const uint16_t *>(p));
+            lo[j] = *as_global(reinterpret_cast<const uint16_t *>(p + rows * 64));
+        }
+    }
+    // the escapes' sums into LDS; n_first is the group's first column
+    __device__ __forceinline__ void finish(int n_first, int lane, float *corr)
+    {
+        const int n = now[0], c1 = now[1] & 0xFFFF;   // header: places taken, itself included; first column << 8 | end of the columns
+        const bool live = lane < rows;
+        for (int c = c1 >> 8; c < (c1 & 0xFF); ++c)
+            if (live) corr[((c >> 4) * rows + lane) * 16 + (c & 15)] = 0.f;
+        float sum = 0.f;
+        int col = -1;
+        for (int j0 = 0; j0 < n; j0 += 8) {
+            if (j0) {
+                now = list[j0 >> 3];
+                request();
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j0 + j > 0 && j0 + j < n) {
+                    const int c = (int)((now[2 * j + 1] - (unsigned)n_first) & 0xFFFF);
+                    if (c != col) sum = 0.f;
+                    col = c;
+                    sum += __uint_as_float(now[2 * j]) * (bf16_to_f32(hi[j]) + bf16_to_f32(lo[j]));
+                    if (live) corr[((c >> 4) * rows + lane) * 16 + (c & 15)] = sum;   // (the last store of a column is its sum)
+                }
+        }
+    }
+};
 
 // One group of NL n-tiles (this workgroup's n-tiles nt_first .. nt_first + NL - 1) over all of K,
 // for rows <= 8 XC (MT = 16-row tiles).
@@ -703,17 +830,20 @@ __device__ __forceinline__ void gemm_entry(char *lds)
 // with 5 rows.  With helper waves that copied input blocks for all streaming waves, a barrier of
 // all waves per block and 8 tiles of every wave in registers instead (us per launch, 5 rows / 40
 // rows): QKV 20.4 / 36.2 -> 19.6 / 27.8, gate/up 31.5 / 43.4 -> 31.2 / 37.8, down 19.4 / 27.6 -> 19.0 / 27.0,
-// LM head 54 / 86 -> 51 / 70.
+// LM head 54 / 86 -> 51 / 70.  Packed weights (PK): three quarters of the bytes, unpacked between LDS and the product by the vector unit that
+// is idle otherwise.  us per launch plain -> packed: 5 rows QKV 18.2 -> 15.1, output 8.8 -> 8.4, gate/up 30.2 -> 24.2, down 17.6 -> 15.5, head 49.2
+// -> 39.8; 16 rows 19.0 -> 18.1, 10.8 -> 10.6, 30.7 -> 25.7, 23.3 -> 21.7, 50.2 -> 42.0; 40 rows (bound by the input's bytes and the LDS passes
+// beside the weights) 26.6 -> 26.0, 15.2 -> 15.2, 37.1 -> 35.6, 25.6 -> 24.8, 60 -> 56.
 //
 // Afterwards the accumulators go through LDS, `ly.chunk` n-tiles at a time, for the
 // cross-wave sum and the stage's epilogue (all waves).
-template <int KIND, int XC, int NL>
+template <int KIND, int XC, int NL, bool PK>
 __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl, const StageLds &ly,
                                            const uint4 *__restrict__ W, const GemmIn &in, const GemmEpi &ep, const Misc &mi,
-                                           char *lds, int nt_first, int seq0, bool first_group)
+                                           char *lds, int nt_first, int seq0, int group)
 {
     constexpr int MT = (XC + 1) / 2, D = ring_depth(XC, NL), PER = NL + XC;
-    constexpr int NW = MT == 3 && NL > 4 ? 4 : NL;   // weight tiles read at a time (registers: three waves per SIMD)
+    constexpr int NW = MT == 3 && NL > 4 ? (PK ? 2 : 4) : NL;   // weight tiles read at a time (registers: three waves per SIMD)
     const ModelDev &md = a.mdv;
     const int tid = opaque(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = a.rows;
@@ -723,22 +853,23 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
         // ---------------- streaming wave
         const int S_w = wave_ksteps(pl.KTs, wave);
         const int lane16 = lane * 16;
-        const size_t wstep = (size_t)pl.nwg * SWAVES * 1024;   // bytes from one tile of the wave's sequence to the next
-        const char *wp = reinterpret_cast<const char *>(W) + (size_t)seq0 * wstep + ((size_t)blockIdx.x * SWAVES + wave) * 1024;
+        const size_t wstep = (size_t)pl.nwg * SWAVES * tile_bytes_of(PK);   // bytes from one tile of the wave's sequence to the next
+        const char *wp = reinterpret_cast<const char *>(W) + (size_t)seq0 * wstep + ((size_t)blockIdx.x * SWAVES + wave) * tile_bytes_of(PK);
         const int tile_bytes = rows * 128;                     // one k-tile of the input: both terms, all rows
+        const int x_last = x_last_offset<XC>(tile_bytes, lane);
         const char *xp = in.x + (size_t)wave * tile_bytes;
         const unsigned ring = lds_offset(lds) + wave * (WAVE_LDS_KB * 1024);
         auto request = [&](unsigned dst) __attribute__((always_inline)) {   // the next stage of the sequence
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
-                load_lds_kb(wp, lane16, dst + i * 1024);
+                load_lds_tile<PK>(wp, lane, dst + i * 1024);
                 wp += wstep;
             }
 #pragma unroll
-            for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, lane16, dst + (NL + i) * 1024);
+            for (int i = 0; i < XC; ++i) load_lds_kb(xp + i * 1024, i == XC - 1 ? x_last : lane16, dst + (NL + i) * 1024);
             xp += SWAVES * tile_bytes;
         };
-        if (first_group) {                                     // (requested at the kernel's start: gemm_entry)
+        if (group == 0) {                                      // (requested at the kernel's start: gemm_entry)
             wp += D * NL * wstep;
             xp += D * SWAVES * tile_bytes;
         } else {
@@ -761,6 +892,7 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
                 wait_pending<0>();
             const char *st = lds + wave * (WAVE_LDS_KB * 1024) + slot * (PER * 1024);
             bf16x8_t w[NW], xh[MT], xl[MT];
+            u32x3_t p[NW];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 xh[mt] = *reinterpret_cast<const bf16x8_t *>(st + NL * 1024 + brow[mt]);
@@ -770,11 +902,21 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
             for (int n0 = 0; n0 < NL; n0 += NW) {
 #pragma unroll
                 for (int i = 0; i < NW; ++i)
-                    if (n0 + i < NL) w[i] = *reinterpret_cast<const bf16x8_t *>(st + (n0 + i) * 1024 + lane16);
+                    if (n0 + i < NL) {
+                        if (PK)
+                            p[i] = *reinterpret_cast<const u32x3_t *>(st + (n0 + i) * 1024 + lane16);
+                        else
+                            w[i] = *reinterpret_cast<const bf16x8_t *>(st + (n0 + i) * 1024 + lane16);
+                    }
                 if (n0 + NW >= NL) {
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read: its place is free
                     if (s + D < S_w) request(ring + slot * (PER * 1024));
                     slot = slot + 1 == D ? 0 : slot + 1;
+                }
+                if (PK) {
+#pragma unroll
+                    for (int i = 0; i < NW; ++i)
+                        if (n0 + i < NL) w[i] = unpack_tile(p[i]);
                 }
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
@@ -787,12 +929,18 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
                 }
             }
         }
-    } else if (first_group) {
+    } else if (PK || group == 0) {
         // ---------------- helper wave: what the epilogue needs, row factors and per-row cache addresses
         const int hwave = wave - SWAVES;
-        if (in.ss) load_rstd<XC>(in.ss, rows, pl.K, md.eps, mi.rstd, hwave, lane);
+        EscapeSums esc;
+        RowFactors<XC> rf;
+        const bool factors = in.ss && group == 0;
+        if (PK) esc.load_part(a, group, hwave, lane);
+        if (factors) rf.request(in.ss, rows, hwave, lane);
+        if (PK) esc.request();
+        if (factors) rf.finish(rows, pl.K, md.eps, mi.rstd, hwave, lane);
         const int ht = tid - SWAVES * 64;
-        if (KIND == G_QKV && ht < rows) {
+        if (KIND == G_QKV && group == 0 && ht < rows) {
             const int m = ht;
             const int pos = row_pos(a, m);
             const int ses = a.mode == 1 ? 0 : div_small(m, a.M);
@@ -801,6 +949,7 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
             mi.pos[m] = pos;
             mi.kvoff[m] = (((long long)a.layer * EE_SESS(a, ses, n_pages) + page) * md.H) * KV_PAGE * 2 * md.hd;  // record of head 0
         }
+        if (PK) esc.finish(nt_first * 16, lane, reinterpret_cast<float *>(lds + ly.corr_off));
         wait_vmem();
     }
     // ---- cross-wave sum and epilogue, ly.chunk n-tiles at a time (the rings are free now)
@@ -823,16 +972,17 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
                 }
         }
         lds_barrier();
+        const float *corr = reinterpret_cast<const float *>(lds + ly.corr_off) + c0 * rows * 16;
         if (MT > 1 && pl.ksl)   // (K is split only for launches of more than one row tile)
-            partial_store(a, pl, ly, nt_first + c0, gn, rows, lds);
+            partial_store<PK>(a, pl, ly, nt_first + c0, gn, rows, lds, corr);
         else
-            gemm_epilogue<KIND>(a, ly, nt_first + c0, gn, rows, ep, mi, lds, SWAVES);
+            gemm_epilogue<KIND, PK, PK>(a, ly, nt_first + c0, gn, rows, ep, mi, lds, SWAVES, corr);
         lds_barrier();
     }
 }
 
 // One GEMM stage of this workgroup: its n-tiles in groups of up to GROUP_TILES.
-template <int KIND, int XC>
+template <int KIND, int XC, bool PK>
 __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, const GemmPlan &pl, const StageLds &ly,
                              const uint4 *__restrict__ W, const GemmIn &in_all, const GemmEpi &ep, char *lds)
 {
@@ -859,16 +1009,15 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, const GemmPlan &
         int seq = 0;  // tiles of a wave's sequence before the group (waves with fewer k-steps leave their slots unused)
         for (int g0 = 0; g0 < n_local; g0 += GROUP_TILES) {
             const int nl = min(GROUP_TILES, n_local - g0);
-            const bool first = g0 == 0;
 #define EE_GROUP(NLV) \
-    case NLV: gemm_group<KIND, XC, NLV>(a, pl, ly, W, in, ep, mi, lds, nt0 + g0, seq, first); break;
+    case NLV: gemm_group<KIND, XC, NLV, PK>(a, pl, ly, W, in, ep, mi, lds, nt0 + g0, seq, g0 / GROUP_TILES); break;
             switch (nl) {
                 EE_GROUP(1) EE_GROUP(2) EE_GROUP(3) EE_GROUP(4) EE_GROUP(5) EE_GROUP(6) EE_GROUP(7) EE_GROUP(8)
             }
 #undef EE_GROUP
             seq += S0 * nl;
         }
-        if (MT > 1 && pl.ksl) split_finish<KIND>(a, pl, ly, ep, mi, lds, nt0, n_local);
+        if (MT > 1 && pl.ksl) split_finish<KIND, PK>(a, pl, ly, ep, mi, lds, nt0, n_local);
     }
     // what the workgroup hands to the following launch
     auto hand_over = [&](int slot, bool mine) __attribute__((always_inline)) {
@@ -959,8 +1108,6 @@ constexpr int att_rec(int hd) { return hd + 4; }
 // ... and of one item's in memory: [ATT_ROWS][hd] outputs, [ATT_ROWS][2] maxima and sums (16-byte accesses without padding)
 constexpr int att_item(int hd) { return ATT_ROWS * (hd + 2); }
 constexpr size_t att_lds(int hd, int rows) { return (size_t)WAVES * (rows < ATT_ROWS ? rows : ATT_ROWS) * att_rec(hd) * sizeof(float) + 16; }
-
-__device__ __forceinline__ float4 load_f4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
 // Workgroup = (split of the cache's pages, head, session or chunk of up to ATT_ROWS = 16 query
 // rows); the host picks the number of splits from the pages, the head size and the items (attention_splits: one where
@@ -1550,18 +1697,18 @@ __device__ __forceinline__ GemmEpi gemm_epi(const PassArgs &a)
     return ep;
 }
 
-// One GEMM of the pass, for rows <= 8 XC.  The kind is a template parameter: every instruction of a launch is
+// One GEMM of the pass, for rows <= 8 XC (gemm_kernel_of gives its address: ee_gemm_*.hip).  The kind is a template parameter: every instruction of a launch is
 // executed once, at the speed of instruction-cache misses, and neither its start nor its epilogue holds another kind's
 // code.  Against one kernel for all kinds, us per launch, 5 rows of the 7B shape, before the first requests went ahead
 // of everything else (gemm_entry): QKV 19.6 -> 18.5, O 10.2 -> 9.1, gate/up 31.2 -> 30.8, down 19.0 -> 18.2, head
 // 51.2 -> 49.8; the smallest model's launches 4.9-6.7 -> 3.8-4.8.
-template <int KIND, int XC>
+template <int KIND, int XC, bool PK>
 __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
-    gemm_entry<XC>(lds);
+    gemm_entry<XC, PK>(lds);
     const PassArgs &a = warmed_arguments();
-    gemm_stage_t<KIND, XC>(a, a.plan0, a.lay, a.entry.W, gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
+    gemm_stage_t<KIND, XC, PK>(a, a.plan0, a.lay, a.entry.W, gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
     if (KIND == G_HEAD && a.fuse_accept) {
         // The workgroup whose candidates arrive last also runs the accept step
         // (one launch less per head); the counter is left at zero.
@@ -1578,156 +1725,12 @@ __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value
     }
 }
 
-// Probabilistic verification: one workgroup per row of the head launch before it (whose logits
-// it reads); the workgroup that finishes last applies the accept rule and publishes, as the
-// head launch's last workgroup does under exact-match verification.
-__global__ void __launch_bounds__(SAMPLE_WAVES * 64) ee_sample_kernel(PassArgs a_by_value)
-{
-    extern __shared__ __align__(16) char lds[];
-    const PassArgs &a = warmed_arguments();
-    sample_stage(a, blockIdx.x, lds);
-    int *lastf = reinterpret_cast<int *>(lds + SAMPLE_LDS_BYTES - 16);   // behind sample_stage's and the accept step's arrays
-    wait_vmem();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int before = __hip_atomic_fetch_add(a.sm.count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *lastf = before == (int)gridDim.x - 1 ? 1 : 0;
-        if (*lastf) __hip_atomic_store(a.sm.count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (*lastf) accept_stage(a, lds);
-}
-
 template <int HD>
 __global__ void __launch_bounds__(WG_THREADS) ee_att_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
     att_stage<HD>(a, lds);
-}
-
-// embedding
-__global__ void __launch_bounds__(WG_THREADS) ee_misc_kernel(PassArgs a_by_value)
-{
-    extern __shared__ __align__(16) char lds[];
-    const PassArgs &a = warmed_arguments();
-    embed_stage(a, lds);
-}
-
-// ------------------------------------------------------------------ load-time kernels
-
-// source row of output column n for the row orders the stages expect
-__device__ __forceinline__ int perm_row(int perm, int n, int d, int hd, int F)
-{
-    if (perm == PERM_QKV) {
-        int sect = n / d, c = n - sect * d;
-        if (sect >= 2) return n;
-        int head = c / hd, e = c - head * hd;
-        int src_e = (e & 1) ? (e >> 1) + (hd >> 1) : (e >> 1);  // RoPE pair (j, j+hd/2) -> columns (2j, 2j+1)
-        return sect * d + head * hd + src_e;
-    }
-    if (perm == PERM_GU) {
-        int tile = n >> 4, r = n & 15;
-        int p = tile >> 1, which = tile & 1;                     // gate tile p, up tile p, gate tile p+1, ...
-        return which * F + p * 16 + r;
-    }
-    return n;
-}
-
-// cos and sin of position blockIdx.x's angle for RoPE pair threadIdx.x, in double
-__global__ void rope_table_kernel(float2 *tab, double base, int hd)
-{
-    const int j = threadIdx.x;
-    const double ang = (double)blockIdx.x * pow(base, -2.0 * (double)j / (double)hd);
-    tab[(size_t)blockIdx.x * blockDim.x + j] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
-// row-major bf16 src[N][K] -> the tiled layout of GemmPlan; block g writes workgroup g's tiles,
-// sub-wave `sub` of the block those of streaming wave w = sub, sub + nsub, ...
-__global__ void tile_weights_kernel(const uint16_t *__restrict__ src, uint4 *__restrict__ dst, GemmPlan pl,
-                                    int perm, int d, int hd, int F)
-{
-    const int g = blockIdx.x;
-    int nt0, n_local;
-    wg_units(pl, g, nt0, n_local);
-    if (n_local == 0) return;
-    const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6, nsub = blockDim.x >> 6;
-    const int S0 = wave_ksteps(pl.KTs, 0);
-    const int kt_first = (g & ((1 << pl.ksl) - 1)) * pl.KTs;   // K split over workgroups: this workgroup's slice
-    for (int w = sub; w < SWAVES; w += nsub) {
-        const int S_w = wave_ksteps(pl.KTs, w);
-        int seq = 0;
-        for (int g0 = 0; g0 < n_local; g0 += GROUP_TILES) {
-            const int nl = min(GROUP_TILES, n_local - g0);
-            for (int s = 0; s < S_w; ++s)
-                for (int nt = 0; nt < nl; ++nt) {
-                    int n = (nt0 + g0 + nt) * 16 + (lane & 15);
-                    int k0 = (kt_first + w + SWAVES * s) * 32 + (lane >> 4) * 8;
-                    uint16_t v[8];
-                    int row = n < pl.N ? perm_row(perm, n, d, hd, F) : -1;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        int k = k0 + e;
-                        v[e] = (row >= 0 && k < pl.K) ? src[(size_t)row * pl.K + k] : (uint16_t)0;
-                    }
-                    uint4 o;
-                    o.x = v[0] | ((uint32_t)v[1] << 16);
-                    o.y = v[2] | ((uint32_t)v[3] << 16);
-                    o.z = v[4] | ((uint32_t)v[5] << 16);
-                    o.w = v[6] | ((uint32_t)v[7] << 16);
-                    const size_t step = (size_t)seq + (size_t)s * nl + nt;
-                    dst[((step * pl.nwg + g) * SWAVES + w) * 64 + lane] = o;
-                }
-            seq += S0 * nl;
-        }
-    }
-}
-
-// counts the x in [0, x_max] with div_small(x, d) != x / d, for every divisor of the list
-__global__ void div_small_check_kernel(const int *__restrict__ divisors, int n_div, int x_max, unsigned long long *bad)
-{
-    unsigned long long mine = 0;
-    for (int j = blockIdx.y; j < n_div; j += gridDim.y) {
-        const int d = divisors[j];
-        for (long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x; x <= x_max; x += (long long)gridDim.x * blockDim.x)
-            mine += div_small((int)x, d) != (int)x / d ? 1 : 0;
-    }
-    if (mine) atomicAdd(bad, mine);
-}
-
-__global__ void bf16_to_f32_kernel(const uint16_t *__restrict__ src, float *__restrict__ dst, int n)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = bf16_to_f32(src[i]);
-}
-
-// Checks the lane layout of v_mfma_f32_16x16x32_bf16 that the kernels assume:
-// A[i][k] from lane (i + 16*(k/8)) element k%8, B[k][j] likewise with j, and
-// D[i][j] in lane (j + 16*(i/4)) element i%4.  out[lane*4 + r] receives D.
-__global__ void mfma_layout_probe_kernel(const uint4 *a, const uint4 *b, float *out)
-{
-    bf16x8_t A = __builtin_bit_cast(bf16x8_t, a[threadIdx.x]);
-    bf16x8_t B = __builtin_bit_cast(bf16x8_t, b[threadIdx.x]);
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc, 0, 0, 0);
-    for (int r = 0; r < 4; ++r) out[threadIdx.x * 4 + r] = acc[r];
-}
-
-// plain copy of n 16-byte words: the reference for what the HBM traffic counters read per byte
-__global__ void __launch_bounds__(256) ee_copy_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) dst[i] = src[i];
-}
-
-// the same for v_mfma_f32_16x16x16bf16_1k: A[i][k] from lane (i + 16*(k/4)) element k%4,
-// B[k][j] likewise with j, D as above
-__global__ void mfma16_layout_probe_kernel(const uint2 *a, const uint2 *b, float *out)
-{
-    s16x4_t A = __builtin_bit_cast(s16x4_t, a[threadIdx.x]);
-    s16x4_t B = __builtin_bit_cast(s16x4_t, b[threadIdx.x]);
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B, acc, 0, 0, 0);
-    for (int r = 0; r < 4; ++r) out[threadIdx.x * 4 + r] = acc[r];
 }
 
 }  // namespace ee

@@ -570,53 +570,11 @@ __global__ void __launch_bounds__(PF_ATT_THREADS, 2) pf_att_kernel(PfArgs a)
     }
 }
 
-// ------------------------------------------------------------------ embedding, last row
-
-__device__ __forceinline__ float pf_block_sum(float s, float *red)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    float t = 0.f;
-    for (int w = 0; w < PF_THREADS / 64; ++w) t += red[w];
-    return t;
-}
-
-// one workgroup per row: h = the token's embedding (or the supplied row), first layer's GEMM input, sum of squares
-__global__ void __launch_bounds__(PF_THREADS) pf_embed_kernel(PfArgs a)
-{
-    __shared__ float red[PF_THREADS / 64];
-    const int m = blockIdx.x, tok = a.tokens[m];
-    const uint16_t *src = tok >= 0 ? a.emb + (size_t)tok * a.d : a.emb_rows + (size_t)m * a.d;
-    float sq = 0.f;
-    for (int c = threadIdx.x * 4; c < a.d; c += PF_THREADS * 4) {
-        const uint2 r = *reinterpret_cast<const uint2 *>(src + c);
-        const float v[4] = {__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xFFFF0000u)};
-        *reinterpret_cast<float4 *>(a.b.h + (size_t)m * a.d + c) = make_float4(v[0], v[1], v[2], v[3]);
-        sq += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-        const float4 g = *reinterpret_cast<const float4 *>(a.gain + c);
-        const float x[4] = {v[0] * g.x, v[1] * g.y, v[2] * g.z, v[3] * g.w};
-        pf_store_split4(a.b.xn, a.b.rt, m, c, x);
-    }
-    sq = pf_block_sum(sq, red);
-    if (threadIdx.x == 0) a.ss_out[m] = sq;
-}
-
-// one workgroup: the chunk's last row as the input of a one-row LM-head launch (xh, sums of squares)
-__global__ void __launch_bounds__(PF_THREADS) pf_last_kernel(PfArgs a, uint16_t *xh, float *ss_h)
-{
-    __shared__ float red[PF_THREADS / 64];
-    const float *h = a.b.h + (size_t)(a.rows - 1) * a.d;
-    float sq = 0.f;
-    for (int c = threadIdx.x * 4; c < a.d; c += PF_THREADS * 4) {
-        const float4 v = *reinterpret_cast<const float4 *>(h + c), g = *reinterpret_cast<const float4 *>(a.gain + c);
-        sq += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        const float x[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
-        store_split4(xh, 1, 0, c, x);
-    }
-    sq = pf_block_sum(sq, red);
-    for (int g = threadIdx.x; g < SS_LD; g += PF_THREADS) ss_h[g] = g == 0 ? sq : 0.f;
-}
+// The address of a GEMM kernel of the chunk; the kernels are in translation units of their own (ee_pf_gemm_*.hip).
+typedef void (*pf_kernel_t)(PfArgs);
+template <int KIND, int WN, int WM, int GRP>
+pf_kernel_t pf_gemm_of();
+// The tile shapes there are: wn, wm, groups (pf_gemm_kernel)
+#define EE_PF_SHAPES(X) X(8, 4, 1) X(4, 4, 1) X(4, 2, 1) X(2, 2, 1) X(4, 4, 2) X(4, 2, 2) X(2, 2, 4)
 
 }  // namespace ee

@@ -12,9 +12,10 @@
 #include <algorithm>
 #include <climits>
 #include <new>
+#include <tuple>
 #include <vector>
 
-#include "ee_prefill.hpp"
+#include "ee_once.hpp"
 
 using namespace ee;
 
@@ -55,6 +56,17 @@ struct ee_model {
     GemmPlan plan[2][G_KINDS];
     const uint4 *w[2][G_KINDS];
     long long wstride[2][G_KINDS];
+    // The same weights packed (PACK_TILE), what launches of up to 48 rows stream: slice l at pk + l * pk_stride (bytes), for the
+    // slices whose `scale` is set; the others, and prefill, take w.
+    struct PackedSlice {
+        size_t esc;                  // first escape in m->escapes
+        int groups, cap;
+        float scale;                 // 0: not packed
+    };
+    unsigned char *pk[2][G_KINDS];
+    size_t pk_stride[2][G_KINDS];
+    std::vector<PackedSlice> packed[2][G_KINDS];
+    const Escape *escapes;           // all matrices' lists
     const int2 *tile_tab[G_KINDS];   // prefill GEMMs: where the tiles of an n-tile lie (PfArgs::tab; trunk kinds only)
     std::vector<void *> allocs;  // every device allocation of the model
     const float *g_exit[EE_MAX_EXITS];
@@ -120,34 +132,16 @@ struct ee_session {
 
 // ------------------------------------------------------------------ planning
 
-typedef void (*pass_kernel_t)(PassArgs);
-
-// A kernel per 8 rows: the kilobytes of a k-tile of the input are compile-time.  With a kernel per 16 rows the odd classes copy
-// one kilobyte per k-tile more: 5 rows 3.01 ms a pass against 2.97, 18 rows 1.091 against 1.060, 40 rows 1.433 against
-// 1.383 (7B shape; the latter two with 8 layers).
-template <int KIND>
-static pass_kernel_t gemm_kernel_of(int rows)
-{
-    switch ((rows + 7) / 8) {
-    case 1: return ee_gemm_kernel<KIND, 1>;
-    case 2: return ee_gemm_kernel<KIND, 2>;
-    case 3: return ee_gemm_kernel<KIND, 3>;
-    case 4: return ee_gemm_kernel<KIND, 4>;
-    case 5: return ee_gemm_kernel<KIND, 5>;
-    default: return ee_gemm_kernel<KIND, 6>;
-    }
-}
-
-static pass_kernel_t gemm_kernel(int kind, int rows)
+static pass_kernel_t gemm_kernel(int kind, int rows, bool packed)
 {
     switch (kind) {
-    case G_QKV: return gemm_kernel_of<G_QKV>(rows);
-    case G_O: return gemm_kernel_of<G_O>(rows);
-    case G_GU: return gemm_kernel_of<G_GU>(rows);
-    case G_DN: return gemm_kernel_of<G_DN>(rows);
-    case G_AD: return gemm_kernel_of<G_AD>(rows);
-    case G_AU: return gemm_kernel_of<G_AU>(rows);
-    default: return gemm_kernel_of<G_HEAD>(rows);
+    case G_QKV: return gemm_kernel_of<G_QKV>(rows, packed);
+    case G_O: return gemm_kernel_of<G_O>(rows, packed);
+    case G_GU: return gemm_kernel_of<G_GU>(rows, packed);
+    case G_DN: return gemm_kernel_of<G_DN>(rows, packed);
+    case G_AD: return gemm_kernel_of<G_AD>(rows, packed);
+    case G_AU: return gemm_kernel_of<G_AU>(rows, packed);
+    default: return gemm_kernel_of<G_HEAD>(rows, packed);
     }
 }
 
@@ -156,7 +150,6 @@ static pass_kernel_t att_kernel(int hd) { return hd == 128 ? ee_att_kernel<128> 
 constexpr size_t PF_PART_FLOATS = (size_t)12 << 20;   // partial tiles of one launch: at most 48 MB
 constexpr int PF_PART_TILES = 4096;
 
-typedef void (*pf_kernel_t)(PfArgs);
 struct PfShape {
     int wn, wm;                  // a wave's accumulators: n-tiles x row tiles (workgroup: twice that each way)
     int grp;                     // groups of four waves that share the workgroup's K
@@ -165,8 +158,8 @@ struct PfShape {
     pf_kernel_t gemm[G_DN + 1];
 };
 #define EE_PF_SHAPE(WN, WM, GRP, T1, T2, OCC)                                                    \
-    {WN, WM, GRP, T1, T2, OCC, {pf_gemm_kernel<G_QKV, WN, WM, GRP>, pf_gemm_kernel<G_O, WN, WM, GRP>, \
-                                pf_gemm_kernel<G_GU, WN, WM, GRP>, pf_gemm_kernel<G_DN, WN, WM, GRP>}}
+    {WN, WM, GRP, T1, T2, OCC, {pf_gemm_of<G_QKV, WN, WM, GRP>(), pf_gemm_of<G_O, WN, WM, GRP>(), \
+                                pf_gemm_of<G_GU, WN, WM, GRP>(), pf_gemm_of<G_DN, WN, WM, GRP>()}}
 static const PfShape PF_SHAPES[] = {
     EE_PF_SHAPE(8, 4, 1, 0.908, 0.716, 2), EE_PF_SHAPE(4, 4, 1, 0.529, 0.407, 2), EE_PF_SHAPE(4, 2, 1, 0.356, 0.247, 2),
     EE_PF_SHAPE(2, 2, 1, 0.226, 0.186, 3), EE_PF_SHAPE(4, 4, 2, 0.480, 0.462, 1), EE_PF_SHAPE(4, 2, 2, 0.285, 0.300, 1),
@@ -281,11 +274,12 @@ static GemmPlan make_plan(int N, int K, int tpu, int nwg_max, int ksl = 0)
 }
 
 // LDS map of one GEMM launch with `rows` rows (see StageLds)
-static bool plan_lds(const GemmPlan &p, int rows, size_t lds_total, StageLds &ly)
+static bool plan_lds(const GemmPlan &p, int rows, size_t lds_total, bool packed, StageLds &ly)
 {
     const size_t misc = (MISC_BYTES + 255) / 256 * 256;
-    if (lds_total < misc + 4096) return false;
-    const size_t avail = (lds_total - misc) / 256 * 256;
+    const size_t corr = packed ? ((size_t)GROUP_TILES * rows * 64 + 255) / 256 * 256 : 0;
+    if (lds_total < misc + corr + 4096) return false;
+    const size_t avail = (lds_total - misc - corr) / 256 * 256;
     memset(&ly, 0, sizeof ly);
     if (avail < (size_t)SWAVES * WAVE_LDS_KB * 1024) return false;
     // cross-wave sum: SWAVES partial tiles plus one logits / squares tile per n-tile of a chunk
@@ -295,7 +289,8 @@ static bool plan_lds(const GemmPlan &p, int rows, size_t lds_total, StageLds &ly
     if (chunk < p.tpu) return false;
     ly.chunk = chunk;
     ly.zbuf_off = (int)((size_t)SWAVES * chunk * rows * 64);
-    ly.misc_off = (int)avail;
+    ly.corr_off = (int)avail;
+    ly.misc_off = (int)(avail + corr);
     return true;
 }
 
@@ -346,6 +341,111 @@ static int upload_gain(const uint16_t *src, int d, uint16_t *tmp, float *dst)
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipDeviceSynchronize());
     return EE_OK;
+}
+
+// Packs one matrix (its rows are in tmp, in file order) into slice `slice` of every variant of its kind, where that pays.
+// A launch's stream gets a quarter shorter, but the helper waves' chain (list, then inputs, then sums) takes 5 us whatever the matrix:
+// with less than 128 KB of weights per compute unit it is what the launch waits for.  us per launch, plain / packed, 5 rows: 1280-wide
+// model QKV (9 MB) 5.3 / 6.4, 2048-wide QKV (25 MB) 7.4 / 8.2, down (22 MB) 9.4 / 9.2, 2560-wide QKV (38 MB) 9.5 / 9.6, gate/up (70 MB)
+// 14.7 / 13.6; 7B shape: output (34 MB) 8.8 / 8.4, down 17.6 / 15.5, QKV 18.2 / 15.1, gate/up 30.2 / 24.2, head 49.2 / 39.8.
+constexpr int PACK_MIN_TILES = 32768;          // 32 MB
+constexpr int PACK_TILES_PER_ESCAPE = 8;       // at most one escape per so many tiles of 512 weights (normally distributed ones: per 20)
+static int pack_slice(ee_model *m, int kind, int perm, size_t slice, size_t n_elems, const uint16_t *tmp, void *work, size_t work_bytes, std::vector<Escape> &lists)
+try {
+    const GemmPlan &p0 = m->plan[0][kind];
+    const int cap = p0.NT * p0.KT / PACK_TILES_PER_ESCAPE;
+    if ((size_t)cap * sizeof(EscapeFound) + 2048 > work_bytes) return fail(EE_EDEVICE, "ee_model_load: packing buffer too small");
+    unsigned *counts = static_cast<unsigned *>(work);                               // [256] exponents, then the escapes found
+    EscapeFound *found = reinterpret_cast<EscapeFound *>(static_cast<char *>(work) + 2048);
+    HIP_TRY(hipMemset(counts, 0, 2048));
+    hipLaunchKernelGGL(exponent_count_kernel, dim3(1024), dim3(256), 0, 0, tmp, n_elems, counts);
+    HIP_TRY(hipGetLastError());
+    unsigned h[256];
+    HIP_TRY(hipMemcpy(h, counts, sizeof h, hipMemcpyDeviceToHost));
+    int base = 1, top = 0;
+    size_t in_base = 0;
+    for (int b = 1; b + 15 < 255; ++b) {
+        size_t in = 0;
+        for (int e = b; e < b + 16; ++e) in += h[e];
+        if (in > in_base) {
+            in_base = in;
+            base = b;
+        }
+    }
+    for (int e = 0; e < 255; ++e)
+        if (h[e]) top = e;
+    // (infinities and NaN are left alone, and so is a window so far off that moving it could overflow a sum)
+    if (n_elems - in_base > (size_t)cap || h[255] || top + PACK_EXP0 - base > 160 || std::abs(PACK_EXP0 - base) > 32) return EE_OK;
+    std::vector<EscapeFound> esc;
+    for (int v = 0; v < 2; ++v) {
+        if (!m->pk[v][kind]) continue;
+        const GemmPlan &pl = m->plan[v][kind];
+        HIP_TRY(hipMemset(counts, 0, 4));
+        hipLaunchKernelGGL(pack_weights_kernel, dim3(pl.nwg), dim3(512), 0, 0, tmp, m->pk[v][kind] + slice * m->pk_stride[v][kind], pl, perm,
+                           m->cfg.d_model, m->cfg.head_dim, m->cfg.d_ffn, base, v == 0 ? found : nullptr, cap, reinterpret_cast<int *>(counts));
+        HIP_TRY(hipGetLastError());
+        if (v == 0) {
+            int n = 0;
+            HIP_TRY(hipMemcpy(&n, counts, sizeof n, hipMemcpyDeviceToHost));
+            if (n > cap) return EE_OK;
+            esc.resize((size_t)n);
+            if (n) HIP_TRY(hipMemcpy(esc.data(), found, (size_t)n * sizeof(EscapeFound), hipMemcpyDeviceToHost));
+        }
+        // by slice of K, column and k; then cut into one part per helper wave of every workgroup and group, at column boundaries
+        const int slice_k = pl.KTs * 32;
+        auto key = [slice_k](const EscapeFound &e) { return std::make_tuple(e.k / slice_k, e.n, e.k); };
+        std::sort(esc.begin(), esc.end(), [&](const EscapeFound &a, const EscapeFound &b) { return key(a) < key(b); });
+        const int groups = (plan_max_local(pl) + GROUP_TILES - 1) / GROUP_TILES;
+        struct Part {
+            int first, end, col0, col1;
+        };
+        std::vector<Part> parts;
+        int most = 0;
+        for (int g = 0; g < pl.nwg; ++g) {
+            int nt0, n_local;
+            wg_units(pl, g, nt0, n_local);
+            for (int gr = 0; gr < groups; ++gr) {
+                const int c0 = (nt0 + std::min(n_local, gr * GROUP_TILES)) * 16, c1 = (nt0 + std::min(n_local, (gr + 1) * GROUP_TILES)) * 16;
+                const int sl = g & ((1 << pl.ksl) - 1);
+                auto at = [&](int col) {
+                    return (int)(std::lower_bound(esc.begin(), esc.end(), std::make_tuple(sl, col, 0), [&](const EscapeFound &e, const std::tuple<int, int, int> &t) { return key(e) < t; }) - esc.begin());
+                };
+                Part p = {at(c0), 0, c0, 0};
+                const int e0 = p.first, e1 = at(c1);
+                for (int w = 1; w <= HWAVES; ++w) {
+                    const int e = e0 + (int)((long long)(e1 - e0) * w / HWAVES);
+                    p.col1 = w < HWAVES && e < e1 ? std::max(p.col0, esc[(size_t)e].n) : (w < HWAVES && e1 == e0 ? c0 + (c1 - c0) * w / HWAVES : c1);
+                    p.end = at(p.col1);
+                    parts.push_back(Part{p.first, p.end, p.col0 - c0, p.col1 - c0});
+                    most = std::max(most, p.end - p.first);
+                    p.first = p.end;
+                    p.col0 = p.col1;
+                }
+            }
+        }
+        if (most > ESCAPES_MAX) return EE_OK;
+        const int cap = (most + 8) & ~7;
+        const size_t at = lists.size();
+        lists.resize(at + parts.size() * (size_t)cap, Escape{0.f, 0});
+        for (size_t i = 0; i < parts.size(); ++i) {
+            const Part &p = parts[i];
+            Escape *t = &lists[at + i * (size_t)cap];
+            const int n = p.end - p.first, places = n + 1;
+            memcpy(&t->delta, &places, 4);
+            t->kn = (unsigned)p.col0 << 8 | (unsigned)p.col1;
+            for (int j = 0; j < n; ++j) {
+                const EscapeFound &e = esc[(size_t)(p.first + j)];
+                const unsigned bits = e.bits << 16;
+                float w;
+                memcpy(&w, &bits, 4);
+                t[1 + j] = Escape{ldexpf(w, PACK_EXP0 - base) - PACK_CODE0, (unsigned)e.k << 16 | ((unsigned)e.n & 0xFFFF)};
+            }
+        }
+        m->packed[v][kind][slice] = {at, groups, cap, ldexpf(1.0f, base - PACK_EXP0)};
+    }
+    return EE_OK;
+} catch (const std::bad_alloc &) {
+    return fail(EE_EDEVICE, "ee_model_load: out of host memory");
 }
 
 // which GEMM kinds get a K-split tile order in models loaded for more than 16 rows, and the splits (ee_tune_k_split)
@@ -546,7 +646,7 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             const GemmPlan &pl = m->plan[v][k];
             if (pl.nwg == 0) continue;
             StageLds ly;
-            if (!plan_lds(pl, max_rows, m->lds_budget, ly)) {
+            if (!plan_lds(pl, max_rows, m->lds_budget, false, ly)) {
                 ee_model_free(m);
                 return fail(EE_EDEVICE, "ee_model_load: max_rows %d needs more LDS than the device's %zu bytes", max_rows, lds_cap);
             }
@@ -571,7 +671,8 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
         }
         std::vector<pass_kernel_t> ks = {att_kernel(64), att_kernel(128), ee_misc_kernel};
         for (int k = 0; k < G_KINDS; ++k)
-            for (int rows = 8; rows <= EE_MAX_ROWS; rows += 8) ks.push_back(gemm_kernel(k, rows));
+            for (int rows = 8; rows <= EE_MAX_ROWS; rows += 8)
+                for (bool packed : {false, true}) ks.push_back(gemm_kernel(k, rows, packed));
         for (pass_kernel_t k : ks) {
             hipError_t fe = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->lds_budget);
@@ -606,8 +707,11 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
     }
     tmp = static_cast<uint16_t *>(tmp_raw);
 
+    void *pack_work = nullptr;
+    size_t pack_work_bytes = 0;
     auto bail = [&](int code) {
         hipFree(tmp_raw);
+        hipFree(pack_work);
         ee_model_free(m);
         return code;
     };
@@ -631,6 +735,38 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             if ((rc = dev_alloc(m->allocs, &wdev[v][k], std::max<size_t>(slices, 1) * (size_t)m->wstride[v][k], true)) != EE_OK) return bail(rc);
             m->w[v][k] = wdev[v][k];
         }
+    // Packed forms.  They come on top of the plain ones, which prefill reads: only where all of them take at most an eighth of the
+    // memory that is free now (so many models as fitted before still fit; 10 GB for the 7B shape, 13 with the K-split order).
+    memset(m->pk, 0, sizeof m->pk);
+    std::vector<Escape> lists;
+    {
+        size_t free_bytes = 0, total_bytes = 0, need = 0;
+        if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
+        bool want[G_KINDS] = {};
+        for (int k = G_QKV; k <= G_HEAD; ++k) {
+            const GemmPlan &p0 = m->plan[0][k];
+            StageLds ly;
+            want[k] = (long long)p0.NT * p0.KT >= PACK_MIN_TILES && p0.K <= 65536;
+            for (int v = 0; v < 2; ++v) {
+                const GemmPlan &pl = m->plan[v][k];
+                if (pl.nwg == 0) continue;
+                want[k] = want[k] && plan_lds(pl, max_rows, m->lds_budget, true, ly);
+                m->pk_stride[v][k] = (size_t)pl.steps * pl.nwg * SWAVES * PACK_TILE;
+                if (want[k]) need += m->pk_stride[v][k] * (k == G_HEAD ? 1 : Lz);
+            }
+            if (want[k]) pack_work_bytes = std::max(pack_work_bytes, (size_t)p0.NT * p0.KT / PACK_TILES_PER_ESCAPE * sizeof(EscapeFound) + 2048);
+        }
+        if (need > free_bytes / 8) pack_work_bytes = 0;
+        if (pack_work_bytes)
+            for (int k = G_QKV; k <= G_HEAD; ++k)
+                for (int v = 0; v < 2; ++v) {
+                    if (!want[k] || m->plan[v][k].nwg == 0) continue;
+                    const size_t slices = k == G_HEAD ? 1 : Lz;
+                    if ((rc = dev_alloc(m->allocs, &m->pk[v][k], slices * m->pk_stride[v][k], true)) != EE_OK) return bail(rc);
+                    m->packed[v][k].assign(slices, ee_model::PackedSlice{0, 0, 0, 0.f});
+                }
+        if (pack_work_bytes && hipMalloc(&pack_work, pack_work_bytes) != hipSuccess) return bail(fail(EE_EDEVICE, "ee_model_load: cannot allocate the packing buffer"));
+    }
     // every variant of a kind from the same upload
     auto tile_all = [&](int kind, int perm, const uint16_t *const *srcs, int n_src, size_t elems_each, size_t slice) {
         for (int v = 0; v < 2; ++v) {
@@ -639,7 +775,7 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
                                        wdev[v][kind] + slice * (size_t)m->wstride[v][kind]);
             if (r != EE_OK) return r;
         }
-        return (int)EE_OK;
+        return m->pk[0][kind] ? pack_slice(m, kind, perm, slice, n_src * elems_each, tmp, pack_work, pack_work_bytes, lists) : (int)EE_OK;
     };
     if ((rc = dev_alloc(m->allocs, &g_attn, Lz * d, false)) != EE_OK) return bail(rc);
     if ((rc = dev_alloc(m->allocs, &g_ffn, Lz * d, false)) != EE_OK) return bail(rc);
@@ -714,11 +850,18 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
         if (hipMemcpy(dev, tab.data(), tab.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess) return bail(fail(EE_EDEVICE, "upload of a tile table failed"));
         m->tile_tab[k] = dev;
     }
+    if (!lists.empty()) {
+        Escape *dev = nullptr;
+        if ((rc = dev_alloc(m->allocs, &dev, lists.size(), false)) != EE_OK) return bail(rc);
+        if (hipMemcpy(dev, lists.data(), lists.size() * sizeof(Escape), hipMemcpyHostToDevice) != hipSuccess) return bail(fail(EE_EDEVICE, "upload of the escapes failed"));
+        m->escapes = dev;
+    }
     md.g_attn = g_attn;
     md.g_ffn = g_ffn;
     md.g_final = g_final_d;
     hipFree(tmp_raw);
-    tmp_raw = nullptr;
+    hipFree(pack_work);
+    tmp_raw = pack_work = nullptr;
     if (hipDeviceSynchronize() != hipSuccess) return bail(fail(EE_EDEVICE, "device error while loading the model"));
     *out = m;
     return EE_OK;
@@ -1090,7 +1233,7 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
         }
         a.fuse_accept = (code == EE_LAUNCH_HEAD && !a.sm.on) ? 1 : 0;
         a.rows = code == EE_LAUNCH_HEAD ? a.head_rows : rows;   // the head launch carries the rows of all exits of its group
-        pass_kernel_t k = gemm ? gemm_kernel(code, a.rows) : (code == EE_LAUNCH_ATT ? att_kernel(m->cfg.head_dim) : ee_misc_kernel);
+        pass_kernel_t k = code == EE_LAUNCH_ATT ? att_kernel(m->cfg.head_dim) : ee_misc_kernel;
         if (gemm) {  // the stage's plan, LDS map and weights travel with the launch
             static_assert(EE_LAUNCH_QKV == G_QKV && EE_LAUNCH_HEAD == G_HEAD && EE_LAUNCH_ADAPTER_DOWN == G_AD && EE_LAUNCH_ADAPTER_UP == G_AU,
                           "launch codes of GEMM stages are their GemmKind");
@@ -1099,9 +1242,20 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             const int v = (a.rows > 16 && m->plan[1][code].nwg > 0 && a.sc.part) ? 1 : 0;
             a.plan0 = m->plan[v][code];
             GemmEntry &en = a.entry;
-            en.W = m->w[v][code] + (size_t)slice * m->wstride[v][code];
+            const bool packed = (size_t)slice < m->packed[v][code].size() && m->packed[v][code][slice].scale != 0.f;
+            k = gemm_kernel(code, a.rows, packed);
+            if (packed) {
+                const ee_model::PackedSlice &ps = m->packed[v][code][slice];
+                en.W = reinterpret_cast<const uint4 *>(m->pk[v][code] + (size_t)slice * m->pk_stride[v][code]);
+                en.esc = m->escapes + ps.esc;
+                en.esc_groups = (uint16_t)ps.groups;
+                en.esc_cap = (uint16_t)ps.cap;
+                en.wscale = ps.scale;
+            } else {
+                en.W = m->w[v][code] + (size_t)slice * m->wstride[v][code];
+            }
             en.X = gemm_input_of(a.sc, code);
-            en.wstep = a.plan0.nwg * SWAVES * 1024;
+            en.wstep = a.plan0.nwg * SWAVES * tile_bytes_of(packed);
             en.tile_bytes = a.rows * 128;
             en.KTs = a.plan0.KTs;
             en.nwg = a.plan0.nwg;
@@ -1109,7 +1263,7 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             en.rem = a.plan0.rem;
             en.tpu = a.plan0.tpu;
             en.ksl = a.plan0.ksl;
-            if (!plan_lds(a.plan0, a.rows, m->lds_budget, a.lay)) return fail(EE_EDEVICE, "no LDS layout for %d rows", a.rows);
+            if (!plan_lds(a.plan0, a.rows, m->lds_budget, packed, a.lay)) return fail(EE_EDEVICE, "no LDS layout for %d rows", a.rows);
         }
         const bool timed = (lead->flags & EE_TIME_LAUNCHES) && a.mode == 0;
         if (timed) {

@@ -1,0 +1,114 @@
+"""Packed weights (12 bits a weight, the rest in lists) against the oracle, which reads the plain ones.
+
+A model as small as the packing rule admits with every kind of matrix above its line, ragged in K (4112 = 128.5 k-tiles) and in
+columns (5003), with weights outside the window of exponents planted where a list or a tile can go wrong."""
+import numpy as np
+import pytest
+
+import eegen
+import paper_2505_21594_amd as ee
+from oracle import oracle as eo
+from tests.parity import check_first_token, check_pass, gpu_logits, oracle_prefill
+from tests.test_gpu_parity import TWO_TERMS, check_two_terms
+
+pytestmark = pytest.mark.gpu
+
+CFG = eegen.ModelConfig(n_layers=2, d_model=4096, n_heads=32, head_dim=128, d_ffn=4112, vocab=5003, exit_layers=(1,))
+
+
+def _bf16(x):
+    return int(eegen.f32_to_bf16(np.array([x]))[0])
+
+
+def _plant(path):
+    t = eegen.open_tensors(path, "r+")
+    rng = np.random.default_rng(5)
+    for name, w in t.items():
+        if w.ndim != 2 or name == "emb":
+            continue
+        N, K = w.shape
+        # outliers at the corners of the matrix and of tiles, on both sides of the groups' and K slices' borders, and anywhere
+        for n, k in [(0, 0), (N - 1, K - 1), (0, K - 1), (N - 1, 0), (15, 31), (16, 32), (N // 2, K // 4 - 1), (N // 2, K // 4)]:
+            w[n, k] = _bf16(-0.75)
+        for n, k in zip(rng.integers(0, N, 60), rng.integers(0, K, 60)):
+            w[n, k] = _bf16(rng.choice([-1.0, 1.0]) * rng.uniform(0.6, 1.5))
+        # one column with more than a batch of eight, neighbours of it with none
+        w[37, rng.permutation(K)[:20]] = _bf16(0.5)
+        # zeros of both signs, the smallest normal and a denormal number, and the window's smallest value's neighbours below
+        w[50, :4] = [0x0000, 0x8000, 0x0080, 0x0003]
+        w[rng.integers(0, N, 80), rng.integers(0, K, 80)] = 0
+    t["l2.wd"][::5] = 0       # far too many: this matrix stays plain, those beside it do not
+
+
+@pytest.fixture(scope="module")
+def pair(model_dir):
+    p = f"{model_dir}/gpu_packed.bin"
+    eegen.write_model(p, CFG, 77, gains="uniform")
+    _plant(p)
+    g, o = ee.Model(p, max_rows=48), eo.Model(p)
+    yield g, o
+    g.free()
+
+
+# rows 2, 5, 8, 9, 16 in one session; 18, 25, 40, 48 over several (K split over workgroups; the last part of every kilobyte count)
+@pytest.mark.parametrize("B,gamma", [(1, 1), (1, 4), (1, 7), (1, 8), (1, 15), (3, 5), (5, 4), (8, 4), (6, 7)])
+def test_packed_pass(pair, B, gamma):
+    """Logits of every head within the two-term bound (check_two_terms: 10 units a layer, two layers and the head: 1.0e-5 by its
+    count, the bound is for four), tokens and accept lengths as everywhere; the same pass again gives the same bits.  An outlier missed or
+    counted twice moves its column by 0.6 to 1.5 of an input, 3e-3 of the logits and more."""
+    g, o = pair
+    sess, osess = [], []
+    try:
+        for b in range(B):
+            toks = eegen.prompt_tokens(900, 7 + 3 * b, o.vocab, session=b)
+            gs = g.session(64, max_gamma=gamma, flags=ee.NO_AUTOCOMMIT | (ee.KEEP_LOGITS if b == 0 else 0))
+            os_ = o.session(64)
+            fo, margin = oracle_prefill(os_, toks)
+            check_first_token(gs, gs.ee_prefill(toks), fo, margin, f"packed B={B} session {b}")
+            sess.append(gs)
+            osess.append(os_)
+        drafts = [eegen.prompt_tokens(901, gamma, o.vocab, session=b) for b in range(B)]
+        seen = []
+        for again in range(2):
+            ee.ee_verify_batch(sess, drafts, [1])
+            for s in sess:
+                s.ee_wait_final()
+            seen.append([s.ee_debug_logits(e).view(np.uint32) for s in sess for e in range(2)])
+        assert all(np.array_equal(x, y) for x, y in zip(*seen))
+        for b in range(B):
+            ro = osess[b].verify(drafts[b], [1], commit=False, want_logits=True)
+            z = gpu_logits(sess[b], 1)
+            check_pass(ro, sess[b].final_result(), z, drafts[b], f"packed B={B} gamma={gamma} session {b}")
+            check_two_terms(ro, z)
+    finally:
+        for s in sess:
+            s.free()
+
+
+@pytest.mark.parametrize("name", ["l1.wq", "l2.wo", "l1.wu", "l1.wd", "w_lm"])
+def test_one_outlier_is_seen(pair, model_dir, name):
+    """A mistake planted in the oracle: without one of a matrix's outliers its logits are far outside the bound, so the test
+    above sees a single escape that is lost."""
+    g, _ = pair
+    p = f"{model_dir}/gpu_packed.bin"
+    t = eegen.open_tensors(p, "r+")[name]
+    n, kept = 0, int(t[0, 0])
+    assert abs(float(eegen.bf16_to_f32(t[0, :1])[0])) == 0.75
+    toks, drafts = eegen.prompt_tokens(902, 9, CFG.vocab), eegen.prompt_tokens(903, 4, CFG.vocab)
+    gs = g.session(64, max_gamma=4, flags=ee.NO_AUTOCOMMIT | ee.KEEP_LOGITS)
+    try:
+        first = gs.ee_prefill(toks)
+        gs.verify_sync(drafts, [1])
+        z = np.stack(gpu_logits(gs, 1)).astype(np.float64)
+        t[n, 0] = 0
+        o = eo.Model(p)
+        os_ = o.session(64)
+        os_.prefill(toks, flags=eo.HOLD_LAST)
+        # the same rows as the GPU's pass: the prompt's last token, then what it took as pending and the drafts
+        os_.verify([(first + 1) % CFG.vocab], commit=True)
+        os_.set_pending(first)
+        ro = os_.verify(drafts, [1], commit=False, want_logits=True)
+        assert np.linalg.norm(z - ro.logits) / np.linalg.norm(ro.logits) > 10 * TWO_TERMS
+    finally:
+        t[n, 0] = kept
+        gs.free()
