@@ -227,7 +227,8 @@ struct PassArgs {
     const float *ad_bdown, *ad_bup;      // adapter biases: [A] and [d] (the bottlenecks' output biases summed)
     int keep_logits;
     int fuse_accept;                     // the head launch also runs the accept step (in the workgroup that finishes last)
-    int att_splits;
+    int att_splits;                      // splits of the position range (of the session with the most pages)
+    int att_pages;                       // > 0: pages a split, sessions with fewer pages have fewer splits; 0: all have att_splits
     int H, d, Kpad_d;                    // copies of the model descriptor's fields for the attention kernel
     float att_scale;
     int layer;                           // layer of this launch's stage

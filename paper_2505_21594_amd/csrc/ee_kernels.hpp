@@ -1109,8 +1109,9 @@ constexpr int att_rec(int hd) { return hd + 4; }
 constexpr int att_item(int hd) { return ATT_ROWS * (hd + 2); }
 constexpr size_t att_lds(int hd, int rows) { return (size_t)WAVES * (rows < ATT_ROWS ? rows : ATT_ROWS) * att_rec(hd) * sizeof(float) + 16; }
 
-// Workgroup = (split of the cache's pages, head, session or chunk of up to ATT_ROWS = 16 query
-// rows); the host picks the number of splits from the pages, the head size and the items (attention_splits: one where
+// Workgroup = (head, split of the cache's pages, session or chunk of up to ATT_ROWS = 16 query
+// rows); heads vary fastest, so that the XCDs, which workgroups are dealt to in turn, get equal shares of a batch whose sessions have
+// different numbers of splits (splits fastest: the third of three sessions began 10 us late, on two XCDs that had the others' work too); the host picks the number of splits from the pages, the head size and the items (attention_splits: one where
 // there are few pages, otherwise enough for the workgroups to cover the chip).  Wave w takes the pages
 // pg_lo + w, pg_lo + w + WAVES, ... of the split (16 positions each), both products on the matrix cores:
 //   scores  S[pos][row] = K . q^T     v_mfma_f32_16x16x32_bf16, A = 16 cached positions x 32
@@ -1140,11 +1141,13 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
     constexpr int REC = att_rec(HD);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, quad = lane >> 4;
-    const int sp = blockIdx.x, hh = blockIdx.y, n_splits = a.att_splits, M = a.M;
+    const int hh = blockIdx.x, sp = blockIdx.y, M = a.M;
     const int s = a.mode == 1 ? 0 : blockIdx.z, ch = a.mode == 1 ? blockIdx.z : 0;
     const int r0 = ch * ATT_ROWS, nr = min(ATT_ROWS, M - r0);
     const int P = a.mode == 1 ? a.pf_pos0 : EE_SESS(a, s, kv_len);  // position of the first row
     const int n_pg = (P + r0 + nr + KV_PAGE - 1) / KV_PAGE;         // pages visible to the chunk's last row
+    const int n_splits = a.att_pages ? min(a.att_splits, div_small(n_pg + a.att_pages - 1, a.att_pages)) : a.att_splits;
+    if (sp >= n_splits) return;                                     // (a session with fewer pages than the longest one)
     const int pg_lo = div_small(n_pg * sp, n_splits), pg_hi = div_small(n_pg * (sp + 1), n_splits);
     const int cbase = EE_SESS(a, s, contig_base), n_pages = EE_SESS(a, s, n_pages);
     const int *page_table = EE_SESS(a, s, page_table);
@@ -1281,7 +1284,7 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
     }
     if (n_splits > 1) {
         const int unit = blockIdx.z * a.H + hh;
-        const WRes part = buffer_resource(a.sc.att_part + (size_t)unit * n_splits * att_item(HD));
+        const WRes part = buffer_resource(a.sc.att_part + (size_t)unit * a.att_splits * att_item(HD));
         constexpr int SP_BYTES = att_item(HD) * 4, MS = ATT_ROWS * HD * 4;
         if (mine) {
             store_dev128(part, sp * SP_BYTES + (i * HD + e) * 4, num);

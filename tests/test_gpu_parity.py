@@ -585,6 +585,36 @@ def test_attention_splits_of_a_batch(model_dir, tiny_path, splits):
         g.free()
 
 
+# the longest session first, last and in the middle; sessions of one page and at the lines of a page; heads of 64 and of 128
+@pytest.mark.parametrize("which,lens", [("tiny", (9, 330)), ("tiny", (170, 300, 11, 28)), ("mid", (260, 90, 5)), ("mid", (75, 76, 300)), ("mid", (330, 330))])
+def test_attention_splits_follow_each_session(tiny_pair, mid_pair, which, lens):
+    """A batch whose sessions have different contexts: every one has the splits its own pages ask for.  Two rounds, the second finds the
+    units' counters as the first left them; every session's logits against the oracle at the bound of two-term operands."""
+    g, o = tiny_pair if which == "tiny" else mid_pair
+    exits, gamma = (TINY_EXITS, 3) if which == "tiny" else ([1, 2], 3)
+    sess, osess = [], []
+    try:
+        for b, n in enumerate(lens):
+            toks = eegen.prompt_tokens(660, n, o.vocab, session=b)
+            gs, os_ = g.session(352, max_gamma=gamma, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT), o.session(352)
+            fo, margin = oracle_prefill(os_, toks)
+            check_first_token(gs, gs.ee_prefill(toks), fo, margin, f"session {b}")
+            sess.append(gs)
+            osess.append(os_)
+        for rnd in range(2):
+            drafts = [eegen.prompt_tokens(661 + rnd, gamma, o.vocab, session=b) for b in range(len(lens))]
+            ee.ee_verify_batch(sess, drafts, exits)
+            for s_ in sess:
+                s_.ee_wait_final()
+            for b in range(len(lens)):
+                ro = osess[b].verify(drafts[b], exits, commit=False, want_logits=True)
+                check_pass(ro, sess[b].final_result(), gpu_logits(sess[b], len(exits)), drafts[b], f"{lens} round {rnd} session {b}")
+                check_two_terms(ro, gpu_logits(sess[b], len(exits)))
+    finally:
+        for s_ in sess:
+            s_.free()
+
+
 def test_gamma_extremes_and_page_boundary(tiny_pair):
     """gamma = 1 and gamma = 15 (the most rows of one attention item), prompts that end right
     before, on and after a page boundary."""
