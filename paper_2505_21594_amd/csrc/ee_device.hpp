@@ -159,8 +159,9 @@ struct Scratch {
                          // of all exits that share one launch of the head, exit after exit
     uint16_t *attn;      // [Kpad_d/32][2][rows][32]  attention output
     uint16_t *u;         // [Kpad_F/32][2][rows][32]  silu(gate)*up
-    uint16_t *xa;        // [Kpad_d/32][2][rows][32]  h itself: input of an exit head's adapters
-    uint16_t *t;         // [Kpad_A/32][2][rows][32]  the adapters' hidden units after the activation
+    uint16_t *xa;        // [Kpad_d/32][2][rows][32]  h itself: input of an exit head's adapters (exit after exit where they share a launch)
+    uint16_t *t;         // [Kpad_A/32][2][rows][32]  the adapters' hidden units after the activation (exit after exit)
+    float *ha;           // [rows_max][d]        h after the layers of the exits whose adapters share a launch, or nullptr
     float *ss_h;         // [rows_max][SS_LD]        partial sums of squares of the LM-head input's rows (head rows)
     float *ss_a;         // [rows_max][SS_LD]        partial sums of h^2 after the FFN block / embedding
     float *ss_f;         // [rows_max][SS_LD]        partial sums of h^2 after the attention block
@@ -195,9 +196,17 @@ struct GemmEntry {
     int wstep;                           // bytes from one tile of a wave's sequence to the next
     int tile_bytes;                      // bytes of one k-tile of the input: all rows, both terms
     int KTs, nwg, base, rem, tpu, ksl;   // of the plan
-    const Escape *esc;                   // packed weights: [workgroup][esc_groups][HWAVES][esc_cap]
-    uint16_t esc_groups, esc_cap;        // groups of n-tiles of the busiest workgroup; places of a part
-    float wscale;                        // packed weights: what the sums are multiplied by (a power of two)
+    union {
+        struct {
+            const Escape *esc;           // packed weights: [workgroup][esc_groups][HWAVES][esc_cap]
+            uint16_t esc_groups, esc_cap; // groups of n-tiles of the busiest workgroup; places of a part
+            float wscale;                // packed weights: what the sums are multiplied by (a power of two)
+        };
+        struct {
+            long long w_next;            // adapters of several exits in one launch (blockIdx.y): bytes from one exit's weights
+            int x_next, unused;          // and input to the next one's
+        };
+    };
 };
 static_assert(sizeof(GemmEntry) == 64, "one line");
 
@@ -225,6 +234,7 @@ struct PassArgs {
     int head_stage;                      // 1: this segment ends with the head launch (else its exit only deposits its rows)
     int adapter;                         // 1: the exit has adapters (stages AD, AU between the last layer and the head)
     const float *ad_bdown, *ad_bup;      // adapter biases: [A] and [d] (the bottlenecks' output biases summed)
+    const float *ad_gain;                // (host) gain of the head behind the adapters: the exit's, or the group's first exit's
     int keep_logits;
     int fuse_accept;                     // the head launch also runs the accept step (in the workgroup that finishes last)
     int att_splits;                      // splits of the position range (of the session with the most pages)
@@ -234,6 +244,8 @@ struct PassArgs {
     int layer;                           // layer of this launch's stage
     const float *gain_xn, *gain_xh;      // O, DN: gain of the next GEMM input; DN, AU: gain of the LM head's input (each may be null)
     const float *bias;                   // AD, AU: bias per output column
+    int t_next, bias_next, gain_next;    // AD, AU of several exits: elements of t, biases and gains from one exit to the next
+    float *ha;                           // adapters of several exits: [head rows][d] h after each exit's layer (DN writes, AU reads), or nullptr
     int xa_out;                          // DN: also emit h itself as the adapters' input
     const SessDev *sess;                 // device array [n_sess] (passes of several sessions only)
     SessDev sess0;                       // session 0: a pass of one session needs nothing but its launch arguments

@@ -368,6 +368,13 @@ __device__ __forceinline__ bool cand_better(float v, int i, float bv, int bi)
 
 __device__ __forceinline__ float4 load_f4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
+// Adapters of several exits in one launch: which of them this workgroup works for.
+template <int KIND>
+__device__ __forceinline__ int exit_of()
+{
+    return KIND == G_AD || KIND == G_AU ? (int)blockIdx.y : 0;
+}
+
 struct GemmEpi {           // what the O / DN / AU epilogue produces besides h
     const float *gain_xn;  // gain of the next GEMM input (xn), or nullptr
     const float *gain_xh;  // gain of the LM-head input (xh, at the exit's head rows), or nullptr
@@ -389,6 +396,8 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
     const float *slots = reinterpret_cast<const float *>(lds);
     const int tid = opaque(threadIdx.x);
     const size_t wstride = (size_t)ly.chunk * rows * 16;  // floats per wave in the slot buffer
+    const int exit = exit_of<KIND>();
+    const float *hsrc = KIND == G_AU && a.ha ? a.ha + (size_t)exit * rows * md.d : a.sc.h;
     if (KIND == G_GU) {
         const int items = (gn >> 1) * rows * 4;
         for (int idx = tid; idx < items; idx += WG_THREADS) {
@@ -435,7 +444,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
         int qkv_sect = 0, qkv_c = 0, qkv_head = 0, qkv_e = 0, qkv_ses = 0;
         if (KIND == G_O || KIND == G_DN || KIND == G_AU) {
             if (n < md.d) {
-                g_a = *as_global(reinterpret_cast<const f32x4_t *>(a.sc.h + (size_t)m * md.d + n));
+                g_a = *as_global(reinterpret_cast<const f32x4_t *>(hsrc + (size_t)m * md.d + n));
                 if (KIND == G_AU) g_b = *as_global(reinterpret_cast<const f32x4_t *>(ep.bias + n));
                 if (ep.gain_xn) g_b = *as_global(reinterpret_cast<const f32x4_t *>(ep.gain_xn + n));
                 if (ep.gain_xh) g_c = *as_global(reinterpret_cast<const f32x4_t *>(ep.gain_xh + n));
@@ -473,7 +482,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
                 float pre[4] = {S.x + b[0], S.y + b[1], S.z + b[2], S.w + b[3]}, o[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = pre[e] / (1.0f + __expf(-pre[e]));
-                store_split4(a.sc.t, rows, m, n, o);
+                store_split4(a.sc.t + exit * a.t_next, rows, m, n, o);
             }
         } else if (KIND == G_O || KIND == G_DN || KIND == G_AU) {
             float sq = 0.f;
@@ -488,7 +497,10 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
                 } else {
                     *hp = (f32x4_t){v[0], v[1], v[2], v[3]};
                 }
-                if (ep.xa_out) store_split4(a.sc.xa, rows, m, n, v);
+                if (ep.xa_out) {
+                    store_split4(a.sc.xa, rows, m, n, v);
+                    if (KIND == G_DN && a.ha) *reinterpret_cast<EE_GLOBAL f32x4_t *>(as_global_mut(a.ha) + (size_t)(a.head_row0 + m) * md.d + n) = (f32x4_t){v[0], v[1], v[2], v[3]};
+                }
                 sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
                 if (ep.gain_xn) {
                     const f32x4_t g = g_b;
@@ -498,7 +510,7 @@ __device__ __forceinline__ void gemm_epilogue(const PassArgs &a, const StageLds 
                 if (ep.gain_xh) {
                     const f32x4_t g = g_c;
                     float x[4] = {v[0] * g[0], v[1] * g[1], v[2] * g[2], v[3] * g[3]};
-                    store_split4(a.sc.xh, a.head_rows, a.head_row0 + m, n, x);
+                    store_split4(a.sc.xh, a.head_rows, a.head_row0 + exit * rows + m, n, x);
                 }
             }
             zbuf[idx] = sq;  // (ntg, m, quad) order
@@ -714,7 +726,7 @@ __device__ __forceinline__ int x_last_offset(int tile_bytes, int lane)
 // cold scalar cache: the code up to these requests is 70 instructions (loops, not unrolled) and needs one line of arguments.
 // With the requests behind the warming of all arguments and the plan's arithmetic, us per launch, 5 rows of the 7B shape: QKV
 // 18.6 -> 18.3, gate/up 30.9 -> 30.0, down 18.1 -> 17.9, head 50.0 -> 49.0; 40 rows, 8 layers, a pass 1390 -> 1372.
-template <int XC, bool PK>
+template <int KIND, int XC, bool PK>
 __device__ __forceinline__ void gemm_entry(char *lds)
 {
     typedef unsigned int u32x16_t __attribute__((ext_vector_type(16), aligned(16)));
@@ -728,6 +740,10 @@ __device__ __forceinline__ void gemm_entry(char *lds)
     const int x_last = x_last_offset<XC>(tile_bytes, lane);
     const char *wp = reinterpret_cast<const char *>((((unsigned long long)v[1] << 32) | v[0]) + (unsigned)((g * SWAVES + wave) * tile_bytes_of(PK)));
     const char *xp = reinterpret_cast<const char *>((((unsigned long long)v[3] << 32) | v[2]) + (unsigned)(((g & ((1 << ksl) - 1)) * KTs + wave) * tile_bytes));
+    if (KIND == G_AD || KIND == G_AU) {   // (w_next, x_next)
+        wp += (long long)(((unsigned long long)v[13] << 32) | v[12]) * blockIdx.y;
+        xp += (int)v[14] * (int)blockIdx.y;
+    }
     unsigned dst = lds_offset(lds) + wave * (WAVE_LDS_KB * 1024);
 #pragma unroll 1
     for (int s = 0; s < stages; ++s) {
@@ -1023,7 +1039,7 @@ __device__ __forceinline__ void gemm_stage_t(const PassArgs &a, const GemmPlan &
     auto hand_over = [&](int slot, bool mine) __attribute__((always_inline)) {
         const float ss = mine ? mi.rowss[hrow] : 0.f;
         if (ep.ss_out) as_global_mut(ep.ss_out)[(size_t)hrow * SS_LD + slot] = ss;
-        if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)(a.head_row0 + hrow) * SS_LD + slot] = ss;
+        if (ep.ss_head) as_global_mut(ep.ss_head)[(size_t)(a.head_row0 + exit_of<KIND>() * rows + hrow) * SS_LD + slot] = ss;
         if (KIND == G_HEAD) {  // device-scope stores: the accept step may run in another workgroup of this launch
             store_dev64(a.sc.cand + (size_t)hrow * SS_LD + slot,
                         make_uint2(__float_as_uint(mine ? mi.bestv[hrow] : -INFINITY), (unsigned)(mine ? mi.besti[hrow] : 0x7FFFFFFF)));
@@ -1674,6 +1690,7 @@ template <int KIND>
 __device__ __forceinline__ GemmIn gemm_input(const PassArgs &a)
 {
     const char *x = reinterpret_cast<const char *>(a.entry.X);
+    if (KIND == G_AD || KIND == G_AU) x += a.entry.x_next * (int)blockIdx.y;
     return GemmIn{x, KIND == G_QKV ? a.sc.ss_a : (KIND == G_GU ? a.sc.ss_f : (KIND == G_HEAD ? a.sc.ss_h : nullptr))};
 }
 
@@ -1691,10 +1708,10 @@ __device__ __forceinline__ GemmEpi gemm_epi(const PassArgs &a)
         ep.xa_out = a.xa_out;                  // the exit's adapters come first
         ep.ss_out = a.sc.ss_a;
     } else if (KIND == G_AD) {
-        ep.bias = a.bias;
+        ep.bias = a.bias + (int)blockIdx.y * a.bias_next;
     } else if (KIND == G_AU) {
-        ep.bias = a.bias;
-        ep.gain_xh = a.gain_xh;
+        ep.bias = a.bias + (int)blockIdx.y * a.bias_next;
+        ep.gain_xh = a.gain_xh + (int)blockIdx.y * a.gain_next;
         ep.ss_head = a.sc.ss_h;
     }
     return ep;
@@ -1709,9 +1726,11 @@ template <int KIND, int XC, bool PK>
 __global__ void __launch_bounds__(WG_THREADS) ee_gemm_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
-    gemm_entry<XC, PK>(lds);
+    gemm_entry<KIND, XC, PK>(lds);
     const PassArgs &a = warmed_arguments();
-    gemm_stage_t<KIND, XC, PK>(a, a.plan0, a.lay, a.entry.W, gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
+    const char *W = reinterpret_cast<const char *>(a.entry.W);
+    if (KIND == G_AD || KIND == G_AU) W += a.entry.w_next * blockIdx.y;
+    gemm_stage_t<KIND, XC, PK>(a, a.plan0, a.lay, reinterpret_cast<const uint4 *>(W), gemm_input<KIND>(a), gemm_epi<KIND>(a), lds);
     if (KIND == G_HEAD && a.fuse_accept) {
         // The workgroup whose candidates arrive last also runs the accept step
         // (one launch less per head); the counter is left at zero.

@@ -796,22 +796,24 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
         const uint16_t *lm[1] = {w_lm};
         if ((rc = tile_all(G_HEAD, PERM_NONE, lm, 1, V * d, 0)) != EE_OK) return bail(rc);
         if ((rc = upload_gain(g_final, c.d_model, tmp, g_final_d)) != EE_OK) return bail(rc);
+        float *ges = nullptr;   // (one allocation, exit after exit: adapters of several exits share a launch)
+        if (c.n_exits && (rc = dev_alloc(m->allocs, &ges, (size_t)c.n_exits * d, false)) != EE_OK) return bail(rc);
         for (int i = 0; i < c.n_exits; ++i) {
-            float *ge = nullptr;
-            if ((rc = dev_alloc(m->allocs, &ge, d, false)) != EE_OK) return bail(rc);
+            float *ge = ges + (size_t)i * d;
             if ((rc = upload_gain(g_exit_src[i], c.d_model, tmp, ge)) != EE_OK) return bail(rc);
             m->g_exit[i] = ge;
         }
     }
     if (A) {
         // adapters: weights in tile order per stored exit; biases as fp32, the bottlenecks' output biases summed in order
+        float *bds = nullptr, *bus = nullptr;
+        if (c.n_exits && (rc = dev_alloc(m->allocs, &bds, (size_t)c.n_exits * A, false)) != EE_OK) return bail(rc);
+        if (c.n_exits && (rc = dev_alloc(m->allocs, &bus, (size_t)c.n_exits * d, false)) != EE_OK) return bail(rc);
         for (int i = 0; i < c.n_exits; ++i) {
             const uint16_t *sd_[1] = {ads[(size_t)i].down}, *su_[1] = {ads[(size_t)i].up};
             if ((rc = tile_all(G_AD, PERM_NONE, sd_, 1, A * d, (size_t)i)) != EE_OK) return bail(rc);
             if ((rc = tile_all(G_AU, PERM_NONE, su_, 1, d * A, (size_t)i)) != EE_OK) return bail(rc);
-            float *bd = nullptr, *bu = nullptr;
-            if ((rc = dev_alloc(m->allocs, &bd, A, false)) != EE_OK) return bail(rc);
-            if ((rc = dev_alloc(m->allocs, &bu, d, false)) != EE_OK) return bail(rc);
+            float *bd = bds + (size_t)i * A, *bu = bus + (size_t)i * d;
             std::vector<float> hb(std::max(A, d));
             auto bf = [](uint16_t v) {
                 uint32_t u32 = (uint32_t)v << 16;
@@ -1079,6 +1081,7 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
     S_TRY(dev_alloc(s->allocs, &sc.u, (size_t)2 * rows_max * md.Kpad_F + X_SLACK));
     S_TRY(dev_alloc(s->allocs, &sc.xa, (size_t)2 * rows_max * md.Kpad_d + X_SLACK));
     S_TRY(dev_alloc(s->allocs, &sc.t, (size_t)2 * rows_max * std::max(md.Kpad_A, 32) + X_SLACK));
+    if (md.A) S_TRY(dev_alloc(s->allocs, &sc.ha, (size_t)rows_max * d));
     S_TRY(dev_alloc(s->allocs, &sc.ss_h, (size_t)SS_LD * rows_max));
     S_TRY(dev_alloc(s->allocs, &sc.ss_a, (size_t)SS_LD * rows_max));
     S_TRY(dev_alloc(s->allocs, &sc.ss_f, (size_t)SS_LD * rows_max));
@@ -1182,7 +1185,7 @@ static int launch_code(const PassArgs &a, int ph)
     }
     idx -= per_layer * nl;
     if (a.head_kind != HEAD_NONE) {
-        const int n_ad = a.adapter ? 2 : 0;
+        const int n_ad = a.adapter && (!a.ha || a.head_stage) ? 2 : 0;   // (adapters of several exits: with the last of them)
         if (idx < n_ad) return EE_LAUNCH_ADAPTER_DOWN + idx;
         if (idx == n_ad && a.head_stage) return EE_LAUNCH_HEAD;
     }
@@ -1230,7 +1233,8 @@ static const uint16_t *gemm_input_of(const Scratch &sc, int kind)
 }
 
 // Enqueues the stages of one segment, one launch each, on the leader's stream.
-static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, SampleUpload *up = nullptr)
+// `many`: the adapters of the group's n_heads exits in one launch each, from stored exit adapter_slot on, `adapter_step` apart.
+static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, SampleUpload *up = nullptr, bool many = false, int adapter_step = 0)
 {
     const ee_model *m = lead->m;
     const int per_layer = 5;
@@ -1244,6 +1248,9 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
         // what the O, DN, AD and AU epilogues produce and read (gemm_epi)
         a.gain_xn = a.gain_xh = a.bias = nullptr;
         a.xa_out = 0;
+        const bool adapter_stage = code == EE_LAUNCH_ADAPTER_DOWN || code == EE_LAUNCH_ADAPTER_UP;
+        const int head_row0 = a.head_row0;
+        if (adapter_stage && many) a.head_row0 = 0;   // (this launch writes the head rows of all exits of the group)
         if (code == EE_LAUNCH_O) a.gain_xn = a.mdv.g_ffn + (size_t)a.layer * a.d;
         if (code == EE_LAUNCH_DN) {
             if (a.layer + 1 < m->cfg.n_layers) a.gain_xn = a.mdv.g_attn + (size_t)(a.layer + 1) * a.d;
@@ -1255,7 +1262,7 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
         if (code == EE_LAUNCH_ADAPTER_DOWN) a.bias = a.ad_bdown;
         if (code == EE_LAUNCH_ADAPTER_UP) {
             a.bias = a.ad_bup;
-            a.gain_xh = a.head_gain;
+            a.gain_xh = a.ad_gain;
         }
         a.fuse_accept = (code == EE_LAUNCH_HEAD && !a.sm.on) ? 1 : 0;
         a.rows = code == EE_LAUNCH_HEAD ? a.head_rows : rows;   // the head launch carries the rows of all exits of its group
@@ -1281,6 +1288,15 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
                 en.W = m->w[v][code] + (size_t)slice * m->wstride[v][code];
             }
             en.X = gemm_input_of(a.sc, code);
+            if (adapter_stage) {
+                const int K = code == EE_LAUNCH_ADAPTER_DOWN ? a.mdv.Kpad_d : a.mdv.Kpad_A;
+                if (code == EE_LAUNCH_ADAPTER_DOWN && many) en.X = lead->sc.xa;   // (a.sc.xa is the last exit's)
+                en.w_next = (long long)m->wstride[v][code] * 16 * adapter_step;
+                en.x_next = 4 * a.rows * K;
+                a.t_next = 2 * a.rows * a.mdv.Kpad_A;
+                a.bias_next = adapter_step * (code == EE_LAUNCH_ADAPTER_DOWN ? a.mdv.A : a.d);
+                a.gain_next = adapter_step * a.d;
+            }
             en.wstep = a.plan0.nwg * SWAVES * tile_bytes_of(packed);
             en.tile_bytes = a.rows * 128;
             en.KTs = a.plan0.KTs;
@@ -1306,8 +1322,9 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             hipLaunchKernelGGL(k, dim3(a.H, a.att_splits, a.mode == 1 ? (a.M + ATT_ROWS - 1) / ATT_ROWS : a.n_sess), dim3(WG_THREADS),
                                att_lds(m->cfg.head_dim, a.M), lead->run_stream, a);
         else
-            hipLaunchKernelGGL(k, dim3(m->nwg), dim3(WG_THREADS), m->lds_budget, lead->run_stream, a);
+            hipLaunchKernelGGL(k, dim3(m->nwg, adapter_stage && many ? a.n_heads : 1), dim3(WG_THREADS), m->lds_budget, lead->run_stream, a);
         HIP_TRY(hipGetLastError());
+        a.head_row0 = head_row0;
         if (timed) HIP_TRY(hipEventRecord(lead->lt_events[2 * lead->lt_codes.size() - 1], lead->run_stream));
         if (code == EE_LAUNCH_HEAD && a.sm.on) {
             // probabilistic verification: the rows' keep tests and draws, one workgroup per head row,
@@ -1791,7 +1808,27 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
         a.adapter = (!fin && m->host_md.A > 0) ? 1 : 0;
         a.ad_bdown = a.adapter ? m->ad_bdown[slots[e]] : nullptr;
         a.ad_bup = a.adapter ? m->ad_bup[slots[e]] : nullptr;
-        if ((rc = launch_segment(lead, a, fin ? 0 : slots[e], &upload)) != EE_OK) return rc;
+        // The adapters of a group's exits run together, in front of the group's head launch, which is what their results wait for: two
+        // launches instead of two per exit (7 exits of the 7B shape, 5 rows: 83 us in 14 launches, now 11 + 23).  Where the exits'
+        // weights lie a constant number of slices apart, and nothing of it is split over workgroups.
+        int slot = fin ? 0 : slots[e], step = 0;
+        bool many = a.adapter && g_size > 1 && lead->sc.ha && !static_scratch;
+        if (many) {
+            step = slots[g_first + 1] - slots[g_first];
+            for (int j = 1; j < g_size; ++j) many = many && slots[g_first + j] - slots[g_first + j - 1] == step;
+            for (int k : {(int)G_AD, (int)G_AU}) many = many && (a.rows <= 16 || m->plan[1][k].nwg == 0);
+        }
+        a.ha = many ? lead->sc.ha : nullptr;
+        if (!static_scratch) a.sc.xa = lead->sc.xa + (many ? (size_t)(e - g_first) * 2 * a.rows * m->host_md.Kpad_d : 0);
+        if (many) {   // (the first exit's)
+            slot = slots[g_first];
+            a.ad_bdown = m->ad_bdown[slot];
+            a.ad_bup = m->ad_bup[slot];
+            a.ad_gain = gains[g_first];
+        } else {
+            a.ad_gain = a.head_gain;
+        }
+        if ((rc = launch_segment(lead, a, slot, &upload, many, step)) != EE_OK) return rc;
         if (fin) {
             HIP_TRY(hipEventRecord(lead->ev_final, lead->run_stream));
         } else if (a.head_stage) {

@@ -967,6 +967,37 @@ def test_exit_heads_in_groups_match_one_by_one(model_dir, adapters):
         g.free()
 
 
+# stored exits apart by one, by two, unevenly (their adapters then run one by one), a last group of one; one, two and three row tiles in all
+@pytest.mark.parametrize("exits,B,gamma", [([2, 3, 4], 1, 4), ([1, 3, 5], 1, 7), ([1, 2, 5], 1, 4), ([1, 2, 3, 4, 5], 1, 11), ([1, 3, 5], 3, 4), ([4, 5], 4, 5)])
+def test_adapters_of_a_group_share_launches(model_dir, exits, B, gamma):
+    """With EE_OPT_HEAD_BATCH the adapters of a group's exits run in one launch each, from copies of the residual stream: the same bits as
+    one exit after the other, in two passes in a row (the second finds the buffers as another grouping left them)."""
+    p = f"{model_dir}/gpu_groups_shared.bin"
+    eegen.write_model(p, AD_TINY, 65, gains="uniform", std=0.05)
+    g = ee.Model(p, max_rows=48)
+    sess = []
+    try:
+        for b in range(B):
+            gs = g.session(96, max_gamma=gamma, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+            gs.ee_prefill(eegen.prompt_tokens(68, 20 + 5 * b, AD_TINY.vocab, session=b))
+            sess.append(gs)
+        drafts = [eegen.prompt_tokens(69, gamma, AD_TINY.vocab, session=b) for b in range(B)]
+        seen = []
+        for k in (1, 9, 2, 9):
+            sess[0].ee_session_option(ee.OPT_HEAD_BATCH, k)
+            ee.ee_verify_batch(sess, drafts, exits)
+            for s_ in sess:
+                s_.ee_wait_final()
+            seen.append([z.view(np.uint32) for s_ in sess for z in gpu_logits(s_, len(exits))] +
+                        [x for s_ in sess for x in (s_.final_result().exit_tokens, s_.final_result().exit_conf.view(np.uint32))])
+        for other in seen[1:]:
+            assert all(np.array_equal(x, y) for x, y in zip(seen[0], other))
+    finally:
+        for s_ in sess:
+            s_.free()
+        g.free()
+
+
 @pytest.mark.parametrize("temperature", [1.0, 0.1, 0.05])
 def test_sampled_verification_tiny(tiny_pair, temperature):
     g, o = tiny_pair
