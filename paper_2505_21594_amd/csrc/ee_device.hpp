@@ -185,7 +185,8 @@ struct SampleDev {
     int on;              // 1: the pass decides by the draft probabilities instead of by exact match
     int *tok;            // [head rows]  token a row emits if the round ends there
     int *kept;           // [head rows]  1: the row's draft passes its test
-    int *count;          // rows of a sampling launch that have delivered; zero between launches
+    int *count;          // rows of a sampling launch that have delivered, then [head rows] parts of a row; zero between launches
+    unsigned long long *sums;   // [2][head rows][parts]  the parts' sums of exponentials, of residual weights (40-bit fixed point)
 };
 
 // What a GEMM launch needs to request its first weights and input: one line of the launch arguments, read with one

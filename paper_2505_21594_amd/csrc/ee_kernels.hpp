@@ -1492,18 +1492,9 @@ __device__ __forceinline__ u64 wave_sum(u64 x)
 }
 
 constexpr int SAMPLE_WAVES = 16;
-constexpr int SAMPLE_CH = 32;   // blocks of 64 tokens a wave holds in registers at once (a chunk)
-
-// values first + 64 j + lane, j < SAMPLE_CH, of a row; `fill` past the end t1
-__device__ __forceinline__ void load_chunk(const EE_GLOBAL float *row, int first, int t1, int lane, float fill, float (&out)[SAMPLE_CH])
-{
-#pragma unroll
-    for (int j = 0; j < SAMPLE_CH; ++j) {
-        const int k = first + 64 * j + lane;
-        out[j] = fill;
-        if (k < t1) out[j] = row[k];
-    }
-}
+constexpr int SAMPLE_BLOCKS = 2;                                     // blocks of 64 tokens a wave holds
+constexpr int SAMPLE_PART = SAMPLE_WAVES * SAMPLE_BLOCKS * 64;       // tokens of a workgroup
+__host__ __device__ constexpr int sample_parts(int V) { return (V + SAMPLE_PART - 1) / SAMPLE_PART; }
 
 // One row of one head under probabilistic verification (Eq. 2 / Eq. 5 of the paper with the
 // draft model's distributions; the keep / replace rule of the speculative sampling scheme the
@@ -1513,109 +1504,152 @@ __device__ __forceinline__ void load_chunk(const EE_GLOBAL float *row, int first
 // cumulative sum in token order with the row's number v_i: the first token whose cumulative
 // weight exceeds v_i * (sum of the weights).
 //
-// Wave w owns the tokens [w * S, (w + 1) * S) and walks them in chunks of SAMPLE_CH blocks of
-// 64 (lane l: token first + 64 j + l, coalesced; a chunk's loads are all requested before the
-// first is used).  Up to 32768 tokens a wave's share is one chunk: logits (then their exponentials)
-// and draft probabilities are loaded once and stay in registers through all the steps; a longer row
-// loads them again in every step.
-// The sums are integers, so the cumulative sum up to a token is the earlier waves' totals + this
-// wave's earlier blocks + a scan inside the block, whatever the order they were added in.
-// One row is one workgroup: bound by the latency of its steps and by one compute unit's vector unit
-// (about 45 instructions per token, a third of them for the two fixed-point conversions).  32000 tokens,
-// 5 rows: 28.7 us; with 12 waves that loaded the row again in every step, 41.9 us.
-__device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds)
+// Workgroup = (part of SAMPLE_PART tokens, row), two launches.  The first sums its part's exponentials (the row's largest logit
+// comes from the head launch's candidates); the second, with Z from all parts, sums the residual weights, and the workgroup
+// that arrives last at the row's counter has all parts' sums: it finds the part the target lies in, then the wave, the block and the
+// token.  The sums are integers: the cumulative sum up to a token is the earlier parts' totals + the earlier waves' + a
+// scan inside the wave, whatever the order they were added in.
+// Bound by latencies (loads, sums, one arrival each for row and launch).  32000 tokens, 5 rows: 4.8 + 15.4 us in two launches; one workgroup per
+// row, which was bound by one unit's vector instructions (about 45 per token), 28 us.
+struct SampleRow {
+    int ses, i, rr, hj;                                          // session, row of it; row of the head, head of the launch
+    const EE_GLOBAL float *z, *p, *uv;                           // logits, the draft's distribution, the session's u, v and 1 / temperature
+};
+__device__ __forceinline__ SampleRow sample_row(const PassArgs &a, int r)
 {
-    static_assert(SAMPLE_WAVES * 8 * 2 + SAMPLE_WAVES * 4 + 16 <= SAMPLE_LDS_BYTES && EE_MAX_ROWS * 8 <= SAMPLE_LDS_BYTES, "LDS of the sampling launch");
-    const int V = a.mdv.V, M = a.M, gamma = M - 1;
-    const int per_head = a.n_sess * M;                          // the launch's rows: head after head, session after session
-    const int hj = div_small(r, per_head), rr = r - hj * per_head;
-    const int ses = div_small(rr, M), i = rr - ses * M;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    u64 *wtot = reinterpret_cast<u64 *>(lds);                   // [SAMPLE_WAVES] the waves' totals (target terms)
-    u64 *rtot = wtot + SAMPLE_WAVES;                            // [SAMPLE_WAVES] the same for the residual weights
-    float *wmax = reinterpret_cast<float *>(rtot + SAMPLE_WAVES);   // [SAMPLE_WAVES]
-    int *found = reinterpret_cast<int *>(wmax + SAMPLE_WAVES);
-    const EE_GLOBAL float *z = as_global(a.sc.logits) + ((size_t)(a.head_idx + hj) * a.mdv.rows_max + rr) * V;
-    const EE_GLOBAL float *p = as_global(a.sm.probs) + ((size_t)ses * gamma + min(i, gamma - 1)) * V;
-    const EE_GLOBAL float *uv = as_global(a.sm.uv) + (size_t)ses * (2 * gamma + 2);   // the session's u, v and 1 / temperature
-    const int S = ((V + SAMPLE_WAVES - 1) / SAMPLE_WAVES + 63) & ~63;   // tokens per wave, whole blocks of 64
-    const int t0 = min(V, wave * S), t1 = min(V, t0 + S);
-    constexpr int CHUNK = SAMPLE_CH * 64;
-    const bool once = S <= CHUNK;                               // the wave's share is one chunk
-    const bool drafted = i < gamma;
-    float e[SAMPLE_CH], pc[SAMPLE_CH];                          // logits, then e_k; draft probabilities
-    load_chunk(z, t0, t1, lane, -INFINITY, e);
-    if (drafted) load_chunk(p, t0, t1, lane, 0.f, pc);
-    const float inv_T = uv[2 * gamma + 1], v_row = uv[gamma + i];
-    float zx = 0.f, px = 0.f, u_row = 0.f;
-    if (drafted) {
-        const int x = draft_of(a, ses, i);
-        zx = z[x];
-        px = p[x];
-        u_row = uv[i];
-    }
-
-    // largest logit
+    const int V = a.mdv.V, M = a.M, gamma = M - 1, per_head = a.n_sess * M;   // the launch's rows: head after head, session after session
+    SampleRow w;
+    w.hj = div_small(r, per_head);
+    w.rr = r - w.hj * per_head;
+    w.ses = div_small(w.rr, M);
+    w.i = w.rr - w.ses * M;
+    w.z = as_global(a.sc.logits) + ((size_t)(a.head_idx + w.hj) * a.mdv.rows_max + w.rr) * V;
+    w.p = as_global(a.sm.probs) + ((size_t)w.ses * gamma + min(w.i, gamma - 1)) * V;
+    w.uv = as_global(a.sm.uv) + (size_t)w.ses * (2 * gamma + 2);
+    return w;
+}
+// largest logit of the row: the best of the head launch's candidates
+__device__ __forceinline__ float sample_max(const PassArgs &a, int r, int lane)
+{
     float mx = -INFINITY;
-    for (int c0 = t0; c0 < t1; c0 += CHUNK) {
-        if (!once) load_chunk(z, c0, t1, lane, -INFINITY, e);
 #pragma unroll
-        for (int j = 0; j < SAMPLE_CH; ++j) mx = fmaxf(mx, e[j]);
+    for (int j = 0; j < SS_LD / 64; ++j) {
+        const int g = lane + 64 * j;
+        if (g < a.plan0.nwg) mx = fmaxf(mx, __int_as_float(as_global(a.sc.cand)[(size_t)r * SS_LD + g].x));
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) wmax[wave] = mx;
-    if (tid == 0) *found = 0;
-    __syncthreads();
-    float zmax = wmax[0];
+    return mx;
+}
+// this lane's tokens of the wave's share: first + 64 j + lane; exponentials of the logits, past the row's end 0
+__device__ __forceinline__ void sample_terms(const SampleRow &w, int first, int V, int lane, float zmax, float inv_T, float (&e)[SAMPLE_BLOCKS])
+{
 #pragma unroll
-    for (int w = 1; w < SAMPLE_WAVES; ++w) zmax = fmaxf(zmax, wmax[w]);
-
-    // Z = sum_k e_k  (a logit of -inf past the row's end contributes exp(-inf) = 0)
-    u64 part = 0;
-    for (int c0 = t0; c0 < t1; c0 += CHUNK) {
-        if (!once) load_chunk(z, c0, t1, lane, -INFINITY, e);
-#pragma unroll
-        for (int j = 0; j < SAMPLE_CH; ++j) {
-            e[j] = target_term(e[j], zmax, inv_T);
-            part += fixed_weight(e[j]);
-        }
+    for (int j = 0; j < SAMPLE_BLOCKS; ++j) {
+        const int k = first + 64 * j + lane;
+        e[j] = -INFINITY;
+        if (k < V) e[j] = w.z[k];
     }
-    part = wave_sum(part);
-    if (lane == 0) wtot[wave] = part;
-    __syncthreads();
-    u64 Zi = 0;
 #pragma unroll
-    for (int w = 0; w < SAMPLE_WAVES; ++w) Zi += wtot[w];
-    const float inv_Z = 1.0f / (float)((double)Zi * (1.0 / (double)SAMPLE_UNIT));
+    for (int j = 0; j < SAMPLE_BLOCKS; ++j) e[j] = target_term(e[j], zmax, inv_T);
+}
+__device__ __forceinline__ void sample_drafted(const SampleRow &w, int first, int V, int lane, float (&p)[SAMPLE_BLOCKS])
+{
+#pragma unroll
+    for (int j = 0; j < SAMPLE_BLOCKS; ++j) {
+        const int k = first + 64 * j + lane;
+        p[j] = 0.f;
+        if (k < V) p[j] = w.p[k];
+    }
+}
+// sum of one value per wave over the workgroup; every thread gets it, wtot[] keeps the waves' values
+__device__ __forceinline__ u64 sample_block_sum(u64 x, u64 *wtot, int wave, int lane)
+{
+    x = wave_sum(x);
+    if (lane == 0) wtot[wave] = x;
+    __syncthreads();
+    u64 t = 0;
+#pragma unroll
+    for (int w = 0; w < SAMPLE_WAVES; ++w) t += wtot[w];
+    return t;
+}
 
-    const u64 *tot = wtot;
+__device__ __forceinline__ void sample_sum_stage(const PassArgs &a, char *lds)
+{
+    const int part = blockIdx.x, r = blockIdx.y, V = a.mdv.V, parts = gridDim.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const SampleRow w = sample_row(a, r);
+    float e[SAMPLE_BLOCKS];
+    const float inv_T = w.uv[2 * (a.M - 1) + 1], zmax = sample_max(a, r, lane);
+    sample_terms(w, part * SAMPLE_PART + wave * (SAMPLE_BLOCKS * 64), V, lane, zmax, inv_T, e);
+    u64 sum = 0;
+#pragma unroll
+    for (int j = 0; j < SAMPLE_BLOCKS; ++j) sum += fixed_weight(e[j]);
+    sum = sample_block_sum(sum, reinterpret_cast<u64 *>(lds), wave, lane);
+    if (threadIdx.x == 0) as_global_mut(a.sm.sums)[(size_t)r * parts + part] = sum;
+}
+
+// sum of a row's parts in [0, n); every lane gets it
+__device__ __forceinline__ u64 sample_load_sum(const u64 *s, int n, int lane)
+{
+    u64 t = 0;
+    for (int i = lane; i < n; i += 64) t += __hip_atomic_load(as_global(s + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return wave_sum(t);
+}
+
+// true in the workgroup that leaves the row's decision behind
+__device__ __forceinline__ bool sample_draw_stage(const PassArgs &a, char *lds)
+{
+    static_assert(SAMPLE_WAVES * 8 + 32 <= SAMPLE_LDS_BYTES && EE_MAX_ROWS * 8 <= SAMPLE_LDS_BYTES, "LDS of the sampling launch");
+    const int r = blockIdx.y, V = a.mdv.V, parts = gridDim.x, gamma = a.M - 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    u64 *wtot = reinterpret_cast<u64 *>(lds);                    // [SAMPLE_WAVES]
+    int *flag = reinterpret_cast<int *>(wtot + SAMPLE_WAVES);    // arrived last; the token
+    const SampleRow w = sample_row(a, r);
+    const bool drafted = w.i < gamma;
+    const u64 *sums_e = a.sm.sums + (size_t)r * parts;
+    u64 *sums_r = a.sm.sums + ((size_t)a.head_rows + r) * parts;
+    const float inv_T = w.uv[2 * gamma + 1], v_row = w.uv[gamma + w.i], zmax = sample_max(a, r, lane);
+    float e[SAMPLE_BLOCKS], pc[SAMPLE_BLOCKS];
+    int part = blockIdx.x;
+    const int mine = wave * (SAMPLE_BLOCKS * 64);
+    if (drafted) {
+        sample_drafted(w, part * SAMPLE_PART + mine, V, lane, pc);
+        sample_terms(w, part * SAMPLE_PART + mine, V, lane, zmax, inv_T, e);
+    }
+    const u64 Zi = sample_load_sum(sums_e, parts, lane);
+    const float inv_Z = 1.0f / (float)((double)Zi * (1.0 / (double)SAMPLE_UNIT));
+    if (drafted) {
+        u64 sum = 0;
+#pragma unroll
+        for (int j = 0; j < SAMPLE_BLOCKS; ++j) sum += fixed_weight(residual_term(e[j], inv_Z, pc[j]));
+        sum = sample_block_sum(sum, wtot, wave, lane);
+        if (tid == 0) {
+            __hip_atomic_store(sums_r + part, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait_vmem();                                         // visible before it is counted
+            int *cnt = a.sm.count + 1 + r;
+            const int before = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *flag = before == parts - 1 ? 1 : 0;
+            if (*flag) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!*flag) return false;
+    } else if (part != 0) {
+        return false;                                            // (a row that draws from q has all it needs from the first launch)
+    }
+    // all parts' sums are there
+    const u64 *tot = sums_e;
     u64 w_total = Zi;
     bool residual = false;
     int kept = 0;
     if (drafted) {
-        const float qx = target_term(zx, zmax, inv_T) * inv_Z;
-        kept = u_row * px < qx ? 1 : 0;
-        u64 rp = 0;
-        for (int c0 = t0; c0 < t1; c0 += CHUNK) {
-            if (!once) {
-                load_chunk(z, c0, t1, lane, -INFINITY, e);
-                load_chunk(p, c0, t1, lane, 0.f, pc);
-#pragma unroll
-                for (int j = 0; j < SAMPLE_CH; ++j) e[j] = target_term(e[j], zmax, inv_T);
-            }
-#pragma unroll
-            for (int j = 0; j < SAMPLE_CH; ++j) rp += fixed_weight(residual_term(e[j], inv_Z, pc[j]));
-        }
-        rp = wave_sum(rp);
-        if (lane == 0) rtot[wave] = rp;
-        __syncthreads();
-        u64 W = 0;
-#pragma unroll
-        for (int w = 0; w < SAMPLE_WAVES; ++w) W += rtot[w];
+        const int x = draft_of(a, w.ses, w.i);
+        const float qx = target_term(w.z[x], zmax, inv_T) * inv_Z;
+        kept = w.uv[w.i] * w.p[x] < qx ? 1 : 0;
+        const u64 W = sample_load_sum(sums_r, parts, lane);
         if (W > 0) {  // otherwise q = p: the draft is always kept and the row never emits; it then draws from q
             residual = true;
-            tot = rtot;
+            tot = sums_r;
             w_total = W;
         }
     }
@@ -1623,61 +1657,60 @@ __device__ __forceinline__ void sample_stage(const PassArgs &a, int r, char *lds
     const double vd = (double)v_row;
     u64 target = (u64)(vd * (double)w_total);
     if (target >= w_total) target = w_total - 1;
-    u64 before = 0;                                              // cumulative weight of the waves before this one
-    for (int w = 0; w < wave; ++w) before += tot[w];
-    if (before <= target && target < before + tot[wave]) {      // exactly one wave
-        u64 run = before;
+    // the target's part: 64 parts at a time
+    u64 run = 0;
+    for (int p0 = 0; p0 < parts; p0 += 64) {
+        const u64 own = p0 + lane < parts ? __hip_atomic_load(as_global(tot + p0 + lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        u64 incl = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const u64 o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        const unsigned long long hit = __ballot(run + incl > target);
+        if (hit) {
+            const int h = __builtin_ctzll(hit);
+            part = p0 + h;
+            run += __shfl(incl, h, 64) - __shfl(own, h, 64);
+            break;
+        }
+        run += __shfl(incl, 63, 64);
+    }
+    // its tokens
+    const int first = part * SAMPLE_PART + mine;
+    sample_terms(w, first, V, lane, zmax, inv_T, e);
+    if (residual) sample_drafted(w, first, V, lane, pc);
+    u64 wk[SAMPLE_BLOCKS], own = 0;
+#pragma unroll
+    for (int j = 0; j < SAMPLE_BLOCKS; ++j) {
+        wk[j] = fixed_weight(residual ? residual_term(e[j], inv_Z, pc[j]) : e[j]);
+        own += wk[j];
+    }
+    __syncthreads();                                             // (wtot is read above)
+    sample_block_sum(own, wtot, wave, lane);
+    for (int k = 0; k < wave; ++k) run += wtot[k];
+    if (run <= target && target < run + wtot[wave]) {            // exactly one wave
         bool done = false;
-        for (int c0 = t0; c0 < t1 && !done; c0 += CHUNK) {
-            if (!once) {
-                load_chunk(z, c0, t1, lane, -INFINITY, e);
-                if (residual) load_chunk(p, c0, t1, lane, 0.f, pc);
 #pragma unroll
-                for (int j = 0; j < SAMPLE_CH; ++j) e[j] = target_term(e[j], zmax, inv_T);
+        for (int j = 0; j < SAMPLE_BLOCKS; ++j) {
+            u64 incl = wk[j];
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const u64 o = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += o;
             }
-            // the blocks' sums, eight at a time (independent reductions overlap), until the target's block is found
-            int jh = -1;
-            u64 mine = 0;
-#pragma unroll
-            for (int j0 = 0; j0 < SAMPLE_CH; j0 += 8)
-                if (jh < 0) {
-                    u64 wk[8], blk[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) wk[j] = fixed_weight(residual ? residual_term(e[j0 + j], inv_Z, pc[j0 + j]) : e[j0 + j]);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const u64 t = wave_sum(wk[j]);
-                        blk[j] = ((u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)t);
-                    }
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (jh < 0) {
-                            if (run + blk[j] > target) {
-                                jh = j0 + j;
-                                mine = wk[j];
-                            } else {
-                                run += blk[j];
-                            }
-                        }
+            const unsigned long long hit = __ballot(run + incl > target);
+            if (!done && hit) {
+                if (lane == 0) {
+                    __hip_atomic_store(a.sm.tok + r, first + 64 * j + __builtin_ctzll(hit), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(a.sm.kept + r, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-            if (jh >= 0) {                                       // the token is in block jh: scan it
-                u64 incl = mine;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const u64 o = __shfl_up(incl, off, 64);
-                    if (lane >= off) incl += o;
-                }
-                const unsigned long long hit = __ballot(run + incl > target);
-                if (lane == 0) *found = c0 + 64 * jh + __builtin_ctzll(hit);
                 done = true;
             }
+            run += __shfl(incl, 63, 64);
         }
     }
-    __syncthreads();
-    if (tid == 0) {
-        __hip_atomic_store(a.sm.tok + r, *found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.sm.kept + r, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    return true;
 }
 
 // ------------------------------------------------------------------ kernels of the pass

@@ -6,20 +6,27 @@
 
 namespace ee {
 
-// Probabilistic verification: one workgroup per row of the head launch before it (whose logits
-// it reads); the workgroup that finishes last applies the accept rule and publishes, as the
+// Probabilistic verification: workgroups (part of the vocabulary, row of the head launch before them, whose logits and candidates they
+// read).  The one whose row's decision is the last of the second launch applies the accept rule and publishes, as the
 // head launch's last workgroup does under exact-match verification.
+__global__ void __launch_bounds__(SAMPLE_WAVES * 64) ee_sample_sum_kernel(PassArgs a_by_value)
+{
+    extern __shared__ __align__(16) char lds[];
+    const PassArgs &a = warmed_arguments();
+    sample_sum_stage(a, lds);
+}
+
 __global__ void __launch_bounds__(SAMPLE_WAVES * 64) ee_sample_kernel(PassArgs a_by_value)
 {
     extern __shared__ __align__(16) char lds[];
     const PassArgs &a = warmed_arguments();
-    sample_stage(a, blockIdx.x, lds);
-    int *lastf = reinterpret_cast<int *>(lds + SAMPLE_LDS_BYTES - 16);   // behind sample_stage's and the accept step's arrays
+    if (!sample_draw_stage(a, lds)) return;
+    int *lastf = reinterpret_cast<int *>(lds + SAMPLE_LDS_BYTES - 16);   // behind the sampling's and the accept step's arrays
     wait_vmem();
     __syncthreads();
     if (threadIdx.x == 0) {
         const int before = __hip_atomic_fetch_add(a.sm.count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *lastf = before == (int)gridDim.x - 1 ? 1 : 0;
+        *lastf = before == (int)gridDim.y - 1 ? 1 : 0;
         if (*lastf) __hip_atomic_store(a.sm.count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();

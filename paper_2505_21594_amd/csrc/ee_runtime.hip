@@ -96,7 +96,8 @@ struct ee_session {
     hipStream_t copy_stream;         // uploads of a sampled pass's distributions (EE_SAMPLING)
     hipEvent_t ev_copy;
     float *dev_sample;               // device copy of the same
-    int *dev_sample_out;             // [2 * EE_MAX_ROWS + 1] rows' tokens, keep flags, arrival counter
+    int *dev_sample_out;             // [3 * EE_MAX_ROWS + 1] rows' tokens, keep flags, arrival counters (launch, rows)
+    unsigned long long *dev_sample_sums;   // SampleDev::sums
     int *dev_pf_tokens;
     int *host_pf_tokens;             // pinned
     uint16_t *dev_pf_emb;
@@ -1105,7 +1106,8 @@ extern "C" int ee_session_create(const ee_model *m, int max_ctx, int max_gamma, 
         S_TRY(dev_alloc(s->allocs, &s->dev_sample, n));
         S_HIP(hipStreamCreate(&s->copy_stream));
         S_HIP(hipEventCreateWithFlags(&s->ev_copy, hipEventDisableTiming));
-        S_TRY(dev_alloc(s->allocs, &s->dev_sample_out, 2 * EE_MAX_ROWS + 1));
+        S_TRY(dev_alloc(s->allocs, &s->dev_sample_out, 3 * EE_MAX_ROWS + 1));
+        S_TRY(dev_alloc(s->allocs, &s->dev_sample_sums, (size_t)2 * rows_max * sample_parts(c.vocab)));
     }
     {
         // partial tiles of the K-split launches: [split][n-tile][row][16] floats for the largest split kind
@@ -1343,7 +1345,10 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
                 lead->lt_codes.push_back(EE_LAUNCH_SAMPLE);
                 HIP_TRY(hipEventRecord(lead->lt_events[2 * i], lead->run_stream));
             }
-            hipLaunchKernelGGL(ee_sample_kernel, dim3(a.head_rows), dim3(SAMPLE_WAVES * 64), SAMPLE_LDS_BYTES, lead->run_stream, a);
+            const dim3 grid(sample_parts(m->cfg.vocab), a.head_rows);
+            hipLaunchKernelGGL(ee_sample_sum_kernel, grid, dim3(SAMPLE_WAVES * 64), SAMPLE_LDS_BYTES, lead->run_stream, a);
+            HIP_TRY(hipGetLastError());
+            hipLaunchKernelGGL(ee_sample_kernel, grid, dim3(SAMPLE_WAVES * 64), SAMPLE_LDS_BYTES, lead->run_stream, a);
             HIP_TRY(hipGetLastError());
             if (timed) HIP_TRY(hipEventRecord(lead->lt_events[2 * lead->lt_codes.size() - 1], lead->run_stream));
         }
@@ -1774,6 +1779,7 @@ static int verify_impl(ee_session *const *sessions, int n_sessions, const int32_
         a.sm.tok = lead->dev_sample_out;
         a.sm.kept = lead->dev_sample_out + EE_MAX_ROWS;
         a.sm.count = lead->dev_sample_out + 2 * EE_MAX_ROWS;
+        a.sm.sums = lead->dev_sample_sums;
         a.keep_logits = 1;   // the sampling launch reads the head launch's logits
     }
     // The first session's descriptor, drafts included, travels with every launch's arguments; a pass of

@@ -1038,6 +1038,23 @@ def test_sampled_verification_at_the_register_limit(model_dir, vocab):
         g.free()
 
 
+# one wave's tokens or part of them, a workgroup's exactly, one more, two and one more, more parts than a wave has lanes (65)
+@pytest.mark.parametrize("vocab", [127, 128, 2048, 2049, 4097, 131200])
+def test_sampled_verification_over_parts(model_dir, vocab):
+    """A row's tokens are spread over workgroups of 2048: sums, the search for the part, the wave and the token at their edges, two passes'
+    worth of counters.  Draws bind where their interval is wider than rounding (test above): with 131200 tokens few in the flat tail do,
+    keep tests and likely tokens always; 0.3 says that the test is not empty."""
+    p = f"{model_dir}/gpu_vocab_parts.bin"
+    eegen.write_model(p, eegen.ModelConfig(2, 256, 4, 64, 688, vocab, (1,)), 79, gains="uniform", std=0.06)
+    g, o = ee.Model(p, max_rows=8), eo.Model(p)
+    try:
+        rounds, gamma = 4, 5
+        _, bound, _, _ = sampled_chain(g, o, eegen.prompt_tokens(45, 40, vocab), gamma, [1], rounds, 0.1, seed=24, what=f"sampled V={vocab}")
+        assert bound >= 0.3 * rounds * 2 * (gamma + 2), bound
+    finally:
+        g.free()
+
+
 @pytest.mark.parametrize("B,gamma,max_rows", [(3, 4, 16), (5, 4, 25), (4, 7, 32)])
 def test_sampled_verification_batch(model_dir, B, gamma, max_rows):
     """Probabilistic verification for several sessions in one pass (one, two row tiles): each
