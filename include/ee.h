@@ -124,7 +124,9 @@ const char *ee_last_error(void);
    uses 16.  With max_rows > 16 the output and down projections are kept in a second
    tile order as well, in which groups of four workgroups share their output columns and
    split K; launches of more than 16 rows use it (about a quarter more device memory for
-   the weights).
+   the weights).  Weight matrices of 32 MB and more are kept in a packed form as well (12 bits a
+   weight, nothing lost: three quarters more memory for them), which is what passes stream, where all
+   packed forms together take at most an eighth of the device memory that is free at the call.
    Cold path; synchronous. */
 int ee_model_load(const char *path, int device, ee_model **out);
 int ee_model_load_ex(const char *path, int device, int max_rows, ee_model **out);
@@ -313,7 +315,7 @@ int ee_device_synchronize(int device);
      streamed once for k consecutive exits (as many as the max_rows of the model allow) and their
      results are published together after the last of them: less traffic when many exits are
      active (the paper runs one after every layer), later results for the earlier exits of a
-     group.
+     group.  The adapters of a group's exits share their launches too.
    EE_OPT_PREFILL_GEMM: 16 * parts + shape = every GEMM of a prompt of more than max_rows rows uses
      this workgroup shape (1..7: 256 columns x 128 rows, 128 x 128, 128 x 64, 64 x 64; 128 x 128 and 128 x 64 with two,
      64 x 64 with four groups of waves that share K) and this many workgroups per tile that share K (1..8, lowered
@@ -338,7 +340,8 @@ int ee_session_option(ee_session *s, int option, int value);
 #define EE_LAUNCH_DN 3      /* down projection + residual + next norm inputs             */
 #define EE_LAUNCH_HEAD 4    /* exit or final head: norm + LM head + argmax, accept rule,
                                publication                                               */
-#define EE_LAUNCH_ADAPTER_DOWN 5 /* exit-head adapters: hidden units                     */
+#define EE_LAUNCH_ADAPTER_DOWN 5 /* exit-head adapters (of a group's exits, EE_OPT_HEAD_BATCH):
+                               hidden units                                              */
 #define EE_LAUNCH_ADAPTER_UP 6   /* exit-head adapters: output + residual + head norm input */
 #define EE_LAUNCH_ATT 8     /* attention over the paged KV cache                         */
 #define EE_LAUNCH_EMBED 7   /* embedding gather                                          */

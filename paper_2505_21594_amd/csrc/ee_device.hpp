@@ -74,7 +74,7 @@ struct StageLds {
 // matrix lie in few binades: with its 16 most common neighbouring exponents as a window, sign, mantissa and 4 bits of
 // exponent say all but about one weight in 10000 of a normal distribution.  Those others stand in the tile as the
 // smallest value of the window (code 0), and in a list of the matrix with the difference to what they should be;
-// helper waves add the list's products to the sums while the weights stream (escape_sums).
+// helper waves add the list's products to the sums while the weights stream (EscapeSums).
 // A tile is 64 lanes x 12 bytes: dwords A and B the low bytes of the lane's eight bf16 values, C their variable high bits (sign and
 // upper three exponent bits, PACK_MASK, of pair j rotated left by 4 j).  The window's exponents are moved to 112 .. 127 (a power of two that
 // the epilogue takes back exactly, GemmEntry::wscale): the constant exponent bits are 0111, and unpacking is a byte permute, a rotate and a

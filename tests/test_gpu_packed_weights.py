@@ -112,3 +112,48 @@ def test_one_outlier_is_seen(pair, model_dir, name):
     finally:
         t[n, 0] = kept
         gs.free()
+
+
+@pytest.mark.parametrize("split,B,gamma", [(False, 1, 4), (False, 3, 7), (True, 1, 4), (True, 3, 5), (True, 8, 5)])
+def test_packed_groups_of_tiles(model_dir, split, B, gamma):
+    """Matrices whose workgroups own more n-tiles than a group has (gate/up 8 and 10, LM head 9 and 10): every group has lists and sums of
+    its own; with K split over workgroups for every kind, every slice."""
+    cfg = eegen.ModelConfig(n_layers=2, d_model=512, n_heads=8, head_dim=64, d_ffn=17408, vocab=40000, exit_layers=(1,))
+    p = f"{model_dir}/gpu_packed_wide.bin"
+    eegen.write_model(p, cfg, 78, gains="uniform", std=0.03)
+    t = eegen.open_tensors(p, "r+")
+    rng = np.random.default_rng(6)
+    for name in ("l1.wg", "l1.wu", "l2.wg", "l2.wu", "w_lm"):
+        w = t[name]
+        for n, k in [(0, 0), (w.shape[0] - 1, w.shape[1] - 1)] + list(zip(rng.integers(0, w.shape[0], 150), rng.integers(0, w.shape[1], 150))):
+            w[n, k] = _bf16(rng.choice([-1.0, 1.0]) * rng.uniform(0.8, 1.6))
+    if split:
+        ee.ee_tune_k_split(127, 2)
+    try:
+        g = ee.Model(p, max_rows=48)
+    finally:
+        ee.ee_tune_k_split(0b1010, 2)   # back to the default
+    o = eo.Model(p)
+    sess, osess = [], []
+    try:
+        for b in range(B):
+            toks = eegen.prompt_tokens(910, 7 + 3 * b, o.vocab, session=b)
+            gs = g.session(64, max_gamma=gamma, flags=ee.NO_AUTOCOMMIT | (ee.KEEP_LOGITS if b == 0 else 0))
+            os_ = o.session(64)
+            fo, margin = oracle_prefill(os_, toks)
+            check_first_token(gs, gs.ee_prefill(toks), fo, margin, f"session {b}")
+            sess.append(gs)
+            osess.append(os_)
+        drafts = [eegen.prompt_tokens(911, gamma, o.vocab, session=b) for b in range(B)]
+        ee.ee_verify_batch(sess, drafts, [1])
+        for s in sess:
+            s.ee_wait_final()
+        for b in range(B):
+            ro = osess[b].verify(drafts[b], [1], commit=False, want_logits=True)
+            z = gpu_logits(sess[b], 1)
+            check_pass(ro, sess[b].final_result(), z, drafts[b], f"groups B={B} session {b}")
+            check_two_terms(ro, z)
+    finally:
+        for s in sess:
+            s.free()
+        g.free()
