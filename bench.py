@@ -96,6 +96,9 @@ def per_launch_roofline(ee, run, passes):
             a[2] += launch_bytes(run.cfg, name, P, run.M, run.B)
     for s in sessions:
         s.free()
+    for k in ("adapter_down", "adapter_up"):   # (exits of a group share these launches)
+        if k in acc:
+            acc[k][2] *= len(run.exits) * (passes - 1) / acc[k][0]
     return {k: {"launches_per_pass": v[0] / (passes - 1), "avg_launch_us": v[1] / v[0] * 1e3,
                 "algorithmic_bytes_per_launch": v[2] / v[0],
                 "achieved_GBps": (v[2] / (v[1] * 1e-3) / 1e9) if v[2] else None} for k, v in acc.items()}
