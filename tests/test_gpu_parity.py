@@ -615,6 +615,37 @@ def test_attention_splits_follow_each_session(tiny_pair, mid_pair, which, lens):
             s_.free()
 
 
+def test_attention_splits_of_more_items_than_units(model_dir):
+    """Sixteen sessions of sixteen heads: more units than compute units have room for once more, two sessions far longer than the others
+    (21 and 13 pages): these are split although their items then take turns on a unit."""
+    cfg = eegen.ModelConfig(2, 1024, 16, 64, 688, 1024, (1,))
+    p = f"{model_dir}/gpu_many_units.bin"
+    eegen.write_model(p, cfg, 92, gains="uniform")
+    g, o = ee.Model(p, max_rows=48), eo.Model(p)
+    sess, osess = [], []
+    try:
+        for b in range(16):
+            toks = eegen.prompt_tokens(670, (330, 200)[b] if b < 2 else 5 + 3 * b, o.vocab, session=b)
+            gs, os_ = g.session(352, max_gamma=1, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT), o.session(352)
+            fo, margin = oracle_prefill(os_, toks)
+            check_first_token(gs, gs.ee_prefill(toks), fo, margin, f"session {b}")
+            sess.append(gs)
+            osess.append(os_)
+        for rnd in range(2):
+            drafts = [eegen.prompt_tokens(671 + rnd, 1, o.vocab, session=b) for b in range(16)]
+            ee.ee_verify_batch(sess, drafts, [1])
+            for s_ in sess:
+                s_.ee_wait_final()
+            for b in range(16):
+                ro = osess[b].verify(drafts[b], [1], commit=False, want_logits=True)
+                check_pass(ro, sess[b].final_result(), gpu_logits(sess[b], 1), drafts[b], f"round {rnd} session {b}")
+                check_two_terms(ro, gpu_logits(sess[b], 1))
+    finally:
+        for s_ in sess:
+            s_.free()
+        g.free()
+
+
 def test_gamma_extremes_and_page_boundary(tiny_pair):
     """gamma = 1 and gamma = 15 (the most rows of one attention item), prompts that end right
     before, on and after a page boundary."""
