@@ -201,7 +201,7 @@ __global__ void pack_weights_kernel(const uint16_t *__restrict__ src, unsigned c
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         const int k = k0 + e;
-                        if (row < 0 || k >= pl.K) continue;   // padding: code 0 (x is zero there, or the column is dropped)
+                        if (row < 0 || k >= pl.K) continue;   // padding: code 0, which is not zero: the column is dropped, or every pass clears the input there (the gate/up launch: gemm_group)
                         const unsigned bits = src[(size_t)row * pl.K + k];
                         const int rel = (int)((bits >> 7) & 0xFF) - base;
                         if (rel >= 0 && rel < 16) {

@@ -157,3 +157,45 @@ def test_packed_groups_of_tiles(model_dir, split, B, gamma):
         for s in sess:
             s.free()
         g.free()
+
+
+# d_ffn = 16 (mod 32): half of the down projection's last k-tile is padding.  4112: 129 k-tiles, never split; 4080: 128, split for more than 16 rows
+@pytest.mark.parametrize("d_ffn,B,gamma", [(4112, 1, 4), (4112, 3, 5), (4080, 1, 4), (4080, 8, 4)])
+def test_padded_k_tile_adds_nothing(model_dir, d_ffn, B, gamma):
+    """A padding weight of a packed tile is not zero, so its input has to be: whatever rows an earlier pass had (its activations
+    lie where the padding columns of another row count are), a pass gives the same bits, and ee_verify_static those of ee_verify."""
+    cfg = eegen.ModelConfig(n_layers=2, d_model=4096, n_heads=32, head_dim=128, d_ffn=d_ffn, vocab=1024, exit_layers=(1,))
+    p = f"{model_dir}/gpu_packed_padded.bin"
+    eegen.write_model(p, cfg, 79, gains="uniform")
+    g = ee.Model(p, max_rows=48)
+    drafts = [eegen.prompt_tokens(921, gamma, cfg.vocab, session=b) for b in range(B)]
+
+    def sessions():
+        out = [g.session(64, max_gamma=15, flags=ee.NO_AUTOCOMMIT | ee.KEEP_LOGITS) for _ in range(B)]
+        for b, s in enumerate(out):
+            s.ee_prefill(eegen.prompt_tokens(920, 3 + b, cfg.vocab, session=b))
+        return out
+
+    def logits(ss, static=False):
+        if static:
+            ss[0].ee_verify_static(drafts[0], [1])
+        else:
+            ee.ee_verify_batch(ss, drafts, [1])
+        for s in ss:
+            s.ee_wait_final()
+        return np.stack([s.ee_debug_logits(e) for s in ss for e in range(2)]).view(np.uint32)
+
+    fresh, used = sessions(), sessions()
+    try:
+        want = logits(fresh)
+        for n, other in ((1, 15), (1, 1), (min(B, 3), 15)):
+            ee.ee_verify_batch(used[:n], [eegen.prompt_tokens(922, other, cfg.vocab, session=b) for b in range(n)], [1])
+            for s in used[:n]:
+                s.ee_wait_final()
+            assert np.array_equal(logits(used), want), (n, other)
+        if B == 1:
+            assert np.array_equal(logits(used, static=True), want)
+    finally:
+        for s in fresh + used:
+            s.free()
+        g.free()
