@@ -1604,7 +1604,7 @@ __device__ __forceinline__ u64 sample_load_sum(const u64 *s, int n, int lane)
     return wave_sum(t);
 }
 
-// true in the workgroup that leaves the row's decision behind
+// true in the workgroup that leaves the row's decision behind (thread 0 stores it)
 __device__ __forceinline__ bool sample_draw_stage(const PassArgs &a, char *lds)
 {
     static_assert(SAMPLE_WAVES * 8 + 32 <= SAMPLE_LDS_BYTES && EE_MAX_ROWS * 8 <= SAMPLE_LDS_BYTES, "LDS of the sampling launch");
@@ -1693,10 +1693,11 @@ __device__ __forceinline__ bool sample_draw_stage(const PassArgs &a, char *lds)
         wk[j] = fixed_weight(residual ? residual_term(e[j], inv_Z, pc[j]) : e[j]);
         own += wk[j];
     }
+    if (tid == 0) flag[1] = 0;                                   // the token where no weight is positive (NaN or infinite logits, 1 / temperature infinite)
     __syncthreads();                                             // (wtot is read above)
     sample_block_sum(own, wtot, wave, lane);
     for (int k = 0; k < wave; ++k) run += wtot[k];
-    if (run <= target && target < run + wtot[wave]) {            // exactly one wave
+    if (run <= target && target < run + wtot[wave]) {            // at most one wave
         bool done = false;
 #pragma unroll
         for (int j = 0; j < SAMPLE_BLOCKS; ++j) {
@@ -1708,14 +1709,16 @@ __device__ __forceinline__ bool sample_draw_stage(const PassArgs &a, char *lds)
             }
             const unsigned long long hit = __ballot(run + incl > target);
             if (!done && hit) {
-                if (lane == 0) {
-                    __hip_atomic_store(a.sm.tok + r, first + 64 * j + __builtin_ctzll(hit), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(a.sm.kept + r, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+                if (lane == 0) flag[1] = first + 64 * j + __builtin_ctzll(hit);
                 done = true;
             }
             run += __shfl(incl, 63, 64);
         }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        __hip_atomic_store(a.sm.tok + r, flag[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.sm.kept + r, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return true;
 }

@@ -22,9 +22,8 @@ __global__ void __launch_bounds__(SAMPLE_WAVES * 64) ee_sample_kernel(PassArgs a
     const PassArgs &a = warmed_arguments();
     if (!sample_draw_stage(a, lds)) return;
     int *lastf = reinterpret_cast<int *>(lds + SAMPLE_LDS_BYTES - 16);   // behind the sampling's and the accept step's arrays
-    wait_vmem();
-    __syncthreads();
     if (threadIdx.x == 0) {
+        wait_vmem();                                                     // the decision is visible before it is counted
         const int before = __hip_atomic_fetch_add(a.sm.count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *lastf = before == (int)gridDim.y - 1 ? 1 : 0;
         if (*lastf) __hip_atomic_store(a.sm.count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -1086,6 +1086,33 @@ def test_sampled_verification_over_parts(model_dir, vocab):
         g.free()
 
 
+@pytest.mark.parametrize("vocab", [1000, 5000])
+def test_sampled_row_without_weight_decides_nothing(model_dir, vocab):
+    """A temperature whose reciprocal is infinite leaves a row no positive weight (the largest logit's exponential is NaN, every other one
+    zero).  Such a row keeps no draft and draws token 0; it does not repeat what the pass before it decided."""
+    p = f"{model_dir}/gpu_no_weight.bin"
+    eegen.write_model(p, eegen.ModelConfig(2, 256, 4, 64, 688, vocab, (1,)), 80, gains="uniform", std=0.06)
+    g, gamma = ee.Model(p), 5
+    gs = g.session(64, max_gamma=gamma, flags=ee.SAMPLING | ee.NO_AUTOCOMMIT)
+    try:
+        gs.ee_prefill(eegen.prompt_tokens(46, 20, vocab))
+        probs = np.full((gamma, vocab), 1.0 / vocab, dtype=np.float32)
+        u, v = np.zeros(gamma, dtype=np.float32), np.full(gamma + 1, 0.7, dtype=np.float32)
+        drafts = 1 + np.arange(gamma)
+        for temperature in (1.0, 1e-39, 0.5, 1e-39):
+            gs.ee_verify_sampled(drafts, probs, u, v, temperature, [1])
+            gs.ee_wait_final()
+            r = gs.final_result()
+            if temperature > 1e-3:   # u = 0 keeps every draft that has a probability at all; 0.7 of the sum is far from token 0
+                assert r.accept_len == gamma and r.exit_accept_len[0] == gamma and np.all(r.final_tokens > 0) and np.all(r.exit_tokens > 0)
+            else:
+                assert r.accept_len == 0 and r.exit_accept_len[0] == 0 and r.next_token == 0
+                assert not np.any(r.final_tokens) and not np.any(r.exit_tokens)
+    finally:
+        gs.free()
+        g.free()
+
+
 @pytest.mark.parametrize("B,gamma,max_rows", [(3, 4, 16), (5, 4, 25), (4, 7, 32)])
 def test_sampled_verification_batch(model_dir, B, gamma, max_rows):
     """Probabilistic verification for several sessions in one pass (one, two row tiles): each
