@@ -13,6 +13,7 @@
 #include <climits>
 #include <new>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "ee_once.hpp"
@@ -56,16 +57,17 @@ struct ee_model {
     GemmPlan plan[2][G_KINDS];
     const uint4 *w[2][G_KINDS];
     long long wstride[2][G_KINDS];
-    // The same weights packed (PACK_TILE), what launches of up to 48 rows stream: slice l at pk + l * pk_stride (bytes), for the
-    // slices whose `scale` is set; the others, and prefill, take w.
+    // The same weights packed (PACK_TILE), what launches of up to 48 rows stream: per slice (pk_bytes each; one allocation
+    // per kind and variant, layers apart in it cost 0.3 % of a pass), for the slices that have them; the others, and prefill, take w.
     struct PackedSlice {
+        const unsigned char *w;      // nullptr: not packed
         size_t esc;                  // first escape in m->escapes
         int groups, cap;
-        float scale;                 // 0: not packed
+        float scale;
     };
     unsigned char *pk[2][G_KINDS];
-    size_t pk_stride[2][G_KINDS];
-    std::vector<PackedSlice> packed[2][G_KINDS];
+    size_t pk_bytes[2][G_KINDS];
+    std::vector<PackedSlice> packed[2][G_KINDS];   // empty: the kind is not packed
     const Escape *escapes;           // all matrices' lists
     const int2 *tile_tab[G_KINDS];   // prefill GEMMs: where the tiles of an n-tile lie (PfArgs::tab; trunk kinds only)
     std::vector<void *> allocs;  // every device allocation of the model
@@ -307,6 +309,19 @@ static int dev_alloc(std::vector<void *> &list, T **out, size_t count, bool zero
     return EE_OK;
 }
 
+// the same for memory that the caller can do without: false, and no error left behind, if there is none
+static bool try_alloc(std::vector<void *> &list, unsigned char **out, size_t bytes)
+{
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    list.push_back(p);
+    *out = static_cast<unsigned char *>(p);
+    return true;
+}
+
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ------------------------------------------------------------------ model load
@@ -379,10 +394,11 @@ try {
     if (n_elems - in_base > (size_t)cap || h[255] || top + PACK_EXP0 - base > 160 || std::abs(PACK_EXP0 - base) > 32) return EE_OK;
     std::vector<EscapeFound> esc;
     for (int v = 0; v < 2; ++v) {
-        if (!m->pk[v][kind]) continue;
+        if (m->packed[v][kind].empty()) continue;
         const GemmPlan &pl = m->plan[v][kind];
+        unsigned char *dst = m->pk[v][kind] + slice * m->pk_bytes[v][kind];
         HIP_TRY(hipMemset(counts, 0, 4));
-        hipLaunchKernelGGL(pack_weights_kernel, dim3(pl.nwg), dim3(512), 0, 0, tmp, m->pk[v][kind] + slice * m->pk_stride[v][kind], pl, perm,
+        hipLaunchKernelGGL(pack_weights_kernel, dim3(pl.nwg), dim3(512), 0, 0, tmp, dst, pl, perm,
                            m->cfg.d_model, m->cfg.head_dim, m->cfg.d_ffn, base, v == 0 ? found : nullptr, cap, reinterpret_cast<int *>(counts));
         HIP_TRY(hipGetLastError());
         if (v == 0) {
@@ -442,11 +458,30 @@ try {
                 t[1 + j] = Escape{ldexpf(w, PACK_EXP0 - base) - PACK_CODE0, (unsigned)e.k << 16 | ((unsigned)e.n & 0xFFFF)};
             }
         }
-        m->packed[v][kind][slice] = {at, groups, cap, ldexpf(1.0f, base - PACK_EXP0)};
+        m->packed[v][kind][slice] = {dst, at, groups, cap, ldexpf(1.0f, base - PACK_EXP0)};
     }
     return EE_OK;
 } catch (const std::bad_alloc &) {
     return fail(EE_EDEVICE, "ee_model_load: out of host memory");
+}
+
+// Gives back the room of a kind's slices that stayed plain: the others move into an allocation of their size, if there is one.
+static int trim_packed(ee_model *m, int v, int kind)
+{
+    std::vector<ee_model::PackedSlice> &slices = m->packed[v][kind];
+    const size_t bytes = m->pk_bytes[v][kind], kept = (size_t)std::count_if(slices.begin(), slices.end(), [](const ee_model::PackedSlice &s) { return s.w; });
+    unsigned char *to = nullptr;
+    if (kept == slices.size() || (kept && !try_alloc(m->allocs, &to, kept * bytes))) return EE_OK;
+    m->allocs.erase(std::find(m->allocs.begin(), m->allocs.end(), m->pk[v][kind]));
+    const unsigned char *from = std::exchange(m->pk[v][kind], to);
+    for (ee_model::PackedSlice &s : slices) {
+        if (!s.w) continue;
+        HIP_TRY(hipMemcpy(to, s.w, bytes, hipMemcpyDeviceToDevice));
+        s.w = to;
+        to += bytes;
+    }
+    HIP_TRY(hipFree(const_cast<unsigned char *>(from)));
+    return EE_OK;
 }
 
 // which GEMM kinds get a K-split tile order in models loaded for more than 16 rows, and the splits (ee_tune_k_split)
@@ -738,7 +773,6 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
         }
     // Packed forms.  They come on top of the plain ones, which prefill reads: only where all of them take at most an eighth of the
     // memory that is free now (so many models as fitted before still fit; 10 GB for the 7B shape, 13 with the K-split order).
-    memset(m->pk, 0, sizeof m->pk);
     std::vector<Escape> lists;
     {
         size_t free_bytes = 0, total_bytes = 0, need = 0;
@@ -752,21 +786,24 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
                 const GemmPlan &pl = m->plan[v][k];
                 if (pl.nwg == 0) continue;
                 want[k] = want[k] && plan_lds(pl, max_rows, m->lds_budget, true, ly);
-                m->pk_stride[v][k] = (size_t)pl.steps * pl.nwg * SWAVES * PACK_TILE;
-                if (want[k]) need += m->pk_stride[v][k] * (k == G_HEAD ? 1 : Lz);
+                m->pk_bytes[v][k] = (size_t)pl.steps * pl.nwg * SWAVES * PACK_TILE;
+                if (want[k]) need += m->pk_bytes[v][k] * (k == G_HEAD ? 1 : Lz);
             }
             if (want[k]) pack_work_bytes = std::max(pack_work_bytes, (size_t)p0.NT * p0.KT / PACK_TILES_PER_ESCAPE * sizeof(EscapeFound) + 2048);
         }
         if (need > free_bytes / 8) pack_work_bytes = 0;
-        if (pack_work_bytes)
-            for (int k = G_QKV; k <= G_HEAD; ++k)
-                for (int v = 0; v < 2; ++v) {
-                    if (!want[k] || m->plan[v][k].nwg == 0) continue;
-                    const size_t slices = k == G_HEAD ? 1 : Lz;
-                    if ((rc = dev_alloc(m->allocs, &m->pk[v][k], slices * m->pk_stride[v][k], true)) != EE_OK) return bail(rc);
-                    m->packed[v][k].assign(slices, ee_model::PackedSlice{0, 0, 0, 0.f});
-                }
-        if (pack_work_bytes && hipMalloc(&pack_work, pack_work_bytes) != hipSuccess) return bail(fail(EE_EDEVICE, "ee_model_load: cannot allocate the packing buffer"));
+        if (pack_work_bytes && hipMalloc(&pack_work, pack_work_bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            pack_work = nullptr;
+        }
+        for (int k = G_QKV; pack_work && k <= G_HEAD; ++k)
+            for (int v = 0; v < 2; ++v) {
+                const size_t slices = k == G_HEAD ? 1 : Lz;
+                if (!want[k] || m->plan[v][k].nwg == 0 || (v == 1 && m->packed[0][k].empty())) continue;
+                if (!try_alloc(m->allocs, &m->pk[v][k], slices * m->pk_bytes[v][k])) continue;   // (this kind stays plain)
+                if (hipMemset(m->pk[v][k], 0, slices * m->pk_bytes[v][k]) != hipSuccess) return bail(fail(EE_EDEVICE, "clearing of a packed matrix failed"));
+                m->packed[v][k].assign(slices, ee_model::PackedSlice{nullptr, 0, 0, 0, 0.f});
+            }
     }
     // every variant of a kind from the same upload
     auto tile_all = [&](int kind, int perm, const uint16_t *const *srcs, int n_src, size_t elems_each, size_t slice) {
@@ -776,7 +813,7 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
                                        wdev[v][kind] + slice * (size_t)m->wstride[v][kind]);
             if (r != EE_OK) return r;
         }
-        return m->pk[0][kind] ? pack_slice(m, kind, perm, slice, n_src * elems_each, tmp, pack_work, pack_work_bytes, lists) : (int)EE_OK;
+        return !m->packed[0][kind].empty() ? pack_slice(m, kind, perm, slice, n_src * elems_each, tmp, pack_work, pack_work_bytes, lists) : (int)EE_OK;
     };
     if ((rc = dev_alloc(m->allocs, &g_attn, Lz * d, false)) != EE_OK) return bail(rc);
     if ((rc = dev_alloc(m->allocs, &g_ffn, Lz * d, false)) != EE_OK) return bail(rc);
@@ -859,6 +896,9 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
         if (hipMemcpy(dev, lists.data(), lists.size() * sizeof(Escape), hipMemcpyHostToDevice) != hipSuccess) return bail(fail(EE_EDEVICE, "upload of the escapes failed"));
         m->escapes = dev;
     }
+    for (int v = 0; v < 2; ++v)
+        for (int k = G_QKV; k <= G_HEAD; ++k)
+            if ((rc = trim_packed(m, v, k)) != EE_OK) return bail(rc);
     md.g_attn = g_attn;
     md.g_ffn = g_ffn;
     md.g_final = g_final_d;
@@ -1291,11 +1331,11 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             const int v = (a.rows > 16 && m->plan[1][code].nwg > 0 && a.sc.part) ? 1 : 0;
             a.plan0 = m->plan[v][code];
             GemmEntry &en = a.entry;
-            const bool packed = (size_t)slice < m->packed[v][code].size() && m->packed[v][code][slice].scale != 0.f;
+            const bool packed = (size_t)slice < m->packed[v][code].size() && m->packed[v][code][slice].w;
             k = gemm_kernel(code, a.rows, packed);
             if (packed) {
                 const ee_model::PackedSlice &ps = m->packed[v][code][slice];
-                en.W = reinterpret_cast<const uint4 *>(m->pk[v][code] + (size_t)slice * m->pk_stride[v][code]);
+                en.W = reinterpret_cast<const uint4 *>(ps.w);
                 en.esc = m->escapes + ps.esc;
                 en.esc_groups = (uint16_t)ps.groups;
                 en.esc_cap = (uint16_t)ps.cap;

@@ -2,6 +2,8 @@
 
 A model as small as the packing rule admits with every kind of matrix above its line, ragged in K (4112 = 128.5 k-tiles) and in
 columns (5003), with weights outside the window of exponents planted where a list or a tile can go wrong."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -199,3 +201,49 @@ def test_padded_k_tile_adds_nothing(model_dir, d_ffn, B, gamma):
         for s in fresh + used:
             s.free()
         g.free()
+
+
+def test_a_matrix_that_stays_plain_takes_no_more_memory(model_dir):
+    """Zeros in a fifth of the rows are far too many weights outside the window: such a matrix has no packed form and holds no memory
+    for one.  Layer 1 alone (layer 2's packed form then moves to its place: a pass against the oracle), then the whole model.  (Places no wave's sequence reaches: up to 5 %; the
+    runtime hands out pages of 2 MB and keeps some.)"""
+    cfg = eegen.ModelConfig(n_layers=2, d_model=4096, n_heads=32, head_dim=128, d_ffn=4096, vocab=5008, exit_layers=(1,))
+    p = f"{model_dir}/gpu_packed_memory.bin"
+    eegen.write_model(p, cfg, 80, gains="uniform")
+    t = eegen.open_tensors(p, "r+")
+    lib = ee.load_library()
+
+    def free_bytes():
+        free, total = ctypes.c_size_t(), ctypes.c_size_t()
+        assert lib.hipMemGetInfo(ctypes.byref(free), ctypes.byref(total)) == 0
+        return free.value
+
+    def used(check=False):
+        before = free_bytes()
+        g = ee.Model(p)
+        took = before - free_bytes()
+        if check:
+            toks, drafts, o = eegen.prompt_tokens(930, 9, cfg.vocab), eegen.prompt_tokens(931, 4, cfg.vocab), eo.Model(p)
+            gs, os_ = g.session(64, max_gamma=4, flags=ee.NO_AUTOCOMMIT | ee.KEEP_LOGITS), o.session(64)
+            fo, margin = oracle_prefill(os_, toks)
+            check_first_token(gs, gs.ee_prefill(toks), fo, margin, "moved")
+            gs.verify_sync(drafts, [1])
+            check_two_terms(os_.verify(drafts, [1], commit=False, want_logits=True), gpu_logits(gs, 1))
+            gs.free()
+        g.free()
+        return took
+
+    ee.Model(p).free()
+    packed = used()
+    for name, w in t.items():
+        if name.startswith("l1.w"):
+            w[::5] = 0
+    half = used(check=True)
+    for name, w in t.items():
+        if name.startswith("l2.w") or name == "w_lm":
+            w[::5] = 0
+    plain = used()
+    d, F, V = cfg.d_model, cfg.d_ffn, cfg.vocab
+    layer, head, emb = 2 * (4 * d * d + 3 * F * d), 2 * V * d, 2 * V * d
+    for took, want in ((plain, 2 * layer + head + emb), (packed - half, 0.75 * layer), (half - plain, 0.75 * (layer + head))):
+        assert 0.97 * want <= took <= 1.08 * want, (took, want)
