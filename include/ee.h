@@ -46,6 +46,7 @@
 #ifndef EE_H
 #define EE_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -124,12 +125,30 @@ const char *ee_last_error(void);
    uses 16.  With max_rows > 16 the output and down projections are kept in a second
    tile order as well, in which groups of four workgroups share their output columns and
    split K; launches of more than 16 rows use it (about a quarter more device memory for
-   the weights).  Weight matrices of 32 MB and more are kept in a packed form as well (12 bits a
-   weight, nothing lost: three quarters more memory for them), which is what passes stream, where all
-   packed forms together take at most an eighth of the device memory that is free at the call.
+   the weights).  Weight matrices of 32 MB and more can be kept in a packed form as well, which
+   passes then stream (ee_model_load_form); these two calls load EE_FORM_AUTO.
    Cold path; synchronous. */
 int ee_model_load(const char *path, int device, ee_model **out);
 int ee_model_load_ex(const char *path, int device, int max_rows, ee_model **out);
+
+/* ee_model_load_ex with a choice of the form in which passes stream the weights.  Packed: 12 bits a
+   weight, no weight changed, three quarters of a matrix's memory on top of its plain form, which
+   prompts of more than max_rows rows read.  Both forms hold the same weights, but their products
+   are summed differently: results agree to fp32 rounding, not to the bit.  A matrix that does not
+   suit the form (too many or too unevenly spread weights outside a window of 16 exponents, infinities, NaN)
+   stays plain in any case and takes no memory for it.
+     EE_FORM_AUTO:   packed if all packed forms together take at most an eighth of the device memory
+                     that is free once everything else is loaded (so what else holds memory then
+                     decides it), and for the kinds of matrices whose allocation succeeds;
+     EE_FORM_PLAIN:  never (no memory taken; results do not depend on what else the device holds);
+     EE_FORM_PACKED: always; EE_EDEVICE if the memory is not there.
+   ee_model_packed_bytes: device memory the model's packed forms hold, without their lists of a few
+   KB per matrix; 0: every matrix is streamed plain. */
+#define EE_FORM_AUTO 0
+#define EE_FORM_PLAIN 1
+#define EE_FORM_PACKED 2
+int ee_model_load_form(const char *path, int device, int max_rows, int form, ee_model **out);
+int ee_model_packed_bytes(const ee_model *m, size_t *bytes);
 
 /* Tuning and test knob, process-wide, for models loaded after the call with max_rows > 16:
    which GEMM kinds get the K-split tile order (kind_mask: bit 0 QKV, 1 output projection,

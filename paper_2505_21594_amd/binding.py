@@ -28,11 +28,12 @@ KEEP_LOGITS = 1
 NO_AUTOCOMMIT = 2
 SAMPLING = 4
 TIME_LAUNCHES = 16
+FORM_AUTO, FORM_PLAIN, FORM_PACKED = 0, 1, 2
 OPT_ATT_SPLITS, OPT_SCATTER_PAGES, OPT_HEAD_BATCH, OPT_PREFILL_GEMM, OPT_PREFILL_ATT_ROWS = 1, 2, 3, 4, 5
 LAUNCH_NAMES = ("qkv", "o", "gu", "dn", "head", "adapter_down", "adapter_up", "embed", "att", "sample")
 
 EXPORTS = [
-    "ee_last_error", "ee_model_load", "ee_model_load_ex", "ee_model_free", "ee_model_info",
+    "ee_last_error", "ee_model_load", "ee_model_load_ex", "ee_model_load_form", "ee_model_free", "ee_model_info", "ee_model_packed_bytes",
     "ee_session_create", "ee_session_free", "ee_prefill", "ee_prefill_embeds", "ee_verify",
     "ee_verify_batch", "ee_verify_static", "ee_verify_sampled", "ee_wait_exit", "ee_query_exit", "ee_wait_final", "ee_query_final",
     "ee_pass_time_ms", "ee_kv_truncate", "ee_set_pending", "ee_kv_len", "ee_pending",
@@ -103,6 +104,8 @@ def load_library():
     lib.ee_last_error.argtypes = []
     lib.ee_model_load.argtypes = [ctypes.c_char_p, ci, P(vp)]
     lib.ee_model_load_ex.argtypes = [ctypes.c_char_p, ci, ci, P(vp)]
+    lib.ee_model_load_form.argtypes = [ctypes.c_char_p, ci, ci, ci, P(vp)]
+    lib.ee_model_packed_bytes.argtypes = [vp, P(ctypes.c_size_t)]
     lib.ee_model_free.argtypes = [vp]
     lib.ee_model_info.argtypes = [vp, P(ModelConfigC)]
     lib.ee_session_create.argtypes = [vp, ci, ci, ctypes.c_uint, P(vp)]
@@ -218,10 +221,10 @@ class VerifyOutput:
 class Model:
     """ee_model_load / ee_model_free / ee_model_info."""
 
-    def __init__(self, path: str, device: int = 0, max_rows: int = 16):
+    def __init__(self, path: str, device: int = 0, max_rows: int = 16, form: int = FORM_AUTO):
         self._l = load_library()
         h = ctypes.c_void_p()
-        _check(self._l.ee_model_load_ex(path.encode(), device, max_rows, ctypes.byref(h)))
+        _check(self._l.ee_model_load_form(path.encode(), device, max_rows, form, ctypes.byref(h)))
         self._h = h
         c = ModelConfigC()
         _check(self._l.ee_model_info(h, ctypes.byref(c)))
@@ -234,6 +237,11 @@ class Model:
         if self._h:
             self._l.ee_model_free(self._h)
             self._h = None
+
+    def packed_bytes(self) -> int:
+        n = ctypes.c_size_t()
+        _check(self._l.ee_model_packed_bytes(self._h, ctypes.byref(n)))
+        return int(n.value)
 
     def session(self, max_ctx: int, max_gamma: int = 8, flags: int = 0) -> "Session":
         return Session(self, max_ctx, max_gamma, flags)

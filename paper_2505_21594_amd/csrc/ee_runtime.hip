@@ -506,9 +506,10 @@ extern "C" int ee_model_free(ee_model *m)
     return EE_OK;
 }
 
-extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_model **out)
+extern "C" int ee_model_load_form(const char *path, int device, int max_rows, int form, ee_model **out)
 {
     if (!path || !out) return fail(EE_EINVAL, "ee_model_load: null argument");
+    if (form < EE_FORM_AUTO || form > EE_FORM_PACKED) return fail(EE_EINVAL, "ee_model_load: form %d not in [%d,%d]", form, EE_FORM_AUTO, EE_FORM_PACKED);
     if (max_rows < 1 || max_rows > EE_MAX_ROWS) return fail(EE_EINVAL, "ee_model_load: max_rows %d not in [1,%d]", max_rows, EE_MAX_ROWS);
     *out = nullptr;
     int fd = open(path, O_RDONLY);
@@ -771,8 +772,9 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             if ((rc = dev_alloc(m->allocs, &wdev[v][k], std::max<size_t>(slices, 1) * (size_t)m->wstride[v][k], true)) != EE_OK) return bail(rc);
             m->w[v][k] = wdev[v][k];
         }
-    // Packed forms.  They come on top of the plain ones, which prefill reads: only where all of them take at most an eighth of the
-    // memory that is free now (so many models as fitted before still fit; 10 GB for the 7B shape, 13 with the K-split order).
+    // Packed forms.  They come on top of the plain ones, which prefill reads (10 GB for the 7B shape, 13 with the K-split order): where the
+    // caller leaves it open, only if all of them take at most an eighth of the memory that is free now, so that little is taken from the
+    // sessions and models still to come, and where an allocation fails the kind stays plain.
     std::vector<Escape> lists;
     {
         size_t free_bytes = 0, total_bytes = 0, need = 0;
@@ -791,16 +793,20 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
             }
             if (want[k]) pack_work_bytes = std::max(pack_work_bytes, (size_t)p0.NT * p0.KT / PACK_TILES_PER_ESCAPE * sizeof(EscapeFound) + 2048);
         }
-        if (need > free_bytes / 8) pack_work_bytes = 0;
+        if (form == EE_FORM_PLAIN || (form == EE_FORM_AUTO && need > free_bytes / 8)) pack_work_bytes = 0;
         if (pack_work_bytes && hipMalloc(&pack_work, pack_work_bytes) != hipSuccess) {
             (void)hipGetLastError();
             pack_work = nullptr;
+            if (form == EE_FORM_PACKED) return bail(fail(EE_EDEVICE, "ee_model_load: no memory for packing the weights"));
         }
         for (int k = G_QKV; pack_work && k <= G_HEAD; ++k)
             for (int v = 0; v < 2; ++v) {
                 const size_t slices = k == G_HEAD ? 1 : Lz;
                 if (!want[k] || m->plan[v][k].nwg == 0 || (v == 1 && m->packed[0][k].empty())) continue;
-                if (!try_alloc(m->allocs, &m->pk[v][k], slices * m->pk_bytes[v][k])) continue;   // (this kind stays plain)
+                if (!try_alloc(m->allocs, &m->pk[v][k], slices * m->pk_bytes[v][k])) {
+                    if (form == EE_FORM_PACKED) return bail(fail(EE_EDEVICE, "ee_model_load: no memory for the packed weights"));
+                    continue;
+                }
                 if (hipMemset(m->pk[v][k], 0, slices * m->pk_bytes[v][k]) != hipSuccess) return bail(fail(EE_EDEVICE, "clearing of a packed matrix failed"));
                 m->packed[v][k].assign(slices, ee_model::PackedSlice{nullptr, 0, 0, 0, 0.f});
             }
@@ -910,9 +916,25 @@ extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_m
     return EE_OK;
 }
 
+extern "C" int ee_model_load_ex(const char *path, int device, int max_rows, ee_model **out)
+{
+    return ee_model_load_form(path, device, max_rows, EE_FORM_AUTO, out);
+}
+
 extern "C" int ee_model_load(const char *path, int device, ee_model **out)
 {
     return ee_model_load_ex(path, device, 16, out);
+}
+
+extern "C" int ee_model_packed_bytes(const ee_model *m, size_t *bytes)
+{
+    if (!m || !bytes) return fail(EE_EINVAL, "ee_model_packed_bytes: null argument");
+    *bytes = 0;
+    for (int v = 0; v < 2; ++v)
+        for (int k = G_QKV; k <= G_HEAD; ++k)
+            if (m->pk[v][k])
+                for (const ee_model::PackedSlice &s : m->packed[v][k]) *bytes += s.w ? m->pk_bytes[v][k] : 0;
+    return EE_OK;
 }
 
 extern "C" int ee_model_info(const ee_model *m, ee_model_config *out)

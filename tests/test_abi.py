@@ -53,6 +53,19 @@ def test_model_load_host_errors(tmp_path):
     assert e.value.code == ee.EE_EIO
 
 
+def test_model_form_is_checked(tmp_path):
+    bad = tmp_path / "bad.bin"
+    bad.write_bytes(b"NOTAMODL" + b"\0" * 1000)
+    lib = ee.load_library()
+    h = ctypes.c_void_p()
+    for form in (-1, 3):
+        assert lib.ee_model_load_form(str(bad).encode(), 0, 16, form, ctypes.byref(h)) == ee.EE_EINVAL
+        assert b"form" in lib.ee_last_error()
+    for form in (ee.FORM_AUTO, ee.FORM_PLAIN, ee.FORM_PACKED):
+        assert lib.ee_model_load_form(str(bad).encode(), 0, 16, form, ctypes.byref(h)) == ee.EE_EFORMAT
+    assert lib.ee_model_packed_bytes(None, None) == ee.EE_EINVAL
+
+
 def test_truncated_model_file_is_rejected(tmp_path):
     import eegen
     path = str(tmp_path / "tiny.bin")

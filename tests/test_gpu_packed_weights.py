@@ -247,3 +247,33 @@ def test_a_matrix_that_stays_plain_takes_no_more_memory(model_dir):
     layer, head, emb = 2 * (4 * d * d + 3 * F * d), 2 * V * d, 2 * V * d
     for took, want in ((plain, 2 * layer + head + emb), (packed - half, 0.75 * layer), (half - plain, 0.75 * (layer + head))):
         assert 0.97 * want <= took <= 1.08 * want, (took, want)
+
+
+@pytest.mark.parametrize("B,gamma", [(1, 4), (8, 4)])
+def test_the_caller_chooses_the_form(pair, model_dir, B, gamma):
+    """EE_FORM_PLAIN holds nothing packed, EE_FORM_PACKED the same as the default on an empty device, bit for bit; plain and packed weights
+    give the same results to rounding: each is within the two-term bound of the oracle, so they are within twice that of each other."""
+    auto, _ = pair
+    p = f"{model_dir}/gpu_packed.bin"
+    plain, packed = ee.Model(p, max_rows=48, form=ee.FORM_PLAIN), ee.Model(p, max_rows=48, form=ee.FORM_PACKED)
+
+    def logits(g):
+        ss = [g.session(64, max_gamma=gamma, flags=ee.NO_AUTOCOMMIT | ee.KEEP_LOGITS) for _ in range(B)]
+        for b, s in enumerate(ss):
+            s.ee_prefill(eegen.prompt_tokens(940, 6 + b, CFG.vocab, session=b))
+        ee.ee_verify_batch(ss, [eegen.prompt_tokens(941, gamma, CFG.vocab, session=b) for b in range(B)], [1])
+        for s in ss:
+            s.ee_wait_final()
+        z = np.stack([s.ee_debug_logits(e) for s in ss for e in range(2)])
+        for s in ss:
+            s.free()
+        return z
+
+    try:
+        assert plain.packed_bytes() == 0 and packed.packed_bytes() == auto.packed_bytes() > 0
+        a, b, c = logits(auto), logits(packed), logits(plain)
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+        assert not np.array_equal(a, c) and np.linalg.norm(a.astype(np.float64) - c) / np.linalg.norm(c.astype(np.float64)) < 2 * TWO_TERMS
+    finally:
+        plain.free()
+        packed.free()
