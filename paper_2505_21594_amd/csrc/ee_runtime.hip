@@ -1310,6 +1310,13 @@ static const uint16_t *gemm_input_of(const Scratch &sc, int kind)
     }
 }
 
+// Whether a launch of so many rows streams the packed form of a matrix that has one.  Up to 16 rows, with K split and in the LM head always.  Beyond,
+// unpacking and the escapes' sums cost every n-tile a time that grows with the rows, and the bytes saved are K's: both forms meet at K = 64 a
+// row, whatever the columns.  us plain / packed at 32, 39 and 48 rows: gate/up of 4 n-tiles a unit, K 2048 16.6 / 17.0, 17.8 / 19.2, 19.1 / 21.7; 2304 19.1 / 18.6,
+// 20.4 / 20.6, 21.7 / 23.6; 2560 20.4 / 19.3, 21.8 / 21.3, 23.1 / 24.5; 3072 23.1 / 21.6, 24.7 / 23.3, 26.5 / 26.2; QKV, K 2560 15.8 / 15.8, 17.3 / 17.6,
+// 18.4 / 19.2; 3072 20.2 / 18.9, 21.8 / 20.8, 23.1 / 22.7; 4096 25.5 / 23.4, 27.9 / 25.9, 29.6 / 28.1.
+static bool packed_pays(int kind, const GemmPlan &p, int rows) { return rows <= 16 || p.ksl > 0 || kind == G_HEAD || p.K >= 64 * rows; }
+
 // Enqueues the stages of one segment, one launch each, on the leader's stream.
 // `many`: the adapters of the group's n_heads exits in one launch each, from stored exit adapter_slot on, `adapter_step` apart.
 static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, SampleUpload *up = nullptr, bool many = false, int adapter_step = 0)
@@ -1353,7 +1360,7 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             const int v = (a.rows > 16 && m->plan[1][code].nwg > 0 && a.sc.part) ? 1 : 0;
             a.plan0 = m->plan[v][code];
             GemmEntry &en = a.entry;
-            const bool packed = (size_t)slice < m->packed[v][code].size() && m->packed[v][code][slice].w;
+            const bool packed = (size_t)slice < m->packed[v][code].size() && m->packed[v][code][slice].w && packed_pays(code, a.plan0, a.rows);
             k = gemm_kernel(code, a.rows, packed);
             if (packed) {
                 const ee_model::PackedSlice &ps = m->packed[v][code][slice];

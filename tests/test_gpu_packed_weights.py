@@ -116,11 +116,11 @@ def test_one_outlier_is_seen(pair, model_dir, name):
         gs.free()
 
 
-@pytest.mark.parametrize("split,B,gamma", [(False, 1, 4), (False, 3, 7), (True, 1, 4), (True, 3, 5), (True, 8, 5)])
-def test_packed_groups_of_tiles(model_dir, split, B, gamma):
+@pytest.mark.parametrize("split,B,gamma,d", [(False, 1, 4, 512), (False, 3, 7, 512), (False, 2, 15, 2048), (True, 1, 4, 512), (True, 3, 5, 512), (True, 8, 5, 512)])
+def test_packed_groups_of_tiles(model_dir, split, B, gamma, d):
     """Matrices whose workgroups own more n-tiles than a group has (gate/up 8 and 10, LM head 9 and 10): every group has lists and sums of
     its own; with K split over workgroups for every kind, every slice."""
-    cfg = eegen.ModelConfig(n_layers=2, d_model=512, n_heads=8, head_dim=64, d_ffn=17408, vocab=40000, exit_layers=(1,))
+    cfg = eegen.ModelConfig(n_layers=2, d_model=d, n_heads=d // 64, head_dim=64, d_ffn=17408, vocab=40000, exit_layers=(1,))
     p = f"{model_dir}/gpu_packed_wide.bin"
     eegen.write_model(p, cfg, 78, gains="uniform", std=0.03)
     t = eegen.open_tensors(p, "r+")
@@ -277,3 +277,37 @@ def test_the_caller_chooses_the_form(pair, model_dir, B, gamma):
     finally:
         plain.free()
         packed.free()
+
+
+# K of 64 a row: 3072 packs QKV and gate/up at 48 rows, 2048 gate/up (all that is large enough to pack) at 32 and not at 33
+@pytest.mark.parametrize("d,F,V,B,gamma,packed", [(3072, 3072, 4096, 3, 15, True), (2048, 5632, 4096, 2, 15, True), (2048, 5632, 4096, 3, 10, False)])
+def test_short_k_beside_many_rows_is_streamed_plain(model_dir, d, F, V, B, gamma, packed):
+    """The dispatch's line: below it a launch is the plain one, bit for bit; on both sides results are within the two-term bound of the oracle."""
+    cfg = eegen.ModelConfig(n_layers=2, d_model=d, n_heads=d // 128, head_dim=128, d_ffn=F, vocab=V, exit_layers=(1,))
+    p = f"{model_dir}/gpu_packed_line.bin"
+    eegen.write_model(p, cfg, 81, gains="uniform")
+    o, z = eo.Model(p), []
+    toks = [eegen.prompt_tokens(950, 50 + b, V, session=b) for b in range(B)]   # (more than max_rows rows: their cache is the same in both forms)
+    drafts = [eegen.prompt_tokens(951, gamma, V, session=b) for b in range(B)]
+    for form in (ee.FORM_PACKED, ee.FORM_PLAIN):
+        g = ee.Model(p, max_rows=48, form=form)
+        ss = [g.session(80, max_gamma=gamma, flags=ee.NO_AUTOCOMMIT | ee.KEEP_LOGITS) for _ in range(B)]
+        firsts = [s.ee_prefill(t) for s, t in zip(ss, toks)]
+        for s in ss:
+            s.ee_set_pending(7)
+        ee.ee_verify_batch(ss, drafts, [1])
+        for s in ss:
+            s.ee_wait_final()
+        z.append(np.stack([s.ee_debug_logits(e) for s in ss for e in range(2)]))
+        if form == ee.FORM_PACKED:
+            for b, s in enumerate(ss):
+                os_ = o.session(80)
+                fo, margin = oracle_prefill(os_, toks[b])
+                check_first_token(s, firsts[b], fo, margin, f"session {b}")
+                os_.set_pending(7)
+                ro = os_.verify(drafts[b], [1], commit=False, want_logits=True)
+                check_two_terms(ro, gpu_logits(s, 1))
+        for s in ss:
+            s.free()
+        g.free()
+    assert np.array_equal(z[0].view(np.uint32), z[1].view(np.uint32)) != packed
