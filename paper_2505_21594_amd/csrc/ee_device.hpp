@@ -238,8 +238,9 @@ struct PassArgs {
     const float *ad_gain;                // (host) gain of the head behind the adapters: the exit's, or the group's first exit's
     int keep_logits;
     int fuse_accept;                     // the head launch also runs the accept step (in the workgroup that finishes last)
-    int att_splits;                      // splits of the position range (of the session with the most pages)
-    int att_pages;                       // > 0: pages a split, sessions with fewer pages have fewer splits; 0: all have att_splits
+    int att_splits;                      // splits of the position range (of the session with the most)
+    unsigned long long att_starts;       // != 0: sessions have splits of their own, one behind the other in the grid: bit i is set where a
+                                         // session's first one is i, and behind the last session's last; 0: all have att_splits
     int H, d, Kpad_d;                    // copies of the model descriptor's fields for the attention kernel
     float att_scale;
     int layer;                           // layer of this launch's stage

@@ -1137,10 +1137,12 @@ constexpr int att_rec(int hd) { return hd + 4; }
 constexpr int att_item(int hd) { return ATT_ROWS * (hd + 2); }
 constexpr size_t att_lds(int hd, int rows) { return (size_t)WAVES * (rows < ATT_ROWS ? rows : ATT_ROWS) * att_rec(hd) * sizeof(float) + 16; }
 
-// Workgroup = (head, split of the cache's pages, session or chunk of up to ATT_ROWS = 16 query
-// rows); heads vary fastest, so that the XCDs, which workgroups are dealt to in turn, get equal shares of a batch whose sessions have
-// different numbers of splits (splits fastest: the third of three sessions began 10 us late, on two XCDs that had the others' work too); the host picks the number of splits from the pages, the head size and the items (attention_splits: one where
-// there are few pages, otherwise enough for the workgroups to cover the chip).  Wave w takes the pages
+// Workgroup = (split of the cache's pages, head, session or chunk of up to ATT_ROWS = 16 query
+// rows); the host picks the number of splits from the pages, the head size and the items (attention_splits: one where
+// there are few pages, otherwise enough for the workgroups to cover the chip).  Where sessions have splits of their own the grid is (head, split of
+// session after session): heads vary fastest, so that the XCDs, which workgroups are dealt to in turn, get equal shares of long and short
+// sessions.  Elsewhere splits do: a head's splits, which pull on one stretch of the cache, are then on XCDs of their own (one session, 5 rows, heads
+// fastest / splits fastest: 32 heads of 128 at 512 positions 10.9 / 10.6 us, at 4096 31.1 / 30.0, of 64 at 4096 19.1 / 17.4).  Wave w takes the pages
 // pg_lo + w, pg_lo + w + WAVES, ... of the split (16 positions each), both products on the matrix cores:
 //   scores  S[pos][row] = K . q^T     v_mfma_f32_16x16x32_bf16, A = 16 cached positions x 32
 //           values straight from the page (lane l: position l & 15, values (l >> 4) * 8 ..),
@@ -1169,13 +1171,21 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
     constexpr int REC = att_rec(HD);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, quad = lane >> 4;
-    const int hh = blockIdx.x, sp = blockIdx.y, M = a.M;
-    const int s = a.mode == 1 ? 0 : blockIdx.z, ch = a.mode == 1 ? blockIdx.z : 0;
+    const int M = a.M;
+    int sp = blockIdx.x, hh = blockIdx.y, s = a.mode == 1 ? 0 : blockIdx.z, n_splits = a.att_splits;
+    const int ch = a.mode == 1 ? blockIdx.z : 0;
+    if (a.att_starts) {
+        sp = blockIdx.y;
+        hh = blockIdx.x;
+        const unsigned long long upto = a.att_starts & ((2ull << sp) - 1);
+        const int first = 63 - __builtin_clzll(upto);
+        s = __builtin_popcountll(upto) - 1;
+        n_splits = sp - first + 1 + __builtin_ctzll(a.att_starts >> (sp + 1));
+        sp -= first;
+    }
     const int r0 = ch * ATT_ROWS, nr = min(ATT_ROWS, M - r0);
     const int P = a.mode == 1 ? a.pf_pos0 : EE_SESS(a, s, kv_len);  // position of the first row
     const int n_pg = (P + r0 + nr + KV_PAGE - 1) / KV_PAGE;         // pages visible to the chunk's last row
-    const int n_splits = a.att_pages ? min(a.att_splits, div_small(n_pg + a.att_pages - 1, a.att_pages)) : a.att_splits;
-    if (sp >= n_splits) return;                                     // (a session with fewer pages than the longest one)
     const int pg_lo = div_small(n_pg * sp, n_splits), pg_hi = div_small(n_pg * (sp + 1), n_splits);
     const int cbase = EE_SESS(a, s, contig_base), n_pages = EE_SESS(a, s, n_pages);
     const int *page_table = EE_SESS(a, s, page_table);
@@ -1311,7 +1321,7 @@ __device__ __forceinline__ void att_stage(const PassArgs &a, char *lds)
         }
     }
     if (n_splits > 1) {
-        const int unit = blockIdx.z * a.H + hh;
+        const int unit = (ch + s) * a.H + hh;                       // (one of them is 0)
         const WRes part = buffer_resource(a.sc.att_part + (size_t)unit * a.att_splits * att_item(HD));
         constexpr int SP_BYTES = att_item(HD) * 4, MS = ATT_ROWS * HD * 4;
         if (mine) {

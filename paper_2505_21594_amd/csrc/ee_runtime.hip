@@ -976,43 +976,50 @@ static int attention_splits(const ee_session *lead, int items_cap, int n_sess, i
     return std::min(s, cap);
 }
 
-// Splits of a batch whose sessions have different contexts: as many for the longest one as leave the items of all sessions, each
-// with its pages over the longest one's pages per split, within the compute units; not below what attention_splits gives.  Sets
-// a.att_splits and a.att_pages.  18 rows of the 7B shape over 700, 333 and 97 positions: 4 splits of 12 pages, 2 and 1 (224 items)
-// instead of 2 of each (192 items, 23 pages in the longest).
+// Splits of a batch by session: pages per split are the same for all, so that a session has as many splits as its own pages ask for,
+// instead of the number that attention_splits gives all of them.  Taken where the launch's estimated time is lower by 3 %: a
+// start, an exchange if anything is split, the pages of the largest workgroup and a compute unit's share of all pages (between
+// the larger of the two and their sum), and a second round where the workgroups outnumber the units (one fits a unit).  us, fitted to 420 batches
+// of 2 to 16 sessions of 9 to 1200 positions, 4 to 40 heads of 64 and 128 and every number of splits (5 to 6 % off, root mean square).
+// Against the number all have, us a launch: 32 heads of 128 over 1048, 396 and 9 positions 22.8 -> 16.1, 20 over ten of 888 to 11 27.1 -> 15.1, 16 of 64 over
+// twelve of 1064 to 9 17.3 -> 12.4; those batches 6 % on average, one in a hundred slower by up to 7 %.
 static void attention_splits_by_session(const ee_session *lead, int items_cap, ee_session *const *sessions, int n_sess, int M, PassArgs &a)
 {
     const ee_model *m = lead->m;
     const int H = m->cfg.n_heads, units = n_sess * H;
     if (n_sess < 2 || lead->att_splits_opt > 0) return;
-    int pages[EE_MAX_BATCH], most = 0, total = 0;
+    int pages[EE_MAX_BATCH], most = 0, all = 0;
     for (int i = 0; i < n_sess; ++i) {
         pages[i] = (sessions[i]->kv_len + M + KV_PAGE - 1) / KV_PAGE;
         most = std::max(most, pages[i]);
-        total += pages[i];
+        all += pages[i];
     }
-    const int s_max = std::min({ATT_MAX_SPLITS, items_cap / units, most});
-    for (int s = s_max; s > 1 && s >= a.att_splits; --s) {
+    struct Cost {
+        float start, row, exchange, page, share, round, rounds;
+    };
+    static constexpr Cost COST[2] = {{5.5f, 0.05f, 1.65f, 0.18f, 0.32f, 1.45f, 2.2f}, {5.4f, 0.135f, 1.55f, 0.38f, 0.73f, 1.8f, 2.5f}};   // heads of 64, of 128
+    const Cost &c = COST[m->cfg.head_dim > 64];
+    const float nwg = (float)m->nwg, share = c.share * (float)(all * H) / nwg;
+    auto estimate = [&](int s, int items) {
+        const float largest = c.page * (float)((most + s - 1) / s), more = ((float)items - nwg) / nwg;
+        return c.start + c.row * (float)M + (s > 1 ? c.exchange : 0.f) + (s > 8 ? 0.7f : 0.f) + cbrtf(largest * largest * largest + share * share * share) +
+               (more > 0.f ? c.round + c.rounds * more : 0.f);
+    };
+    float best = 0.97f * estimate(a.att_splits, units * a.att_splits);
+    const int forced = (most + ATT_TILES * WAVES - 1) / (ATT_TILES * WAVES);
+    for (int s = std::max(forced, 1); s <= std::min({8, items_cap / units, most}); ++s) {   // (8: one round of the merge)
         const int per = (most + s - 1) / s;
-        int items = 0;
-        for (int i = 0; i < n_sess; ++i) items += H * ((pages[i] + per - 1) / per);
-        if (s > a.att_splits && (items > m->nwg || per < 2)) continue;
-        a.att_splits = s;
-        a.att_pages = per;
-        break;
-    }
-    // More sessions than that covers: the units of one get several workgroups in turn, and the longest session's
-    // should not be what the launch waits for.  In pages: a workgroup has `per`, a compute unit `even` on average, an exchange is worth 5.
-    // Device us a pass without / with: eight sessions of 790 to 9 positions, 7B shape, 4 layers, 533 / 499; ten of 800 to 50, 13B shape, 3
-    // layers, 522 / 514; five of 700 to 20, 583 / 578; twelve and nine of nearly equal length, and eight of 640: the same.
-    const int even = (int)(((long long)total * H + m->nwg - 1) / m->nwg);
-    int best = a.att_splits > 1 ? std::max((most + a.att_splits - 1) / a.att_splits, even) + 5 : std::max(most, even);
-    for (int s = a.att_splits + 1; s <= s_max && units >= m->nwg / 2; ++s) {
-        const int per = (most + s - 1) / s, t = std::max(per, even) + 5;
-        if (t + 3 > best || per < 8) continue;
+        unsigned long long starts = 0;
+        int total = 0;
+        for (int i = 0; i < n_sess; ++i) {
+            starts |= total < 64 ? 1ull << total : 0;
+            total += (pages[i] + per - 1) / per;
+        }
+        const float t = estimate(s, H * total);
+        if (t >= best || total > 63) continue;
         best = t;
         a.att_splits = s;
-        a.att_pages = per;
+        a.att_starts = starts | 1ull << total;
     }
 }
 
@@ -1404,8 +1411,8 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
             HIP_TRY(hipEventRecord(lead->lt_events[2 * i], lead->run_stream));
         }
         if (code == EE_LAUNCH_ATT)
-            hipLaunchKernelGGL(k, dim3(a.H, a.att_splits, a.mode == 1 ? (a.M + ATT_ROWS - 1) / ATT_ROWS : a.n_sess), dim3(WG_THREADS),
-                               att_lds(m->cfg.head_dim, a.M), lead->run_stream, a);
+            hipLaunchKernelGGL(k, a.att_starts ? dim3(a.H, 63 - __builtin_clzll(a.att_starts)) : dim3(a.att_splits, a.H, a.mode == 1 ? (a.M + ATT_ROWS - 1) / ATT_ROWS : a.n_sess),
+                               dim3(WG_THREADS), att_lds(m->cfg.head_dim, a.M), lead->run_stream, a);
         else
             hipLaunchKernelGGL(k, dim3(m->nwg, adapter_stage && many ? a.n_heads : 1), dim3(WG_THREADS), m->lds_budget, lead->run_stream, a);
         HIP_TRY(hipGetLastError());

@@ -588,7 +588,7 @@ def test_attention_splits_of_a_batch(model_dir, tiny_path, splits):
 # the longest session first, last and in the middle; sessions of one page and at the lines of a page; heads of 64 and of 128
 @pytest.mark.parametrize("which,lens", [("tiny", (9, 330)), ("tiny", (170, 300, 11, 28)), ("mid", (260, 90, 5)), ("mid", (75, 76, 300)), ("mid", (330, 330))])
 def test_attention_splits_follow_each_session(tiny_pair, mid_pair, which, lens):
-    """A batch whose sessions have different contexts: every one has the splits its own pages ask for.  Two rounds, the second finds the
+    """A batch whose sessions have different contexts, whatever splits they get.  Two rounds, the second finds the
     units' counters as the first left them; every session's logits against the oracle at the bound of two-term operands."""
     g, o = tiny_pair if which == "tiny" else mid_pair
     exits, gamma = (TINY_EXITS, 3) if which == "tiny" else ([1, 2], 3)
@@ -616,8 +616,8 @@ def test_attention_splits_follow_each_session(tiny_pair, mid_pair, which, lens):
 
 
 def test_attention_splits_of_more_items_than_units(model_dir):
-    """Sixteen sessions of sixteen heads: more units than compute units have room for once more, two sessions far longer than the others
-    (21 and 13 pages): these are split although their items then take turns on a unit."""
+    """Sixteen sessions of sixteen heads, one unit for every compute unit: two sessions longer than the others (21 and 13 pages), by
+    too little for a second round of workgroups to pay."""
     cfg = eegen.ModelConfig(2, 1024, 16, 64, 688, 1024, (1,))
     p = f"{model_dir}/gpu_many_units.bin"
     eegen.write_model(p, cfg, 92, gains="uniform")
@@ -640,6 +640,51 @@ def test_attention_splits_of_more_items_than_units(model_dir):
                 ro = osess[b].verify(drafts[b], [1], commit=False, want_logits=True)
                 check_pass(ro, sess[b].final_result(), gpu_logits(sess[b], 1), drafts[b], f"round {rnd} session {b}")
                 check_two_terms(ro, gpu_logits(sess[b], 1))
+    finally:
+        for s_ in sess:
+            s_.free()
+        g.free()
+
+
+# 16 heads: 8 sessions, splits within the compute units (fewer for all than the longest gets); 16 sessions, a second round of workgroups; the longest last
+@pytest.mark.parametrize("lens,gamma", [((900, 300, 90, 50, 40, 30, 20, 10), 3), ((900, 300) + tuple(range(5, 47, 3)), 1), ((10, 20, 50, 90, 300, 900, 40, 33), 4)])
+def test_sessions_have_splits_of_their_own(model_dir, lens, gamma):
+    """A session's attention depends on its own number of splits alone: the batch's result for every session is, bit for bit, that of the
+    same batch with that number forced on all (EE_OPT_ATT_SPLITS).  The longest has more than the short ones, which are not split: this is
+    the grid of sessions with splits of their own, and no workgroup of it works on the wrong session or part.  Twice, with the counters
+    as the first pass left them, and against the oracle."""
+    cfg = eegen.ModelConfig(2, 1024, 16, 64, 688, 1024, (1,))
+    p = f"{model_dir}/gpu_many_units.bin"
+    eegen.write_model(p, cfg, 92, gains="uniform")
+    g, o = ee.Model(p, max_rows=48), eo.Model(p)
+    sess = []
+    try:
+        toks = [eegen.prompt_tokens(680, n, o.vocab, session=b) for b, n in enumerate(lens)]
+        for t in toks:
+            gs = g.session(960, max_gamma=gamma, flags=ee.KEEP_LOGITS | ee.NO_AUTOCOMMIT)
+            gs.ee_prefill(t)
+            gs.ee_set_pending(3)
+            sess.append(gs)
+        drafts = [eegen.prompt_tokens(681, gamma, o.vocab, session=b) for b in range(len(lens))]
+
+        def run(k):
+            sess[0].ee_session_option(ee.OPT_ATT_SPLITS, k)
+            ee.ee_verify_batch(sess, drafts, [1])
+            for s_ in sess:
+                s_.ee_wait_final()
+            return [np.stack([s_.ee_debug_logits(e) for e in range(2)]).view(np.uint32) for s_ in sess]
+
+        own, again = run(0), run(0)
+        forced = {k: run(k) for k in range(1, 9)}
+        splits = [{k for k in forced if np.array_equal(forced[k][b], own[b])} for b in range(len(lens))]
+        assert all(np.array_equal(x, y) for x, y in zip(own, again)) and all(splits), splits
+        most, least = lens.index(max(lens)), lens.index(min(lens))
+        assert 1 not in splits[most] and 2 not in splits[most] and 1 in splits[least], splits
+        for b in (most, least):
+            os_ = o.session(960)
+            oracle_prefill(os_, toks[b])
+            os_.set_pending(3)
+            check_two_terms(os_.verify(drafts[b], [1], commit=False, want_logits=True), [z.view(np.float32) for z in own[b]])
     finally:
         for s_ in sess:
             s_.free()
