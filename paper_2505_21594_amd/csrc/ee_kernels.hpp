@@ -970,15 +970,15 @@ __device__ __forceinline__ void gemm_group(const PassArgs &a, const GemmPlan &pl
             mi.pos[m] = pos;
             mi.kvoff[m] = (((long long)a.layer * EE_SESS(a, ses, n_pages) + page) * md.H) * KV_PAGE * 2 * md.hd;  // record of head 0
         }
+        if (PK) esc.finish(nt_first * 16, lane, reinterpret_cast<float *>(lds + ly.corr_off));
+        wait_vmem();
         // The down projection's input: the padding columns of its last k-tile (F = 16 mod 32).  Their place depends on the rows, another
-        // pass's values may lie there, and a packed padding weight is not zero (PACK_CODE0).  16 bytes a thread: (term, row) and half.
+        // pass's values may lie there, and a packed padding weight is not zero (PACK_CODE0).  16 bytes a thread: (term, row) and half.  (Nothing waits for it.)
         if (KIND == G_GU && group == 0 && blockIdx.x == 0 && (md.F & 16) && ht < rows * 4) {
             const int row = ht >> 1;   // [term][row] of the last k-tile
             uint16_t *p = a.sc.u + (size_t)(md.F >> 5) * 2 * rows * 32 + row * 32 + 16 + (ht & 1) * 8;
             *reinterpret_cast<EE_GLOBAL u32x4_t *>(as_global_mut(p)) = (u32x4_t){0, 0, 0, 0};
         }
-        if (PK) esc.finish(nt_first * 16, lane, reinterpret_cast<float *>(lds + ly.corr_off));
-        wait_vmem();
     }
     // ---- cross-wave sum and epilogue, ly.chunk n-tiles at a time (the rings are free now)
     lds_barrier();                                 // every streaming wave has read its last stage
