@@ -1097,8 +1097,7 @@ def test_sampled_verification_mid(mid_pair):
 
 @pytest.mark.parametrize("vocab", [1000, 32768, 32832])
 def test_sampled_verification_at_the_register_limit(model_dir, vocab):
-    """A row's logits stay in registers up to 32768 tokens (1000: most waves own none); one block more
-    and every step loads them again in two chunks."""
+    """1000 tokens: one workgroup, half of whose waves own none; 32768: sixteen full ones; 32832: a seventeenth with 64."""
     p = f"{model_dir}/gpu_vocab.bin"
     eegen.write_model(p, eegen.ModelConfig(2, 256, 4, 64, 688, vocab, (1,)), 78, gains="uniform", std=0.06)
     g, o = ee.Model(p), eo.Model(p)
