@@ -132,18 +132,19 @@ int ee_model_load(const char *path, int device, ee_model **out);
 int ee_model_load_ex(const char *path, int device, int max_rows, ee_model **out);
 
 /* ee_model_load_ex with a choice of the form in which passes stream the weights.  Packed: 12 bits a
-   weight, no weight changed, three quarters of a matrix's memory on top of its plain form, which
-   prompts of more than max_rows rows read.  Both forms hold the same weights, but their products
-   are summed differently: results agree to fp32 rounding, not to the bit.  A matrix that does not
-   suit the form (too many or too unevenly spread weights outside a window of 16 exponents, infinities, NaN)
-   stays plain in any case and takes no memory for it.
+   weight, three quarters of a matrix's memory on top of its plain form, which prompts of more than
+   max_rows rows read (and passes of more than 16 rows where K is less than 64 a row).  Both forms
+   hold the same weights (the packed one those far below a matrix's largest to within 2^-40 of it), but
+   their products are summed differently: results agree to fp32 rounding, not to the bit.  A
+   matrix that does not suit the form (too many or too unevenly spread weights outside a window of 16
+   exponents, infinities, NaN) stays plain in any case and takes no memory for it.
      EE_FORM_AUTO:   packed if all packed forms together take at most an eighth of the device memory
                      that is free once everything else is loaded (so what else holds memory then
                      decides it), and for the kinds of matrices whose allocation succeeds;
      EE_FORM_PLAIN:  never (no memory taken; results do not depend on what else the device holds);
      EE_FORM_PACKED: always; EE_EDEVICE if the memory is not there.
-   ee_model_packed_bytes: device memory the model's packed forms hold, without their lists of a few
-   KB per matrix; 0: every matrix is streamed plain. */
+   ee_model_packed_bytes: device memory the model's packed forms hold, without their lists of
+   some 100 KB a matrix; 0: every matrix is streamed plain. */
 #define EE_FORM_AUTO 0
 #define EE_FORM_PLAIN 1
 #define EE_FORM_PACKED 2

@@ -70,11 +70,13 @@ struct StageLds {
     int misc_off;
 };
 
-// Packed weights: the same tiles in the same slots, a weight in 12 bits instead of 16, nothing lost.  The bf16 weights of a
+// Packed weights: the same tiles in the same slots, a weight in 12 bits instead of 16.  The bf16 weights of a
 // matrix lie in few binades: with its 16 most common neighbouring exponents as a window, sign, mantissa and 4 bits of
 // exponent say all but about one weight in 10000 of a normal distribution.  Those others stand in the tile as the
 // smallest value of the window (code 0), and in a list of the matrix with the difference to what they should be;
-// helper waves add the list's products to the sums while the weights stream (EscapeSums).
+// helper waves add the list's products to the sums while the weights stream (EscapeSums).  The difference is fp32: exact for weights between
+// 2^-31 and 2^9 on the moved scale below (its window ends at 2), beyond that off by 2^-39 or by 2^-24 of the weight; and as the product is the sum
+// of two, an infinite input times a positive weight below the window is no infinity but NaN.
 // A tile is 64 lanes x 12 bytes: dwords A and B the low bytes of the lane's eight bf16 values, C their variable high bits (sign and
 // upper three exponent bits, PACK_MASK, of pair j rotated left by 4 j).  The window's exponents are moved to 112 .. 127 (a power of two that
 // the epilogue takes back exactly, GemmEntry::wscale): the constant exponent bits are 0111, and unpacking is a byte permute, a rotate and a

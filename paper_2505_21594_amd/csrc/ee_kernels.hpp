@@ -853,8 +853,8 @@ struct EscapeSums {
 // rows): QKV 20.4 / 36.2 -> 19.6 / 27.8, gate/up 31.5 / 43.4 -> 31.2 / 37.8, down 19.4 / 27.6 -> 19.0 / 27.0,
 // LM head 54 / 86 -> 51 / 70.  Packed weights (PK): three quarters of the bytes, unpacked between LDS and the product by the vector unit that
 // is idle otherwise.  us per launch plain -> packed: 5 rows QKV 18.2 -> 15.1, output 8.8 -> 8.4, gate/up 30.2 -> 24.2, down 17.6 -> 15.5, head 49.2
-// -> 39.8; 16 rows 19.0 -> 18.1, 10.8 -> 10.6, 30.7 -> 25.7, 23.3 -> 21.7, 50.2 -> 42.0; 40 rows (bound by the input's bytes and the LDS passes
-// beside the weights) 26.6 -> 26.0, 15.2 -> 15.2, 37.1 -> 35.6, 25.6 -> 24.8, 60 -> 56.
+// -> 39.8; 16 rows 19.0 -> 18.1, 10.8 -> 10.6, 30.7 -> 25.7, 23.3 -> 21.7, 50.2 -> 42.0; 39 rows (bound by the input's bytes and the LDS passes
+// beside the weights; between events, 2 us more each) 27.8 -> 26.0, 17.1 -> 17.0, 38.6 -> 35.1, 27.4 -> 25.4, 59.9 -> 54.5.
 //
 // Afterwards the accumulators go through LDS, `ly.chunk` n-tiles at a time, for the
 // cross-wave sum and the stage's epilogue (all waves).

@@ -362,8 +362,8 @@ static int upload_gain(const uint16_t *src, int d, uint16_t *tmp, float *dst)
 // Packs one matrix (its rows are in tmp, in file order) into slice `slice` of every variant of its kind, where that pays.
 // A launch's stream gets a quarter shorter, but the helper waves' chain (list, then inputs, then sums) takes 5 us whatever the matrix:
 // with less than 128 KB of weights per compute unit it is what the launch waits for.  us per launch, plain / packed, 5 rows: 1280-wide
-// model QKV (9 MB) 5.3 / 6.4, 2048-wide QKV (25 MB) 7.4 / 8.2, down (22 MB) 9.4 / 9.2, 2560-wide QKV (38 MB) 9.5 / 9.6, gate/up (70 MB)
-// 14.7 / 13.6; 7B shape: output (34 MB) 8.8 / 8.4, down 17.6 / 15.5, QKV 18.2 / 15.1, gate/up 30.2 / 24.2, head 49.2 / 39.8.
+// model QKV (9 MB) 5.3 / 6.4, 2048-wide QKV (25 MB) 7.4 / 8.2, down (22 MB) 9.4 / 9.2, 2560-wide QKV (38 MB, between events) 11.1 / 10.7, gate/up
+// (70 MB) 14.7 / 13.6; 7B shape: output (34 MB) 8.8 / 8.4, down 17.6 / 15.5, QKV 18.2 / 15.1, gate/up 30.2 / 24.2, head 49.2 / 39.8.
 constexpr int PACK_MIN_TILES = 32768;          // 32 MB
 constexpr int PACK_TILES_PER_ESCAPE = 8;       // at most one escape per so many tiles of 512 weights (normally distributed ones: per 20)
 static int pack_slice(ee_model *m, int kind, int perm, size_t slice, size_t n_elems, const uint16_t *tmp, void *work, size_t work_bytes, std::vector<Escape> &lists)
@@ -1419,7 +1419,7 @@ static int launch_segment(ee_session *lead, PassArgs &a, int adapter_slot, Sampl
         a.head_row0 = head_row0;
         if (timed) HIP_TRY(hipEventRecord(lead->lt_events[2 * lead->lt_codes.size() - 1], lead->run_stream));
         if (code == EE_LAUNCH_HEAD && a.sm.on) {
-            // probabilistic verification: the rows' keep tests and draws, one workgroup per head row,
+            // probabilistic verification: the rows' keep tests and draws, workgroups of SAMPLE_PART tokens of a head row,
             // then the accept rule and the publication (in the workgroup that finishes last)
             if (up && up->sp) {
                 const int rc = upload_sampling(lead, *up);
