@@ -319,6 +319,8 @@ def main():
     achieved = g_bytes / (g_ms * 1e-3) / 1e9
     committed = sum(a + B for a in accepted)
     kernel_name = "ee_gemm_kernel<*,%d>" % ((B * M + 7) // 8)   # all GEMM kinds
+    traffic = measured_traffic(kernel_name, args.workload)
+    moved = traffic / (g_ms / g_n * 1e-3) / 1e9 if traffic else None
     out = {
         "metric": "verify passes/s (Llama2-7B-shape, gamma=4, ctx 512)" if args.workload == "llama7b_g4_ctx512"
         else f"verify passes/s ({args.workload})",
@@ -340,7 +342,10 @@ def main():
         "exit0_lead_seen_by_host_ms": {"median": statistics.median(host_lead), "passes_with_exit_before_final": len(host_lead)} if host_lead else None,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": measured_traffic(kernel_name, args.workload),
+                     "achieved_counts": "algorithmic bytes, two a weight; packed weights move one and a half (moved)",
+                     "packed_weight_bytes": model.packed_bytes(),
+                     "moved": {"achieved": moved, "frac": moved / HBM_PEAK_GBS, "unit": "GB/s", "counts": "traffic / avg_launch_us"} if moved else None,
+                     "traffic": traffic,
                      "traffic_source": "committed rocprofv3 --pmc summary profiles/hbm_traffic.md (FETCH_SIZE + WRITE_SIZE, "
                                        "scaled by a plain copy kernel's reading); not measured in this run",
                      "kernel": kernel_name,
