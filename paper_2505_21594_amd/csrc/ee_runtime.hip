@@ -977,12 +977,12 @@ static int attention_splits(const ee_session *lead, int items_cap, int n_sess, i
 }
 
 // Splits of a batch by session: pages per split are the same for all, so that a session has as many splits as its own pages ask for,
-// instead of the number that attention_splits gives all of them.  Taken where the launch's estimated time is lower by 3 %: a
-// start, an exchange if anything is split, the pages of the largest workgroup and a compute unit's share of all pages (between
-// the larger of the two and their sum), and a second round where the workgroups outnumber the units (one fits a unit).  us, fitted to 420 batches
-// of 2 to 16 sessions of 9 to 1200 positions, 4 to 40 heads of 64 and 128 and every number of splits (5 to 6 % off, root mean square).
+// instead of the number that attention_splits gives all of them.  Taken where the launch's estimated time is lower by 5 %: a
+// start, an exchange if anything is split (its merge takes eight at a time), the pages of the largest workgroup and a compute unit's share of
+// all pages (a little more than the larger of the two), and a second round where the workgroups outnumber the units (one fits a unit).  us, fitted
+// to 670 batches of 2 to 16 sessions of 9 to 9000 positions, 4 to 40 heads of 64 and 128 and every number of splits (6 % off, root mean square).
 // Against the number all have, us a launch: 32 heads of 128 over 1048, 396 and 9 positions 22.8 -> 16.1, 20 over ten of 888 to 11 27.1 -> 15.1, 16 of 64 over
-// twelve of 1064 to 9 17.3 -> 12.4; those batches 6 % on average, one in a hundred slower by up to 7 %.
+// twelve of 1064 to 9 17.3 -> 12.4; those batches 5 % on average, one in a hundred slower by up to 9 %.
 static void attention_splits_by_session(const ee_session *lead, int items_cap, ee_session *const *sessions, int n_sess, int M, PassArgs &a)
 {
     const ee_model *m = lead->m;
@@ -995,19 +995,19 @@ static void attention_splits_by_session(const ee_session *lead, int items_cap, e
         all += pages[i];
     }
     struct Cost {
-        float start, row, exchange, page, share, round, rounds;
+        float start, row, exchange, merge, page, share, round, rounds;
     };
-    static constexpr Cost COST[2] = {{5.5f, 0.05f, 1.65f, 0.18f, 0.32f, 1.45f, 2.2f}, {5.4f, 0.135f, 1.55f, 0.38f, 0.73f, 1.8f, 2.5f}};   // heads of 64, of 128
+    static constexpr Cost COST[2] = {{5.6f, 0.05f, 1.6f, 0.8f, 0.18f, 0.35f, 1.2f, 2.4f}, {5.4f, 0.145f, 1.55f, 0.55f, 0.385f, 0.73f, 1.65f, 2.8f}};   // heads of 64, of 128
     const Cost &c = COST[m->cfg.head_dim > 64];
     const float nwg = (float)m->nwg, share = c.share * (float)(all * H) / nwg;
     auto estimate = [&](int s, int items) {
         const float largest = c.page * (float)((most + s - 1) / s), more = ((float)items - nwg) / nwg;
-        return c.start + c.row * (float)M + (s > 1 ? c.exchange : 0.f) + (s > 8 ? 0.7f : 0.f) + cbrtf(largest * largest * largest + share * share * share) +
+        return c.start + c.row * (float)M + (s > 1 ? c.exchange : 0.f) + (s > 8 ? c.merge : 0.f) + sqrtf(hypotf(largest * largest, share * share)) +
                (more > 0.f ? c.round + c.rounds * more : 0.f);
     };
-    float best = 0.97f * estimate(a.att_splits, units * a.att_splits);
+    float best = 0.95f * estimate(a.att_splits, units * a.att_splits);
     const int forced = (most + ATT_TILES * WAVES - 1) / (ATT_TILES * WAVES);
-    for (int s = std::max(forced, 1); s <= std::min({8, items_cap / units, most}); ++s) {   // (8: one round of the merge)
+    for (int s = std::max(forced, 1); s <= std::min({ATT_MAX_SPLITS, items_cap / units, most}); ++s) {
         const int per = (most + s - 1) / s;
         unsigned long long starts = 0;
         int total = 0;

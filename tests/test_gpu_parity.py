@@ -675,7 +675,7 @@ def test_sessions_have_splits_of_their_own(model_dir, lens, gamma):
             return [np.stack([s_.ee_debug_logits(e) for e in range(2)]).view(np.uint32) for s_ in sess]
 
         own, again = run(0), run(0)
-        forced = {k: run(k) for k in range(1, 9)}
+        forced = {k: run(k) for k in range(1, 17)}
         splits = [{k for k in forced if np.array_equal(forced[k][b], own[b])} for b in range(len(lens))]
         assert all(np.array_equal(x, y) for x, y in zip(own, again)) and all(splits), splits
         most, least = lens.index(max(lens)), lens.index(min(lens))
